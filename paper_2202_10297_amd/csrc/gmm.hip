@@ -25,9 +25,9 @@
 //   q_bar_kd = W_k - exp(q_kd) G_k[d][d],
 //   l_bar_k[r,c] = -G_k[r][c]  (r > c).
 // Per (component, point chunk) blocks write FP32 partials of S_k and u_k
-// (accumulated in the MFMA registers over at most 4096 points per wave); a
-// per-component kernel sums them in FP64 in a fixed order, forms G_k and v_k
-// and applies the parameter maps.
+// (accumulated in the MFMA registers over at most 4096 points per wave), which
+// are summed in FP64 in a fixed order; a per-component kernel then forms G_k
+// and v_k and applies the parameter maps.
 #include <math.h>
 
 #include "common.h"
@@ -100,17 +100,25 @@ __global__ __launch_bounds__(256) void gmm_prep_kernel(const float* __restrict__
         const int s = f - fidx(rt, 0);
         Qf[((int64_t)k * C::NF + f) * 64 + lane] = Q[32 * rt + (lane & 31)][2 * s + (lane >> 5)];
     }
-    if (threadIdx.x == 0) {
-        double b = (double)alpha[k];
-        for (int d = 0; d < D; ++d) b += (double)q[(int64_t)k * D + d];
-        bias[k] = b;
-        if (k == 0) {
-            double mx = -INFINITY;
-            for (int j = 0; j < K; ++j) mx = fmax(mx, (double)alpha[j]);
-            double s = 0.0;
-            for (int j = 0; j < K; ++j) s += exp((double)alpha[j] - mx);
-            *lse_alpha = mx + log(s);
-        }
+    // One wave each for the bias and (block 0) LSE(alpha): with one thread the
+    // K exponentials in a row took most of the kernel (37 -> 14 us at K = 200).
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (w == 0) {
+        double b = lane < D ? (double)q[(int64_t)k * D + lane] : 0.0;
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) b += __shfl_xor(b, d, kWave);
+        if (lane == 0) bias[k] = (double)alpha[k] + b;
+    }
+    if (w == 1 && k == 0) {
+        double mx = -INFINITY;
+        for (int j = lane; j < K; j += 64) mx = fmax(mx, (double)alpha[j]);
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) mx = fmax(mx, __shfl_xor(mx, d, kWave));
+        double s = 0.0;
+        for (int j = lane; j < K; j += 64) s += exp((double)alpha[j] - mx);
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) s += __shfl_xor(s, d, kWave);
+        if (lane == 0) *lse_alpha = mx + log(s);
     }
 }
 
@@ -228,6 +236,48 @@ struct GmmHdr {
 };
 
 // ------------------------------------------------------------------ forward
+// Online log-sum-exp step: one exponential whichever side is larger (a branch
+// per side runs both when the lanes disagree).
+__device__ __forceinline__ void lse_step(double sv, double& m, double& ssum) {
+    const bool up = sv > m;
+    const double e = exp(up ? m - sv : sv - m);
+    ssum = up ? ssum * e + 1.0 : ssum + e;
+    m = up ? sv : m;
+}
+
+// Sum of every thread's v over the grid (blocks of 256), by the last block in
+// a fixed order, into the log-likelihood.
+__device__ __forceinline__ void finish_loglik(double v, int64_t N, int D, const double* lse_alpha, double* parts,
+                                              GmmHdr* hdr, double* loglik) {
+    __shared__ double red[4];
+    __shared__ int s_last;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, kWave);
+    if (lane == 0) red[w] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        st_coherent(&parts[blockIdx.x], (red[0] + red[1]) + (red[2] + red[3]));
+        const uint32_t d = __hip_atomic_fetch_add(&hdr->done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        s_last = (d == gridDim.x - 1);
+    }
+    __syncthreads();
+    if (!s_last) return;
+    // Last block: fixed-order sum of the block partials.
+    double acc = 0.0;
+    for (int b = threadIdx.x; b < (int)gridDim.x; b += 256) acc += ld_coherent(&parts[b]);
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) acc += __shfl_xor(acc, d, kWave);
+    __syncthreads();
+    if (lane == 0) red[w] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const double tot = (red[0] + red[1]) + (red[2] + red[3]);
+        *loglik = tot - (double)N * (*lse_alpha) - 0.5 * (double)N * D * kLog2Pi;
+        __hip_atomic_store(&hdr->done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
 // The block's four waves share each batch of CPB components: Q_k's fragments
 // and c_k are staged in LDS once per block, and each wave interleaves the
 // independent MFMA chains of the batch (CPB components x the row tiles of
@@ -265,18 +315,21 @@ __device__ __forceinline__ void fwd_fetch(const float* __restrict__ Qf, const fl
     }
 }
 
+// The grid's second dimension splits the components where the points alone
+// leave the chip idle: block row y takes components [y kper, (y + 1) kper) and
+// leaves each point's (max, sum) to gmm_lse_merge_kernel (N = 10,007, D = 32,
+// K = 50: 79 blocks in 71 us, now 1,027 in 20 and the merge's 9).  With one
+// row the block finishes its points itself.
 template <int D>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void gmm_fwd_kernel(const float* __restrict__ X, int64_t N, int K,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void gmm_fwd_kernel(const float* __restrict__ X, int64_t N, int K, int kper,
                                                       const float* __restrict__ Qf, const float* __restrict__ cvec,
                                                       const double* __restrict__ bias,
                                                       const double* __restrict__ lse_alpha, double* __restrict__ lse,
-                                                      double* __restrict__ sck, double* parts, GmmHdr* hdr,
-                                                      double* loglik) {
+                                                      double* __restrict__ sck, double2* __restrict__ msum,
+                                                      double* parts, GmmHdr* hdr, double* loglik) {
     using C = Gm<D>;
     using F = GmFwd<D>;
     __shared__ float sm[F::LDS];
-    __shared__ double red[4];
-    __shared__ int s_last;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int64_t p0 = ((int64_t)blockIdx.x * 4 + w) * 32;
     float* Xs = sm + w * 32 * D;
@@ -291,10 +344,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void g
 
     double m = -INFINITY, ssum = 0.0;
     const bool own = (lane < 32) && (p < N);
-    for (int k0 = 0; k0 < K; k0 += F::CPB) {
+    const int kbeg = blockIdx.y * kper, kend = min(K, kbeg + kper);
+    for (int k0 = kbeg; k0 < kend; k0 += F::CPB) {
         {
             float nxt[F::PER];
-            fwd_fetch<D>(Qf, cvec, k0, K, nxt);
+            fwd_fetch<D>(Qf, cvec, k0, kend, nxt);
             __syncthreads();  // every wave is done with the previous batch (or with X)
 #pragma unroll
             for (int u = 0; u < F::PER; ++u) sm[u * 256 + threadIdx.x] = nxt[u];
@@ -317,7 +371,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void g
 #pragma unroll
         for (int c = 0; c < F::CPB; ++c) {
             const int k = k0 + c;
-            if (k >= K) break;
+            if (k >= kend) break;
             double nrm = 0.0;
 #pragma unroll
             for (int rt = 0; rt < C::RT; ++rt) {
@@ -330,43 +384,41 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void g
             nrm += __shfl_xor(nrm, 32, kWave);
             const double sv = bias[k] - 0.5 * nrm;
             if (sck && own) sck[(int64_t)k * N + p] = sv;  // component-major: 32 points per wave in a row
-            if (sv > m) {
-                ssum = ssum * exp(m - sv) + 1.0;
-                m = sv;
-            } else {
-                ssum += exp(sv - m);
-            }
+            lse_step(sv, m, ssum);
         }
     }
+    if (gridDim.y > 1) {
+        if (own) msum[(int64_t)blockIdx.y * N + p] = make_double2(m, ssum);
+        return;
+    }
     const double l_i = m + log(ssum);
-    const bool valid = (lane < 32) && (p < N);
-    if (valid && lse) lse[p] = l_i;
+    if (own && lse) lse[p] = l_i;
+    finish_loglik(own ? l_i : 0.0, N, D, lse_alpha, parts, hdr, loglik);
+}
 
-    double v = valid ? l_i : 0.0;
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, kWave);
-    if (lane == 0) red[w] = v;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        st_coherent(&parts[blockIdx.x], (red[0] + red[1]) + (red[2] + red[3]));
-        const uint32_t d = __hip_atomic_fetch_add(&hdr->done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-        s_last = (d == gridDim.x - 1);
+// The points' LSE from the (max, sum) of each range of components, in range
+// order, and the log-likelihood.
+template <int D>
+__global__ __launch_bounds__(256) void gmm_lse_merge_kernel(int64_t N, int ny, const double2* __restrict__ msum,
+                                                            const double* __restrict__ lse_alpha,
+                                                            double* __restrict__ lse, double* parts, GmmHdr* hdr,
+                                                            double* loglik) {
+    const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    double l_i = 0.0;
+    if (p < N) {
+        // the maximum first: the exponentials are then independent
+        double m = -INFINITY, s = 0.0;
+#pragma unroll 8
+        for (int y = 0; y < ny; ++y) m = fmax(m, msum[(int64_t)y * N + p].x);
+#pragma unroll 8
+        for (int y = 0; y < ny; ++y) {
+            const double2 v = msum[(int64_t)y * N + p];
+            s += v.y * (v.x == m ? 1.0 : exp(v.x - m));
+        }
+        l_i = m + log(s);
+        if (lse) lse[p] = l_i;
     }
-    __syncthreads();
-    if (!s_last) return;
-    // Last block: fixed-order sum of the block partials.
-    double acc = 0.0;
-    for (int b = threadIdx.x; b < (int)gridDim.x; b += 256) acc += ld_coherent(&parts[b]);
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) acc += __shfl_xor(acc, d, kWave);
-    __syncthreads();
-    if (lane == 0) red[w] = acc;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const double tot = (red[0] + red[1]) + (red[2] + red[3]);
-        *loglik = tot - (double)N * (*lse_alpha) - 0.5 * (double)N * D * kLog2Pi;
-        __hip_atomic_store(&hdr->done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    finish_loglik(l_i, N, D, lse_alpha, parts, hdr, loglik);
 }
 
 // ----------------------------------------------------------------- backward
@@ -539,43 +591,67 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
 }
 
 // ------------------------------------------------------ reduce + parameters
+// The chunks' partials of S_k (lower 32x32 blocks), u_k and W_k summed in FP64
+// in chunk order, into sred[k][NGT * 1024 + D + 1].  A thread per entry, all
+// components at once: done by the K blocks of the parameter kernel the chunk
+// loop was the longest part of a small gradient (N = 10,007, D = 32, K = 50:
+// 127 us for both, now 5 + 7; N = 10^6, D = 64, K = 200: 363, now 27 + 20).
 template <int D>
-__global__ __launch_bounds__(256) void gmm_param_kernel(int64_t N, int K, int nch, const float* __restrict__ alpha,
+__global__ __launch_bounds__(256) void gmm_reduce_kernel(int nch, const float* __restrict__ gpart,
+                                                         const float* __restrict__ vpart,
+                                                         const double* __restrict__ wpart,
+                                                         double* __restrict__ sred) {
+    constexpr int NG = Gm<D>::NGT * 1024;
+    const int64_t k = blockIdx.y;
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    if (e > NG + D) return;
+    double s = 0.0;
+    if (e < NG) {
+        const float* src = gpart + k * nch * NG + e;
+#pragma unroll 8
+        for (int c = 0; c < nch; ++c) s += (double)src[(int64_t)c * NG];
+    } else if (e < NG + D) {
+        const float* src = vpart + k * nch * D + (e - NG);
+#pragma unroll 8
+        for (int c = 0; c < nch; ++c) s += (double)src[(int64_t)c * D];
+    } else {
+#pragma unroll 8
+        for (int c = 0; c < nch; ++c) s += wpart[k * nch + c];
+    }
+    sred[k * (NG + D + 1) + e] = s;
+}
+
+// G_k = Q_k S_k (the entries the adjoints read: r >= c), v_k = Q_k u_k and the
+// parameter maps, a block per component.  The dot products read LDS four
+// steps ahead and 16 D threads share them: with 256 threads and one step at a
+// time LDS latency took 55 us at D = 64, K = 200.
+template <int D>
+__global__ __launch_bounds__(16 * D) void gmm_param_kernel(int64_t N, const float* __restrict__ alpha,
                                                         const float* __restrict__ q, const float* __restrict__ l,
                                                         const double* __restrict__ lse_alpha, double ell_bar,
-                                                        const float* __restrict__ gpart,
-                                                        const float* __restrict__ vpart,
-                                                        const double* __restrict__ wpart, float* __restrict__ abar,
+                                                        const double* __restrict__ sred, float* __restrict__ abar,
                                                         float* __restrict__ mbar, float* __restrict__ qbar,
                                                         float* __restrict__ lbar, int accumulate) {
-    using C = Gm<D>;
+    constexpr int NG = Gm<D>::NGT * 1024;
     const int k = blockIdx.x;
     const int64_t tri = (int64_t)D * (D - 1) / 2;
-    __shared__ double G[D][D + 1];
-    __shared__ double v[D];
-    __shared__ double Wk;
+    __shared__ double S[D][D + 1];
+    __shared__ double u[D], v[D];
     __shared__ float Q[D][D + 1];
-    // G (lower-triangular 32x32 blocks) summed over chunks in FP64, chunk order.
-    for (int e = threadIdx.x; e < C::NGT * 1024; e += blockDim.x) {
+    const double* src = sred + (int64_t)k * (NG + D + 1);
+    for (int e = threadIdx.x; e < NG; e += 16 * D) {
+        // block g of the lower triangle: (0,0), (1,0), (1,1); the off-diagonal
+        // one is mirrored, the diagonal ones are whole
         const int g = e / 1024, t = (e / 64) % 16, lane = e % 64;
-        int rt = 0, ct = 0;
-        if (g == 1) rt = 1;
-        if (g == 2) rt = 1, ct = 1;
-        double s = 0.0;
-        for (int c = 0; c < nch; ++c) s += (double)gpart[(((int64_t)k * nch + c) * C::NGT * 16 + g * 16 + t) * 64 + lane];
-        G[32 * rt + drow(t, lane)][32 * ct + (lane & 31)] = s;
+        const int rt = g > 0, ct = g > 1;
+        const int r = 32 * rt + drow(t, lane), c = 32 * ct + (lane & 31);
+        if (g == 1 || r >= c) {
+            S[r][c] = src[e];
+            S[c][r] = src[e];
+        }
     }
-    for (int r = threadIdx.x; r < D; r += blockDim.x) {
-        double s = 0.0;
-        for (int c = 0; c < nch; ++c) s += (double)vpart[((int64_t)k * nch + c) * D + r];
-        v[r] = s;
-    }
-    if (threadIdx.x == 0) {
-        double s = 0.0;
-        for (int c = 0; c < nch; ++c) s += wpart[(int64_t)k * nch + c];
-        Wk = s;
-    }
-    for (int e = threadIdx.x; e < D * D; e += blockDim.x) {
+    if (threadIdx.x < D) u[threadIdx.x] = src[NG + threadIdx.x];
+    for (int e = threadIdx.x; e < D * D; e += 16 * D) {
         const int r = e / D, c = e % D;
         float x = 0.f;
         if (r == c)
@@ -584,66 +660,57 @@ __global__ __launch_bounds__(256) void gmm_param_kernel(int64_t N, int K, int nc
             x = l[(int64_t)k * tri + r * (r - 1) / 2 + c];
         Q[r][c] = x;
     }
+    const double W = src[NG + D];
     __syncthreads();
-    {
-        // The partials hold S_k (lower 32x32 blocks, symmetric) and u_k:
-        // mirror S, then G_k = Q_k S_k row by row from the bottom (row r of G
-        // needs rows <= r of S, which are still unchanged) and v_k = Q_k u_k.
-        for (int e = threadIdx.x; e < D * D; e += blockDim.x) {
-            const int r = e / D, c = e % D;
-            if (c > r) G[r][c] = G[c][r];
-        }
-        __syncthreads();
-        for (int r = D - 1; r >= 0; --r) {
-            double gr = 0.0;
-            const int c = threadIdx.x;
-            if (c < D)
-                for (int j2 = 0; j2 <= r; ++j2) gr += (double)Q[r][j2] * G[j2][c];
-            double vr = 0.0;
-            if (threadIdx.x == 0)
-                for (int j2 = 0; j2 <= r; ++j2) vr += (double)Q[r][j2] * v[j2];
-            __syncthreads();
-            if (c < D) G[r][c] = gr;
-            if (threadIdx.x == 0) v[r] = vr;
-            __syncthreads();
-        }
+    for (int r = threadIdx.x; r < D; r += 16 * D) {
+        double s = 0.0;
+#pragma unroll 4
+        for (int j = 0; j <= r; ++j) s += (double)Q[r][j] * u[j];
+        v[r] = s;
     }
-    const double W = Wk;
     if (threadIdx.x == 0) {
         const double a = W - (double)N * ell_bar * exp((double)alpha[k] - *lse_alpha);
         abar[k] = accumulate ? abar[k] + (float)a : (float)a;
     }
-    for (int c = threadIdx.x; c < D; c += blockDim.x) {
-        double s = 0.0;  // (Q_k^T v_k)_c = sum_{r >= c} Q[r][c] v[r]
-        for (int r = c; r < D; ++r) s += (double)Q[r][c] * v[r];
-        const int64_t o = (int64_t)k * D + c;
-        mbar[o] = accumulate ? mbar[o] + (float)s : (float)s;
-        const double qd = W - (double)Q[c][c] * G[c][c];
-        qbar[o] = accumulate ? qbar[o] + (float)qd : (float)qd;
-    }
-    for (int e = threadIdx.x; e < tri; e += blockDim.x) {
-        // packed strictly-lower index e -> (r, c), r > c, e = r(r-1)/2 + c
-        int r = (int)((1.0 + sqrt(1.0 + 8.0 * (double)e)) / 2.0);
-        while (r * (r - 1) / 2 > e) --r;
-        while ((r + 1) * r / 2 <= e) ++r;
-        const int c = e - r * (r - 1) / 2;
-        const int64_t o = (int64_t)k * tri + e;
-        const float g = (float)(-G[r][c]);
-        lbar[o] = accumulate ? lbar[o] + g : g;
+    __syncthreads();
+    for (int e = threadIdx.x; e < D * D; e += 16 * D) {
+        const int r = e / D, c = e % D;
+        if (c > r) continue;
+        double g = 0.0;
+#pragma unroll 4
+        for (int j = 0; j <= r; ++j) g += (double)Q[r][j] * S[j][c];
+        if (r == c) {
+            const int64_t o = (int64_t)k * D + c;
+            double s = 0.0;  // (Q_k^T v_k)_c = sum_{i >= c} Q[i][c] v[i]
+#pragma unroll 4
+            for (int i = c; i < D; ++i) s += (double)Q[i][c] * v[i];
+            mbar[o] = accumulate ? mbar[o] + (float)s : (float)s;
+            const double qd = W - (double)Q[c][c] * g;
+            qbar[o] = accumulate ? qbar[o] + (float)qd : (float)qd;
+        } else {
+            const int64_t o = (int64_t)k * tri + r * (r - 1) / 2 + c;
+            const float x = (float)(-g);
+            lbar[o] = accumulate ? lbar[o] + x : x;
+        }
     }
 }
 
 // ------------------------------------------------------------------ host
 struct GmmLayout {
-    size_t Qf, cvec, bias, scal, fparts, lse, gpart, vpart, wpart, total;
+    size_t Qf, cvec, bias, scal, fparts, lse, gpart, vpart, wpart, sred, msum, total;
     int64_t nch, chunk;
     unsigned fgrid;
+    int kper, ny;  // components per block row of the forward, rows
 };
 
 static GmmLayout gmm_layout(int64_t N, int D, int K) {
     GmmLayout L{};
     const int RT = D / 32;
     const int NF = 16 * RT * (RT + 1) / 2, NGT = RT * (RT + 1) / 2;
+    // About 4,096 blocks of at least 128 points.  Fewer are faster for small N
+    // (objective and gradient at N = 10,007, D = 32, K = 50 with 1,024, 2,048
+    // and 4,096: 89, 92 and 102 us) but lengthen the FP32 accumulation: with
+    // 1,024 the gradient's error there went from 1.3e-7 to 2.4e-7.
     int64_t target = 4096 / K;
     if (target < 1) target = 1;
     int64_t chunk = ceil_div(ceil_div(N > 0 ? N : 1, target), 128) * 128;
@@ -652,6 +719,15 @@ static GmmLayout gmm_layout(int64_t N, int D, int K) {
     L.chunk = chunk;
     L.nch = ceil_div(N > 0 ? N : 1, chunk);
     L.fgrid = (unsigned)ceil_div(N > 0 ? N : 1, 128);
+    // The forward takes a 128-point block through all components; with fewer
+    // than 1,024 such blocks (three fit a CU) the components are split too,
+    // in whole batches.
+    const int cpb = D == 64 ? 2 : 4;
+    const int64_t batches = ceil_div(K, cpb);
+    int64_t rows = ceil_div(1024, L.fgrid);
+    if (rows > batches) rows = batches;
+    L.kper = (int)(ceil_div(batches, rows) * cpb);
+    L.ny = (int)ceil_div(K, L.kper);
     size_t o = 0;
     auto take = [&](size_t bytes) {
         size_t at = o;
@@ -667,6 +743,8 @@ static GmmLayout gmm_layout(int64_t N, int D, int K) {
     L.gpart = take((size_t)K * L.nch * NGT * 1024 * 4);
     L.vpart = take((size_t)K * L.nch * D * 4);
     L.wpart = take((size_t)K * L.nch * 8);
+    L.sred = take((size_t)K * (NGT * 1024 + D + 1) * 8);
+    L.msum = take(L.ny > 1 ? (size_t)L.ny * (N > 0 ? N : 1) * 16 : 0);
     L.total = o;
     return L;
 }
@@ -683,9 +761,14 @@ template <int D>
 static void launch_fwd(const float* X, int64_t N, int K, char* ws, const GmmLayout& L, double* lse, double* sck,
                        double* loglik, hipStream_t st) {
     double* scal = reinterpret_cast<double*>(ws + L.scal + sizeof(GmmHdr));
-    hipLaunchKernelGGL(gmm_fwd_kernel<D>, dim3(L.fgrid), dim3(256), 0, st, X, N, K, (const float*)(ws + L.Qf),
-                       (const float*)(ws + L.cvec), (const double*)(ws + L.bias), (const double*)scal, lse, sck,
-                       (double*)(ws + L.fparts), (GmmHdr*)(ws + L.scal), loglik);
+    hipLaunchKernelGGL(gmm_fwd_kernel<D>, dim3(L.fgrid, L.ny), dim3(256), 0, st, X, N, K, L.kper,
+                       (const float*)(ws + L.Qf), (const float*)(ws + L.cvec), (const double*)(ws + L.bias),
+                       (const double*)scal, lse, sck, (double2*)(ws + L.msum), (double*)(ws + L.fparts),
+                       (GmmHdr*)(ws + L.scal), loglik);
+    if (L.ny > 1)
+        hipLaunchKernelGGL(gmm_lse_merge_kernel<D>, dim3((unsigned)ceil_div(N > 0 ? N : 1, 256)), dim3(256), 0, st, N,
+                           L.ny, (const double2*)(ws + L.msum), (const double*)scal, lse, (double*)(ws + L.fparts),
+                           (GmmHdr*)(ws + L.scal), loglik);
 }
 
 template <int D, bool FROM_S>
@@ -697,9 +780,11 @@ static void launch_bwd_t(const float* X, int64_t N, int K, const float* alpha, c
                        (int)L.nch, (const float*)(ws + L.Qf), (const float*)(ws + L.cvec), mu,
                        (const double*)(ws + L.bias), lse, sck, ell_bar, (float*)(ws + L.gpart),
                        (float*)(ws + L.vpart), (double*)(ws + L.wpart));
-    hipLaunchKernelGGL((gmm_param_kernel<D>), dim3(K), dim3(256), 0, st, N, K, (int)L.nch, alpha, q, l,
-                       (const double*)scal, ell_bar, (const float*)(ws + L.gpart), (const float*)(ws + L.vpart),
-                       (const double*)(ws + L.wpart), ab, mb, qb, lb, acc);
+    hipLaunchKernelGGL(gmm_reduce_kernel<D>, dim3(Gm<D>::NGT * 4 + 1, K), dim3(256), 0, st, (int)L.nch,
+                       (const float*)(ws + L.gpart), (const float*)(ws + L.vpart), (const double*)(ws + L.wpart),
+                       (double*)(ws + L.sred));
+    hipLaunchKernelGGL(gmm_param_kernel<D>, dim3(K), dim3(16 * D), 0, st, N, alpha, q, l, (const double*)scal, ell_bar,
+                       (const double*)(ws + L.sred), ab, mb, qb, lb, acc);
 }
 
 template <int D>

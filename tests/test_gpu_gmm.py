@@ -91,6 +91,26 @@ def test_gmm_several_point_chunks(ops, orc):
             assert err <= TOL_F32, (s, name, err)
 
 
+@pytest.mark.parametrize("N,D,K", [(127, 32, 4), (128, 64, 2), (129, 32, 9), (4095, 64, 3), (130944, 32, 7),
+                                   (130945, 32, 7)])
+def test_gmm_lse_over_component_ranges(ops, orc, N, D, K):
+    # up to 1,023 blocks of 128 points the objective splits the components
+    # over block rows and merges each point's (max, sum); one point more and
+    # a block takes all components.  K around whole batches of components.
+    X, alpha, mu, q, l = workloads.gmm(N, D, K, seed=7 * N + K)
+    ll, lse = ops.gmm_objective(dev(X), dev(alpha), dev(mu), dev(q), dev(l))
+    idx = np.unique(np.r_[0:min(N, 20), max(0, N - 20):N])
+    _, rlse = orc.gmm_objective(X[idx], alpha, mu, q, l)
+    assert rel_l2(host(lse)[idx], rlse) <= TOL_F32
+    from scipy.special import logsumexp
+
+    expect = host(lse).sum() - N * logsumexp(alpha.astype(np.float64)) - 0.5 * N * D * np.log(2 * np.pi)
+    assert abs(host(ll)[0] - expect) <= 1e-12 * abs(expect)
+    # weights over the components sum to one: so do the objective's alpha adjoints with the softmax term
+    ab = host(ops.gmm_vjp(dev(X), dev(alpha), dev(mu), dev(q), dev(l), lse=lse)[0])
+    assert abs(ab.sum()) <= TOL_F32 * N
+
+
 def test_gmm_vjp_without_checkpoint_and_accumulate(ops, orc):
     N, D, K = 500, 64, 6
     X, alpha, mu, q, l = workloads.gmm(N, D, K, seed=3)
