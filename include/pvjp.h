@@ -519,8 +519,9 @@ pvjp_status pvjp_seg_batch_vjp(pvjp_dtype dtype, const void* a, const void* b, c
 /*   loglik = sum_i LSE_k(s_ik) - N*LSE(alpha) - (N*D/2)*log(2*pi).            */
 /* X: N x D row-major FP32 (16-byte aligned); alpha [K]; mu, q: K x D; l:      */
 /* K x D(D-1)/2; all FP32.  D must be 32 or 64 (PVJP_EUNSUPPORTED otherwise).  */
-/* The contraction Q_k (x_i - mu_k) runs on FP32 MFMA; |z|^2, the log-sum-exp  */
-/* and all cross-tile sums are FP64.                                           */
+/* The contraction Q_k (x_i - mu_k) runs on FP32 MFMA, or from 2^17 points on  */
+/* bf16 MFMA with every FP32 operand as the exact sum of three bf16 values;    */
+/* |z|^2, the log-sum-exp and all cross-tile sums are FP64.                    */
 /* ------------------------------------------------------------------------ */
 
 size_t pvjp_gmm_ws_bytes(int64_t N, int D, int K);

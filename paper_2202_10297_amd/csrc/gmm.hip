@@ -590,14 +590,464 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
     }
 }
 
+// ------------------------------------------- large N: bf16 triples on MFMA
+// An FP32 value is exactly the sum of three bf16 values (8 bits of its
+// significand each, rounded to nearest, so the remainders have either sign):
+// x = h + m + l.  A product's terms hh, hm, mh, hl, lh, mm in bf16 MFMA with
+// FP32 accumulators leave out ml, lm, ll, below 2^-26 of it and of either
+// sign.  One 32x32x16 bf16 step takes 32 cycles, the eight 32x32x2 FP32 steps
+// it replaces 512, so six of them are 2.7 times faster.  Inputs, weights, the
+// sums over chunks, |z|^2 and the log-sum-exp keep their types.
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ f32x16 mfma16(bf16x8 a, bf16x8 b, f32x16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+
+// NV values (even) into three planes of packed pairs: a pair shares the
+// converting instruction, and each half is widened from the packed pair (a
+// shift, a mask).
+template <int NV>
+__device__ __forceinline__ void split(const float (&x)[NV], uint32_t (&o)[3][NV / 2]) {
+#pragma unroll
+    for (int i = 0; i < NV / 2; ++i) {
+        float a = x[2 * i], b = x[2 * i + 1];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            const bf16x2 v = {(__bf16)a, (__bf16)b};
+            const uint32_t u = __builtin_bit_cast(uint32_t, v);
+            o[q][i] = u;
+            a -= __builtin_bit_cast(float, u << 16);
+            b -= __builtin_bit_cast(float, u & 0xffff0000u);
+        }
+    }
+}
+__device__ __forceinline__ void split8(const float (&x)[8], bf16x8 (&p)[3]) {
+    uint32_t o[3][4];
+    split(x, o);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const u32x4 v = {o[q][0], o[q][1], o[q][2], o[q][3]};
+        p[q] = __builtin_bit_cast(bf16x8, v);
+    }
+}
+
+// The six terms in the order they are accumulated, small ones first.
+__device__ constexpr int kTermA[6] = {0, 2, 1, 0, 1, 0};
+__device__ constexpr int kTermB[6] = {2, 0, 1, 1, 0, 0};
+
+template <int D>
+struct Gs {
+    static constexpr int RT = D / 32;        // 32-row tiles of Q_k
+    static constexpr int KS = D / 16;        // 16-wide contraction steps over a full row
+    static constexpr int F = RT * (RT + 1);  // steps in the lower triangle (row tile rt needs 2 (rt + 1))
+    static constexpr int Q16 = F * 3 * 64;   // 16-byte fragments of a component
+    static constexpr int U16 = Q16 + D / 4;  // and its c_k in FP32
+};
+// A fragment of step s for row tile rt: lane l holds row 32 rt + l % 32,
+// columns 16 s + 8 (l / 32) + 0..7.
+__host__ __device__ constexpr int sidx(int rt, int s) { return rt * (rt + 1) + s; }
+
+// Q_k x of a wave's TL 32-point tiles.  qa(f, plane) and xb(tile, s, plane)
+// give the operand fragments.  Both sweeps run this sequence and
+// split_square's, so the return sweep recomputes the forward's s_ik bit for
+// bit.
+template <int D, int TL, class QA, class XB>
+__device__ __forceinline__ void split_qx(QA qa, XB xb, f32x16 (&acc)[Gs<D>::RT][TL]) {
+    using C = Gs<D>;
+#pragma unroll
+    for (int rt = 0; rt < C::RT; ++rt)
+#pragma unroll
+        for (int tl = 0; tl < TL; ++tl)
+#pragma unroll
+            for (int t = 0; t < 16; ++t) acc[rt][tl][t] = 0.f;
+#pragma unroll
+    for (int s = 0; s < C::KS; ++s) {
+        bf16x8 a[C::RT][3], b[TL][3];
+#pragma unroll
+        for (int pl = 0; pl < 3; ++pl) {
+#pragma unroll
+            for (int rt = 0; rt < C::RT; ++rt)
+                if (s < 2 * (rt + 1)) a[rt][pl] = qa(sidx(rt, s), pl);
+#pragma unroll
+            for (int tl = 0; tl < TL; ++tl) b[tl][pl] = xb(tl, s, pl);
+        }
+#pragma unroll
+        for (int q = 0; q < 6; ++q)
+#pragma unroll
+            for (int rt = 0; rt < C::RT; ++rt)
+#pragma unroll
+                for (int tl = 0; tl < TL; ++tl)
+                    if (s < 2 * (rt + 1)) acc[rt][tl] = mfma16(a[rt][kTermA[q]], b[tl][kTermB[q]], acc[rt][tl]);
+    }
+}
+
+// |z|^2, z = Q_k x - c_k, in FP64 (the difference too: started from -c_k the
+// FP32 accumulators lose more than the FP32 form did) of the lane's point:
+// point l % 32 of the tile, or with two tiles point l of the 64 (each half-wave
+// holds half of every point's rows).
+template <int D, int TL>
+__device__ __forceinline__ double split_square(const f32x16 (&acc)[Gs<D>::RT][TL], const float* cs) {
+    using C = Gs<D>;
+    const int h = (threadIdx.x >> 5) & 1;
+    double nrm[2] = {0.0, 0.0};
+#pragma unroll
+    for (int rt = 0; rt < C::RT; ++rt)
+#pragma unroll
+        for (int t4 = 0; t4 < 4; ++t4) {
+            const float4 c = *reinterpret_cast<const float4*>(cs + 32 * rt + 8 * t4 + 4 * h);
+            const double cv[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int tl = 0; tl < TL; ++tl) {
+                    const double z = (double)acc[rt][tl][4 * t4 + i] - cv[i];
+                    nrm[tl] = fma(z, z, nrm[tl]);
+                }
+        }
+    if (TL == 1) return nrm[0] + __shfl_xor(nrm[0], 32, kWave);
+    const bool up = threadIdx.x & 32;
+    return (up ? nrm[1] : nrm[0]) + __shfl_xor(up ? nrm[0] : nrm[1], 32, kWave);
+}
+
+// Q_k's fragments in three planes, followed by c_k: what a block stages per
+// component.
+template <int D>
+__global__ __launch_bounds__(256) void gmm_split_q_kernel(const float* __restrict__ q, const float* __restrict__ l,
+                                                          const float* __restrict__ cvec, bf16x8* __restrict__ Qs) {
+    using C = Gs<D>;
+    const int64_t k = blockIdx.x;
+    const int64_t tri = (int64_t)D * (D - 1) / 2;
+    for (int e = threadIdx.x; e < C::F * 64; e += 256) {
+        const int f = e / 64, lane = e % 64;
+        const int rt = f < 2 ? 0 : 1, s = f - sidx(rt, 0);
+        const int r = 32 * rt + (lane & 31), c0 = 16 * s + 8 * (lane >> 5);
+        float x[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int c = c0 + i;
+            x[i] = 0.f;
+            if (r == c)
+                x[i] = (float)exp((double)q[k * D + r]);
+            else if (r > c)
+                x[i] = l[k * tri + r * (r - 1) / 2 + c];
+        }
+        bf16x8 p[3];
+        split8(x, p);
+#pragma unroll
+        for (int pl = 0; pl < 3; ++pl) Qs[k * C::U16 + (f * 3 + pl) * 64 + lane] = p[pl];
+    }
+    if (threadIdx.x < D)
+        reinterpret_cast<float*>(Qs + k * C::U16 + C::Q16)[threadIdx.x] = cvec[k * D + threadIdx.x];
+}
+
+// Forward: a wave keeps 64 points' X fragments in registers (split once) and
+// takes its block row's components one after another, their Q fragments and
+// c_k staged in LDS for the block's four waves, the next component's loaded
+// while this one computes.  Bound by the bf16 matrix pipe (2,304 cycles for 64
+// points and a component at D = 64, 75% busy) at the 1.75 GHz the card holds
+// under it: N = 10^6, D = 64, K = 200 in 5.4 ms (12.1 in FP32 MFMA), 1.35
+// PFLOP/s of bf16 where a large library product of random matrices reaches
+// 1.2.
+template <int D>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void gmm_fwd_split_kernel(
+    const float* __restrict__ X, int64_t N, int K, int kper, const bf16x8* __restrict__ Qs,
+    const double* __restrict__ bias, const double* __restrict__ lse_alpha, double* __restrict__ lse,
+    double* __restrict__ sck, double2* __restrict__ msum, double* parts, GmmHdr* hdr, double* loglik) {
+    using C = Gs<D>;
+    constexpr int TOT = C::U16;  // 16-byte units staged per component
+    constexpr int PER = (TOT + 255) / 256;
+    __shared__ u32x4 st[2][TOT];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t p0 = ((int64_t)blockIdx.x * 4 + w) * 64;
+    const int kbeg = blockIdx.y * kper, kend = min(K, kbeg + kper);
+
+    u32x4 nxt[PER];
+    auto fetch = [&](int k) {
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int e = min(u * 256 + (int)threadIdx.x, TOT - 1);
+            nxt[u] = reinterpret_cast<const u32x4*>(Qs)[(int64_t)k * TOT + e];
+        }
+    };
+    auto put = [&](int b) {
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int e = u * 256 + (int)threadIdx.x;
+            if (e < TOT) st[b][e] = nxt[u];
+        }
+    };
+    fetch(kbeg);
+    bf16x8 xf[2][C::KS][3];
+#pragma unroll
+    for (int tl = 0; tl < 2; ++tl) {
+        const int64_t p = p0 + 32 * tl + (lane & 31);
+#pragma unroll
+        for (int s = 0; s < C::KS; ++s) {
+            float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            if (p < N) {
+                const float4* src = reinterpret_cast<const float4*>(X + p * D + 16 * s + 8 * (lane >> 5));
+                const float4 u = src[0], v = src[1];
+                x[0] = u.x, x[1] = u.y, x[2] = u.z, x[3] = u.w;
+                x[4] = v.x, x[5] = v.y, x[6] = v.z, x[7] = v.w;
+            }
+            split8(x, xf[tl][s]);
+        }
+    }
+    put(0);
+    const int64_t p = p0 + lane;
+    double m = -INFINITY, ssum = 0.0;
+    for (int k = kbeg; k < kend; ++k) {
+        const int b = (k - kbeg) & 1;
+        if (k + 1 < kend) fetch(k + 1);
+        __syncthreads();  // buffer b is filled, and the other one no longer read
+        const bf16x8* qf = reinterpret_cast<const bf16x8*>(st[b]);
+        f32x16 acc[C::RT][2];
+        split_qx<D, 2>([&](int f, int pl) { return qf[(f * 3 + pl) * 64 + lane]; },
+                       [&](int tl, int s, int pl) { return xf[tl][s][pl]; }, acc);
+        const double sv = bias[k] - 0.5 * split_square<D, 2>(acc, reinterpret_cast<const float*>(&st[b][C::Q16]));
+        if (k + 1 < kend) put(b ^ 1);
+        if (sck && p < N) sck[(int64_t)k * N + p] = sv;
+        lse_step(sv, m, ssum);
+    }
+    if (gridDim.y > 1) {
+        if (p < N) msum[(int64_t)blockIdx.y * N + p] = make_double2(m, ssum);
+        return;
+    }
+    const double l_i = m + log(ssum);
+    if (p < N && lse) lse[p] = l_i;
+    finish_loglik(p < N ? l_i : 0.0, N, D, lse_alpha, parts, hdr, loglik);
+}
+
+// 2x for the bf16 pairs of a remainder plane: one on each exponent (a zero
+// becomes 2^-126, which is nothing beside the leading plane's product; where
+// the value is not finite that product is not either).
+__device__ __forceinline__ bf16x8 twice(bf16x8 v) {
+    u32x4 u = __builtin_bit_cast(u32x4, v);
+    u += 0x00800080u;
+    return __builtin_bit_cast(bf16x8, u);
+}
+
+// Return sweep: a wave per component, eight to a block, all on the block's
+// stream of tiles (32 points at D = 64, 64 at D = 32; loaded two tiles ahead,
+// split once, kept in LDS as B fragments and as X^T).  Each wave keeps Q_k's
+// leading plane and the lower blocks of S_k in registers: s_ik as in the
+// forward, then S_k += V^T V with the rows v_i = sqrt(w_i) (x_i - mu_k), whose
+// fragments serve as both operands (a lane holds one dimension of eight
+// points either way).  On a diagonal block hm + mh and hl + lh are taken as
+// h (2m) and h (2l), whose symmetric part is the same; the parameter kernel
+// takes that part.  A tile's product is summed from zero and then added to
+// S_k: one FP32 rounding of the long sum per tile (one per 2 points in the
+// FP32 form, over at most 4,096 points against 32,768 here; accumulated in
+// place over 4,096 points q_bar's error was 1.4e-6 against 1.4e-7).  A 32-point
+// tile and component take 2,048 MFMA cycles and about as many of vector work
+// (forming and splitting v, squares, weights), which hardly overlap: a wave
+// waiting to issue an MFMA keeps the other wave's vector instructions from
+// issuing.  N = 10^6, D = 64, K = 200: 26.5 -> 13.0 ms.
+template <int D, bool FROM_S>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void gmm_bwd_split_kernel(
+    const float* __restrict__ X, int64_t N, int K, int64_t chunk, int nch, const bf16x8* __restrict__ Qs,
+    const float* __restrict__ mu, const double* __restrict__ bias, const double* __restrict__ lse,
+    const double* __restrict__ sck, float* __restrict__ gpart, float* __restrict__ vpart,
+    double* __restrict__ wpart) {
+    using C = Gs<D>;
+    constexpr int RT = C::RT, NGT = Gm<D>::NGT;
+    constexpr int TL = 2 / RT;  // 32-point tiles taken at once
+    constexpr int NP = 32 * TL;  // points per tile: 2,048 values of X, four to a thread
+    constexpr int XT = NP + 4;      // the pad spreads the 16-byte column reads over the banks
+    constexpr int NV = 2 * TL;   // 16-point contraction steps per tile
+    __shared__ bf16x8 xp[FROM_S ? 1 : 2][TL][C::KS][3][64];
+    __shared__ bf16x8 ql[FROM_S ? 1 : 8][C::F][2][64];  // the two lower planes of each wave's Q_k
+    __shared__ __align__(16) float xt[3][D][XT];
+    __shared__ __align__(16) float sws[8][NP];
+    __shared__ __align__(16) float cs[8][D];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int j = lane & 31, h = lane >> 5;
+    const int groups = (K + 7) / 8;
+    const int ch = blockIdx.x / groups;
+    const int k = (blockIdx.x % groups) * 8 + w;
+    const int kk = min(k, K - 1);  // the last group's spare waves repeat a component and write nothing
+    const int64_t cbeg = (int64_t)ch * chunk, cend = min(N, cbeg + chunk);
+
+    bf16x8 qa[C::F];
+    if (!FROM_S) {
+        const bf16x8* src = Qs + (int64_t)kk * C::U16;
+#pragma unroll
+        for (int f = 0; f < C::F; ++f) {
+            qa[f] = src[f * 3 * 64 + lane];
+#pragma unroll
+            for (int pl = 1; pl < 3; ++pl) ql[w][f][pl - 1][lane] = src[(f * 3 + pl) * 64 + lane];
+        }
+        if (lane < D) cs[w][lane] = reinterpret_cast<const float*>(src + C::Q16)[lane];
+    }
+    float mub[RT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) mub[rt] = mu[(int64_t)kk * D + 32 * rt + j];
+    const double bk = bias[kk];
+
+    f32x16 S[NGT];
+#pragma unroll
+    for (int g = 0; g < NGT; ++g)
+#pragma unroll
+        for (int t = 0; t < 16; ++t) S[g][t] = 0.f;
+    float u[RT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) u[rt] = 0.f;
+    double wsum = 0.0;
+
+    // A thread loads four dimensions of one point.
+    const int lp = threadIdx.x % NP, lg = threadIdx.x / NP;
+    const int wp = lane & (NP - 1);  // the point whose weight this lane forms
+    float4 xn;
+    double lse_n = 0.0, s_n = 0.0;
+    auto fetch = [&](int64_t pb) {
+        xn = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (pb + lp < N) xn = *reinterpret_cast<const float4*>(X + (pb + lp) * D + 4 * lg);
+    };
+    auto fetch_lse = [&](int64_t pb) {
+        const int64_t p = min(pb + wp, N - 1);
+        lse_n = lse[p];
+        if (FROM_S) s_n = sck[(int64_t)kk * N + p];
+    };
+    auto put = [&](int b, int b3) {
+        const float x[4] = {xn.x, xn.y, xn.z, xn.w};
+        if (!FROM_S) {
+            uint32_t o[3][2];
+            split(x, o);
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+                reinterpret_cast<uint2*>(&xp[b][lp >> 5][lg >> 2][q][(lp & 31) + 32 * ((lg >> 1) & 1)])[lg & 1] =
+                    make_uint2(o[q][0], o[q][1]);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) xt[b3][4 * lg + i][lp] = x[i];
+    };
+    f32x16 acc[C::RT][TL];
+    auto form_z = [&](int b) {
+        split_qx<D, TL>([&](int f, int pl) { return pl == 0 ? qa[f] : ql[w][f][pl - 1][lane]; },
+                        [&](int tl, int s, int pl) { return xp[b][tl][s][pl][lane]; }, acc);
+    };
+    // sqrt(w_i) of the tile at pb into the wave's row of sws.
+    auto weights = [&](int64_t pb) {
+        const double sv = FROM_S ? s_n : bk - 0.5 * split_square<D, TL>(acc, cs[w]);
+        const double e = exp(0.5 * (sv - lse_n));
+        const double swd = pb + wp < cend ? e : 0.0;
+        wsum = fma(swd, swd, wsum);
+        return swd;
+    };
+    auto keep = [&](double swd) {
+        wave_lds_sync();
+        sws[w][wp] = (float)swd;  // with 32 points both half-waves write the same value
+        wave_lds_sync();
+    };
+    const int tiles = (int)((cend - cbeg + NP - 1) / NP);
+    fetch(cbeg);
+    put(0, 0);
+    fetch(cbeg + NP);
+    put(1, 1);
+    fetch_lse(cbeg);
+    __syncthreads();
+    if (!FROM_S) form_z(0);
+    keep(weights(cbeg));
+    int b3 = 0;  // tile it is in buffer it % 3 of xt
+    for (int it = 0; it < tiles; ++it) {
+        const int64_t pb = cbeg + (int64_t)it * NP;
+        fetch(pb + 2 * NP);
+        fetch_lse(pb + NP);
+        __builtin_amdgcn_sched_barrier(0);
+        // the next tile's z (past the last tile the buffers hold an old one,
+        // and its weights are zero), then this tile's v
+        if (!FROM_S) form_z((it + 1) & 1);
+        bf16x8 vf[NV][RT][3];
+        float us[RT];
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) us[rt] = 0.f;
+#pragma unroll
+        for (int s = 0; s < NV; ++s) {
+            const int at = 16 * s + 8 * h;
+            const float4 s0 = *reinterpret_cast<const float4*>(&sws[w][at]);
+            const float4 s1 = *reinterpret_cast<const float4*>(&sws[w][at + 4]);
+            const float sq[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                const float4 x0 = *reinterpret_cast<const float4*>(&xt[b3][32 * rt + j][at]);
+                const float4 x1 = *reinterpret_cast<const float4*>(&xt[b3][32 * rt + j][at + 4]);
+                const float xv[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+                float v[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    v[i] = sq[i] * (xv[i] - mub[rt]);
+                    us[rt] = fmaf(sq[i], v[i], us[rt]);
+                }
+                split8(v, vf[s][rt]);
+            }
+        }
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) u[rt] += us[rt];
+        __builtin_amdgcn_sched_barrier(0);
+        // its contraction, then the next tile's weights
+        f32x16 tmp[NGT];
+#pragma unroll
+        for (int g = 0; g < NGT; ++g)
+#pragma unroll
+            for (int t = 0; t < 16; ++t) tmp[g][t] = 0.f;
+#pragma unroll
+        for (int s = 0; s < NV; ++s)
+#pragma unroll
+            for (int q = 0; q < 6; ++q) {
+                int g = 0;
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                    for (int ct = 0; ct <= rt; ++ct, ++g) {
+                        if (ct < rt)
+                            tmp[g] = mfma16(vf[s][rt][kTermA[q]], vf[s][ct][kTermB[q]], tmp[g]);
+                        else if (kTermA[q] == kTermB[q])
+                            tmp[g] = mfma16(vf[s][rt][kTermA[q]], vf[s][rt][kTermB[q]], tmp[g]);
+                        else if (kTermA[q] == 0)
+                            tmp[g] = mfma16(vf[s][rt][0], twice(vf[s][rt][kTermB[q]]), tmp[g]);
+                    }
+            }
+        const double swd = weights(pb + NP);
+#pragma unroll
+        for (int g = 0; g < NGT; ++g)
+#pragma unroll
+            for (int t = 0; t < 16; ++t) S[g][t] += tmp[g][t];
+        __builtin_amdgcn_sched_barrier(0);
+        keep(swd);
+        b3 = b3 == 2 ? 0 : b3 + 1;
+        put(it & 1, b3 == 2 ? 0 : b3 + 1);  // tile it + 2
+        __syncthreads();
+    }
+
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) u[rt] += __shfl_xor(u[rt], 32, kWave);
+    if (lane >= NP) wsum = 0.0;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) wsum += __shfl_xor(wsum, d, kWave);
+    if (k >= K) return;
+    const int64_t rec = (int64_t)k * nch + ch;
+#pragma unroll
+    for (int g = 0; g < NGT; ++g)
+#pragma unroll
+        for (int t = 0; t < 16; ++t) gpart[(rec * NGT * 16 + g * 16 + t) * 64 + lane] = S[g][t];
+    if (lane < 32) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) vpart[rec * D + 32 * rt + j] = u[rt];
+    }
+    if (lane == 0) wpart[rec] = wsum;
+}
+
 // ------------------------------------------------------ reduce + parameters
 // The chunks' partials of S_k (lower 32x32 blocks), u_k and W_k summed in FP64
-// in chunk order, into sred[k][NGT * 1024 + D + 1].  A thread per entry, all
+// in chunk order, times `scale`, into sred[k][NGT * 1024 + D + 1].  A thread per entry, all
 // components at once: done by the K blocks of the parameter kernel the chunk
 // loop was the longest part of a small gradient (N = 10,007, D = 32, K = 50:
 // 127 us for both, now 5 + 7; N = 10^6, D = 64, K = 200: 363, now 27 + 20).
 template <int D>
-__global__ __launch_bounds__(256) void gmm_reduce_kernel(int nch, const float* __restrict__ gpart,
+__global__ __launch_bounds__(256) void gmm_reduce_kernel(int nch, double scale, const float* __restrict__ gpart,
                                                          const float* __restrict__ vpart,
                                                          const double* __restrict__ wpart,
                                                          double* __restrict__ sred) {
@@ -618,7 +1068,7 @@ __global__ __launch_bounds__(256) void gmm_reduce_kernel(int nch, const float* _
 #pragma unroll 8
         for (int c = 0; c < nch; ++c) s += wpart[k * nch + c];
     }
-    sred[k * (NG + D + 1) + e] = s;
+    sred[k * (NG + D + 1) + e] = scale * s;
 }
 
 // G_k = Q_k S_k (the entries the adjoints read: r >= c), v_k = Q_k u_k and the
@@ -629,9 +1079,10 @@ template <int D>
 __global__ __launch_bounds__(16 * D) void gmm_param_kernel(int64_t N, const float* __restrict__ alpha,
                                                         const float* __restrict__ q, const float* __restrict__ l,
                                                         const double* __restrict__ lse_alpha, double ell_bar,
-                                                        const double* __restrict__ sred, float* __restrict__ abar,
-                                                        float* __restrict__ mbar, float* __restrict__ qbar,
-                                                        float* __restrict__ lbar, int accumulate) {
+                                                        const double* __restrict__ sred, int sym,
+                                                        float* __restrict__ abar, float* __restrict__ mbar,
+                                                        float* __restrict__ qbar, float* __restrict__ lbar,
+                                                        int accumulate) {
     constexpr int NG = Gm<D>::NGT * 1024;
     const int k = blockIdx.x;
     const int64_t tri = (int64_t)D * (D - 1) / 2;
@@ -641,13 +1092,27 @@ __global__ __launch_bounds__(16 * D) void gmm_param_kernel(int64_t N, const floa
     const double* src = sred + (int64_t)k * (NG + D + 1);
     for (int e = threadIdx.x; e < NG; e += 16 * D) {
         // block g of the lower triangle: (0,0), (1,0), (1,1); the off-diagonal
-        // one is mirrored, the diagonal ones are whole
+        // one is mirrored, the diagonal ones are whole (with sym their
+        // symmetric part is S_k, otherwise their lower half)
         const int g = e / 1024, t = (e / 64) % 16, lane = e % 64;
         const int rt = g > 0, ct = g > 1;
         const int r = 32 * rt + drow(t, lane), c = 32 * ct + (lane & 31);
-        if (g == 1 || r >= c) {
+        if (g == 1 || (r >= c && !sym)) {
             S[r][c] = src[e];
             S[c][r] = src[e];
+        } else if (sym) {
+            S[r][c] = src[e];
+        }
+    }
+    if (sym) {
+        __syncthreads();
+        for (int e = threadIdx.x; e < D * D; e += 16 * D) {
+            const int r = e / D, c = e % D;
+            if (r > c && (r ^ c) < 32) {
+                const double s = 0.5 * (S[r][c] + S[c][r]);
+                S[r][c] = s;
+                S[c][r] = s;
+            }
         }
     }
     if (threadIdx.x < D) u[threadIdx.x] = src[NG + threadIdx.x];
@@ -697,37 +1162,67 @@ __global__ __launch_bounds__(16 * D) void gmm_param_kernel(int64_t N, const floa
 
 // ------------------------------------------------------------------ host
 struct GmmLayout {
-    size_t Qf, cvec, bias, scal, fparts, lse, gpart, vpart, wpart, sred, msum, total;
+    size_t Qf, Qs, cvec, bias, scal, fparts, lse, gpart, vpart, wpart, sred, msum, total;
     int64_t nch, chunk;
     unsigned fgrid;
     int kper, ny;  // components per block row of the forward, rows
+    bool split;    // bf16 triples (large N) or FP32 MFMA
 };
+
+// From 2^17 points on the bf16 triples: N = 10^6, D = 64, K = 200 takes 18.6 ms
+// (objective and gradient) against 38.6 in FP32 MFMA.
+// Below, a call is a few hundred microseconds of which the matrix pipe is a
+// part only, and the FP64 log-likelihood of few points keeps the FP32 chains'
+// rounding (the two forms differ by about 5e-8 N^(-1/2) of it).  At least five
+// components keep most of a block's eight waves busy.
+static bool gmm_split(int64_t N, int K) { return N >= ((int64_t)1 << 17) && K >= 5; }
 
 static GmmLayout gmm_layout(int64_t N, int D, int K) {
     GmmLayout L{};
     const int RT = D / 32;
     const int NF = 16 * RT * (RT + 1) / 2, NGT = RT * (RT + 1) / 2;
-    // About 4,096 blocks of at least 128 points.  Fewer are faster for small N
-    // (objective and gradient at N = 10,007, D = 32, K = 50 with 1,024, 2,048
-    // and 4,096: 89, 92 and 102 us) but lengthen the FP32 accumulation: with
-    // 1,024 the gradient's error there went from 1.3e-7 to 2.4e-7.
-    int64_t target = 4096 / K;
-    if (target < 1) target = 1;
-    int64_t chunk = ceil_div(ceil_div(N > 0 ? N : 1, target), 128) * 128;
-    if (chunk > 16384) chunk = 16384;
-    if (chunk < 128) chunk = 128;
-    L.chunk = chunk;
-    L.nch = ceil_div(N > 0 ? N : 1, chunk);
-    L.fgrid = (unsigned)ceil_div(N > 0 ? N : 1, 128);
-    // The forward takes a 128-point block through all components; with fewer
-    // than 1,024 such blocks (three fit a CU) the components are split too,
-    // in whole batches.
-    const int cpb = D == 64 ? 2 : 4;
-    const int64_t batches = ceil_div(K, cpb);
-    int64_t rows = ceil_div(1024, L.fgrid);
-    if (rows > batches) rows = batches;
-    L.kper = (int)(ceil_div(batches, rows) * cpb);
-    L.ny = (int)ceil_div(K, L.kper);
+    L.split = gmm_split(N, K);
+    if (L.split) {
+        // One block of eight waves fits a CU: whole rounds of 256 blocks, as
+        // few of them as keep a chunk within 32,768 points (the FP32 sums).
+        const int64_t groups = ceil_div(K, 8);
+        for (int64_t r = 1;; ++r) {
+            const int64_t per = 256 * r / groups > 0 ? 256 * r / groups : 1;
+            L.chunk = ceil_div(ceil_div(N, per), 64) * 64;
+            if (L.chunk <= 32768) break;
+        }
+        L.nch = ceil_div(N, L.chunk);
+        // The forward's 256-point blocks, two a CU: component ranges of 16 or
+        // more until there are some eight rounds of them.
+        L.fgrid = (unsigned)ceil_div(N, 256);
+        int64_t rows = ceil_div(4096, L.fgrid);
+        if (rows > K / 16) rows = K / 16;
+        if (rows < 1) rows = 1;
+        L.kper = (int)ceil_div(K, rows);
+        L.ny = (int)ceil_div(K, L.kper);
+    } else {
+        // About 4,096 blocks of at least 128 points.  Fewer are faster for small N
+        // (objective and gradient at N = 10,007, D = 32, K = 50 with 1,024, 2,048
+        // and 4,096: 89, 92 and 102 us) but lengthen the FP32 accumulation: with
+        // 1,024 the gradient's error there went from 1.3e-7 to 2.4e-7.
+        int64_t target = 4096 / K;
+        if (target < 1) target = 1;
+        int64_t chunk = ceil_div(ceil_div(N > 0 ? N : 1, target), 128) * 128;
+        if (chunk > 16384) chunk = 16384;
+        if (chunk < 128) chunk = 128;
+        L.chunk = chunk;
+        L.nch = ceil_div(N > 0 ? N : 1, chunk);
+        L.fgrid = (unsigned)ceil_div(N > 0 ? N : 1, 128);
+        // The forward takes a 128-point block through all components; with fewer
+        // than 1,024 such blocks (three fit a CU) the components are split too,
+        // in whole batches.
+        const int cpb = D == 64 ? 2 : 4;
+        const int64_t batches = ceil_div(K, cpb);
+        int64_t rows = ceil_div(1024, L.fgrid);
+        if (rows > batches) rows = batches;
+        L.kper = (int)(ceil_div(batches, rows) * cpb);
+        L.ny = (int)ceil_div(K, L.kper);
+    }
     size_t o = 0;
     auto take = [&](size_t bytes) {
         size_t at = o;
@@ -736,6 +1231,7 @@ static GmmLayout gmm_layout(int64_t N, int D, int K) {
     };
     L.scal = take(sizeof(GmmHdr) + 256);  // header, lse_alpha, loglik scratch
     L.Qf = take((size_t)K * NF * 64 * 4);
+    L.Qs = take(L.split ? (size_t)K * (RT * (RT + 1) * 3 * 64 + D / 4) * 16 : 0);
     L.cvec = take((size_t)K * D * 4);
     L.bias = take((size_t)K * 8);
     L.fparts = take((size_t)L.fgrid * 8);
@@ -755,16 +1251,25 @@ static void launch_prep(const float* alpha, const float* mu, const float* q, con
     double* scal = reinterpret_cast<double*>(ws + L.scal + sizeof(GmmHdr));
     hipLaunchKernelGGL(gmm_prep_kernel<D>, dim3(K), dim3(256), 0, st, alpha, mu, q, l, K, (float*)(ws + L.Qf),
                        (float*)(ws + L.cvec), (double*)(ws + L.bias), scal);
+    if (L.split)
+        hipLaunchKernelGGL(gmm_split_q_kernel<D>, dim3(K), dim3(256), 0, st, q, l, (const float*)(ws + L.cvec),
+                           (bf16x8*)(ws + L.Qs));
 }
 
 template <int D>
 static void launch_fwd(const float* X, int64_t N, int K, char* ws, const GmmLayout& L, double* lse, double* sck,
                        double* loglik, hipStream_t st) {
     double* scal = reinterpret_cast<double*>(ws + L.scal + sizeof(GmmHdr));
-    hipLaunchKernelGGL(gmm_fwd_kernel<D>, dim3(L.fgrid, L.ny), dim3(256), 0, st, X, N, K, L.kper,
-                       (const float*)(ws + L.Qf), (const float*)(ws + L.cvec), (const double*)(ws + L.bias),
-                       (const double*)scal, lse, sck, (double2*)(ws + L.msum), (double*)(ws + L.fparts),
-                       (GmmHdr*)(ws + L.scal), loglik);
+    if (L.split)
+        hipLaunchKernelGGL(gmm_fwd_split_kernel<D>, dim3(L.fgrid, L.ny), dim3(256), 0, st, X, N, K, L.kper,
+                           (const bf16x8*)(ws + L.Qs), (const double*)(ws + L.bias),
+                           (const double*)scal, lse, sck, (double2*)(ws + L.msum), (double*)(ws + L.fparts),
+                           (GmmHdr*)(ws + L.scal), loglik);
+    else
+        hipLaunchKernelGGL(gmm_fwd_kernel<D>, dim3(L.fgrid, L.ny), dim3(256), 0, st, X, N, K, L.kper,
+                           (const float*)(ws + L.Qf), (const float*)(ws + L.cvec), (const double*)(ws + L.bias),
+                           (const double*)scal, lse, sck, (double2*)(ws + L.msum), (double*)(ws + L.fparts),
+                           (GmmHdr*)(ws + L.scal), loglik);
     if (L.ny > 1)
         hipLaunchKernelGGL(gmm_lse_merge_kernel<D>, dim3((unsigned)ceil_div(N > 0 ? N : 1, 256)), dim3(256), 0, st, N,
                            L.ny, (const double2*)(ws + L.msum), (const double*)scal, lse, (double*)(ws + L.fparts),
@@ -776,15 +1281,21 @@ static void launch_bwd_t(const float* X, int64_t N, int K, const float* alpha, c
                          const float* l, double ell_bar, const double* lse, const double* sck, float* ab, float* mb,
                          float* qb, float* lb, int acc, char* ws, const GmmLayout& L, hipStream_t st) {
     double* scal = reinterpret_cast<double*>(ws + L.scal + sizeof(GmmHdr));
-    hipLaunchKernelGGL((gmm_bwd_kernel<D, FROM_S>), dim3((unsigned)(K * L.nch)), dim3(256), 0, st, X, N, K, L.chunk,
-                       (int)L.nch, (const float*)(ws + L.Qf), (const float*)(ws + L.cvec), mu,
-                       (const double*)(ws + L.bias), lse, sck, ell_bar, (float*)(ws + L.gpart),
-                       (float*)(ws + L.vpart), (double*)(ws + L.wpart));
+    if (L.split)
+        hipLaunchKernelGGL((gmm_bwd_split_kernel<D, FROM_S>), dim3((unsigned)(ceil_div(K, 8) * L.nch)), dim3(512), 0,
+                           st, X, N, K, L.chunk, (int)L.nch, (const bf16x8*)(ws + L.Qs),
+                           mu, (const double*)(ws + L.bias), lse, sck, (float*)(ws + L.gpart),
+                           (float*)(ws + L.vpart), (double*)(ws + L.wpart));
+    else
+        hipLaunchKernelGGL((gmm_bwd_kernel<D, FROM_S>), dim3((unsigned)(K * L.nch)), dim3(256), 0, st, X, N, K,
+                           L.chunk, (int)L.nch, (const float*)(ws + L.Qf), (const float*)(ws + L.cvec), mu,
+                           (const double*)(ws + L.bias), lse, sck, ell_bar, (float*)(ws + L.gpart),
+                           (float*)(ws + L.vpart), (double*)(ws + L.wpart));
     hipLaunchKernelGGL(gmm_reduce_kernel<D>, dim3(Gm<D>::NGT * 4 + 1, K), dim3(256), 0, st, (int)L.nch,
-                       (const float*)(ws + L.gpart), (const float*)(ws + L.vpart), (const double*)(ws + L.wpart),
+                       L.split ? ell_bar : 1.0, (const float*)(ws + L.gpart), (const float*)(ws + L.vpart), (const double*)(ws + L.wpart),
                        (double*)(ws + L.sred));
     hipLaunchKernelGGL(gmm_param_kernel<D>, dim3(K), dim3(16 * D), 0, st, N, alpha, q, l, (const double*)scal, ell_bar,
-                       (const double*)(ws + L.sred), ab, mb, qb, lb, acc);
+                       (const double*)(ws + L.sred), (int)L.split, ab, mb, qb, lb, acc);
 }
 
 template <int D>

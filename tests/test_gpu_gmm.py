@@ -111,6 +111,32 @@ def test_gmm_lse_over_component_ranges(ops, orc, N, D, K):
     assert abs(ab.sum()) <= TOL_F32 * N
 
 
+@pytest.mark.parametrize("N,D,K", [(131072, 64, 5), (131073, 32, 8), (131135, 64, 9), (200001, 32, 17),
+                                   (262143, 64, 33)])
+def test_gmm_large_n_form(ops, orc, N, D, K):
+    # from 2^17 points the contractions run as bf16 triples: around a tile, a
+    # block of eight components and a component range.  LSE_i against the oracle
+    # on sampled points; the gradient against the sum over two parts, which are
+    # short enough for the FP32 form (each side within TOL_F32, so twice that).
+    X, alpha, mu, q, l = workloads.gmm(N, D, K, seed=N + K)
+    Xd, P = dev(X), [dev(a) for a in (alpha, mu, q, l)]
+    ll, lse, sck = ops.gmm_objective_ckpt(Xd, *P)
+    idx = np.unique(np.r_[0:10, N // 2:N // 2 + 10, N - 40:N])
+    _, rlse = orc.gmm_objective(X[idx], alpha, mu, q, l)
+    assert rel_l2(host(lse)[idx], rlse) <= TOL_F32
+    cut = [0, 100001, min(N, 220001), N] if N > 231071 else [0, 100001, N]
+    parts = [[host(g) for g in ops.gmm_vjp(dev(X[a:b]), *P, ell_bar=-0.75)] for a, b in zip(cut, cut[1:]) if b > a]
+    ref = [sum(p[i].astype(np.float64) for p in parts) for i in range(4)]
+    base = [workloads.rng(i).standard_normal(a.shape).astype(np.float32) for i, a in enumerate((alpha, mu, q, l))]
+    for s in (None, sck):
+        out = tuple(dev(b) for b in base)
+        ops.gmm_vjp(Xd, *P, lse=lse, s=s, ell_bar=-0.75, out=out, accumulate=True)
+        got = ops.gmm_vjp(Xd, *P, lse=lse, s=s, ell_bar=-0.75)
+        for g, o, b, r in zip(got, out, base, ref):
+            assert rel_l2(host(g), r) <= 2 * TOL_F32
+            assert rel_l2(host(o), b + r) <= 2 * TOL_F32
+
+
 def test_gmm_vjp_without_checkpoint_and_accumulate(ops, orc):
     N, D, K = 500, 64, 6
     X, alpha, mu, q, l = workloads.gmm(N, D, K, seed=3)
