@@ -6,24 +6,31 @@
 // The operator need not commute, so each bin's elements must meet in index
 // order:
 //   1. a stable sort of the in-range elements by bin: passes of up to 8 bits
-//      (9 for large records when that saves a pass; the bin's bits split evenly), low digit first, each a per-chunk digit
-//      count, a digit-major scan of the counts and a stable scatter staged in
-//      LDS (ranks among equal digits from wave ballots, so equal bins keep
-//      their order; each digit's records leave as contiguous runs).  The sort
-//      moves whole records -- bin, element index and the element's
-//      components -- so x is read once, in index order, instead of gathered
-//      at random into sorted order;
-//   2. bin starts, by binary search of the sorted bins;
-//   3. over the sorted elements, segmented exclusive scans: forward (the
-//      fold of the bin's earlier elements, ls) and reversed (of its later
-//      ones, rs), with the usual lifted operator that restarts at a flagged
-//      element (a bin's first element forward, its last one reversed), over
-//      fixed tiles: tile folds, the tiles' carries (a wave per 64 tiles, one
-//      block over the groups, a wave per group again), then per tile the
-//      in-tile scans with the tile's carry;
-//   4. the primal writes each bin's fold at its last element; the VJP maps
-//      f(ls, x, rs, hs_bar[bin]) (the reduce rule, y_bar = the bin's hs_bar)
-//      over the sorted elements and writes it at the element's own index.
+//      (9 when that saves a pass; the bin's bits split evenly), low digit
+//      first, each a per-chunk digit count, a digit-major scan of the counts
+//      and a stable scatter staged in LDS (ranks among equal digits from wave
+//      ballots, so equal bins keep their order; each digit's records leave as
+//      contiguous runs).  The sort moves whole records -- bin and components
+//      -- so x is read once, in index order, instead of gathered at random
+//      into sorted order.  For the VJP each pass also keeps where every one of
+//      its records went;
+//   2. over the sorted elements, segmented exclusive scans: forward (the
+//      fold of the bin's earlier elements, ls) and, for the VJP, reversed (of
+//      its later ones, rs), with the usual lifted operator that restarts at a
+//      flagged element (a bin's first element forward, its last one
+//      reversed), over fixed tiles: tile folds, the tiles' carries (a wave per
+//      64 tiles, one block over the groups, a wave per group again), then per
+//      tile the in-tile scans with the tile's carry;
+//   3. the primal writes each bin's fold at its last element (over the neutral
+//      element, which empty bins keep); the VJP maps f(ls, x, rs, hs_bar[bin])
+//      (the reduce rule, y_bar = the bin's hs_bar) over the sorted elements;
+//   4. the VJP's adjoints, in sorted order, go back through the passes'
+//      positions, last pass first: each step gathers in the order the pass
+//      read its records, so it reads the runs that the pass wrote (a block's
+//      2,048 records are some 64 bytes each from 256 places) and writes in
+//      order.  Storing each adjoint at its element's index from sorted order
+//      instead is K scattered words an element (2^24 elements, K = 2: 468 us;
+//      the two steps back take 235).
 // Folds are formed in FP64 for FP32 and FP64 data alike.
 #include <algorithm>
 
@@ -33,35 +40,49 @@
 
 namespace pvjp {
 
-// Row length of the per-chunk digit counts (a pass uses at most
-// kHgPassDigits of a row's entries).
-constexpr int kHgDigitBits = 12;
-constexpr int kHgDigits = 1 << kHgDigitBits;
-constexpr int64_t kHgChunk = 32768;  // elements per sort chunk (one block)
+constexpr int kHgDigits = 512;  // row length of the per-chunk digit counts
 constexpr int kHgCountBlock = 256;
 constexpr int kHgColChunk = 64;      // sort chunks per column-scan chunk
-constexpr int kHgScanThreads = 1024;
+constexpr int kHgScanThreads = 512;  // at 1,024 the two directions' FP64 states spill
 constexpr int kHgBlock = 256;
-constexpr int kHgIpt = 2;  // of 1, 2, 4, 8: 2 the fastest (adjacent lanes 32 bytes apart)
-constexpr int kHgTile = kHgBlock * kHgIpt;
+// Sorted elements per thread of the tile kernels.  Objective and VJP at 2^24
+// FP32, m = 2^16 with 2, 4 and 8: linear recurrence 1.28, 1.25, 1.40 ms, 2x2
+// product 2.12, 2.06, 2.30 ms; the FP64 2x2 product's 36-byte records are
+// faster with 2 (n = 9,000,003, m = 300: 1.11, 1.24, 1.44 ms).
+constexpr int hg_ipt(size_t rec_bytes) { return rec_bytes <= 20 ? 4 : 2; }
 constexpr size_t kHgSlot = 64;       // bytes per tile for a lifted state
 constexpr int64_t kHgMaxBins = (int64_t)1 << 24;  // three sort passes of 8 bits
 
-// A sort record: word 0 the bin, word 1 the element index, from word 2 the
-// element's K components (T each), padded to whole 16-byte vectors so that a
-// record moves with full-width loads and stores.
+// A sort record: word 0 the bin, from word 1 the element's K components (T
+// each, as words).
 template <int W>
-struct alignas(16) HgRec {
+struct HgRec {
     uint32_t w[W];
 };
 template <class T, int K>
 constexpr int hg_words() {
-    return (2 + K * (int)(sizeof(T) / 4) + 3) / 4 * 4;
+    return 1 + K * (int)(sizeof(T) / 4);
 }
 template <class T, int W>
 __device__ __forceinline__ T hg_comp(const HgRec<W>& r, int k) {
-    return reinterpret_cast<const T*>(&r.w[2])[k];
+    if constexpr (sizeof(T) == 4) return __builtin_bit_cast(T, r.w[1 + k]);
+    else return __builtin_bit_cast(T, ((uint64_t)r.w[2 + 2 * k] << 32) | r.w[1 + 2 * k]);
 }
+template <class T, int W>
+__device__ __forceinline__ void hg_set_comp(HgRec<W>& r, int k, T v) {
+    if constexpr (sizeof(T) == 4) r.w[1 + k] = __builtin_bit_cast(uint32_t, v);
+    else {
+        const uint64_t b = __builtin_bit_cast(uint64_t, v);
+        r.w[1 + 2 * k] = (uint32_t)b;
+        r.w[2 + 2 * k] = (uint32_t)(b >> 32);
+    }
+}
+
+// One element's K adjoints, as they lie in sorted order.
+template <class T, int K>
+struct alignas(K * sizeof(T) < 16 ? K * sizeof(T) : 16) HgAdj {
+    T c[K];
+};
 
 // Up to four component arrays of one dtype.
 template <class T>
@@ -75,23 +96,32 @@ struct HgOut {
 
 // ------------------------------------------------------------------ sort
 // Digit counts of one chunk (any order: counting needs no stability).  The
-// first pass reads the indices (out-of-range ones skipped), the second the
-// first pass's output, whose length is on the device.
+// first pass reads the indices (out-of-range ones skipped), the later ones the
+// pass before's output, whose length is on the device.
 template <int W>
 __global__ __launch_bounds__(kHgCountBlock) void hg_count_kernel(const int32_t* __restrict__ keys,
                                                                  const HgRec<W>* __restrict__ recs, int64_t n,
-                                                                 const int32_t* __restrict__ nvalid, int32_t m,
-                                                                 int shift, int dmask, int ndig,
+                                                                 const int32_t* __restrict__ nvalid, int chunk,
+                                                                 int32_t m, int shift, int dmask, int ndig,
                                                                  int32_t* __restrict__ cntb) {
+    constexpr int U = 8;  // loads in flight per thread
     __shared__ int32_t cnt[kHgDigits];
     for (int d = threadIdx.x; d < ndig; d += kHgCountBlock) cnt[d] = 0;
     __syncthreads();
     const int64_t ne = nvalid ? (int64_t)*nvalid : n;
-    const int64_t lo = (int64_t)blockIdx.x * kHgChunk;
-    const int64_t hi = (lo + kHgChunk < ne) ? lo + kHgChunk : ne;
-    for (int64_t i = lo + threadIdx.x; i < hi; i += kHgCountBlock) {
-        const int32_t k = keys ? keys[i] : (int32_t)recs[i].w[0];
-        if ((uint32_t)k < (uint32_t)m) atomicAdd(&cnt[(k >> shift) & dmask], 1);
+    const int64_t lo = (int64_t)blockIdx.x * chunk;
+    const int64_t hi = (lo + chunk < ne) ? lo + chunk : ne;
+    for (int64_t i0 = lo + threadIdx.x; i0 < hi; i0 += U * kHgCountBlock) {
+        int32_t k[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t i = i0 + u * kHgCountBlock < hi ? i0 + u * kHgCountBlock : hi - 1;
+            k[u] = keys ? keys[i] : (int32_t)recs[i].w[0];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i0 + u * kHgCountBlock < hi && (uint32_t)k[u] < (uint32_t)m)
+                atomicAdd(&cnt[(k[u] >> shift) & dmask], 1);
     }
     __syncthreads();
     for (int d = threadIdx.x; d < ndig; d += kHgCountBlock) cntb[(int64_t)blockIdx.x * kHgDigits + d] = cnt[d];
@@ -121,38 +151,36 @@ __global__ __launch_bounds__(kHgCountBlock) void hg_colscan_kernel(int32_t* __re
     ctot[(int64_t)c * kHgDigits + d] = run;
 }
 
-// One block: ctot[c][d] becomes the start of (column chunk c, digit d) in the
-// sorted output (the digit's start plus its earlier column chunks), and the
-// number of sorted elements is written once.
-__global__ __launch_bounds__(kHgScanThreads) void hg_digitscan_kernel(int32_t* __restrict__ ctot, int nchunks,
-                                                                      int ndig, int32_t* __restrict__ nvalid) {
-    __shared__ IntSum::S wtot[kHgScanThreads / kWave];
-    constexpr int DPT = kHgDigits / kHgScanThreads;
-    int tot[DPT], sum = 0;
+// One block, a thread per digit: ctot[c][d] becomes the start of (column chunk
+// c, digit d) in the sorted output (the digit's start plus its earlier column
+// chunks), and the number of sorted elements is written once.
+__global__ __launch_bounds__(kHgDigits) void hg_digitscan_kernel(int32_t* __restrict__ ctot, int nchunks, int ndig,
+                                                                 int32_t* __restrict__ nvalid) {
+    __shared__ IntSum::S wtot[kHgDigits / kWave];
+    constexpr int U = 16;  // loads in flight
+    const int d = threadIdx.x;
+    int sum = 0;
+    if (d < ndig)
+        for (int c0 = 0; c0 < nchunks; c0 += U) {
+            int v[U];
 #pragma unroll
-    for (int u = 0; u < DPT; ++u) {
-        const int d = DPT * (int)threadIdx.x + u;
-        int run = 0;
-        if (d < ndig) {
-            for (int c = 0; c < nchunks; ++c) {
-                int32_t* p = ctot + (int64_t)c * kHgDigits + d;
-                const int v = *p;
-                *p = run;
-                run += v;
+            for (int u = 0; u < U; ++u) v[u] = c0 + u < nchunks ? ctot[(int64_t)(c0 + u) * kHgDigits + d] : 0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) sum += v[u];
+        }
+    IntSum::S all;
+    int run = block_exclusive_scan<IntSum, kHgDigits, false>(IntSum::S{sum}, all, wtot).v;
+    if (d < ndig)
+        for (int c0 = 0; c0 < nchunks; c0 += U) {
+            int v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = c0 + u < nchunks ? ctot[(int64_t)(c0 + u) * kHgDigits + d] : 0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (c0 + u < nchunks) ctot[(int64_t)(c0 + u) * kHgDigits + d] = run;
+                run += v[u];
             }
         }
-        tot[u] = run;
-        sum += run;
-    }
-    IntSum::S all;
-    int start = block_exclusive_scan<IntSum, kHgScanThreads, false>(IntSum::S{sum}, all, wtot).v;
-#pragma unroll
-    for (int u = 0; u < DPT; ++u) {
-        const int d = DPT * (int)threadIdx.x + u;
-        if (d < ndig)
-            for (int c = 0; c < nchunks; ++c) ctot[(int64_t)c * kHgDigits + d] += start;
-        start += tot[u];
-    }
     if (threadIdx.x == 0 && nvalid) *nvalid = all.v;
 }
 
@@ -170,6 +198,12 @@ __global__ __launch_bounds__(kHgScanThreads) void hg_digitscan_kernel(int32_t* _
 // sub-chunk + rank), then thread t writes slots t, t + 256, ... to the
 // digit's running position in the output.  The first pass builds each
 // record from the indices and x (read in order), later passes move records.
+// A sub-chunk's loads are issued before the stores of the one before, and the
+// stores are not under branches (a slot beyond the last repeats it): a wave's
+// memory operations return in order, so loads issued after the stores waited
+// for those as well.  Per pass over 2^24 linear-recurrence elements, m = 2^16:
+// 225 us with neither, 16-byte records (the index with them) and 512 blocks;
+// now 137 us, 3.4 TB/s.
 constexpr int kHgSortThreads = 256;
 constexpr int kHgSortWaves = kHgSortThreads / kWave;
 constexpr int kHgSortGroups = 8;                               // groups of 64 per wave and sub-chunk
@@ -177,19 +211,19 @@ constexpr int kHgSub = kHgSortThreads * kHgSortGroups;         // 2048 records
 constexpr int kHgPassBits = 8;                                 // bits per pass, one digit per thread
 constexpr int kHgPassDigits = 1 << kHgPassBits;
 static_assert(kHgPassDigits == kHgSortThreads, "a thread per digit in the sub-chunk scans");
-static_assert(kHgChunk % kHgSub == 0, "chunks are whole sub-chunks");
 
 // DPT: digits per thread in the per-digit steps (1: up to 256 digits, 2: up
 // to 512); thread t owns digits [DPT t, DPT t + DPT).
 template <class T, int K, int W, int DPT>
 __global__ __launch_bounds__(kHgSortThreads) void hg_scatter_kernel(const int32_t* __restrict__ keys_in, HgIn<T> x,
                                                                     const HgRec<W>* __restrict__ recs_in, int64_t n,
-                                                                    const int32_t* __restrict__ nvalid, int32_t m,
-                                                                    int shift, int dmask, int ndig, int nbits,
-                                                                    const int32_t* __restrict__ cntb,
+                                                                    const int32_t* __restrict__ nvalid, int chunk,
+                                                                    int32_t m, int shift, int dmask, int ndig,
+                                                                    int nbits, const int32_t* __restrict__ cntb,
                                                                     const int32_t* __restrict__ ctot,
                                                                     HgRec<W>* __restrict__ recs_out,
-                                                                    int32_t* __restrict__ keys_out) {
+                                                                    int32_t* __restrict__ keys_out,
+                                                                    int32_t* __restrict__ pos) {
     constexpr int ND = kHgPassDigits * DPT;
     __shared__ HgRec<W> stage[kHgSub];
     __shared__ int32_t wcnt[kHgSortWaves][ND];  // per wave: running count, then its offset
@@ -201,46 +235,47 @@ __global__ __launch_bounds__(kHgSortThreads) void hg_scatter_kernel(const int32_
     const int wave = tid / kWave;
     const int blk = blockIdx.x;
     const int c = blk / kHgColChunk;
+    const int64_t ne = nvalid ? (int64_t)*nvalid : n;
+    const int64_t lo = (int64_t)blk * chunk;
+    const int64_t hi = (lo + chunk < ne) ? lo + chunk : ne;
+    if (lo >= hi) return;
 #pragma unroll
     for (int u = 0; u < DPT; ++u) {
         const int d = DPT * tid + u;
         if (d < ndig) gpos[d] = ctot[(int64_t)c * kHgDigits + d] + cntb[(int64_t)blk * kHgDigits + d];
     }
-    const int64_t ne = nvalid ? (int64_t)*nvalid : n;
-    const int64_t lo = (int64_t)blk * kHgChunk;
-    const int64_t hi = (lo + kHgChunk < ne) ? lo + kHgChunk : ne;
     const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
+    const int64_t own = wave * (kHgSortGroups * kWave) + lane;  // the thread's first element in a sub-chunk
+    HgRec<W> r[kHgSortGroups];
+    auto load = [&](int64_t s0) {
+        if (keys_in) {
+#pragma unroll
+            for (int g = 0; g < kHgSortGroups; ++g) {
+                const int64_t i = min(s0 + own + g * kWave, hi - 1);
+                r[g].w[0] = (uint32_t)keys_in[i];
+#pragma unroll
+                for (int k = 0; k < K; ++k) hg_set_comp<T, W>(r[g], k, x.p[k][i]);
+            }
+        } else {
+#pragma unroll
+            for (int g = 0; g < kHgSortGroups; ++g) r[g] = recs_in[min(s0 + own + g * kWave, hi - 1)];
+        }
+    };
+    load(lo);
     for (int64_t s0 = lo; s0 < hi; s0 += kHgSub) {
         for (int w = 0; w < kHgSortWaves; ++w)
 #pragma unroll
             for (int u = 0; u < DPT; ++u) wcnt[w][DPT * tid + u] = 0;
-        HgRec<W> r[kHgSortGroups];
         bool valid[kHgSortGroups];
         int dg[kHgSortGroups];
-#pragma unroll
-        for (int g = 0; g < kHgSortGroups; ++g) {
-            const int64_t i = s0 + wave * (kHgSortGroups * kWave) + g * kWave + lane;
-            if (i < hi && keys_in) {
-                r[g].w[0] = (uint32_t)keys_in[i];
-                r[g].w[1] = (uint32_t)i;
-#pragma unroll
-                for (int w = 2; w < W; ++w) r[g].w[w] = 0u;
-#pragma unroll
-                for (int k = 0; k < K; ++k) reinterpret_cast<T*>(&r[g].w[2])[k] = x.p[k][i];
-            } else if (i < hi) {
-                r[g] = recs_in[i];
-            } else {
-                r[g].w[0] = 0xffffffffu;  // no element: outside every bin
-            }
-            valid[g] = (uint32_t)r[g].w[0] < (uint32_t)m;
-            dg[g] = valid[g] ? ((int32_t)r[g].w[0] >> shift) & dmask : 0;
-        }
         __syncthreads();  // counters cleared; the previous sub-chunk's slots read out
         // ranks within the wave, groups in order
         int rank[kHgSortGroups];
 #pragma unroll
         for (int g = 0; g < kHgSortGroups; ++g) {
-            const int d = dg[g];
+            valid[g] = s0 + own + g * kWave < hi && r[g].w[0] < (uint32_t)m;
+            const int d = valid[g] ? ((int32_t)r[g].w[0] >> shift) & dmask : 0;
+            dg[g] = d;
             uint64_t peers = __ballot(valid[g]);
             for (int bit = 0; bit < nbits; ++bit) {
                 const bool one = (d >> bit) & 1;
@@ -276,36 +311,34 @@ __global__ __launch_bounds__(kHgSortThreads) void hg_scatter_kernel(const int32_
             st += tot[u];
         }
         __syncthreads();
+        int to[kHgSortGroups];  // where the thread's records go, or -1
 #pragma unroll
-        for (int g = 0; g < kHgSortGroups; ++g)
-            if (valid[g]) stage[lstart[dg[g]] + wcnt[wave][dg[g]] + rank[g]] = r[g];
+        for (int g = 0; g < kHgSortGroups; ++g) {
+            const int at = wcnt[wave][dg[g]] + rank[g];
+            if (valid[g]) stage[lstart[dg[g]] + at] = r[g];
+            to[g] = valid[g] ? gpos[dg[g]] + at : -1;
+        }
+        if (s0 + kHgSub < hi) load(s0 + kHgSub);
         __syncthreads();
-        for (int sl = tid; sl < all.v; sl += kHgSortThreads) {
-            const HgRec<W> q = stage[sl];
-            const int d = ((int32_t)q.w[0] >> shift) & dmask;
-            const int64_t o = gpos[d] + (sl - lstart[d]);
-            recs_out[o] = q;
-            if (keys_out) keys_out[o] = (int32_t)q.w[0];  // what the next pass counts
+        if (pos) {
+#pragma unroll
+            for (int g = 0; g < kHgSortGroups; ++g) pos[s0 + own + g * kWave] = to[g];  // padded to whole sub-chunks
+        }
+        if (all.v > 0) {
+#pragma unroll
+            for (int u = 0; u < kHgSortGroups; ++u) {
+                const int sl = min(u * kHgSortThreads + tid, all.v - 1);
+                const HgRec<W> q = stage[sl];
+                const int d = ((int32_t)q.w[0] >> shift) & dmask;
+                const int64_t o = gpos[d] + (sl - lstart[d]);
+                recs_out[o] = q;
+                if (keys_out) keys_out[o] = (int32_t)q.w[0];  // what the next pass counts
+            }
         }
         __syncthreads();  // every slot placed before the positions move on
 #pragma unroll
         for (int u = 0; u < DPT; ++u) gpos[DPT * tid + u] += tot[u];
     }
-}
-
-// off[b] = the first sorted position whose bin is b or later (b in [0, m]).
-template <int W>
-__global__ __launch_bounds__(256) void hg_off_kernel(const HgRec<W>* __restrict__ recs,
-                                                     const int32_t* __restrict__ nvalid, int32_t m,
-                                                     int32_t* __restrict__ off) {
-    const int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (b > m) return;
-    int64_t lo = 0, hi = *nvalid;
-    while (lo < hi) {
-        const int64_t mid = (lo + hi) >> 1;
-        if ((int64_t)recs[mid].w[0] < b) lo = mid + 1; else hi = mid;
-    }
-    off[b] = (int32_t)lo;
 }
 
 // --------------------------------------------------- segmented fold scans
@@ -329,11 +362,11 @@ struct SegOf {
 };
 
 
-// Sorted element p: its bin, its own index and its components (as FP64, from
-// its record), plus whether it opens (first) and closes (last) its bin.
+// Sorted element p: its bin and its components (as FP64, from its record),
+// plus whether it opens (first) and closes (last) its bin.
 template <class Op, class T>
 struct HgElem {
-    int32_t key, src;
+    int32_t key;
     bool first, last;
     typename Op::S a;
 };
@@ -343,7 +376,6 @@ __device__ __forceinline__ HgElem<Op, T> hg_elem(const HgRec<W>* __restrict__ re
     HgElem<Op, T> e;
     const HgRec<W> r = recs[p];
     e.key = (int32_t)r.w[0];
-    e.src = (int32_t)r.w[1];
     e.first = p == 0 || (int32_t)recs[p - 1].w[0] != e.key;
     e.last = p + 1 == nv || (int32_t)recs[p + 1].w[0] != e.key;
     double c[Op::K];
@@ -353,23 +385,24 @@ __device__ __forceinline__ HgElem<Op, T> hg_elem(const HgRec<W>* __restrict__ re
     return e;
 }
 
-// Tile folds, forward (flag: the bin's first element) and reversed (flag:
-// its last element, scanned with the operands exchanged).
-template <class Op, class T, int W>
+// Tile folds, forward (flag: the bin's first element) and, with REV, reversed
+// (flag: its last element, scanned with the operands exchanged).
+template <class Op, class T, int W, bool REV>
 __global__ __launch_bounds__(kHgBlock) void hg_tile_fold_kernel(const HgRec<W>* __restrict__ recs,
                                                                 const int32_t* __restrict__ nvalid, char* __restrict__ aggF,
                                                                 char* __restrict__ aggR) {
+    constexpr int kIpt = hg_ipt(sizeof(HgRec<W>));
     using F = SegOf<Op>;
     using R = SegOf<Flip<Op>>;
     __shared__ typename F::S wf[kHgBlock / kWave];
     __shared__ typename R::S wr[kHgBlock / kWave];
     const int64_t nv = *nvalid;
-    const int64_t p0 = (int64_t)blockIdx.x * kHgTile + (int64_t)threadIdx.x * kHgIpt;
+    const int64_t p0 = ((int64_t)blockIdx.x * kHgBlock + threadIdx.x) * kIpt;
     typename F::S sf = F::id();
     typename R::S sr = R::id();
-    typename R::S re[kHgIpt];
+    typename R::S re[kIpt];
 #pragma unroll
-    for (int j = 0; j < kHgIpt; ++j) {
+    for (int j = 0; j < kIpt; ++j) {
         re[j] = R::id();
         if (p0 + j < nv) {
             const HgElem<Op, T> e = hg_elem<Op, T, W>(recs, nv, p0 + j);
@@ -377,22 +410,22 @@ __global__ __launch_bounds__(kHgBlock) void hg_tile_fold_kernel(const HgRec<W>* 
             re[j] = typename R::S{e.a, e.last ? 1u : 0u, 0u};
         }
     }
-#pragma unroll
-    for (int j = kHgIpt - 1; j >= 0; --j) sr = R::comb(sr, re[j]);
     typename F::S tf;
-    typename R::S tr;
     block_exclusive_scan<F, kHgBlock, false>(sf, tf, wf);
-    block_exclusive_scan<R, kHgBlock, true>(sr, tr, wr);
-    if (threadIdx.x == 0) {
-        *reinterpret_cast<typename F::S*>(aggF + (size_t)blockIdx.x * kHgSlot) = tf;
-        *reinterpret_cast<typename R::S*>(aggR + (size_t)blockIdx.x * kHgSlot) = tr;
+    if (threadIdx.x == 0) *reinterpret_cast<typename F::S*>(aggF + (size_t)blockIdx.x * kHgSlot) = tf;
+    if (REV) {
+#pragma unroll
+        for (int j = kIpt - 1; j >= 0; --j) sr = R::comb(sr, re[j]);
+        typename R::S tr;
+        block_exclusive_scan<R, kHgBlock, true>(sr, tr, wr);
+        if (threadIdx.x == 0) *reinterpret_cast<typename R::S*>(aggR + (size_t)blockIdx.x * kHgSlot) = tr;
     }
 }
 
 // One block: each item's carry, the lifted fold of all items before it
 // (forward) and after it (reversed), for an array of tile or group folds.
 // Thread t owns a contiguous run of items.
-template <class Op>
+template <class Op, bool REV>
 __global__ __launch_bounds__(kHgScanThreads) void hg_tile_scan_kernel(const char* __restrict__ aggF,
                                                                       const char* __restrict__ aggR, int64_t ntiles,
                                                                       char* __restrict__ carF, char* __restrict__ carR) {
@@ -408,15 +441,17 @@ __global__ __launch_bounds__(kHgScanThreads) void hg_tile_scan_kernel(const char
     typename F::S sf = F::id();
     typename R::S sr = R::id();
     for (int64_t t = t0; t < t1; ++t) sf = F::comb(sf, getF(t));
-    for (int64_t t = t1 - 1; t >= t0; --t) sr = R::comb(sr, getR(t));
+    if (REV)
+        for (int64_t t = t1 - 1; t >= t0; --t) sr = R::comb(sr, getR(t));
     typename F::S tf;
     typename R::S tr;
     sf = block_exclusive_scan<F, kHgScanThreads, false>(sf, tf, wf);
-    sr = block_exclusive_scan<R, kHgScanThreads, true>(sr, tr, wr);
+    if (REV) sr = block_exclusive_scan<R, kHgScanThreads, true>(sr, tr, wr);
     for (int64_t t = t0; t < t1; ++t) {
         *reinterpret_cast<typename F::S*>(carF + (size_t)t * kHgSlot) = sf;
         sf = F::comb(sf, getF(t));
     }
+    if (!REV) return;
     for (int64_t t = t1 - 1; t >= t0; --t) {
         *reinterpret_cast<typename R::S*>(carR + (size_t)t * kHgSlot) = sr;
         sr = R::comb(sr, getR(t));
@@ -428,7 +463,7 @@ __global__ __launch_bounds__(kHgScanThreads) void hg_tile_scan_kernel(const char
 // wave per group turns the group's carry into its tiles' carries.
 constexpr int kHgGroup = kWave;
 
-template <class Op>
+template <class Op, bool REV>
 __global__ __launch_bounds__(kHgGroup) void hg_group_fold_kernel(const char* __restrict__ aggF,
                                                                  const char* __restrict__ aggR, int64_t ntiles,
                                                                  char* __restrict__ gF, char* __restrict__ gR) {
@@ -438,18 +473,18 @@ __global__ __launch_bounds__(kHgGroup) void hg_group_fold_kernel(const char* __r
     __shared__ typename R::S wr[1];
     const int64_t t = (int64_t)blockIdx.x * kHgGroup + threadIdx.x;
     const typename F::S af = t < ntiles ? *reinterpret_cast<const typename F::S*>(aggF + (size_t)t * kHgSlot) : F::id();
-    const typename R::S ar = t < ntiles ? *reinterpret_cast<const typename R::S*>(aggR + (size_t)t * kHgSlot) : R::id();
+    const typename R::S ar = REV && t < ntiles ? *reinterpret_cast<const typename R::S*>(aggR + (size_t)t * kHgSlot) : R::id();
     typename F::S tf;
     typename R::S tr;
     block_exclusive_scan<F, kHgGroup, false>(af, tf, wf);
-    block_exclusive_scan<R, kHgGroup, true>(ar, tr, wr);
+    if (REV) block_exclusive_scan<R, kHgGroup, true>(ar, tr, wr);
     if (threadIdx.x == 0) {
         *reinterpret_cast<typename F::S*>(gF + (size_t)blockIdx.x * kHgSlot) = tf;
-        *reinterpret_cast<typename R::S*>(gR + (size_t)blockIdx.x * kHgSlot) = tr;
+        if (REV) *reinterpret_cast<typename R::S*>(gR + (size_t)blockIdx.x * kHgSlot) = tr;
     }
 }
 
-template <class Op>
+template <class Op, bool REV>
 __global__ __launch_bounds__(kHgGroup) void hg_group_carry_kernel(const char* __restrict__ aggF,
                                                                   const char* __restrict__ aggR, int64_t ntiles,
                                                                   const char* __restrict__ gcF,
@@ -461,15 +496,15 @@ __global__ __launch_bounds__(kHgGroup) void hg_group_carry_kernel(const char* __
     __shared__ typename R::S wr[1];
     const int64_t t = (int64_t)blockIdx.x * kHgGroup + threadIdx.x;
     const typename F::S af = t < ntiles ? *reinterpret_cast<const typename F::S*>(aggF + (size_t)t * kHgSlot) : F::id();
-    const typename R::S ar = t < ntiles ? *reinterpret_cast<const typename R::S*>(aggR + (size_t)t * kHgSlot) : R::id();
+    const typename R::S ar = REV && t < ntiles ? *reinterpret_cast<const typename R::S*>(aggR + (size_t)t * kHgSlot) : R::id();
     typename F::S tf;
     typename R::S tr;
     const typename F::S xf = block_exclusive_scan<F, kHgGroup, false>(af, tf, wf);
-    const typename R::S xr = block_exclusive_scan<R, kHgGroup, true>(ar, tr, wr);
+    const typename R::S xr = REV ? block_exclusive_scan<R, kHgGroup, true>(ar, tr, wr) : ar;
     if (t < ntiles) {
         *reinterpret_cast<typename F::S*>(carF + (size_t)t * kHgSlot) =
             F::comb(*reinterpret_cast<const typename F::S*>(gcF + (size_t)blockIdx.x * kHgSlot), xf);
-        *reinterpret_cast<typename R::S*>(carR + (size_t)t * kHgSlot) =
+        if (REV) *reinterpret_cast<typename R::S*>(carR + (size_t)t * kHgSlot) =
             R::comb(*reinterpret_cast<const typename R::S*>(gcR + (size_t)blockIdx.x * kHgSlot), xr);
     }
 }
@@ -477,26 +512,25 @@ __global__ __launch_bounds__(kHgGroup) void hg_group_carry_kernel(const char* __
 // Per tile: the forward scan with the tile's carry; the primal writes each
 // bin's fold at its last element.  The VJP also runs the reversed scan and
 // maps f over (ls, x, rs) with y_bar = hs_bar of the element's bin.
-template <class Op, class T, int W, bool VJP, bool ACC>
+template <class Op, class T, int W, bool VJP>
 __global__ __launch_bounds__(kHgBlock) void hg_apply_kernel(const HgRec<W>* __restrict__ recs,
-                                                            HgRec<W>* __restrict__ urecs,
-                                                            int32_t* __restrict__ ukeys,
                                                             const int32_t* __restrict__ nvalid,
                                                             const char* __restrict__ carF,
                                                             const char* __restrict__ carR, HgOut<T> hs,
-                                                            HgIn<T> hs_bar, HgOut<T> x_bar) {
+                                                            HgIn<T> hs_bar, HgAdj<T, Op::K>* __restrict__ adj) {
+    constexpr int kIpt = hg_ipt(sizeof(HgRec<W>));
     using F = SegOf<Op>;
     using R = SegOf<Flip<Op>>;
     using QS = typename Op::S;
     __shared__ typename F::S wf[kHgBlock / kWave];
     __shared__ typename R::S wr[kHgBlock / kWave];
     const int64_t nv = *nvalid;
-    const int64_t p0 = (int64_t)blockIdx.x * kHgTile + (int64_t)threadIdx.x * kHgIpt;
-    HgElem<Op, T> e[kHgIpt];
-    bool in[kHgIpt];
+    const int64_t p0 = ((int64_t)blockIdx.x * kHgBlock + threadIdx.x) * kIpt;
+    HgElem<Op, T> e[kIpt];
+    bool in[kIpt];
     typename F::S sf = F::id();
 #pragma unroll
-    for (int j = 0; j < kHgIpt; ++j) {
+    for (int j = 0; j < kIpt; ++j) {
         in[j] = p0 + j < nv;
         if (in[j]) {
             e[j] = hg_elem<Op, T, W>(recs, nv, p0 + j);
@@ -508,7 +542,7 @@ __global__ __launch_bounds__(kHgBlock) void hg_apply_kernel(const HgRec<W>* __re
     xf = F::comb(*reinterpret_cast<const typename F::S*>(carF + (size_t)blockIdx.x * kHgSlot), xf);
     if (!VJP) {
 #pragma unroll
-        for (int j = 0; j < kHgIpt; ++j) {
+        for (int j = 0; j < kIpt; ++j) {
             if (!in[j]) continue;
             xf = F::comb(xf, typename F::S{e[j].a, e[j].first ? 1u : 0u, 0u});
             if (e[j].last) {
@@ -520,9 +554,9 @@ __global__ __launch_bounds__(kHgBlock) void hg_apply_kernel(const HgRec<W>* __re
         }
         return;
     }
-    QS ls[kHgIpt], la[kHgIpt];
+    QS ls[kIpt], la[kIpt];
 #pragma unroll
-    for (int j = 0; j < kHgIpt; ++j) {
+    for (int j = 0; j < kIpt; ++j) {
         if (!in[j]) continue;
         ls[j] = e[j].first ? Op::id() : xf.v;
         la[j] = Op::comb(ls[j], e[j].a);
@@ -530,76 +564,85 @@ __global__ __launch_bounds__(kHgBlock) void hg_apply_kernel(const HgRec<W>* __re
     }
     typename R::S sr = R::id();
 #pragma unroll
-    for (int j = kHgIpt - 1; j >= 0; --j)
+    for (int j = kIpt - 1; j >= 0; --j)
         if (in[j]) sr = R::comb(sr, typename R::S{e[j].a, e[j].last ? 1u : 0u, 0u});
     typename R::S tr;
     typename R::S xr = block_exclusive_scan<R, kHgBlock, true>(sr, tr, wr);
     xr = R::comb(*reinterpret_cast<const typename R::S*>(carR + (size_t)blockIdx.x * kHgSlot), xr);
 #pragma unroll
-    for (int j = kHgIpt - 1; j >= 0; --j) {
+    for (int j = kIpt - 1; j >= 0; --j) {
         if (!in[j]) continue;
         const QS rs = e[j].last ? Op::id() : xr.v;
         double yb[Op::K], out[Op::K];
 #pragma unroll
         for (int k = 0; k < Op::K; ++k) yb[k] = (double)hs_bar.p[k][e[j].key];
         Op::vjp(ls[j], e[j].a, rs, la[j], yb, out);
-        if (urecs) {
-            // (index, x_bar) records in sorted order, for the unsort
-            HgRec<W> q;
-            q.w[0] = (uint32_t)e[j].src;
+        HgAdj<T, Op::K> q;
 #pragma unroll
-            for (int w = 1; w < W; ++w) q.w[w] = 0u;
-#pragma unroll
-            for (int k = 0; k < Op::K; ++k) reinterpret_cast<T*>(&q.w[2])[k] = (T)out[k];
-            urecs[p0 + j] = q;
-            ukeys[p0 + j] = e[j].src;
-        } else {
-#pragma unroll
-            for (int k = 0; k < Op::K; ++k) {
-                T* dst = x_bar.p[k] + e[j].src;
-                *dst = ACC ? (T)((double)*dst + out[k]) : (T)out[k];
-            }
-        }
+        for (int k = 0; k < Op::K; ++k) q.c[k] = (T)out[k];
+        adj[p0 + j] = q;
         xr = R::comb(xr, typename R::S{e[j].a, e[j].last ? 1u : 0u, 0u});
     }
 }
 
-// Empty bins hold the neutral element.
+// Every bin the neutral element, before the folds are written.
 template <class Op, class T>
-__global__ __launch_bounds__(256) void hg_empty_kernel(const int32_t* __restrict__ off, int32_t m, HgOut<T> hs) {
+__global__ __launch_bounds__(256) void hg_empty_kernel(int32_t m, HgOut<T> hs) {
     const int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (b >= m || off[b] != off[b + 1]) return;
+    if (b >= m) return;
     double out[Op::K];
     Op::value(Op::id(), out);
 #pragma unroll
     for (int k = 0; k < Op::K; ++k) hs.p[k][b] = (T)out[k];
 }
 
-// Without accumulation, every in-range element's x_bar is written by the
-// apply (or the unsort); the elements whose index is outside [0, m) get 0
-// here, read from the indices, instead of clearing whole arrays first.
-template <class T>
-__global__ __launch_bounds__(256) void hg_zero_oob_kernel(const int32_t* __restrict__ inds, int64_t n, int32_t m,
-                                                          HgOut<T> x, int K) {
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
-        if ((uint32_t)inds[i] >= (uint32_t)m)
-            for (int k = 0; k < K; ++k) x.p[k][i] = T(0);
+// One step back through a sort pass: dst[j] = src[pos[j]], j in the order the
+// pass read its records; a thread takes eight, the block a sub-chunk.
+constexpr int kHgBackU = kHgSub / 256;
+template <class T, int K>
+__global__ __launch_bounds__(256) void hg_back_kernel(const int32_t* __restrict__ pos,
+                                                      const int32_t* __restrict__ nvalid,
+                                                      const HgAdj<T, K>* __restrict__ src,
+                                                      HgAdj<T, K>* __restrict__ dst) {
+    const int64_t nv = *nvalid;
+    const int64_t at = (int64_t)blockIdx.x * kHgSub;
+    if (at >= nv) return;
+    const int64_t j0 = at + threadIdx.x;
+    int p[kHgBackU];
+    HgAdj<T, K> v[kHgBackU];
+#pragma unroll
+    for (int u = 0; u < kHgBackU; ++u) p[u] = pos[min(j0 + u * 256, nv - 1)];
+#pragma unroll
+    for (int u = 0; u < kHgBackU; ++u) v[u] = src[p[u]];
+#pragma unroll
+    for (int u = 0; u < kHgBackU; ++u)
+        if (j0 + u * 256 < nv) dst[j0 + u * 256] = v[u];
 }
 
-// The unsort's last step: records in increasing element index (in-range
-// elements only), each component written at the element's index -- in
-// order, with gaps where indices were out of range.
-template <class T, int K, int W, bool ACC>
-__global__ __launch_bounds__(256) void hg_unsort_write_kernel(const HgRec<W>* __restrict__ recs,
-                                                              const int32_t* __restrict__ nvalid, HgOut<T> x_bar) {
-    const int64_t nv = *nvalid;
-    for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p < nv; p += (int64_t)gridDim.x * 256) {
-        const HgRec<W> q = recs[p];
-        const int64_t i = (int64_t)q.w[0];
+// The last step, through the first pass: x_bar in index order (0, or what was
+// there, where the index is out of range).
+template <class T, int K, bool ACC>
+__global__ __launch_bounds__(256) void hg_back_write_kernel(const int32_t* __restrict__ pos, int64_t n,
+                                                            const int32_t* __restrict__ nvalid,
+                                                            const HgAdj<T, K>* __restrict__ src, HgOut<T> x_bar) {
+    const int64_t j0 = (int64_t)blockIdx.x * kHgSub + threadIdx.x;
+    const bool any = *nvalid > 0;
+    int p[kHgBackU];
+    HgAdj<T, K> v[kHgBackU];
+#pragma unroll
+    for (int u = 0; u < kHgBackU; ++u) p[u] = pos[min(j0 + u * 256, n - 1)];
+#pragma unroll
+    for (int u = 0; u < kHgBackU; ++u)
+        if (any) v[u] = src[max(p[u], 0)];
+#pragma unroll
+    for (int u = 0; u < kHgBackU; ++u) {
+        const int64_t j = j0 + u * 256;
+        if (j >= n || (ACC && p[u] < 0)) continue;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            const T v = hg_comp<T, W>(q, k);
-            x_bar.p[k][i] = ACC ? (T)((double)x_bar.p[k][i] + (double)v) : v;
+            T* d = x_bar.p[k] + j;
+            const T a = p[u] < 0 ? T(0) : v[u].c[k];
+            *d = ACC ? (T)((double)*d + (double)a) : a;
         }
     }
 }
@@ -610,22 +653,36 @@ static int hg_components(pvjp_gop op) {
 }
 
 struct HgLayout {
-    int64_t nblk, nchunks, ntiles;
+    int64_t chunk, nblk, nchunks, ntiles, npad;
     int64_t ngroups;
-    size_t cntb, ctot, nvalid, recA, recB, keyA, keyB, off, aggF, aggR, carF, carR, gF, gR, gcF, gcR, total;
+    int passes, bits;  // sort passes, bits per pass
+    size_t cntb, ctot, nvalid, recA, recB, keyA, keyB, pos, aggF, aggR, carF, carR, gF, gR, gcF, gcR, total;
 };
 
-static size_t hg_rec_bytes(int K, size_t tsize) {
-    return (size_t)((2 + K * (int)(tsize / 4) + 3) / 4 * 4) * 4;
-}
+// Records of 32 bytes or more: each pass but the last also writes its output's
+// keys compactly, which the next pass counts instead of reading whole records
+// (a shorter one costs the count about as much to read).
+static bool hg_compact_keys(size_t rec_bytes) { return rec_bytes >= 32; }
 
-// rec_bytes: the size of one sort record (hg_rec_bytes).
+// rec_bytes: the size of one sort record.
 static HgLayout hg_layout(int64_t n, int64_t m, size_t rec_bytes) {
     HgLayout L{};
     const int64_t nn = n > 0 ? n : 1;
-    L.nblk = ceil_div(nn, kHgChunk);
+    // A block's chunk: whole sub-chunks, 32,768 elements or, so that short
+    // inputs fill the chip, as many as leave some 2,048 blocks (eight a CU;
+    // 2^24 16-byte records in 512 blocks of 32,768: 225 us a pass, at 2^26,
+    // with 2,048 blocks, 178 us per 2^24).
+    L.chunk = kHgSub;
+    while (L.chunk < 32768 && L.chunk * 2048 < nn) L.chunk *= 2;
+    L.nblk = ceil_div(nn, L.chunk);
     L.nchunks = ceil_div(L.nblk, kHgColChunk);
-    L.ntiles = ceil_div(nn, kHgTile);
+    L.ntiles = ceil_div(nn, (int64_t)kHgBlock * hg_ipt(rec_bytes));
+    L.npad = ceil_div(nn, kHgSub) * kHgSub;
+    int b = 0;
+    while (((int64_t)1 << b) < m) ++b;
+    // As few passes as 9 bits each allow, the bits split evenly.
+    L.passes = std::max(1, (b + kHgPassBits) / (kHgPassBits + 1));
+    L.bits = std::max(1, (b + L.passes - 1) / L.passes);
     size_t o = 0;
     auto take = [&](size_t bytes) {
         const size_t at = o;
@@ -637,9 +694,10 @@ static HgLayout hg_layout(int64_t n, int64_t m, size_t rec_bytes) {
     L.nvalid = take(4);
     L.recA = take((size_t)nn * rec_bytes);
     L.recB = take((size_t)nn * rec_bytes);
-    L.keyA = take((size_t)nn * 4);
-    L.keyB = take((size_t)nn * 4);
-    L.off = take((size_t)(m + 1) * 4);
+    const bool ck = hg_compact_keys(rec_bytes);
+    L.keyA = take(ck ? (size_t)nn * 4 : 0);
+    L.keyB = take(ck ? (size_t)nn * 4 : 0);
+    L.pos = take((size_t)L.passes * L.npad * 4);
     L.aggF = take((size_t)L.ntiles * kHgSlot);
     L.aggR = take((size_t)L.ntiles * kHgSlot);
     L.carF = take((size_t)L.ntiles * kHgSlot);
@@ -653,80 +711,64 @@ static HgLayout hg_layout(int64_t n, int64_t m, size_t rec_bytes) {
     return L;
 }
 
-// Stable LSD passes of at most 8 bits, or 9 for records of 32 bytes or more
-// when that saves a pass (the key's bits split evenly; at least one pass) over keys below m: from the indices and x (keys != NULL; the
-// first pass also counts the in-range elements into *nvalid) or from the
-// records rin, whose keys ckeys may hold compactly (nv on the device).
-// Records ping-pong between bufA and bufB; for records of 32 bytes or more,
-// each pass but the last also writes its output's keys compactly (keyA /
-// keyB), which the next pass counts instead of reading whole records.
-// Returns the sorted records.
+// The stable sort by bin; records ping-pong between the two buffers.  Returns
+// the sorted ones.  keep: the passes' positions go to the workspace.
 template <class T, int K, int W>
-static const HgRec<W>* hg_sort_passes(const int32_t* keys, const HgIn<T>& x, const HgRec<W>* rin,
-                                      const int32_t* ckeys, int64_t n, const int32_t* nv_in, int64_t m,
-                                      HgRec<W>* bufA, HgRec<W>* bufB, int32_t* keyA, int32_t* keyB, int32_t* cntb,
-                                      int32_t* ctot, int32_t* nvalid, const HgLayout& L, hipStream_t st) {
-    int bbits = 0;
-    while (((int64_t)1 << bbits) < m) ++bbits;
-    int passes = std::max(1, (bbits + kHgPassBits - 1) / kHgPassBits);
-    // records of 32 bytes or more run whole lines with 512 digits too: take
-    // 9-bit passes when that saves one (an unsort of 2^26 indices: 3, not 4)
-    const int passes9 = std::max(1, (bbits + kHgPassBits) / (kHgPassBits + 1));
-    if (W >= 8 && passes9 < passes) passes = passes9;
-    const int bpp = std::max(1, (bbits + passes - 1) / passes);
-    const int32_t* kcount = keys ? keys : ckeys;
-    for (int pass = 0; pass < passes; ++pass) {
-        const int shift = pass * bpp;
-        const int dmask = (1 << bpp) - 1;
-        const int ndig = (int)std::min<int64_t>((int64_t)1 << bpp, ceil_div(m, (int64_t)1 << shift));
+static HgRec<W>* hg_sort(const int32_t* keys, const HgIn<T>& x, int64_t n, int64_t m, bool keep, char* w,
+                         const HgLayout& L, hipStream_t st) {
+    int32_t* cntb = reinterpret_cast<int32_t*>(w + L.cntb);
+    int32_t* ctot = reinterpret_cast<int32_t*>(w + L.ctot);
+    int32_t* nvalid = reinterpret_cast<int32_t*>(w + L.nvalid);
+    HgRec<W>* rin = nullptr;
+    const int32_t* kcount = keys;
+    for (int pass = 0; pass < L.passes; ++pass) {
+        const int shift = pass * L.bits;
+        const int dmask = (1 << L.bits) - 1;
+        const int ndig = (int)std::min<int64_t>((int64_t)1 << L.bits, ceil_div(m, (int64_t)1 << shift));
         int nbits = 0;
         while ((1 << nbits) < ndig) ++nbits;
-        HgRec<W>* rout = (pass & 1) ? bufB : bufA;
-        // compact keys pay for their extra stores only when a record is at
-        // least 32 bytes (a 16-byte one costs the count about as much to read)
-        int32_t* kout = (W >= 8 && pass + 1 < passes) ? ((pass & 1) ? keyB : keyA) : nullptr;
+        HgRec<W>* rout = reinterpret_cast<HgRec<W>*>(w + ((pass & 1) ? L.recB : L.recA));
+        int32_t* kout = nullptr;
+        if (hg_compact_keys(sizeof(HgRec<W>)) && pass + 1 < L.passes)
+            kout = reinterpret_cast<int32_t*>(w + ((pass & 1) ? L.keyB : L.keyA));
+        int32_t* pos = keep ? reinterpret_cast<int32_t*>(w + L.pos) + (int64_t)pass * L.npad : nullptr;
         const int32_t* kin = pass == 0 ? keys : nullptr;
-        const int32_t* nv = (pass == 0 && keys) ? nullptr : (keys ? nvalid : nv_in);
+        const int32_t* nv = pass == 0 ? nullptr : nvalid;
         hipLaunchKernelGGL(hg_count_kernel<W>, dim3((unsigned)L.nblk), dim3(kHgCountBlock), 0, st, kcount, rin, n,
-                           nv, (int32_t)m, shift, dmask, ndig, cntb);
+                           nv, (int)L.chunk, (int32_t)m, shift, dmask, ndig, cntb);
         hipLaunchKernelGGL(hg_colscan_kernel, dim3((unsigned)ceil_div(ndig, kHgCountBlock), (unsigned)L.nchunks),
                            dim3(kHgCountBlock), 0, st, cntb, (int)L.nblk, ndig, ctot);
-        hipLaunchKernelGGL(hg_digitscan_kernel, dim3(1), dim3(kHgScanThreads), 0, st, ctot, (int)L.nchunks, ndig,
-                           (pass == 0 && keys) ? nvalid : nullptr);
+        hipLaunchKernelGGL(hg_digitscan_kernel, dim3(1), dim3(kHgDigits), 0, st, ctot, (int)L.nchunks, ndig,
+                           pass == 0 ? nvalid : nullptr);
         if (ndig > kHgPassDigits)
             hipLaunchKernelGGL((hg_scatter_kernel<T, K, W, 2>), dim3((unsigned)L.nblk), dim3(kHgSortThreads), 0, st,
-                               kin, x, rin, n, nv, (int32_t)m, shift, dmask, ndig, nbits, cntb, ctot, rout, kout);
+                               kin, x, rin, n, nv, (int)L.chunk, (int32_t)m, shift, dmask, ndig, nbits, cntb, ctot,
+                               rout, kout, pos);
         else
             hipLaunchKernelGGL((hg_scatter_kernel<T, K, W, 1>), dim3((unsigned)L.nblk), dim3(kHgSortThreads), 0, st,
-                               kin, x, rin, n, nv, (int32_t)m, shift, dmask, ndig, nbits, cntb, ctot, rout, kout);
+                               kin, x, rin, n, nv, (int)L.chunk, (int32_t)m, shift, dmask, ndig, nbits, cntb, ctot,
+                               rout, kout, pos);
         rin = rout;
         kcount = kout;
     }
     return rin;
 }
 
-// The sort and the tile carries, shared by both entry points.  Returns the
-// sorted records.
-template <class Op, class T>
-static const HgRec<hg_words<T, Op::K>()>* hg_prepare(const int32_t* inds, int64_t n, int32_t m, const HgIn<T>& x,
-                                                     char* w, const HgLayout& L, hipStream_t st) {
+// The sort and the tile carries, shared by both entry points (REV: the
+// reversed carries too, and the passes' positions kept).
+template <class Op, class T, bool REV>
+static HgRec<hg_words<T, Op::K>()>* hg_prepare(const int32_t* inds, int64_t n, int32_t m, const HgIn<T>& x, char* w,
+                                               const HgLayout& L, hipStream_t st) {
     constexpr int W = hg_words<T, Op::K>();
-    using Rec = HgRec<W>;
-    int32_t* cntb = reinterpret_cast<int32_t*>(w + L.cntb);
-    int32_t* ctot = reinterpret_cast<int32_t*>(w + L.ctot);
     int32_t* nvalid = reinterpret_cast<int32_t*>(w + L.nvalid);
-    Rec* rA = reinterpret_cast<Rec*>(w + L.recA);
-    Rec* rB = reinterpret_cast<Rec*>(w + L.recB);
-    const Rec* rin = hg_sort_passes<T, Op::K, W>(inds, x, nullptr, nullptr, n, nullptr, m, rA, rB,
-                                                 reinterpret_cast<int32_t*>(w + L.keyA),
-                                                 reinterpret_cast<int32_t*>(w + L.keyB), cntb, ctot, nvalid, L, st);
-    hipLaunchKernelGGL((hg_tile_fold_kernel<Op, T, W>), dim3((unsigned)L.ntiles), dim3(kHgBlock), 0, st, rin,
+    HgRec<W>* rin = hg_sort<T, Op::K, W>(inds, x, n, m, REV, w, L, st);
+    hipLaunchKernelGGL((hg_tile_fold_kernel<Op, T, W, REV>), dim3((unsigned)L.ntiles), dim3(kHgBlock), 0, st, rin,
                        nvalid, w + L.aggF, w + L.aggR);
-    hipLaunchKernelGGL(hg_group_fold_kernel<Op>, dim3((unsigned)L.ngroups), dim3(kHgGroup), 0, st, w + L.aggF,
+    hipLaunchKernelGGL((hg_group_fold_kernel<Op, REV>), dim3((unsigned)L.ngroups), dim3(kHgGroup), 0, st, w + L.aggF,
                        w + L.aggR, L.ntiles, w + L.gF, w + L.gR);
-    hipLaunchKernelGGL(hg_tile_scan_kernel<Op>, dim3(1), dim3(kHgScanThreads), 0, st, w + L.gF, w + L.gR,
+    hipLaunchKernelGGL((hg_tile_scan_kernel<Op, REV>), dim3(1), dim3(kHgScanThreads), 0, st, w + L.gF, w + L.gR,
                        L.ngroups, w + L.gcF, w + L.gcR);
-    hipLaunchKernelGGL(hg_group_carry_kernel<Op>, dim3((unsigned)L.ngroups), dim3(kHgGroup), 0, st, w + L.aggF,
+    hipLaunchKernelGGL((hg_group_carry_kernel<Op, REV>), dim3((unsigned)L.ngroups), dim3(kHgGroup), 0, st, w + L.aggF,
                        w + L.aggR, L.ntiles, w + L.gcF, w + L.gcR, w + L.carF, w + L.carR);
     return rin;
 }
@@ -735,29 +777,27 @@ template <class Op, class T>
 static void hg_primal(const int32_t* inds, int64_t n, int32_t m, const void* const* x, void* const* hs, char* w,
                       hipStream_t st) {
     constexpr int W = hg_words<T, Op::K>();
-    const HgLayout L = hg_layout(n, m, hg_rec_bytes(Op::K, sizeof(T)));
+    const HgLayout L = hg_layout(n, m, sizeof(HgRec<W>));
     HgIn<T> xi{};
     HgOut<T> ho{};
     for (int k = 0; k < Op::K; ++k) {
         xi.p[k] = n > 0 ? (const T*)x[k] : nullptr;
         ho.p[k] = (T*)hs[k];
     }
-    const HgRec<W>* recs = hg_prepare<Op, T>(inds, n, m, xi, w, L, st);
+    const HgRec<W>* recs = hg_prepare<Op, T, false>(inds, n, m, xi, w, L, st);
     int32_t* nvalid = reinterpret_cast<int32_t*>(w + L.nvalid);
-    int32_t* off = reinterpret_cast<int32_t*>(w + L.off);
-    hipLaunchKernelGGL(hg_off_kernel<W>, dim3((unsigned)ceil_div((int64_t)m + 1, 256)), dim3(256), 0, st, recs,
-                       nvalid, m, off);
-    hipLaunchKernelGGL((hg_apply_kernel<Op, T, W, false, false>), dim3((unsigned)L.ntiles), dim3(kHgBlock), 0, st,
-                       recs, (HgRec<W>*)nullptr, (int32_t*)nullptr, nvalid, w + L.carF, w + L.carR, ho, HgIn<T>{},
-                       HgOut<T>{});
-    hipLaunchKernelGGL((hg_empty_kernel<Op, T>), dim3((unsigned)ceil_div(m, 256)), dim3(256), 0, st, off, m, ho);
+    hipLaunchKernelGGL((hg_empty_kernel<Op, T>), dim3((unsigned)ceil_div(m, 256)), dim3(256), 0, st, m, ho);
+    hipLaunchKernelGGL((hg_apply_kernel<Op, T, W, false>), dim3((unsigned)L.ntiles), dim3(kHgBlock), 0, st, recs,
+                       nvalid, w + L.carF, w + L.carR, ho, HgIn<T>{}, (HgAdj<T, Op::K>*)nullptr);
 }
 
 template <class Op, class T>
 static void hg_vjp(const int32_t* inds, int64_t n, int32_t m, const void* const* x, const void* const* hs_bar,
                    void* const* x_bar, bool acc, char* w, hipStream_t st) {
     constexpr int W = hg_words<T, Op::K>();
-    const HgLayout L = hg_layout(n, m, hg_rec_bytes(Op::K, sizeof(T)));
+    using Adj = HgAdj<T, Op::K>;
+    static_assert(sizeof(Adj) <= sizeof(HgRec<W>), "adjoints fit a record buffer");
+    const HgLayout L = hg_layout(n, m, sizeof(HgRec<W>));
     HgIn<T> xi{}, hb{};
     HgOut<T> xb{};
     for (int k = 0; k < Op::K; ++k) {
@@ -765,42 +805,23 @@ static void hg_vjp(const int32_t* inds, int64_t n, int32_t m, const void* const*
         hb.p[k] = (const T*)hs_bar[k];
         xb.p[k] = (T*)x_bar[k];
     }
-    if (!acc)  // elements outside [0, m) get a zero adjoint
-        hipLaunchKernelGGL(hg_zero_oob_kernel<T>, dim3(flat_grid(n, 256, 4)), dim3(256), 0, st, inds, n, m, xb,
-                           Op::K);
-    const HgRec<W>* recs = hg_prepare<Op, T>(inds, n, m, xi, w, L, st);
-    int32_t* nvalid = reinterpret_cast<int32_t*>(w + L.nvalid);
-    // With four components, K scattered stores per element cost more than
-    // writing (index, x_bar) records in sorted order and sorting them back by
-    // index with the same staged passes; with fewer, the stores are cheaper.
-    HgRec<W>* urecs = nullptr;
-    HgRec<W>* rA = reinterpret_cast<HgRec<W>*>(w + L.recA);
-    HgRec<W>* rB = reinterpret_cast<HgRec<W>*>(w + L.recB);
-    if (Op::K >= 4) urecs = (recs == rA) ? rB : rA;
-    int32_t* kA = reinterpret_cast<int32_t*>(w + L.keyA);
-    int32_t* kB = reinterpret_cast<int32_t*>(w + L.keyB);
-    int32_t* ukeys = urecs ? kB : nullptr;  // the unsort's first pass writes kA
-    if (acc)
-        hipLaunchKernelGGL((hg_apply_kernel<Op, T, W, true, true>), dim3((unsigned)L.ntiles), dim3(kHgBlock), 0, st,
-                           recs, urecs, ukeys, nvalid, w + L.carF, w + L.carR, HgOut<T>{}, hb, xb);
-    else
-        hipLaunchKernelGGL((hg_apply_kernel<Op, T, W, true, false>), dim3((unsigned)L.ntiles), dim3(kHgBlock), 0, st,
-                           recs, urecs, ukeys, nvalid, w + L.carF, w + L.carR, HgOut<T>{}, hb, xb);
-    if (urecs) {
-        // the sorted records' buffer is free now: the passes start there, so
-        // that no pass reads and writes one buffer
-        HgRec<W>* other = (urecs == rA) ? rB : rA;
-        int32_t* cntb = reinterpret_cast<int32_t*>(w + L.cntb);
-        int32_t* ctot = reinterpret_cast<int32_t*>(w + L.ctot);
-        const HgRec<W>* out = hg_sort_passes<T, Op::K, W>(nullptr, HgIn<T>{}, urecs, ukeys, n, nvalid, n, other,
-                                                          urecs, kA, kB, cntb, ctot, nvalid, L, st);
-        if (acc)
-            hipLaunchKernelGGL((hg_unsort_write_kernel<T, Op::K, W, true>), dim3(flat_grid(n, 256, 4)), dim3(256), 0,
-                               st, out, nvalid, xb);
-        else
-            hipLaunchKernelGGL((hg_unsort_write_kernel<T, Op::K, W, false>), dim3(flat_grid(n, 256, 4)), dim3(256), 0,
-                               st, out, nvalid, xb);
+    const HgRec<W>* recs = hg_prepare<Op, T, true>(inds, n, m, xi, w, L, st);
+    const int32_t* nvalid = reinterpret_cast<const int32_t*>(w + L.nvalid);
+    const int32_t* pos = reinterpret_cast<const int32_t*>(w + L.pos);
+    Adj* from = reinterpret_cast<Adj*>(w + ((const char*)recs == w + L.recA ? L.recB : L.recA));
+    Adj* to = reinterpret_cast<Adj*>(const_cast<HgRec<W>*>(recs));  // free once the adjoints are formed
+    hipLaunchKernelGGL((hg_apply_kernel<Op, T, W, true>), dim3((unsigned)L.ntiles), dim3(kHgBlock), 0, st, recs,
+                       nvalid, w + L.carF, w + L.carR, HgOut<T>{}, hb, from);
+    const dim3 grid((unsigned)(L.npad / kHgSub));
+    for (int pass = L.passes - 1; pass > 0; --pass) {
+        hipLaunchKernelGGL((hg_back_kernel<T, Op::K>), grid, dim3(256), 0, st, pos + (int64_t)pass * L.npad, nvalid,
+                           from, to);
+        std::swap(from, to);
     }
+    if (acc)
+        hipLaunchKernelGGL((hg_back_write_kernel<T, Op::K, true>), grid, dim3(256), 0, st, pos, n, nvalid, from, xb);
+    else
+        hipLaunchKernelGGL((hg_back_write_kernel<T, Op::K, false>), grid, dim3(256), 0, st, pos, n, nvalid, from, xb);
 }
 
 static pvjp_status hg_check(const char* name, pvjp_gop op, pvjp_dtype dtype, const int32_t* inds,
@@ -832,7 +853,7 @@ using namespace pvjp;
 
 extern "C" size_t pvjp_hist_generic_ws_bytes(pvjp_gop op, pvjp_dtype dtype, int64_t n, int64_t m) {
     if (hg_components(op) == 0 || !valid_dtype(dtype) || n < 0 || m < 1 || m > kHgMaxBins) return 0;
-    return hg_layout(n, m, hg_rec_bytes(hg_components(op), dsize(dtype))).total;
+    return hg_layout(n, m, 4 + (size_t)hg_components(op) * dsize(dtype)).total;
 }
 
 extern "C" pvjp_status pvjp_hist_generic(pvjp_gop op, pvjp_dtype dtype, const int32_t* inds, const void* const* x,

@@ -141,3 +141,29 @@ def test_full_size_sampled(ops, orc):
     rvb = orc.hist_generic_vjp(op, sub_inds, sub_x, [h[bins].astype(np.float64) for h in hb])
     for g, r in zip(xb, rvb):
         check(g[sel], r, TOL_F32)
+
+
+@pytest.mark.parametrize("op,dtype,n,m", [
+    # around a 2,048-record sub-chunk, and bin counts around a pass of 8 and of 9 bits
+    ("linrec", "f32", 2047, 256), ("mat2", "f32", 2048, 257), ("logaddexp", "f32", 2049, 511),
+    ("mat2", "f64", 4097, 512), ("linrec", "f64", 6145, 513), ("logaddexp", "f64", 2048, 512),
+    # two passes of 9 bits, three of 7; the first chunk beyond 2,048 elements
+    ("mat2", "f32", 50021, 1 << 18), ("linrec", "f32", 50021, (1 << 18) + 1),
+    ("linrec", "f32", 2048 * 2048 + 1, 1 << 10),
+])
+def test_sort_pass_edges(ops, orc, op, dtype, n, m):
+    run_case(ops, orc, op, n, m, dtype, seed=n + m)
+
+
+@pytest.mark.parametrize("m", [3, 700])
+def test_every_index_out_of_range(ops, m):
+    n = 5000
+    _, xs, hb = workloads.hist_generic("linrec", n, m, "uniform", "f32", seed=m)
+    di = dev(np.where(np.arange(n) % 2, -1, m).astype(np.int32))
+    dx = [dev(x) for x in xs]
+    hs = [host(h) for h in ops.hist_generic("linrec", di, dx, m)]
+    assert np.all(hs[0] == 1) and np.all(hs[1] == 0)
+    for acc, base in ((False, 0.0), (True, 0.25)):
+        xb = [dev(np.full(n, 0.25, dtype=np.float32)) for _ in dx]
+        ops.hist_generic_vjp("linrec", di, dx, [dev(h) for h in hb], x_bar=xb, accumulate=acc)
+        assert all(np.all(host(g) == np.float32(base)) for g in xb)
