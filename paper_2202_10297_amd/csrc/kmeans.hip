@@ -13,6 +13,11 @@
 // Distances are formed in FP64 by the chain acc = fma(x_d - c_d, x_d - c_d,
 // acc), d = 0..D-1, so every implementation of that chain (the oracle's
 // included) decides the same nearest centre, ties going to the lowest k.
+// Large searches form the chains of few centres only: those that FP32 sums of
+// bf16 products, with a bound on their error, leave within reach of the
+// nearest.
+#include <math.h>
+
 #include "common.h"
 #include "prims.h"
 
@@ -25,6 +30,8 @@ constexpr int kKmPts = 256;          // points per distance block, one per lane
 constexpr int kKmSumBlocks = 1024;   // fixed partition of the objective's sum
 constexpr int kKmSmallK = 16;        // register accumulators in the gradient up to this K
 constexpr int kKmChunkMax = 4096;
+constexpr int kKmNearPts = 128;      // points per block of the bounded search
+constexpr int kKmNearSlices = 16;    // at most this many ranges of centres in it
 
 // Centres per slice: as many as kKmSliceBytes of FP64 holds (>= 4), at most 32.
 static int km_cps(int D, int K) {
@@ -49,6 +56,13 @@ __global__ __launch_bounds__(256) void km_widen_kernel(const float* __restrict__
     }
 }
 
+// Whether any of n flags is set (the whole block asks).
+__device__ __forceinline__ bool km_any(const int32_t* __restrict__ f, int n) {
+    int any = 0;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) any |= f[i];
+    return __syncthreads_or(any);
+}
+
 // Block (bx, s) takes points [bx 256, bx 256 + 256), one per lane, and centre
 // slice s (centres [s cps, s cps + cps)).  X comes in 32-dimension chunks,
 // copied into LDS with consecutive threads on consecutive addresses.  For each
@@ -60,7 +74,9 @@ __global__ __launch_bounds__(256) void km_widen_kernel(const float* __restrict__
 template <int CPS>
 __global__ __launch_bounds__(256) void km_dist_kernel(const float* __restrict__ X, int64_t N, int D,
                                                       const double* __restrict__ Cw, int K, int cps,
+                                                      const int32_t* __restrict__ bad, int nbad,
                                                       double* __restrict__ bd, int32_t* __restrict__ bk) {
+    if (bad && !km_any(bad, nbad)) return;  // the bounded search has it
     constexpr int kStride = kKmChunkD + 1;  // odd row stride: lanes hit distinct banks
     __shared__ float xs[kKmPts * kStride];
     const int s = blockIdx.y;
@@ -121,14 +137,310 @@ __global__ __launch_bounds__(256) void km_dist_kernel(const float* __restrict__ 
     bk[(int64_t)s * N + p0 + t] = k0 + bkk;
 }
 
+// -------------------------------------------------------- bounded search
+// x and c are taken relative to the first centre (a common offset of the data
+// would only widen the bound).  Then
+// |x - c|^2 - |x|^2 = |c|^2 - 2 x.c, with x.c as FP32 sums of bf16 products:
+// x = h + m + r, |r| <= 2^-18 |x|, and the terms hh, hm, mh, so each of the D
+// products is off by less than 3.2 2^-18 of it, and the 3 D additions (a step
+// of the matrix unit may truncate: 2^-23 each) by less than 4 (D + 16) 2^-23
+// of sum |x_d c_d| <= |x| |c|.  With beta the sum of both, the FP32 value g of
+// centre k is within
+//   e = |c| (2 beta |x| + 2^-21 |c|) + 2^-38 |x|^2 + 2^-100
+// of the exact one, up to what all centres of a point share (2^-21 and the
+// slack of beta cover the rounding of the differences, of |c|^2, g and the
+// bounds; the last terms that of the FP64 chain itself and underflow).  A centre
+// whose g - e exceeds the smallest g + e is not the nearest.  Per point and
+// range of centres the three smallest g - e are kept, two with their centre;
+// then the FP64 chains of those within reach decide, of a whole range where
+// its third is within reach too.
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ void km_split8(const float (&x)[8], bf16x8 (&p)[2]) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const __bf16 hi = (__bf16)x[i];
+        p[0][i] = hi;
+        p[1][i] = (__bf16)(x[i] - (float)hi);
+    }
+}
+
+// Eight dimensions from d0 of one row, relative to row `ref` (zero beyond D).
+__device__ __forceinline__ void km_row8(const float* __restrict__ row, const float* __restrict__ ref, int d0, int D,
+                                        bool vec, float (&x)[8]) {
+    if (vec && d0 + 8 <= D) {
+        const float4 a = *reinterpret_cast<const float4*>(row + d0), b = *reinterpret_cast<const float4*>(row + d0 + 4);
+        const float4 r = *reinterpret_cast<const float4*>(ref + d0), s = *reinterpret_cast<const float4*>(ref + d0 + 4);
+        x[0] = a.x - r.x, x[1] = a.y - r.y, x[2] = a.z - r.z, x[3] = a.w - r.w;
+        x[4] = b.x - s.x, x[5] = b.y - s.y, x[6] = b.z - s.z, x[7] = b.w - s.w;
+    } else {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = d0 + i < D ? row[d0 + i] - ref[d0 + i] : 0.f;
+    }
+}
+
+// A tile of 32 centres: its fragments (lane l: centre l % 32, dimensions 16 s
+// + 8 (l / 32) + 0..7, planes h and m), |c|^2, a bound of |c| and 2^-21 |c|^2
+// (a row past K: |c|^2 infinite), and the flag of a |c|^2 that FP32 cannot
+// work with, which sends the call to the FP64 search.
+template <int KS>
+__global__ __launch_bounds__(256) void km_near_prep_kernel(const float* __restrict__ C, int K, int D, bool vec,
+                                                           bf16x8* __restrict__ Cf, float* __restrict__ cst,
+                                                           int32_t* __restrict__ bad) {
+    __shared__ double sq[256];
+    const int t = threadIdx.x, tile = blockIdx.x;
+    const int k = 32 * tile + (t & 31);
+    double s = 0.0;
+    for (int e = t; e < KS * 64; e += 256) {  // e % 64 is the thread's lane throughout
+        float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        if (k < K) km_row8(C + (int64_t)k * D, C, 16 * (e / 64) + 8 * ((e >> 5) & 1), D, vec, x);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) s = fma((double)x[i], (double)x[i], s);
+        bf16x8 p[2];
+        km_split8(x, p);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) Cf[((int64_t)tile * KS * 2 + (e / 64) * 2 + q) * 64 + (e & 63)] = p[q];
+    }
+    sq[t] = s;
+    __syncthreads();
+    if (t < 32) {
+        for (int g = 1; g < 8; ++g) s += sq[t + 32 * g];
+        const float nc = (float)sqrt(s) * 1.001f;
+        float* o = cst + (int64_t)tile * 96 + t;
+        o[0] = k < K ? (float)s : INFINITY;
+        o[32] = k < K ? nc : 0.f;
+        o[64] = k < K ? nc * nc * 0x1p-21f : 0.f;
+        const uint64_t b = __ballot(k < K && !(s < 1e36));
+        if (t == 0) bad[tile] = b != 0;
+    }
+}
+
+struct KmNear {
+    float u;           // the smallest g + e
+    float m1, m2, m3;  // the smallest g - e
+    int32_t k1, k2;    // of the first two, the centres
+};
+
+// Block (bx, s): points [128 bx, 128 bx + 128), 32 to a wave, and centre tiles
+// [s per, (s + 1) per).  A wave keeps its points' fragments in registers; the
+// centre tiles pass through LDS, the next one loaded while this one is worked
+// on.  Bound by LDS reads and MFMA at D = 256 (48 steps of 32 cycles per tile)
+// and by the 13 vector instructions per pair at small D.
+// N = 10,000, D = 256, K = 1,024: 40 us (the FP64 chains of all pairs: 231).
+template <int KS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void km_near_kernel(
+    const float* __restrict__ X, int64_t N, int D, const float* __restrict__ C, bool vec,
+    const bf16x8* __restrict__ Cf, const float* __restrict__ cst, int ntiles, int per, KmNear* __restrict__ out) {
+    constexpr int U = KS * 2 * 64;  // 16-byte units per tile
+    constexpr int PER = U / 256;
+    static_assert(U % 256 == 0, "a tile is whole rounds of the block");
+    __shared__ u32x4 ct[2][U];
+    __shared__ __align__(16) float cc[2][96];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const int j = lane & 31, h = lane >> 5;
+    const int64_t p = (int64_t)blockIdx.x * kKmNearPts + w * 32 + j;
+    const int t0 = blockIdx.y * per, t1 = min(ntiles, t0 + per);
+    u32x4 nx[PER];
+    float nk = 0.f;
+    auto fetch = [&](int tile) {
+#pragma unroll
+        for (int u = 0; u < PER; ++u) nx[u] = reinterpret_cast<const u32x4*>(Cf)[(int64_t)tile * U + u * 256 + t];
+        if (t < 96) nk = cst[(int64_t)tile * 96 + t];
+    };
+    auto put = [&](int b) {
+#pragma unroll
+        for (int u = 0; u < PER; ++u) ct[b][u * 256 + t] = nx[u];
+        if (t < 96) cc[b][t] = nk;
+    };
+    fetch(t0);
+    bf16x8 xf[KS][2];
+    float x2 = 0.f;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+        float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        if (p < N) km_row8(X + p * D, C, 16 * s + 8 * h, D, vec, x);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x2 = fmaf(x[i], x[i], x2);
+        km_split8(x, xf[s]);
+    }
+    x2 += __shfl_xor(x2, 32, kWave);
+    x2 *= 1.001f;
+    constexpr float kBeta = 3.2f * 0x1p-18f + 4.f * (16.f * KS + 16.f) * 0x1p-23f;
+    const float ex = 2.f * kBeta * sqrtf(x2);
+    put(0);
+    float u = INFINITY, m1 = INFINITY, m2 = INFINITY, m3 = INFINITY;
+    int k1 = 0, k2 = 0;
+    for (int tile = t0; tile < t1; ++tile) {
+        const int b = (tile - t0) & 1;
+        if (tile + 1 < t1) fetch(tile + 1);
+        __syncthreads();  // buffer b is filled, and the other one no longer read
+        const bf16x8* cf = reinterpret_cast<const bf16x8*>(ct[b]);
+        f32x16 acc;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const bf16x8 ch = cf[(s * 2) * 64 + lane], cm = cf[(s * 2 + 1) * 64 + lane];
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cm, xf[s][0], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ch, xf[s][1], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ch, xf[s][0], acc, 0, 0, 0);
+        }
+        const int kb = 32 * tile + 4 * h;
+#pragma unroll
+        for (int t4 = 0; t4 < 4; ++t4) {
+            const float4 a = *reinterpret_cast<const float4*>(&cc[b][8 * t4 + 4 * h]);
+            const float4 n = *reinterpret_cast<const float4*>(&cc[b][32 + 8 * t4 + 4 * h]);
+            const float4 d = *reinterpret_cast<const float4*>(&cc[b][64 + 8 * t4 + 4 * h]);
+            const float c2[4] = {a.x, a.y, a.z, a.w}, nc[4] = {n.x, n.y, n.z, n.w}, dc[4] = {d.x, d.y, d.z, d.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float g = fmaf(-2.f, acc[4 * t4 + i], c2[i]);
+                const float e = fmaf(nc[i], ex, dc[i]);
+                const float lo = g - e;
+                const int k = kb + 8 * t4 + i;
+                u = fminf(u, g + e);
+                const bool b1 = lo < m1, b2 = lo < m2;
+                m3 = fminf(m3, fmaxf(m2, lo));
+                m2 = fminf(m2, fmaxf(m1, lo));
+                m1 = fminf(m1, lo);
+                k2 = b1 ? k1 : (b2 ? k : k2);
+                k1 = b1 ? k : k1;
+            }
+        }
+        if (tile + 1 < t1) put(b ^ 1);
+    }
+    if (p >= N) return;
+    const float e0 = fmaf(x2, 0x1p-38f, 0x1p-100f);
+    KmNear r;
+    r.u = x2 < 1e36f ? u + e0 : NAN;  // NaN: every centre's chain is formed
+    r.m1 = m1 - e0, r.m2 = m2 - e0, r.m3 = m3 - e0;
+    r.k1 = k1, r.k2 = k2;
+    out[((int64_t)blockIdx.y * 2 + h) * N + p] = r;
+}
+
+// The distance chain of point row x and centre row c.
+__device__ __forceinline__ double km_chain(const float* __restrict__ x, const float* __restrict__ c, int D, bool vec) {
+    double acc = 0.0;
+    int d = 0;
+    if (vec) {
+#pragma unroll 4
+        for (; d + 4 <= D; d += 4) {
+            const float4 a = *reinterpret_cast<const float4*>(x + d), b = *reinterpret_cast<const float4*>(c + d);
+            const double u0 = (double)a.x - (double)b.x, u1 = (double)a.y - (double)b.y;
+            const double u2 = (double)a.z - (double)b.z, u3 = (double)a.w - (double)b.w;
+            acc = fma(u3, u3, fma(u2, u2, fma(u1, u1, fma(u0, u0, acc))));
+        }
+    } else {
+#pragma unroll 8
+        for (; d < D; ++d) {
+            const double u = (double)x[d] - (double)c[d];
+            acc = fma(u, u, acc);
+        }
+    }
+    return acc;
+}
+
+// Four lanes per point: the centres within reach, their chains, the nearest
+// (the lowest of equal ones).  Where an entry's third is within reach too, or
+// the point's norm was beyond FP32, the block afterwards forms the chains of
+// all its centres together.  Centres that all agree to within the
+// bound send every point there, some three times slower than the FP64 search.
+__global__ __launch_bounds__(256) void km_decide_kernel(const float* __restrict__ X, int64_t N, int D,
+                                                        const float* __restrict__ C, int K, bool vec,
+                                                        const KmNear* __restrict__ near, int nent, int per,
+                                                        const int32_t* __restrict__ bad, int ntiles,
+                                                        double* __restrict__ bd, int32_t* __restrict__ bk) {
+    constexpr int kEnt = 2 * kKmNearSlices;
+    constexpr int32_t kNone = 0x7fffffff;
+    __shared__ int32_t list[64][2 * kEnt];   // single centres
+    __shared__ int32_t whole[64 * kEnt];     // point of the block * (kEnt + 1) + entry (kEnt: every centre)
+    __shared__ int32_t cnt[64], nwhole;
+    __shared__ double sd[64], rd[4];
+    __shared__ int32_t sk[64], rk[4];
+    if (km_any(bad, ntiles)) return;
+    const int q = threadIdx.x & 3, pt = threadIdx.x >> 2;
+    const int64_t p = (int64_t)blockIdx.x * 64 + pt;
+    if (threadIdx.x < 64) cnt[threadIdx.x] = 0;
+    if (threadIdx.x == 0) nwhole = 0;
+    __syncthreads();
+    if (p < N) {
+        float u = INFINITY;
+        bool all = false;
+        for (int e = q; e < nent; e += 4) {
+            const float v = near[(int64_t)e * N + p].u;
+            all |= v != v;
+            u = fminf(u, v);
+        }
+        u = fminf(u, __shfl_xor(u, 1, kWave));
+        u = fminf(u, __shfl_xor(u, 2, kWave));
+        all = __shfl((int)all, threadIdx.x & 60, kWave);  // entry 0 is lane 0's, and all entries agree
+        if (all) {
+            if (q == 0) whole[atomicAdd(&nwhole, 1)] = pt * (kEnt + 1) + kEnt;
+        } else {
+            for (int e = q; e < nent; e += 4) {
+                const KmNear r = near[(int64_t)e * N + p];
+                if (r.m3 <= u) {
+                    whole[atomicAdd(&nwhole, 1)] = pt * (kEnt + 1) + e;
+                } else {
+                    if (r.m1 <= u) list[pt][atomicAdd(&cnt[pt], 1)] = r.k1;
+                    if (r.m2 <= u) list[pt][atomicAdd(&cnt[pt], 1)] = r.k2;
+                }
+            }
+        }
+    }
+    __syncthreads();
+    double best = INFINITY;
+    int32_t bestk = kNone;
+    auto take = [&](double d, int32_t k) {
+        if (d < best || (d == best && k < bestk)) best = d, bestk = k;
+    };
+    auto meet = [&](int o) {
+        const double d = __shfl_xor(best, o, kWave);
+        const int32_t k = __shfl_xor(bestk, o, kWave);
+        take(d, k);
+    };
+    if (p < N)
+        for (int i = q; i < cnt[pt]; i += 4)
+            take(km_chain(X + p * D, C + (int64_t)list[pt][i] * D, D, vec), list[pt][i]);
+    meet(1);
+    meet(2);
+    if (q == 0) sd[pt] = best, sk[pt] = bestk;
+    __syncthreads();
+    for (int i = 0; i < nwhole; ++i) {
+        const int wpt = whole[i] / (kEnt + 1), e = whole[i] % (kEnt + 1);
+        const float* x = X + ((int64_t)blockIdx.x * 64 + wpt) * D;
+        const int first = e == kEnt ? 0 : (e >> 1) * per, last = e == kEnt ? ntiles : min(ntiles, first + per);
+        best = INFINITY, bestk = kNone;
+        for (int c = 32 * first + (int)threadIdx.x; c < min(K, 32 * last); c += 256)
+            if (e == kEnt || ((c >> 2) & 1) == (e & 1)) take(km_chain(x, C + (int64_t)c * D, D, vec), c);
+#pragma unroll
+        for (int o = 1; o < kWave; o *= 2) meet(o);
+        if ((threadIdx.x & 63) == 0) rd[threadIdx.x >> 6] = best, rk[threadIdx.x >> 6] = bestk;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            best = sd[wpt], bestk = sk[wpt];
+            for (int w = 0; w < 4; ++w) take(rd[w], rk[w]);
+            // no distance compares: none is a number, and centre 0 keeps the point
+            if (bestk == kNone && e == kEnt) best = km_chain(x, C, D, vec), bestk = 0;
+            sd[wpt] = best, sk[wpt] = bestk;
+        }
+        __syncthreads();
+    }
+    if (q == 0 && p < N) bd[p] = sd[pt], bk[p] = sk[pt];
+}
+
 // Nearest centre over the slices in increasing order (strict <: ties keep
 // the lower centre), and the block's share of the objective: block b takes
 // points b 256 + t + r G 256 (G = gridDim.x, fixed by N), sums them per
 // thread in r order and then over the block in a fixed tree.
 __global__ __launch_bounds__(256) void km_combine_kernel(const double* __restrict__ bd, const int32_t* __restrict__ bk,
-                                                         int64_t N, int nslice, int32_t* __restrict__ assign,
+                                                         int64_t N, int nslice, const int32_t* __restrict__ bad,
+                                                         int nbad, int32_t* __restrict__ assign,
                                                          double* __restrict__ part) {
     __shared__ double sh[256];
+    if (bad && !km_any(bad, nbad)) nslice = 1;  // the bounded search's decisions
     double acc = 0.0;
     for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < N; p += (int64_t)gridDim.x * blockDim.x) {
         double best = bd[p];
@@ -334,8 +646,22 @@ struct KmPlan {
     bool small;  // register accumulators in the gradient
     int cpb, nslices_acc;
     int64_t chunk, nchunk;
-    size_t cd, bd, bk, part, spart, npart, total;
+    int near_ks, near_tiles, near_per, near_slices;  // the bounded search (0: not used)
+    size_t cd, bd, bk, part, spart, npart, cf, cst, bad, near, total;
 };
+
+// The bounded search wants enough pairs to pay for its three more launches and
+// its decisions, fragments that fit the registers (D <= 256), and chains longer
+// than the 13 vector instructions it spends on a pair; rows of no whole 16
+// bytes load slowly and want twice the work.  Objective and gradient, FP64
+// search against this one, just above the line: N = 40,000, D = 64, K = 128:
+// 78 and 65 us; N = 65,536, D = 16, K = 256: 77 and 66; N = 4,099, D = 256, K =
+// 256: 128 and 64; N = 70,003, D = 35, K = 1,000: 250 and 133 (but N =
+// 100,003, D = 35, K = 77: 95 and 106).
+static bool km_near(int64_t N, int D, int K) {
+    const int64_t least = (int64_t)1 << (D % 4 ? 30 : 28);
+    return D >= 16 && D <= 256 && K >= 64 && N * K >= least / D;
+}
 
 static KmPlan km_plan(int64_t N, int D, int K) {
     KmPlan p{};
@@ -377,6 +703,23 @@ static KmPlan km_plan(int64_t N, int D, int K) {
     p.part = take((size_t)kKmSumBlocks * 8);
     p.spart = take((size_t)p.nchunk * K * D * 8);
     p.npart = take((size_t)p.nchunk * K * 4);
+    if (km_near(N, D, K)) {
+        p.near_ks = D <= 32 ? 2 : D <= 64 ? 4 : D <= 128 ? 8 : 16;
+        p.near_tiles = (int)ceil_div(K, 32);
+        // some 512 blocks (two fit a CU; a block splits its points once), in
+        // at most kKmNearSlices ranges.  N = 10,000, D = 256, K = 1,024 and
+        // N = 20,001, D = 128, K = 1,001, all of a step, with 256, 512, 1,024:
+        // 87, 91, 96 us and 90, 88, 94 us.
+        int64_t s = ceil_div(512, ceil_div(N, kKmNearPts));
+        if (s > kKmNearSlices) s = kKmNearSlices;
+        if (s > p.near_tiles) s = p.near_tiles;
+        p.near_per = (int)ceil_div(p.near_tiles, s);
+        p.near_slices = (int)ceil_div(p.near_tiles, p.near_per);
+        p.cf = take((size_t)p.near_tiles * p.near_ks * 2 * 1024);
+        p.cst = take((size_t)p.near_tiles * 96 * 4);
+        p.bad = take((size_t)p.near_tiles * 4);
+        p.near = take((size_t)p.near_slices * 2 * N * sizeof(KmNear));
+    }
     p.total = o;
     return p;
 }
@@ -385,7 +728,24 @@ template <int CPS>
 static void launch_dist(const float* X, int64_t N, int D, int K, const KmPlan& p, char* ws, hipStream_t st) {
     const dim3 grid((unsigned)ceil_div(N, kKmPts), (unsigned)p.nslice);
     hipLaunchKernelGGL((km_dist_kernel<CPS>), grid, dim3(kKmPts), 0, st, X, N, D, (const double*)(ws + p.cd), K,
-                       p.cps, (double*)(ws + p.bd), (int32_t*)(ws + p.bk));
+                       p.cps, p.near_ks ? (const int32_t*)(ws + p.bad) : nullptr, p.near_tiles, (double*)(ws + p.bd),
+                       (int32_t*)(ws + p.bk));
+}
+
+template <int KS>
+static void launch_near(const float* X, int64_t N, int D, const float* C, int K, const KmPlan& p, char* ws,
+                        hipStream_t st) {
+    const bool vec = D % 4 == 0 && aligned(X, 16) && aligned(C, 16);
+    bf16x8* cf = reinterpret_cast<bf16x8*>(ws + p.cf);
+    float* cst = reinterpret_cast<float*>(ws + p.cst);
+    int32_t* bad = reinterpret_cast<int32_t*>(ws + p.bad);
+    KmNear* near = reinterpret_cast<KmNear*>(ws + p.near);
+    hipLaunchKernelGGL(km_near_prep_kernel<KS>, dim3((unsigned)p.near_tiles), dim3(256), 0, st, C, K, D, vec, cf, cst,
+                       bad);
+    hipLaunchKernelGGL(km_near_kernel<KS>, dim3((unsigned)ceil_div(N, kKmNearPts), (unsigned)p.near_slices), dim3(256),
+                       0, st, X, N, D, C, vec, cf, cst, p.near_tiles, p.near_per, near);
+    hipLaunchKernelGGL(km_decide_kernel, dim3((unsigned)ceil_div(N, 64)), dim3(256), 0, st, X, N, D, C, K, vec, near,
+                       2 * p.near_slices, p.near_per, bad, p.near_tiles, (double*)(ws + p.bd), (int32_t*)(ws + p.bk));
 }
 
 template <int KM>
@@ -431,12 +791,19 @@ extern "C" pvjp_status pvjp_kmeans_objective(const float* X, int64_t N, int D, c
         const int64_t nw = (int64_t)p.nslice * D * p.cpsT;
         hipLaunchKernelGGL(km_widen_kernel, dim3(flat_grid(nw, 256, 4)), dim3(256), 0, st, C, K, D, p.cps, p.cpsT, nw,
                            (double*)(w + p.cd));
+        if (p.near_ks == 2) launch_near<2>(X, N, D, C, K, p, w, st);
+        else if (p.near_ks == 4) launch_near<4>(X, N, D, C, K, p, w, st);
+        else if (p.near_ks == 8) launch_near<8>(X, N, D, C, K, p, w, st);
+        else if (p.near_ks == 16) launch_near<16>(X, N, D, C, K, p, w, st);
+        // after a bounded search the FP64 one runs only if a centre's norm is
+        // beyond FP32 (or not a number): the kernel asks the flags
         if (p.cpsT == 4) launch_dist<4>(X, N, D, K, p, w, st);
         else if (p.cpsT == 8) launch_dist<8>(X, N, D, K, p, w, st);
         else if (p.cpsT == 16) launch_dist<16>(X, N, D, K, p, w, st);
         else launch_dist<32>(X, N, D, K, p, w, st);
         hipLaunchKernelGGL(km_combine_kernel, dim3((unsigned)p.sum_blocks), dim3(256), 0, st,
-                           (const double*)(w + p.bd), (const int32_t*)(w + p.bk), N, p.nslice, assign,
+                           (const double*)(w + p.bd), (const int32_t*)(w + p.bk), N, p.nslice,
+                           p.near_ks ? (const int32_t*)(w + p.bad) : nullptr, p.near_tiles, assign,
                            (double*)(w + p.part));
     }
     hipLaunchKernelGGL(km_sum_kernel, dim3(1), dim3(1024), 0, st, (const double*)(w + p.part),

@@ -100,3 +100,58 @@ def test_autograd(orc):
     assert rel_l2(host(c.grad), ref) <= TOL_F32
     fv = float(f.detach())
     assert abs(fv - orc.kmeans_objective(X, C)[0]) <= 1e-12 * fv
+
+
+# searches large enough for the bounded form (D from 16 to 256, K >= 64): widths
+# around its fragments, rows that are no whole 16 bytes, a ragged last tile of
+# centres and block of points
+@pytest.mark.parametrize("N,D,K,off", [(262145, 16, 64, 0.0), (60003, 35, 515, 0.0), (70001, 64, 65, 1000.0),
+                                       (20011, 100, 257, -30.0), (8099, 255, 530, 0.0), (17000, 256, 64, 3.0e4)])
+def test_bounded_search(ops, orc, N, D, K, off):
+    X, C = workloads.kmeans(N, D, K, "f32", seed=N + D + K)
+    X, C = X + np.float32(off), C + np.float32(off)
+    # ties: equal centres, in pairs and in a row of five, the lowest wins
+    C[K - 1] = C[0]
+    C[20:25] = C[20]
+    f, a = ops.kmeans_objective(dev(X), dev(C))
+    rf, ra = orc.kmeans_objective(X, C)
+    assert np.array_equal(host(a), ra)
+    assert abs(host(f)[0] - rf) <= 1e-12 * rf
+
+
+def test_bounded_search_close_centres(ops, orc):
+    # every centre within rounding of the others' distance: the FP64 chains decide
+    N, D, K = 9000, 128, 256
+    g = workloads.rng(77)
+    X = g.standard_normal((N, D)).astype(np.float32)
+    C = (1e-5 * g.standard_normal((K, D))).astype(np.float32)
+    f, a = ops.kmeans_objective(dev(X), dev(C))
+    rf, ra = orc.kmeans_objective(X, C)
+    assert np.array_equal(host(a), ra) and abs(host(f)[0] - rf) <= 1e-12 * rf
+
+
+def test_bounded_search_extreme_values(ops, orc):
+    # points beyond the FP32 norms, tiny ones, zero centres
+    N, D, K = 40000, 64, 128
+    X, C = workloads.kmeans(N, D, K, "f32", seed=9)
+    X[5], X[6, 3], X[7] = 1e19, 3e30, 1e-30
+    C[3] = 0.0
+    f, a = ops.kmeans_objective(dev(X), dev(C))
+    _, ra = orc.kmeans_objective(X, C)
+    assert np.array_equal(host(a), ra)
+    # a point that is no number: all its distances are, centre 0 keeps it
+    X[5], X[6, 3] = 0.0, 0.0
+    X[11, 5] = np.nan
+    _, a = ops.kmeans_objective(dev(X), dev(C))
+    _, ra = orc.kmeans_objective(np.delete(X, 11, 0), C)
+    assert np.array_equal(np.delete(host(a), 11), ra) and host(a)[11] == 0
+    # a centre that is no number wins nothing; one out of FP32's reach neither
+    X[11, 5] = 0.0
+    for v in (np.nan, 1e25):
+        D_ = C.copy()
+        D_[5, 2] = v
+        _, a = ops.kmeans_objective(dev(X), dev(D_))
+        far = C.copy()
+        far[5] = 1e15
+        _, ra = orc.kmeans_objective(X, far)
+        assert np.array_equal(host(a), ra)
