@@ -588,8 +588,8 @@ __global__ __launch_bounds__(256) void hist_vjp_winner_kernel(const int32_t* __r
 //      coalesced stores whatever the bucket count) and records the tile's
 //      bucket offsets;
 //   2. per bucket, an exclusive scan of its run lengths over the tiles;
-//      each bucket is split into work items of about kPartSeg records made
-//      of whole runs;
+//      each bucket is split into work items of about seg records (kPartSegMin
+//      .. kPartSeg) made of whole runs;
 //   3. one block per work item walks its runs and accumulates the bucket's
 //      4096 bins in LDS, then writes them out as a partial;
 //   4. merge the partials of each bin in work-item order.
@@ -598,7 +598,8 @@ __global__ __launch_bounds__(256) void hist_vjp_winner_kernel(const int32_t* __r
 constexpr int kPartShift = 12;
 constexpr int kPartBins = 1 << kPartShift;
 constexpr int kPartMaxBuckets = 1024;
-constexpr int64_t kPartSeg = (int64_t)1 << 17;
+constexpr int64_t kPartSeg = (int64_t)1 << 17;     // records per work item, at most
+constexpr int64_t kPartSegMin = (int64_t)1 << 14;  // and at least
 constexpr int kPartScanThreads = 1024;
 constexpr int kTileThreads = 512;
 constexpr int kTileQuads = 4;                              // quads of elements per thread
@@ -606,7 +607,7 @@ constexpr int kTile = 4 * kTileThreads * kTileQuads;       // 8192 elements
 constexpr int kTileBucketsPerThread = kPartMaxBuckets / kTileThreads;
 static_assert(kTile <= 65536, "an element's position in its tile must fit 16 bits");
 static_assert(kPartMaxBuckets % kTileThreads == 0, "tile threads own whole groups of buckets in the scan");
-static_assert(kTile < kPartSeg, "a work item must hold any single run");
+static_assert(kTile < kPartSegMin, "a work item must hold any single run");
 
 // Stores of the first cnt staged words of a tile, 16 bytes per lane.
 __device__ __forceinline__ void tile_store_u32(uint32_t* __restrict__ dst, const uint32_t* stage, int cnt) {
@@ -626,18 +627,37 @@ __device__ __forceinline__ void tile_store_u16(uint16_t* __restrict__ dst, const
     }
 }
 
+// Whether a record keeps its position in the tile (min/max: the winner).
+template <int OP>
+__host__ __device__ constexpr bool part_keys() {
+    return OP == PVJP_MIN || OP == PVJP_MAX;
+}
+template <class T>
+__device__ __forceinline__ uint32_t val_word(T v, int hi) {
+    if constexpr (sizeof(T) == 4) return __float_as_uint(v);
+    else return (uint32_t)((uint64_t)__double_as_longlong(v) >> (32 * hi));
+}
+template <class T>
+__device__ __forceinline__ T val_of(uint32_t lo, uint32_t hi) {
+    if constexpr (sizeof(T) == 4) return __uint_as_float(lo);
+    else return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
 // Tile sort.  Tile t owns records [t * kTile, t * kTile + valid) of every
 // record array; toff[t][b] is the start of bucket b's run in the tile and
 // toff[t][nb] the number of in-range elements.  Record of element e with bin
-// k = b * 4096 + j: rval = the value's bits; for + rbin = j (2 bytes), for
-// min/max rbin = j | (e - t * kTile) << 16 (4 bytes: the position in the
-// tile gives back the element index for the lowest-index rule).
-template <int OP, bool VEC>
+// k = b * 4096 + j: rval = the value's bits (FP64: its low word, the high one
+// in rhi, so that both widths stage one word per record at a time); for + and
+// * rbin = j (2 bytes), for min/max rbin = j | (e - t * kTile) << 16 (4 bytes:
+// the position in the tile gives back the element index for the lowest-index
+// rule).
+template <class T, int OP, bool VEC>
 __global__ __launch_bounds__(kTileThreads) void hpart_tile_kernel(const int32_t* __restrict__ inds,
-                                                                const float* __restrict__ vs, int64_t n, int32_t m,
+                                                                const T* __restrict__ vs, int64_t n, int32_t m,
                                                                 int nb, uint32_t* __restrict__ rval,
-                                                                void* __restrict__ rbin, int32_t* __restrict__ toff) {
-    constexpr bool KEYS = OP != PVJP_ADD;
+                                                                uint32_t* __restrict__ rhi, void* __restrict__ rbin,
+                                                                int32_t* __restrict__ toff) {
+    constexpr bool KEYS = part_keys<OP>();
     __shared__ int32_t bcnt[kPartMaxBuckets];  // counts, then run starts
     __shared__ __align__(16) uint32_t sval[kTile];
     __shared__ __align__(16) uint32_t sbin[KEYS ? kTile : kTile / 2];
@@ -645,10 +665,10 @@ __global__ __launch_bounds__(kTileThreads) void hpart_tile_kernel(const int32_t*
     const int64_t base = (int64_t)blockIdx.x * kTile;
     const int64_t hi = (base + kTile < n) ? base + kTile : n;
     for (int b = threadIdx.x; b < nb; b += kTileThreads) bcnt[b] = 0;
-    Quad<float> q[kTileQuads];
+    Quad<T> q[kTileQuads];
 #pragma unroll
     for (int u = 0; u < kTileQuads; ++u)
-        q[u] = load_quad<float, VEC>(inds, vs, base + 4 * ((int64_t)u * kTileThreads + threadIdx.x), hi);
+        q[u] = load_quad<T, VEC>(inds, vs, base + 4 * ((int64_t)u * kTileThreads + threadIdx.x), hi);
     __syncthreads();
     int rank[4 * kTileQuads];
 #pragma unroll
@@ -687,10 +707,11 @@ __global__ __launch_bounds__(kTileThreads) void hpart_tile_kernel(const int32_t*
         const int32_t kk[4] = {q[u].k.x, q[u].k.y, q[u].k.z, q[u].k.w};
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            if (rank[4 * u + t] < 0) continue;
-            const int slot = bcnt[kk[t] >> kPartShift] + rank[4 * u + t];
+            int& slot = rank[4 * u + t];  // from here on the record's slot
+            if (slot < 0) continue;
+            slot += bcnt[kk[t] >> kPartShift];
             const uint32_t j = (uint32_t)kk[t] & (kPartBins - 1);
-            sval[slot] = __float_as_uint(q[u].v[t]);
+            sval[slot] = val_word<T>(q[u].v[t], 0);
             if (KEYS)
                 sbin[slot] = j | ((uint32_t)(4 * (u * kTileThreads + (int)threadIdx.x) + t) << 16);
             else
@@ -703,6 +724,16 @@ __global__ __launch_bounds__(kTileThreads) void hpart_tile_kernel(const int32_t*
         tile_store_u32(reinterpret_cast<uint32_t*>(rbin) + base, sbin, tot.v);
     else
         tile_store_u16(reinterpret_cast<uint16_t*>(rbin) + base, sbin16, tot.v);
+    if (sizeof(T) == 8) {
+        __syncthreads();  // the low words have been read out
+#pragma unroll
+        for (int u = 0; u < kTileQuads; ++u)
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                if (rank[4 * u + t] >= 0) sval[rank[4 * u + t]] = val_word<T>(q[u].v[t], 1);
+        __syncthreads();
+        tile_store_u32(rhi + base, sval, tot.v);
+    }
 }
 
 // Per chunk c of kColChunk tiles (grid y) and group of kColThreads buckets
@@ -769,13 +800,13 @@ __global__ __launch_bounds__(kColThreads) void hpart_colscan_kernel(const int32_
 
 // Per bucket (one block each): chunk prefixes (ctot is overwritten with the
 // exclusive prefix) and the bucket's work-item count -- item i takes the
-// runs that start in [i * kPartSeg, (i + 1) * kPartSeg), so the count is one
-// more than the last non-empty run's start over kPartSeg, none for an empty
-// bucket.
+// runs that start in [i * seg, (i + 1) * seg), so the count is one more than
+// the last non-empty run's start over seg, none for an empty bucket.
 constexpr int kBscanThreads = 256;
 __global__ __launch_bounds__(kBscanThreads) void hpart_bscan_kernel(int32_t* __restrict__ ctot,
                                                                     const int32_t* __restrict__ clast,
-                                                                    int nchunks, int32_t* __restrict__ bitems) {
+                                                                    int nchunks, int seg,
+                                                                    int32_t* __restrict__ bitems) {
     __shared__ IntSum::S wtot[kBscanThreads / kWave];
     __shared__ int lastp;
     const int b = blockIdx.x;
@@ -794,7 +825,7 @@ __global__ __launch_bounds__(kBscanThreads) void hpart_bscan_kernel(int32_t* __r
         carry += tot.v;
     }
     __syncthreads();
-    if (threadIdx.x == 0) bitems[b] = lastp >= 0 ? (int)(lastp / kPartSeg) + 1 : 0;
+    if (threadIdx.x == 0) bitems[b] = lastp >= 0 ? lastp / seg + 1 : 0;
 }
 
 // One block: work-item starts per bucket.
@@ -810,15 +841,15 @@ __global__ __launch_bounds__(kPartScanThreads) void hpart_scan_kernel(const int3
 }
 
 // First tile of every work item: item i of bucket b takes the tiles whose run
-// of b starts in [i * kPartSeg, (i + 1) * kPartSeg), i.e. from the first tile
-// t with P[b][t] >= i * kPartSeg, where P[b][t] = Ploc + the chunk prefix is
+// of b starts in [i * seg, (i + 1) * seg), i.e. from the first tile
+// t with P[b][t] >= i * seg, where P[b][t] = Ploc + the chunk prefix is
 // the start of b's run in tile t within the bucket.  Non-empty runs start at
-// 0 and are shorter than kPartSeg, so up to the last non-empty run every
+// 0 and are shorter than seg, so up to the last non-empty run every
 // such interval holds a run start, and exactly one thread finds the first
 // tile of each item.
 __global__ __launch_bounds__(256) void hpart_items_kernel(const int32_t* __restrict__ Ploc,
                                                           const int32_t* __restrict__ cpre, int ntiles, int nb,
-                                                          int nchunks, const int32_t* __restrict__ istart,
+                                                          int nchunks, int seg, const int32_t* __restrict__ istart,
                                                           int32_t* __restrict__ itile) {
     const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (g >= (int64_t)nb * ntiles) return;
@@ -831,8 +862,8 @@ __global__ __launch_bounds__(256) void hpart_items_kernel(const int32_t* __restr
     if (t == 0) {
         i = 0;
     } else {
-        i = P(t) / kPartSeg;
-        if (i == 0 || i * kPartSeg <= P(t - 1)) return;
+        i = P(t) / seg;
+        if (i == 0 || i * seg <= P(t - 1)) return;
     }
     if (i < items) itile[istart[b] + i] = t;
 }
@@ -898,12 +929,14 @@ __device__ __forceinline__ uint32_t acc_slot(const AccGroup& G, int r) {
     return o + (uint32_t)r;
 }
 
-template <int OP, bool COUNTS>
-__device__ __forceinline__ void acc_record(uint64_t* acc, int32_t* cnt, uint32_t copy, int64_t tile_base,
-                                           uint32_t at, uint32_t v, uint32_t bn) {
+template <class T, int OP, bool COUNTS>
+__device__ __forceinline__ void acc_record(uint64_t* acc, int32_t* cnt, int32_t* aux, uint32_t copy,
+                                           int64_t tile_base, uint32_t at, T v, uint32_t bn) {
     const uint32_t j = bn & (kPartBins - 1);
-    if (OP != PVJP_ADD) {
+    uint64_t* w = &acc[j * kAccCopies + copy];
+    if (part_keys<OP>()) {
         // the tile start plus the position in the tile: the element index
+        // (part of an FP32 key; FP64 winners are found in a second sweep)
         const int64_t e = tile_base + (int64_t)(at & ~(uint32_t)(kTile - 1)) + (int64_t)(bn >> 16);
         // A key only ever grows, so a record whose key does not exceed the
         // word read now cannot win and skips the atomic.  A read of one word
@@ -911,12 +944,16 @@ __device__ __forceinline__ void acc_record(uint64_t* acc, int32_t* cnt, uint32_t
         // on a hot bin almost every record stops here, and on a uniform one
         // the expected number of winners among k records is the k-th
         // harmonic number.
-        const uint64_t key = elem_key<OP>(__uint_as_float(v), e);
-        uint64_t* w = &acc[j * kAccCopies + copy];
+        const uint64_t key = elem_key<OP>(v, e);
         if (key > __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))
             atomicMax(reinterpret_cast<unsigned long long*>(w), (unsigned long long)key);
+    } else if (OP == PVJP_MUL) {
+        if (v == T(0))
+            atomicAdd(&aux[j], 1);
+        else
+            mul_f64_atomic(w, (double)v);
     } else {
-        atomicAdd(reinterpret_cast<double*>(&acc[j * kAccCopies + copy]), (double)__uint_as_float(v));
+        atomicAdd(reinterpret_cast<double*>(w), (double)v);
     }
     if (COUNTS) atomicAdd(&cnt[j], 1);
 }
@@ -955,10 +992,11 @@ __device__ __forceinline__ PartItem part_item(int nb, int ntiles, const int32_t*
 }
 
 // Walks the item's records (see above) and hands each lane's records to
-// fn(tile_base, ok, slot, value bits, bin word), the whole wave calling.
-template <bool KEYS, class Fn>
-__device__ __forceinline__ void part_walk(const uint32_t* __restrict__ rval, const void* __restrict__ rbin,
-                                          const uint32_t* __restrict__ D, int ntiles, const PartItem& I, Fn fn) {
+// fn(tile_base, ok, slot, value, bin word), the whole wave calling.
+template <class T, bool KEYS, class Fn>
+__device__ __forceinline__ void part_walk(const uint32_t* __restrict__ rval, const uint32_t* __restrict__ rhi,
+                                          const void* __restrict__ rbin, const uint32_t* __restrict__ D, int ntiles,
+                                          const PartItem& I, Fn fn) {
     constexpr int NW = kAccBlock / kWave;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
@@ -972,6 +1010,7 @@ __device__ __forceinline__ void part_walk(const uint32_t* __restrict__ rval, con
         const int nc = (w1 - c0 < kWave) ? w1 - c0 : kWave;
         const int64_t tbase = (int64_t)c0 * kTile;
         const char* cv = reinterpret_cast<const char*>(rval + tbase);
+        const char* ch = sizeof(T) == 8 ? reinterpret_cast<const char*>(rhi + tbase) : nullptr;
         const char* cb = reinterpret_cast<const char*>(rbin) + tbase * (KEYS ? 4 : 2);
         // a pass reads kAccPar groups of kAccGroup consecutive runs side by
         // side; fewer runs than one pass takes are split evenly between them
@@ -989,6 +1028,7 @@ __device__ __forceinline__ void part_walk(const uint32_t* __restrict__ rval, con
             }
             for (int r0 = 0; r0 < R; r0 += kAccSlots * kWave) {
                 uint32_t at[kAccPar * kAccSlots], vv[kAccPar * kAccSlots], bb[kAccPar * kAccSlots];
+                uint32_t vh[kAccPar * kAccSlots];
                 bool ok[kAccPar * kAccSlots];
 #pragma unroll
                 for (int s = 0; s < kAccPar * kAccSlots; ++s) {
@@ -1001,83 +1041,115 @@ __device__ __forceinline__ void part_walk(const uint32_t* __restrict__ rval, con
                     at[s] = ok[s] ? acc_slot(G[p], r) : 0u;
                     // a uniform base and a 32-bit byte offset per lane
                     vv[s] = *reinterpret_cast<const uint32_t*>(cv + (at[s] << 2));
+                    vh[s] = sizeof(T) == 8 ? *reinterpret_cast<const uint32_t*>(ch + (at[s] << 2)) : 0u;
                     bb[s] = KEYS ? *reinterpret_cast<const uint32_t*>(cb + (at[s] << 2))
                                  : (uint32_t)*reinterpret_cast<const uint16_t*>(cb + (at[s] << 1));
                 }
 #pragma unroll
-                for (int s = 0; s < kAccPar * kAccSlots; ++s) fn(tbase, ok[s], at[s], vv[s], bb[s]);
+                for (int s = 0; s < kAccPar * kAccSlots; ++s) fn(tbase, ok[s], at[s], val_of<T>(vv[s], vh[s]), bb[s]);
             }
         }
     }
 }
 
-template <int OP, bool COUNTS>
+// Per bin beside the accumulator: the zeros of a product, the lowest winning
+// index of FP64 extremes.
+template <class T, int OP>
+__host__ __device__ constexpr bool part_aux() {
+    return OP == PVJP_MUL || (sizeof(T) == 8 && part_keys<OP>());
+}
+
+template <class T, int OP, bool COUNTS>
 __global__ __launch_bounds__(kAccBlock) void hpart_acc_kernel(const uint32_t* __restrict__ rval,
+                                                              const uint32_t* __restrict__ rhi,
                                                               const void* __restrict__ rbin, int nb, int ntiles,
                                                               const uint32_t* __restrict__ D,
                                                               const int32_t* __restrict__ istart,
                                                               const int32_t* __restrict__ itile,
                                                               uint64_t* __restrict__ pacc,
-                                                              int32_t* __restrict__ pcnt) {
-    constexpr bool KEYS = OP != PVJP_ADD;
+                                                              int32_t* __restrict__ pcnt,
+                                                              int32_t* __restrict__ paux) {
+    constexpr bool KEYS = part_keys<OP>();
+    constexpr bool AUX = part_aux<T, OP>();
+    constexpr bool WINNERS = AUX && KEYS;
     __shared__ uint64_t acc[kPartBins * kAccCopies];
     __shared__ int32_t cnt[COUNTS ? kPartBins : 1];
+    __shared__ int32_t aux[AUX ? kPartBins : 1];
     const PartItem I = part_item(nb, ntiles, istart, itile);
     if (I.item < 0) return;
     const int item = I.item;
     for (int j = threadIdx.x; j < kPartBins * kAccCopies; j += kAccBlock) acc[j] = acc_identity<OP>();
     if (COUNTS)
         for (int j = threadIdx.x; j < kPartBins; j += kAccBlock) cnt[j] = 0;
+    if (AUX)
+        for (int j = threadIdx.x; j < kPartBins; j += kAccBlock) aux[j] = WINNERS ? 0x7fffffff : 0;
     __syncthreads();
     const uint32_t copy = threadIdx.x & (kAccCopies - 1);
-    part_walk<KEYS>(rval, rbin, D, ntiles, I, [&](int64_t tbase, bool ok, uint32_t at, uint32_t v, uint32_t bn) {
-        if (ok) acc_record<OP, COUNTS>(acc, cnt, copy, tbase, at, v, bn);
+    part_walk<T, KEYS>(rval, rhi, rbin, D, ntiles, I, [&](int64_t tbase, bool ok, uint32_t at, T v, uint32_t bn) {
+        if (ok) acc_record<T, OP, COUNTS>(acc, cnt, aux, copy, tbase, at, v, bn);
     });
     __syncthreads();
     for (int j = threadIdx.x; j < kPartBins; j += kAccBlock) {
         uint64_t v = acc[j * kAccCopies];
 #pragma unroll
         for (int c = 1; c < kAccCopies; ++c) {
-            const uint64_t w = acc[j * kAccCopies + c];
-            if (OP == PVJP_ADD)
-                v = (uint64_t)__double_as_longlong(__longlong_as_double((long long)v) + __longlong_as_double((long long)w));
-            else
-                v = w > v ? w : v;
+            int32_t zz = 0, cc = 0;
+            merge_fold<OP>(v, zz, cc, acc[j * kAccCopies + c], 0, 0);
         }
         pacc[(int64_t)item * kPartBins + j] = v;
         if (COUNTS) pcnt[(int64_t)item * kPartBins + j] = cnt[j];
+        if (WINNERS) acc[j * kAccCopies] = v;
+        if (OP == PVJP_MUL) paux[(int64_t)item * kPartBins + j] = aux[j];
+    }
+    if (WINNERS) {
+        // the records again: the lowest index among those equal to the extreme
+        __syncthreads();
+        part_walk<T, KEYS>(rval, rhi, rbin, D, ntiles, I, [&](int64_t tbase, bool ok, uint32_t at, T v, uint32_t bn) {
+            const uint32_t j = bn & (kPartBins - 1);
+            if (!ok || elem_key<OP>(v, 0) != acc[j * kAccCopies]) return;
+            const int32_t e = (int32_t)(tbase + (int64_t)(at & ~(uint32_t)(kTile - 1)) + (int64_t)(bn >> 16));
+            if (e < __hip_atomic_load(&aux[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) atomicMin(&aux[j], e);
+        });
+        __syncthreads();
+        for (int j = threadIdx.x; j < kPartBins; j += kAccBlock) paux[(int64_t)item * kPartBins + j] = aux[j];
     }
 }
+
 template <class T, int OP>
 __global__ __launch_bounds__(256) void hpart_merge_kernel(const uint64_t* __restrict__ pacc,
                                                           const int32_t* __restrict__ pcnt,
+                                                          const int32_t* __restrict__ paux,
                                                           const int32_t* __restrict__ istart, int32_t m,
                                                           const T* __restrict__ vs, int32_t* __restrict__ gcount,
                                                           HistOut<T> o) {
     // A thread per bin; eight work items' partials in flight, folded in order,
     // and the bin's outputs.
     constexpr int U = 8;
+    constexpr bool WINNERS = part_aux<T, OP>() && part_keys<OP>();
     for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < m; k += (int64_t)gridDim.x * blockDim.x) {
         const int b = (int)(k >> kPartShift), j = (int)(k & (kPartBins - 1));
         uint64_t acc = acc_identity<OP>();
-        int32_t zz = 0, cc = 0;
-        const int i1 = istart[b + 1];
-        int it = istart[b];
-        for (; it + U <= i1; it += U) {
+        int32_t zz = 0, cc = 0, win = 0x7fffffff;
+        const int i0 = istart[b], i1 = istart[b + 1];
+        for (int it = i0; it < i1; it += U) {
             uint64_t v[U];
-            int32_t c[U];
+            int32_t c[U], x[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                v[u] = pacc[(int64_t)(it + u) * kPartBins + j];
-                c[u] = pcnt ? pcnt[(int64_t)(it + u) * kPartBins + j] : 0;
+                const int64_t at = (int64_t)min(it + u, i1 - 1) * kPartBins + j;
+                v[u] = pacc[at];
+                c[u] = pcnt ? pcnt[at] : 0;
+                x[u] = part_aux<T, OP>() ? paux[at] : 0;
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u) merge_fold<OP>(acc, zz, cc, v[u], 0, c[u]);
+            for (int u = 0; u < U; ++u) {
+                if (it + u >= i1) continue;
+                if (WINNERS) win = v[u] > acc ? x[u] : (v[u] == acc && x[u] < win ? x[u] : win);
+                merge_fold<OP>(acc, zz, cc, v[u], x[u], c[u]);
+            }
         }
-        for (; it < i1; ++it)
-            merge_fold<OP>(acc, zz, cc, pacc[(int64_t)it * kPartBins + j], 0, pcnt ? pcnt[(int64_t)it * kPartBins + j] : 0);
         if (gcount) gcount[k] = cc;
-        hist_finish<T, OP>(o, vs, k, acc, zz, 0);
+        hist_finish<T, OP>(o, vs, k, acc, zz, win);
     }
 }
 
@@ -1105,15 +1177,15 @@ __global__ __launch_bounds__(kAccBlock) void hpart_lae_acc_kernel(const uint32_t
     for (int j = threadIdx.x; j < kPartBins; j += kAccBlock) mx[j] = 0u;
     for (int j = threadIdx.x; j < kPartBins * kAccCopies; j += kAccBlock) sm[j] = 0.0;
     __syncthreads();
-    part_walk<false>(rval, rbin, D, ntiles, I, [&](int64_t, bool ok, uint32_t, uint32_t v, uint32_t bn) {
-        if (ok) atomicMax(&mx[bn & (kPartBins - 1)], ord32(__uint_as_float(v)));
+    part_walk<float, false>(rval, nullptr, rbin, D, ntiles, I, [&](int64_t, bool ok, uint32_t, float x, uint32_t bn) {
+        if (ok) atomicMax(&mx[bn & (kPartBins - 1)], ord32(x));
     });
     __syncthreads();
     const uint32_t copy = threadIdx.x & (kAccCopies - 1);
-    part_walk<false>(rval, rbin, D, ntiles, I, [&](int64_t, bool ok, uint32_t, uint32_t v, uint32_t bn) {
+    part_walk<float, false>(rval, nullptr, rbin, D, ntiles, I, [&](int64_t, bool ok, uint32_t, float x, uint32_t bn) {
         if (!ok) return;
         const uint32_t j = bn & (kPartBins - 1);
-        const float x = __uint_as_float(v), m = unord32(mx[j]);
+        const float m = unord32(mx[j]);
         if (x != -INFINITY && m != -INFINITY)
             atomicAdd(&sm[j * kAccCopies + copy], (double)(x == m ? 1.0f : expf(x - m)));
     });
@@ -1217,25 +1289,44 @@ static HistPlan hist_plan(int op, int64_t n, int64_t m, bool counts) {
     return P;
 }
 
-// The bucket-partitioned path serves FP32 + / min / max when m does not fit
-// one block's LDS and the buckets fit the scan block.
-static bool use_partition(int op, bool f32, int64_t m, bool counts) {
+// The bucket-partitioned path serves m beyond one block's LDS, up to the
+// buckets of the scan block.  Short inputs keep the LDS bin cache with global
+// atomics: the partition's eight launches cost more than the atomics, which
+// are fewer where the cache holds a good part of the bins.  Primal and VJP with
+// the cache and with the partition, in us:
+//   FP32 +, Zipf, m = 20,000: n = 800,000 32, 43; 1.6 10^6 48, 49; 3.2 10^6 129, 60
+//   FP32 +, Zipf, m = 200,000: 800,000 41, 49; 1.6 10^6 92, 56
+//   FP32 max, uniform, m = 10^6: 800,000 53, 54; 1.6 10^6 86, 55
+//   FP64 max (a second sweep for the winners), Zipf, m = 20,000: 1.6 10^6 61,
+//   71; 3.2 10^6 91, 71
+// A product's updates are compare-and-swap loops, so its line is lower (FP32,
+// n = 2^17, m = 30,000: 72, 40).
+static bool use_partition(int op, bool f32, int64_t n, int64_t m, bool counts) {
     const int full_slots = (int)(kHistLds / slot_bytes(op, counts, false));
-    return f32 && op != PVJP_MUL && m > full_slots && ceil_div(m, kPartBins) <= kPartMaxBuckets;
+    if (m <= full_slots || ceil_div(m, kPartBins) > kPartMaxBuckets) return false;
+    if (op == PVJP_MUL) return n >= ((int64_t)1 << 17);
+    if (m > 65536) return n >= ((int64_t)1 << 20);
+    return n >= (f32 || op == PVJP_ADD ? (int64_t)3 << 19 : (int64_t)1 << 21);
 }
 
 struct PartLayout {
     int nb, ntiles, nchunks;
+    int seg;  // records per work item
     int64_t items_max;
-    size_t toff, D, Ploc, ctot, clast, bitems, istart, itile, rval, rbin, pacc, pcnt, total;
+    size_t toff, D, Ploc, ctot, clast, bitems, istart, itile, rval, rhi, rbin, pacc, pcnt, paux, total;
 };
 
-static PartLayout part_layout(int64_t n, int64_t m) {
+static PartLayout part_layout(int64_t n, int64_t m, bool f32) {
     PartLayout L{};
+    // Work items of 2^17 records once there are 512 of them (two a CU), fewer
+    // records before that: a short input's buckets would otherwise be one item
+    // each (n = 10^6, m = 100,000 Zipf, primal and VJP: 116 us, now 48).
+    L.seg = (int)kPartSegMin;
+    while (L.seg < kPartSeg && (int64_t)L.seg * 512 < n) L.seg *= 2;
     L.nb = (int)ceil_div(m, kPartBins);
     L.ntiles = (int)ceil_div(n > 0 ? n : 1, kTile);
     L.nchunks = (int)ceil_div(L.ntiles, kColChunk);
-    L.items_max = ceil_div(n > 0 ? n : 1, kPartSeg) + L.nb;
+    L.items_max = ceil_div(n > 0 ? n : 1, L.seg) + L.nb;
     const size_t slots = (size_t)L.ntiles * kTile;
     size_t o = 0;
     auto take = [&](size_t bytes) {
@@ -1252,9 +1343,11 @@ static PartLayout part_layout(int64_t n, int64_t m) {
     L.istart = take((size_t)(L.nb + 1) * 4);
     L.itile = take((size_t)L.items_max * 4);
     L.rval = take(slots * 4);
-    L.rbin = take(slots * 4);  // 2 bytes per record for +, 4 for min/max
+    L.rhi = take(f32 ? 0 : slots * 4);
+    L.rbin = take(slots * 4);  // 2 bytes per record for + and *, 4 for min/max
     L.pacc = take((size_t)L.items_max * kPartBins * 8);
     L.pcnt = take((size_t)L.items_max * kPartBins * 4);
+    L.paux = take((size_t)L.items_max * kPartBins * 4);
     L.total = o;
     return L;
 }
@@ -1262,15 +1355,16 @@ static PartLayout part_layout(int64_t n, int64_t m) {
 // Covers both plans (with and without counts): the FULL/CACHE choice and the
 // grid depend on whether counts are requested.
 static size_t hist_ws(int op, int64_t n, int64_t m, bool f32) {
-    if (use_partition(op, f32, m, false) || use_partition(op, f32, m, true)) {
+    if (use_partition(op, f32, n, m, false) || use_partition(op, f32, n, m, true)) {
         // either plan may run: reserve the larger of the two layouts below
-        const size_t part = part_layout(n, m).total;
+        const size_t part = part_layout(n, m, f32).total;
         size_t other = 0;
         for (int counts = 0; counts < 2; ++counts) {
             const HistPlan P = hist_plan(op, n, m, counts != 0);
             if (!P.cache) other = std::max(other, align_up((size_t)(P.grid + kMergeSlices) * m * 16, 256));
         }
-        return align_up((size_t)m * 8, 256) + std::max(part, other);
+        return align_up((size_t)m * 8, 256) + (op == PVJP_MUL ? align_up((size_t)m * 4, 256) : 0) +
+               std::max(part, other);
     }
     size_t part = 0;
     for (int counts = 0; counts < 2; ++counts) {
@@ -1286,8 +1380,8 @@ static size_t hist_ws(int op, int64_t n, int64_t m, bool f32) {
 
 // The partition shared by the accumulators: the tile sort, the run
 // descriptors and the work items.
-template <int OP>
-static void part_sort(const int32_t* inds, const float* vs, int64_t n, int32_t m, const PartLayout& L, char* base,
+template <class T, int OP>
+static void part_sort(const int32_t* inds, const T* vs, int64_t n, int32_t m, const PartLayout& L, char* base,
                       hipStream_t st) {
     int32_t* toff = reinterpret_cast<int32_t*>(base + L.toff);
     uint32_t* D = reinterpret_cast<uint32_t*>(base + L.D);
@@ -1298,57 +1392,62 @@ static void part_sort(const int32_t* inds, const float* vs, int64_t n, int32_t m
     int32_t* istart = reinterpret_cast<int32_t*>(base + L.istart);
     int32_t* itile = reinterpret_cast<int32_t*>(base + L.itile);
     uint32_t* rval = reinterpret_cast<uint32_t*>(base + L.rval);
+    uint32_t* rhi = reinterpret_cast<uint32_t*>(base + L.rhi);
     void* rbin = base + L.rbin;
     const bool vec = aligned(inds, 16) && aligned(vs, 16);
     // n == 0 still runs one (empty) tile, so every table is written
     if (vec)
-        hipLaunchKernelGGL((hpart_tile_kernel<OP, true>), dim3(L.ntiles), dim3(kTileThreads), 0, st, inds, vs, n, m,
-                           L.nb, rval, rbin, toff);
+        hipLaunchKernelGGL((hpart_tile_kernel<T, OP, true>), dim3(L.ntiles), dim3(kTileThreads), 0, st, inds, vs, n, m,
+                           L.nb, rval, rhi, rbin, toff);
     else
-        hipLaunchKernelGGL((hpart_tile_kernel<OP, false>), dim3(L.ntiles), dim3(kTileThreads), 0, st, inds, vs, n, m,
-                           L.nb, rval, rbin, toff);
+        hipLaunchKernelGGL((hpart_tile_kernel<T, OP, false>), dim3(L.ntiles), dim3(kTileThreads), 0, st, inds, vs, n, m,
+                           L.nb, rval, rhi, rbin, toff);
     hipLaunchKernelGGL(hpart_colscan_kernel, dim3((unsigned)ceil_div(L.nb, kColThreads), L.nchunks),
                        dim3(kColThreads), 0, st, toff, L.ntiles, L.nb, L.nchunks, D, Ploc, ctot, clast);
-    hipLaunchKernelGGL(hpart_bscan_kernel, dim3(L.nb), dim3(kBscanThreads), 0, st, ctot, clast, L.nchunks, bitems);
+    hipLaunchKernelGGL(hpart_bscan_kernel, dim3(L.nb), dim3(kBscanThreads), 0, st, ctot, clast, L.nchunks, L.seg, bitems);
     hipLaunchKernelGGL(hpart_scan_kernel, dim3(1), dim3(kPartScanThreads), 0, st, bitems, L.nb, istart);
     hipLaunchKernelGGL(hpart_items_kernel, dim3((unsigned)ceil_div((int64_t)L.nb * L.ntiles, 256)), dim3(256), 0, st,
-                       Ploc, ctot, L.ntiles, L.nb, L.nchunks, istart, itile);
+                       Ploc, ctot, L.ntiles, L.nb, L.nchunks, L.seg, istart, itile);
 }
 
-template <int OP>
-static void run_partitioned(const int32_t* inds, const float* vs, int64_t n, int32_t m, int32_t* count, char* w,
-                            size_t off, const HistOut<float>& o, hipStream_t st) {
-    const PartLayout L = part_layout(n, m);
+template <class T, int OP>
+static void run_partitioned(const int32_t* inds, const T* vs, int64_t n, int32_t m, int32_t* count, char* w,
+                            size_t off, const HistOut<T>& o, hipStream_t st) {
+    const PartLayout L = part_layout(n, m, sizeof(T) == 4);
     char* base = w + off;
-    part_sort<OP>(inds, vs, n, m, L, base, st);
+    part_sort<T, OP>(inds, vs, n, m, L, base, st);
     const uint32_t* D = reinterpret_cast<const uint32_t*>(base + L.D);
     const int32_t* istart = reinterpret_cast<const int32_t*>(base + L.istart);
     const int32_t* itile = reinterpret_cast<const int32_t*>(base + L.itile);
     const uint32_t* rval = reinterpret_cast<const uint32_t*>(base + L.rval);
+    const uint32_t* rhi = reinterpret_cast<const uint32_t*>(base + L.rhi);
     const void* rbin = base + L.rbin;
+    int32_t* paux = reinterpret_cast<int32_t*>(base + L.paux);
     uint64_t* pacc = reinterpret_cast<uint64_t*>(base + L.pacc);
     int32_t* pcnt = reinterpret_cast<int32_t*>(base + L.pcnt);
     const unsigned agrid = (unsigned)(ceil_div(L.items_max, (int64_t)kXcds) * kXcds);
     if (count)
-        hipLaunchKernelGGL((hpart_acc_kernel<OP, true>), dim3(agrid), dim3(kAccBlock), 0, st, rval, rbin, L.nb,
-                           L.ntiles, D, istart, itile, pacc, pcnt);
+        hipLaunchKernelGGL((hpart_acc_kernel<T, OP, true>), dim3(agrid), dim3(kAccBlock), 0, st, rval, rhi, rbin,
+                           L.nb, L.ntiles, D, istart, itile, pacc, pcnt, paux);
     else
-        hipLaunchKernelGGL((hpart_acc_kernel<OP, false>), dim3(agrid), dim3(kAccBlock), 0, st, rval, rbin, L.nb,
-                           L.ntiles, D, istart, itile, pacc, pcnt);
-    hipLaunchKernelGGL((hpart_merge_kernel<float, OP>), dim3(flat_grid(m, 256, 1)), dim3(256), 0, st, pacc,
-                       count ? pcnt : nullptr, istart, m, vs, count, o);
+        hipLaunchKernelGGL((hpart_acc_kernel<T, OP, false>), dim3(agrid), dim3(kAccBlock), 0, st, rval, rhi, rbin,
+                           L.nb, L.ntiles, D, istart, itile, pacc, pcnt, paux);
+    hipLaunchKernelGGL((hpart_merge_kernel<T, OP>), dim3(flat_grid(m, 256, 1)), dim3(256), 0, st, pacc,
+                       count ? pcnt : nullptr, paux, istart, m, vs, count, o);
 }
 
 // The log-add-exp reduce_by_index on the partition (FP32, the bins beyond
 // one block's LDS): one tile sort, two sweeps per work item, one merge.
 bool hist_lae_partition_ok(pvjp_dtype dtype, int64_t m) {
-    return dtype == PVJP_F32 && use_partition(PVJP_ADD, true, m, false);
+    return dtype == PVJP_F32 && use_partition(PVJP_ADD, true, INT64_MAX, m, false);  // whatever the length
 }
+
+size_t hist_lae_partition_bytes(int64_t n, int64_t m) { return part_layout(n, m, true).total; }
 
 void hist_lae_partitioned(const int32_t* inds, const float* x, int64_t n, int32_t m, float* hs, char* ws,
                           hipStream_t st) {
-    const PartLayout L = part_layout(n, m);
-    part_sort<PVJP_ADD>(inds, x, n, m, L, ws, st);
+    const PartLayout L = part_layout(n, m, true);
+    part_sort<float, PVJP_ADD>(inds, x, n, m, L, ws, st);
     double* psum = reinterpret_cast<double*>(ws + L.pacc);
     uint32_t* pmax = reinterpret_cast<uint32_t*>(ws + L.pcnt);
     const unsigned agrid = (unsigned)(ceil_div(L.items_max, (int64_t)kXcds) * kXcds);
@@ -1384,11 +1483,9 @@ static void run_hist(const int32_t* inds, const T* vs, int64_t n, int32_t m, T* 
         off += align_up((size_t)m * 4, 256);
     }
     const bool counts = count != nullptr;
-    if constexpr (sizeof(T) == 4 && OP != PVJP_MUL) {
-        if (use_partition(OP, true, m, counts)) {
-            run_partitioned<OP>(inds, (const float*)vs, n, m, count, w, off, HistOut<float>{hs, winner, p, z}, st);
-            return;
-        }
+    if (use_partition(OP, sizeof(T) == 4, n, m, counts)) {
+        run_partitioned<T, OP>(inds, vs, n, m, count, w, off, HistOut<T>{hs, winner, p, z}, st);
+        return;
     }
     const HistPlan P = hist_plan(OP, n, m, counts);
     uint64_t* pacc = reinterpret_cast<uint64_t*>(w + off);
@@ -1518,10 +1615,11 @@ extern "C" pvjp_status pvjp_hist_plan_info(pvjp_op op, pvjp_dtype dtype, int64_t
     PVJP_REQUIRE(n >= 0 && n <= INT32_MAX && m >= 1 && m <= kMaxBins, "pvjp_hist_plan_info: n or m out of range");
     PVJP_REQUIRE(info != nullptr, "pvjp_hist_plan_info: info is NULL");
     info[1] = info[2] = info[3] = 0;
-    if (use_partition(op, dtype == PVJP_F32, m, counts != 0)) {
+    if (use_partition(op, dtype == PVJP_F32, n, m, counts != 0)) {
         info[0] = PVJP_HIST_PATH_PARTITION;
         info[1] = kPartBins;
-        info[2] = kPartSeg + kTile;  // runs start within kPartSeg records; a run is below kTile
+        // runs start within seg records; a run is below kTile
+        info[2] = part_layout(n, m, dtype == PVJP_F32).seg + kTile;
         info[3] = ceil_div(m, kPartBins);
     } else {
         info[0] = hist_plan(op, n, m, counts != 0).cache ? PVJP_HIST_PATH_CACHE : PVJP_HIST_PATH_LDS;

@@ -117,6 +117,10 @@ static HlPlan hl_plan(pvjp_dtype dtype, int64_t n, int64_t m) {
     p.hsum = take((size_t)m * es);
     const size_t a = pvjp_hist_ws_bytes(PVJP_MAX, dtype, n, m), b = pvjp_hist_ws_bytes(PVJP_ADD, dtype, n, m);
     p.hist_bytes = align_up(a > b ? a : b, 256);
+    if (hist_lae_partition_ok(dtype, m)) {
+        const size_t c = align_up(hist_lae_partition_bytes(n, m), 256);
+        if (c > p.hist_bytes) p.hist_bytes = c;
+    }
     p.hist = take(p.hist_bytes);
     p.total = o;
     return p;

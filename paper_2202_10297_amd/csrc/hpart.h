@@ -12,9 +12,9 @@ namespace pvjp {
 // Whether the partitioned form serves (dtype, m): FP32 with bins beyond one
 // block's LDS and at most 2^22 of them.
 bool hist_lae_partition_ok(pvjp_dtype dtype, int64_t m);
+size_t hist_lae_partition_bytes(int64_t n, int64_t m);
 // hs[b] = log sum of e^x over bin b (-inf for an empty bin or -inf elements
-// only); ws: at least pvjp_hist_ws_bytes(PVJP_ADD, PVJP_F32, n, m) bytes,
-// 256-byte aligned.
+// only); ws: at least hist_lae_partition_bytes(n, m), 256-byte aligned.
 void hist_lae_partitioned(const int32_t* inds, const float* x, int64_t n, int32_t m, float* hs, char* ws,
                           hipStream_t st);
 

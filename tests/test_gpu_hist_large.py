@@ -106,3 +106,44 @@ def test_plan_info_names_the_paths(ops):
         for op in ("add", "max"):
             info = plan(op, N, m, False)
             assert info[0] in (capi.HIST_PATH_CACHE, capi.HIST_PATH_PARTITION)
+
+
+# On either side of the lengths where the partition takes over, bins around one
+# block's LDS and whole buckets: every operator and type, indices out of range,
+# ties and zeros.
+EDGES = [(op, n, m, dist) for op in ("add", "max", "min")
+         for n, m, dist in (((3 << 19) - 1, 8193, "zipf"), (3 << 19, 8193, "zipf"), ((3 << 19) + 4097, 20480, "uniform"),
+                            ((1 << 20) - 1, 131073, "zipf"), (1 << 20, 131073, "uniform"), (1 << 21, 20481, "zipf"))]
+EDGES += [("mul", n, m, "uniform") for n, m in (((1 << 17) - 1, 8193), (1 << 17, 8193), ((1 << 17) + 8193, 20480))]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("op,n,m,dist", EDGES)
+def test_partition_edges(ops, orc, op, n, m, dist, dtype):
+    inds, vs, hb = workloads.hist(n, m, dist, dtype, seed=n + m)
+    inds[::101] = -1
+    inds[7::103] = m
+    if op == "mul":
+        # factors near one, so that a hot bin's product stays in range; some zeros
+        vs = np.exp(1e-3 * vs).astype(vs.dtype)
+        vs[::5003] = 0.0
+        vs[2501::5003] = -0.0
+    elif op != "add":
+        vs = (np.round(vs * 8) / 8).astype(vs.dtype)
+        vs[::13] = -0.0
+    di, dv = dev(inds), dev(vs)
+    ref = orc.hist(op, inds, vs, m)
+    bar = TOL_F32 if dtype == "f32" else 1e-12
+    for counts in (False, True):
+        hs, aux = ops.hist(op, di, dv, m, counts=counts)
+        if counts:
+            assert np.array_equal(host(aux["count"]), ref["count"])
+        if op in ("min", "max"):
+            assert np.array_equal(host(aux["winner"]), ref["winner"])
+            got = host(hs)
+            assert np.array_equal(got, ref["hs"]) and np.array_equal(np.signbit(got), np.signbit(ref["hs"]))
+        else:
+            assert rel_l2(host(hs), ref["hs"]) <= bar
+        if op == "mul":
+            assert np.array_equal(host(aux["z"]), ref["z"])
+            assert rel_l2(host(aux["p"]), ref["p"]) <= bar
