@@ -15,31 +15,8 @@ struct GS {
     T c[K];
 };
 
-template <class T, int K>
-struct GShfl {
-    using S = GS<T, K>;
-    __device__ static __forceinline__ S up(S v, int d) {
-        S r;
-#pragma unroll
-        for (int c = 0; c < K; ++c) r.c[c] = shfl_up1(v.c[c], d);
-        return r;
-    }
-    __device__ static __forceinline__ S down(S v, int d) {
-        S r;
-#pragma unroll
-        for (int c = 0; c < K; ++c) r.c[c] = shfl_down1(v.c[c], d);
-        return r;
-    }
-    __device__ static __forceinline__ S idx(S v, int s) {
-        S r;
-#pragma unroll
-        for (int c = 0; c < K; ++c) r.c[c] = shfl_idx1(v.c[c], s);
-        return r;
-    }
-};
-
-// An operator provides: K input components; a state S (its shuffles come
-// from GShfl) with elem() turning an element's components into a state and
+// An operator provides: K input components; a state S with elem() turning an
+// element's components into a state and
 // value() turning a state back into K result components; the neutral id();
 // comb(x, y) = x (.) y with x earlier in index order; and the function f,
 // vjp(l, a, r, la, yb, out): out = (d(l (.) a (.) r)/da)^T yb, where la is
@@ -62,8 +39,9 @@ __device__ __forceinline__ double lae_log(double x) { return log(x); }
 // Log-add-exp with the state (m, s) in T and the exponentials evaluated in E
 // (E = T, or FP32 with an FP64 state: see the scans' widening below).
 template <class T, class E = T>
-struct GLogAddExpE : GShfl<T, 2> {
+struct GLogAddExpE {
     static constexpr int K = 1;
+    static constexpr bool kLinFromElems = false;  // J_left of the scan needs the state
     using Acc = T;
     using S = GS<T, 2>;
     __device__ static __forceinline__ T ex(T a) { return (T)lae_exp((E)a); }
@@ -103,8 +81,9 @@ template <class T>
 using GLogAddExp = GLogAddExpE<T, T>;
 
 template <class T>
-struct GLinRec : GShfl<T, 2> {
+struct GLinRec {
     static constexpr int K = 2;
+    static constexpr bool kLinFromElems = true;
     using Acc = T;
     using S = GS<T, 2>;
     __device__ static __forceinline__ S id() { return S{{T(1), T(0)}}; }
@@ -127,8 +106,9 @@ struct GLinRec : GShfl<T, 2> {
 };
 
 template <class T>
-struct GMat2 : GShfl<T, 4> {
+struct GMat2 {
     static constexpr int K = 4;
+    static constexpr bool kLinFromElems = true;
     using Acc = T;
     using S = GS<T, 4>;
     __device__ static __forceinline__ S id() { return S{{T(1), T(0), T(0), T(1)}}; }

@@ -48,7 +48,7 @@ constexpr size_t slot_of() {
 // log-add-exp: state (m, s, t) with value m + log s and tangent t / s (t is
 // the tangent sum weighted like s: t = sum e^(x_j - m) x_dot_j).
 template <class T>
-struct GLaeDual : GShfl<T, 3> {
+struct GLaeDual {
     static constexpr int K = 2;
     using Acc = T;
     using S = GS<T, 3>;
@@ -74,7 +74,7 @@ struct GLaeDual : GShfl<T, 3> {
 // linear recurrence: (A, B, A_dot, B_dot); (later) o (earlier) by the
 // product rule.
 template <class T>
-struct GLinRecDual : GShfl<T, 4> {
+struct GLinRecDual {
     static constexpr int K = 4;
     using Acc = T;
     using S = GS<T, 4>;
@@ -91,7 +91,7 @@ struct GLinRecDual : GShfl<T, 4> {
 
 // 2x2 matrix product: (X, X_dot) (.) (Y, Y_dot) = (X Y, X_dot Y + X Y_dot).
 template <class T>
-struct GMat2Dual : GShfl<T, 8> {
+struct GMat2Dual {
     static constexpr int K = 8;
     using Acc = T;
     using S = GS<T, 8>;
@@ -157,26 +157,6 @@ struct LinG {
         }
         return r;
     }
-    template <class F>
-    __device__ static __forceinline__ S map(const S& v, F f) {
-        S r;
-#pragma unroll
-        for (int i = 0; i < D; ++i) {
-            r.v[i] = f(v.v[i]);
-#pragma unroll
-            for (int j = 0; j < D; ++j) r.c[i][j] = f(v.c[i][j]);
-        }
-        return r;
-    }
-    __device__ static __forceinline__ S up(S v, int d) {
-        return map(v, [d](A a) { return shfl_up1(a, d); });
-    }
-    __device__ static __forceinline__ S down(S v, int d) {
-        return map(v, [d](A a) { return shfl_down1(a, d); });
-    }
-    __device__ static __forceinline__ S idx(S v, int s) {
-        return map(v, [s](A a) { return shfl_idx1(a, s); });
-    }
 };
 
 // lin_o states of the scan VJP per operator.  The general form keeps J_left^T
@@ -205,26 +185,6 @@ struct LinKron {
 #pragma unroll
             for (int c = 0; c < 2; ++c) r.m[a][c] = y.m[a][0] * x.m[0][c] + y.m[a][1] * x.m[1][c];
         return r;
-    }
-    template <class F>
-    __device__ static __forceinline__ S map(const S& v, F f) {
-        S r;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) r.v[i] = f(v.v[i]);
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int c = 0; c < 2; ++c) r.m[a][c] = f(v.m[a][c]);
-        return r;
-    }
-    __device__ static __forceinline__ S up(S v, int d) {
-        return map(v, [d](A a) { return shfl_up1(a, d); });
-    }
-    __device__ static __forceinline__ S down(S v, int d) {
-        return map(v, [d](A a) { return shfl_down1(a, d); });
-    }
-    __device__ static __forceinline__ S idx(S v, int s) {
-        return map(v, [s](A a) { return shfl_idx1(a, s); });
     }
 };
 
@@ -569,16 +529,12 @@ constexpr int gs_tile() {
     return kGrBlock * gs_ipt<Op, T>();
 }
 
-// A thread's run of IPT elements starting at `base` (cnt of them exist):
-// the elements in the arithmetic type, the element right after the run (xn,
-// if it exists), the state before the run (sp: the tile prefix folded with
-// the block scan of the runs) and the inclusive states ys[k].
+// A thread's run of IPT elements starting at `base` (cnt of them exist): the
+// elements in the arithmetic type and the element right after the run (xn, if
+// it exists).
 template <class Op, class T, int IPT, bool VEC>
-__device__ __forceinline__ void gs_run_states(const GPtrs<T>& x, int64_t n, int64_t base, int cnt,
-                                              const typename Op::S& tpre, typename Op::S* wtot,
-                                              typename Op::Acc (&xa)[Op::K][IPT], typename Op::Acc (&xn)[Op::K],
-                                              typename Op::S (&ys)[IPT], typename Op::S& sp) {
-    using S = typename Op::S;
+__device__ __forceinline__ void gs_run_elems(const GPtrs<T>& x, int64_t n, int64_t base, int cnt,
+                                             typename Op::Acc (&xa)[Op::K][IPT], typename Op::Acc (&xn)[Op::K]) {
     using A = typename Op::Acc;
     constexpr int K = Op::K;
     T v[K][IPT];
@@ -591,6 +547,19 @@ __device__ __forceinline__ void gs_run_states(const GPtrs<T>& x, int64_t n, int6
 #pragma unroll
         for (int k = 0; k < IPT; ++k) xa[c][k] = (A)v[c][k];
     }
+}
+
+// The run's elements with the state before it (sp: the tile prefix folded
+// with the block scan of the runs) and the inclusive states ys[k].
+template <class Op, class T, int IPT, bool VEC>
+__device__ __forceinline__ void gs_run_states(const GPtrs<T>& x, int64_t n, int64_t base, int cnt,
+                                              const typename Op::S& tpre, typename Op::S* wtot,
+                                              typename Op::Acc (&xa)[Op::K][IPT], typename Op::Acc (&xn)[Op::K],
+                                              typename Op::S (&ys)[IPT], typename Op::S& sp) {
+    using S = typename Op::S;
+    using A = typename Op::Acc;
+    constexpr int K = Op::K;
+    gs_run_elems<Op, T, IPT, VEC>(x, n, base, cnt, xa, xn);
     S run = Op::id();
 #pragma unroll
     for (int k = 0; k < IPT; ++k) {
@@ -669,7 +638,9 @@ __global__ __launch_bounds__(kGrBlock) void gscan_fwd_kernel(GPtrs<T> x, int64_t
     for (int c = 0; c < K; ++c) gr_store<T, IPT, VEC>(y.p[c] + base, cnt, out[c]);
 }
 
-// VJP pass 1: the lin_o fold of every tile, in reversed index order.
+// VJP pass 1: the lin_o fold of every tile, in reversed index order.  Where
+// J_left depends on the next element only (the linear recurrence, the 2x2
+// product), the states are not formed.
 template <class Op, class T, int IPT, bool VEC>
 __global__ __launch_bounds__(kGrBlock) void gscan_vjp_agg_kernel(
     GPtrs<T> x, int64_t n, const typename Op::S* __restrict__ pre, GPtrs<T> ybar,
@@ -689,7 +660,13 @@ __global__ __launch_bounds__(kGrBlock) void gscan_vjp_agg_kernel(
     for (int c = 0; c < K; ++c) gr_load<T, IPT, VEC>(ybar.p[c] + base, cnt, yb[c]);
     A xa[K][IPT], xn[K];
     S ys[IPT], sp;
-    gs_run_states<Op, T, IPT, VEC>(x, n, base, cnt, pre[seg_tile()], wtot, xa, xn, ys, sp);
+    if (Op::kLinFromElems) {
+        gs_run_elems<Op, T, IPT, VEC>(x, n, base, cnt, xa, xn);
+#pragma unroll
+        for (int k = 0; k < IPT; ++k) ys[k] = Op::id();
+    } else {
+        gs_run_states<Op, T, IPT, VEC>(x, n, base, cnt, pre[seg_tile()], wtot, xa, xn, ys, sp);
+    }
     const typename LG::S run = gs_run_lin<Op, T, IPT>(ys, xa, xn, yb, n, base, cnt);
     typename LG::S tot;
     block_exclusive_scan<LG, kGrBlock, true>(run, tot, ltot);
@@ -699,9 +676,11 @@ __global__ __launch_bounds__(kGrBlock) void gscan_vjp_agg_kernel(
 // VJP pass 3: lsuf[t] is the lin_o fold of every tile after t; with the
 // reversed block scan of the runs it gives the adjoint r after each run,
 // then r_k = y_bar_k + J_left(k)^T r_{k+1} walks the run down and
-// x_bar_k (+)= J_right(k)^T r_k.
+// x_bar_k (+)= J_right(k)^T r_k.  The 2x2 product is held to three waves per
+// SIMD (it takes 170 registers otherwise, two over; 2 10^7 FP32 elements, scan
+// and VJP: 588 -> 560 us; with four it spills, 932).
 template <class Op, class T, int IPT, bool VEC, bool ACC>
-__global__ __launch_bounds__(kGrBlock) void gscan_vjp_kernel(
+__global__ __launch_bounds__(kGrBlock, Op::K == 4 ? 3 : 1) void gscan_vjp_kernel(
     GPtrs<T> x, int64_t n, const typename Op::S* __restrict__ pre, GPtrs<T> ybar,
     const typename LinOf<Op>::L::S* __restrict__ lsuf, GOut<T> xbar) {
     using S = typename Op::S;

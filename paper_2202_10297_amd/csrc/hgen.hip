@@ -353,12 +353,6 @@ struct SegOf {
     };
     __device__ static __forceinline__ S id() { return S{Q::id(), 0u, 0u}; }
     __device__ static __forceinline__ S comb(S x, S y) { return y.f ? y : S{Q::comb(x.v, y.v), x.f, 0u}; }
-    __device__ static __forceinline__ S up(S v, int d) {
-        return S{Q::up(v.v, d), (uint32_t)shfl_up1((int)v.f, d), 0u};
-    }
-    __device__ static __forceinline__ S down(S v, int d) {
-        return S{Q::down(v.v, d), (uint32_t)shfl_down1((int)v.f, d), 0u};
-    }
 };
 
 
