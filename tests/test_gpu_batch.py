@@ -143,3 +143,28 @@ def test_batch_full_size_sampled(batch, orc):
         assert rel_l2([ab[lo:hi].cpu().numpy(), bb[lo:hi].cpu().numpy()], [ra, rb]) <= TOL_F32, s
     sxh = sx.cpu().numpy()
     assert np.array_equal(sxh, np.repeat(sy, lengths))
+
+
+# Chains of tiles: kept whole up to 8 tiles, then cut into pieces of 4 (or twice
+# a block's share of the tiles), with remainders, heads in mid-tile, and ends on
+# a tile's edge.
+CHAINS = [[8 * 1024], [9 * 1024], [9 * 1024 + 1], [300, 13 * 1024, 5], [1024, 8 * 1024, 9 * 1024, 1], [1 << 18] * 3,
+          [500] * 2200 + [100000, 3]]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("case", range(len(CHAINS)))
+def test_cut_chains(batch, orc, dtype, case):
+    lengths = np.array(CHAINS[case], dtype=np.int64)
+    a, b, ya, yb, sy = seg_inputs(lengths, dtype, seed=40 + case)
+    plan = batch.SegPlan(lengths, torch.float32 if dtype == "f32" else torch.float64, tile=1024, grid=64)
+    refs = [[], [], [], []]
+    for s, e in zip(plan.offsets[:-1], plan.offsets[1:]):
+        for lst, v in zip(refs, orc.linrec_scan(a[s:e], b[s:e]) + orc.linrec_scan_vjp(a[s:e], b[s:e], ya[s:e], yb[s:e])):
+            lst.append(v)
+    R = [np.concatenate(x) for x in refs]
+    for _ in range(2):  # the queue's counter returns to rest
+        A, B, ck = plan.scan(dev(a), dev(b))
+        ab, bb, _ = plan.vjp(dev(a), dev(b), dev(ya), dev(yb), ck, sum_ybar=dev(sy))
+        assert rel_l2([host(A), host(B)], R[:2]) <= tol(dtype)
+        assert rel_l2([host(ab), host(bb)], R[2:]) <= tol(dtype)
