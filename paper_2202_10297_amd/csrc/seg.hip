@@ -598,9 +598,9 @@ static void launch_fwd(const void* a, const void* b, int64_t total, int64_t nseg
     const int32_t* counts = (const int32_t*)(ws + L.counts);
     const unsigned grid = (unsigned)(L.ntiles < kSegGrid ? L.ntiles : kSegGrid);
     if (L.ntiles > kSegWhole)
-            hipLaunchKernelGGL((seg_fwd_fold_kernel<T, IPT>), dim3(grid), dim3(kSegBlock), 0, st, (const T*)a, (const T*)b,
-                       total, nseg, (const int64_t*)(ws + L.offs), (const int32_t*)(ws + L.seg0),
-                       (const SegFold*)(ws + L.folds[0]), counts + 1, ws + L.states);
+            hipLaunchKernelGGL((seg_fwd_fold_kernel<T, IPT>), dim3(grid), dim3(kSegBlock), 0, st, (const T*)a,
+                           (const T*)b, total, nseg, (const int64_t*)(ws + L.offs), (const int32_t*)(ws + L.seg0),
+                           (const SegFold*)(ws + L.folds[0]), counts + 1, ws + L.states);
     hipLaunchKernelGGL((seg_linrec_fwd_kernel<T, IPT>), dim3(grid), dim3(kSegBlock), 0, st, (const T*)a, (const T*)b,
                        total, nseg, (const int64_t*)(ws + L.offs), (const int32_t*)(ws + L.seg0), (T*)A, (T*)B,
                        (T*)ckpt, (LookbackHdr*)ws, (const SegWalk*)(ws + L.walks[0]), counts, ws + L.states);
