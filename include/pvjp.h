@@ -220,11 +220,13 @@ pvjp_status pvjp_reduce_vjp(pvjp_op op, pvjp_dtype dtype, const void* x, int64_t
 /* Workspace bytes for pvjp_hist (device memory, zero-initialised once by the
  * caller, owned by the caller, reusable across calls on one stream).  Small
  * m (the bins fit one block's LDS): per-block partial histograms, O(m) with
- * a few hundred rows.  FP32 + / min / max with m beyond that and at most
- * 2^22 bins: the bucket-partitioned path, which sorts every tile of 8192
- * elements by bucket and stores per element the value (4 bytes) and its bin
- * in the bucket (+: 2 bytes; min/max: 4 bytes with the position in the
- * tile): about 8n bytes plus per-tile bucket offsets and per-item partials. */
+ * a few hundred rows.  Up to about 10^5 bins, long inputs: partial histograms
+ * in ranges of bins, up to 288 rows of m.  Beyond that and at most 2^22 bins, or
+ * with counts, or FP64 extremes: every tile of 8192 elements is sorted by
+ * bucket, with 4 (FP64: 8) bytes per element for its value and 4 for its bin
+ * in the bucket (min/max: with the position in the tile), plus per-tile bucket
+ * offsets and per-item partials.  The bytes cover calls with and without
+ * counts. */
 size_t pvjp_hist_ws_bytes(pvjp_op op, pvjp_dtype dtype, int64_t n, int64_t m);
 /* Which path pvjp_hist takes for (op, dtype, n, m, counts != 0), for tests
  * and tuning: info[0] = PVJP_HIST_PATH_*; for the partitioned path info[1] =
@@ -233,7 +235,9 @@ size_t pvjp_hist_ws_bytes(pvjp_op op, pvjp_dtype dtype, int64_t n, int64_t m);
  * = number of buckets; 0 otherwise.  info: int64 [4] host memory. */
 #define PVJP_HIST_PATH_LDS 0       /* every bin in each block's LDS, per-block partials merged */
 #define PVJP_HIST_PATH_CACHE 1     /* LDS cache of bins in front of device-memory atomics */
-#define PVJP_HIST_PATH_PARTITION 2 /* records sorted into buckets of bins, each bucket accumulated in LDS */
+/* bins split into buckets, each accumulated in LDS: the records sorted into the
+ * buckets first, or every chunk of the input read once per bucket */
+#define PVJP_HIST_PATH_PARTITION 2
 pvjp_status pvjp_hist_plan_info(pvjp_op op, pvjp_dtype dtype, int64_t n, int64_t m, int counts, int64_t* info);
 /* inds [n] int32, vs [n] dtype, 1 <= m <= 2^30, n < 2^31.
  * hs [m] dtype (required).

@@ -31,6 +31,7 @@ constexpr int kHistBlock = 256;
 constexpr int kHistLds = 64 * 1024;   // dynamic LDS per block
 constexpr int kCacheSlots = 4096;     // LDS cache slots when the bins do not fit
 constexpr int32_t kEmptyTag = -1;
+constexpr int kXcds = 8;  // accelerator dies of an MI355X, each with its own L2
 
 __device__ __forceinline__ int64_t ceil_div_dev(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
@@ -52,6 +53,12 @@ __device__ __forceinline__ uint64_t elem_key(float v, int64_t i) {
 template <int OP>
 __device__ __forceinline__ uint64_t elem_key(double v, int64_t) {
     return (OP == PVJP_MAX) ? ord64(v) : ~ord64(v);
+}
+
+// Whether an update competes by key (min/max) and has a winner.
+template <int OP>
+__host__ __device__ constexpr bool part_keys() {
+    return OP == PVJP_MIN || OP == PVJP_MAX;
 }
 
 template <int OP>
@@ -232,6 +239,78 @@ __global__ __launch_bounds__(kHistBlock) void hist_acc_kernel(
         if (k < 0 || k >= m) continue;
         acc_merge<OP>(&gacc[k], OP == PVJP_MUL ? &gz[k] : nullptr, sacc[s], OP == PVJP_MUL ? szc[s] : 0);
         if (COUNTS && scnt[s]) atomicAdd(&gcount[k], scnt[s]);
+    }
+}
+
+// The bins in R ranges, each as large as one CU's LDS holds.  R blocks, one per
+// range, read the same chunk of the input and keep the updates of their own
+// range; the chunk's partials are merged as in FULL mode.  Blocks go to the
+// XCDs round-robin, and the R blocks of a chunk are eight apart, so they share
+// one L2: the input comes from HBM once (n = 2^26, R = 4: of 17 M lines read, 4.5
+// M miss L2) and the kernel is bound by the CUs' reads from L2, 10.7 TB/s.
+// Sorting the records into buckets first (hpart_tile_kernel and its
+// successors) moves each one out to HBM and back instead.  All kernels of the
+// primal, n = 2^26 FP32 values, +: 65,536 bins 295 -> 213 us, 20,000 328 -> 120.
+constexpr int kRangeBlock = 1024;
+// Bins of a range: 160 KB of accumulators (products: and zero counters), one
+// block per CU.
+constexpr int range_bins(int op) { return 160 * 1024 / (op == PVJP_MUL ? 12 : 8) / 64 * 64; }
+
+template <class T, int OP, bool VEC>
+__global__ __launch_bounds__(kRangeBlock) void hist_range_kernel(const int32_t* __restrict__ inds,
+                                                                 const T* __restrict__ vs, int64_t n, int32_t m,
+                                                                 int64_t chunk, int R, int32_t per,
+                                                                 uint64_t* __restrict__ pacc,
+                                                                 int32_t* __restrict__ pz) {
+    constexpr int BATCH = sizeof(T) == 4 ? 4 : 2;
+    __shared__ uint64_t acc[range_bins(OP)];
+    __shared__ int32_t zc[OP == PVJP_MUL ? range_bins(OP) : 1];
+    const int xcd = (int)blockIdx.x % kXcds, slot = (int)blockIdx.x / kXcds;
+    const int64_t c = (int64_t)(slot / R) * kXcds + xcd;
+    const int32_t k0 = (slot % R) * per;
+    const uint32_t cnt = (uint32_t)(m - k0 < per ? m - k0 : per);
+    for (uint32_t j = threadIdx.x; j < cnt; j += kRangeBlock) {
+        acc[j] = acc_identity<OP>();
+        if (OP == PVJP_MUL) zc[j] = 0;
+    }
+    __syncthreads();
+    const int64_t lo = c * chunk;
+    const int64_t hi = (lo + chunk < n) ? lo + chunk : n;
+    constexpr int64_t kStride = 4 * kRangeBlock * BATCH;
+    Quad<T> cur[BATCH], nxt[BATCH];
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u)
+        cur[u] = load_quad<T, VEC>(inds, vs, lo + 4 * ((int64_t)u * kRangeBlock + threadIdx.x), hi);
+    for (int64_t base = lo; base < hi; base += kStride) {
+        const int64_t nb = base + kStride;
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u)
+            nxt[u] = load_quad<T, VEC>(inds, vs, nb + 4 * ((int64_t)u * kRangeBlock + threadIdx.x), hi);
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+            const int32_t kk[4] = {cur[u].k.x, cur[u].k.y, cur[u].k.z, cur[u].k.w};
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                // an index below 0 or beyond m is in no range
+                const uint32_t j = (uint32_t)kk[t] - (uint32_t)k0;
+                if (j >= cnt) continue;
+                if (!part_keys<OP>()) {
+                    acc_update<T, OP>(&acc[j], &zc[OP == PVJP_MUL ? j : 0], cur[u].v[t], 0);
+                } else {
+                    const int64_t e = base + 4 * ((int64_t)u * kRangeBlock + threadIdx.x) + t;
+                    const uint64_t key = elem_key<OP>(cur[u].v[t], e);
+                    if (key > __hip_atomic_load(&acc[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))
+                        atomicMax(reinterpret_cast<unsigned long long*>(&acc[j]), (unsigned long long)key);
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) cur[u] = nxt[u];
+    }
+    __syncthreads();
+    for (uint32_t j = threadIdx.x; j < cnt; j += kRangeBlock) {
+        pacc[c * m + k0 + j] = acc[j];
+        if (OP == PVJP_MUL) pz[c * m + k0 + j] = zc[j];
     }
 }
 
@@ -627,11 +706,6 @@ __device__ __forceinline__ void tile_store_u16(uint16_t* __restrict__ dst, const
     }
 }
 
-// Whether a record keeps its position in the tile (min/max: the winner).
-template <int OP>
-__host__ __device__ constexpr bool part_keys() {
-    return OP == PVJP_MIN || OP == PVJP_MAX;
-}
 template <class T>
 __device__ __forceinline__ uint32_t val_word(T v, int hi) {
     if constexpr (sizeof(T) == 4) return __float_as_uint(v);
@@ -887,7 +961,6 @@ __global__ __launch_bounds__(256) void hpart_items_kernel(const int32_t* __restr
 // in flight.
 constexpr int kAccBlock = 1024;
 constexpr int kAccCopies = 2;
-constexpr int kXcds = 8;  // accelerator dies of an MI355X, each with its own L2
 constexpr int kXcdMapBuckets = 128;
 constexpr int kAccGroup = 8;
 constexpr int kAccSlots = 4;  // records per lane and group in flight
@@ -1289,8 +1362,8 @@ static HistPlan hist_plan(int op, int64_t n, int64_t m, bool counts) {
     return P;
 }
 
-// The bucket-partitioned path serves m beyond one block's LDS, up to the
-// buckets of the scan block.  Short inputs keep the LDS bin cache with global
+// Where the form in ranges does not serve: the bucket-partitioned path takes m
+// beyond one block's LDS, up to the buckets of the scan block.  Short inputs keep the LDS bin cache with global
 // atomics: the partition's eight launches cost more than the atomics, which
 // are fewer where the cache holds a good part of the bins.  Primal and VJP with
 // the cache and with the partition, in us:
@@ -1307,6 +1380,53 @@ static bool use_partition(int op, bool f32, int64_t n, int64_t m, bool counts) {
     if (op == PVJP_MUL) return n >= ((int64_t)1 << 17);
     if (m > 65536) return n >= ((int64_t)1 << 20);
     return n >= (f32 || op == PVJP_ADD ? (int64_t)3 << 19 : (int64_t)1 << 21);
+}
+
+// The form in ranges reads the input once per range, the partition reads and
+// writes it about twice whatever m.  Primal and VJP with the partition and with
+// ranges, in us, n = 2^26 FP32 (2^25 products and FP64):
+//   +: 81,920 bins (4 ranges) 485, 395; 100,000 (5) 502, 470; 122,000 (6) 535, 537
+//   max: 122,000 439, 390; 140,000 (7) 436, 461
+//   *: 27,000 (2) 646, 524; 65,536 (5) 634, 643
+//   + FP64: 65,536 398, 310; 100,000 426, 351
+// Short inputs, + FP32 Zipf, with the bin cache (below) and with ranges:
+//   n = 400,000: m = 10,000 (one range) 25.7, 24.8; 20,000 25.8, 25.7; 40,000 28, 36
+//   n = 10^6: 10,000 31, 25; 40,000 42, 37; 65,000 47, 41; 100,000 53, 47
+// Bins that fit 64 KB (FULL mode): m = 4,099, n = 2^21 27.5, 25.8; 2^22 31.6,
+// 29.0; 2^23 45, 46; FP64 2^22 39, 34; m = 8,000 2^22 36.5, 33.5, max 2^25 111,
+// 101; with fewer bins there is little to gain (m = 1,024, n = 2^23: 39, 42).
+// Counts would take half the bins again and FP64 extremes need their winners:
+// both keep the other paths.
+static bool use_range(int op, bool f32, int64_t n, int64_t m, bool counts) {
+    const bool keys = op == PVJP_MIN || op == PVJP_MAX;
+    if (counts || (keys && !f32)) return false;
+    const int64_t R = ceil_div(m, range_bins(op));
+    if (R > (op == PVJP_MUL ? 4 : keys ? 6 : 5)) return false;
+    if (m <= kHistLds / (int64_t)slot_bytes(op, false, false)) return m >= 4096 && n >= (int64_t)1 << 21;
+    if (op == PVJP_MUL) return n >= (int64_t)1 << 17;
+    return n >= (R == 1 ? (int64_t)3 << 17 : (int64_t)15 << 16);
+}
+
+struct RangePlan {
+    int R;        // ranges
+    int32_t per;  // bins of a range
+    int64_t C, chunk;
+};
+
+// As many chunks as fill the chip with R blocks each, in whole rounds over the
+// XCDs; fewer for short inputs, whose partials (m per chunk) would cost more
+// than the updates (n = 400,000, m = 10,000: 29.4 us with chunks of 32,768, 24.8
+// with 8,192 or 16,384; m = 65,000, n = 10^6: 45.6, 42.4 with 16,384, 41.0 with
+// 8,192).
+static RangePlan range_plan(int op, int64_t n, int64_t m) {
+    RangePlan P{};
+    P.R = (int)ceil_div(m, range_bins(op));
+    P.per = (int32_t)ceil_div(m, P.R);
+    P.C = std::min<int64_t>(kXcds * (kCuCount / kXcds / P.R), std::max<int64_t>(kXcds, n / 8192 / kXcds * kXcds));
+    const int64_t quantum = 4 * kRangeBlock;
+    P.chunk = ceil_div(ceil_div(n, P.C), quantum) * quantum;
+    P.C = ceil_div(ceil_div(n, P.chunk), kXcds) * kXcds;
+    return P;
 }
 
 struct PartLayout {
@@ -1355,27 +1475,20 @@ static PartLayout part_layout(int64_t n, int64_t m, bool f32) {
 // Covers both plans (with and without counts): the FULL/CACHE choice and the
 // grid depend on whether counts are requested.
 static size_t hist_ws(int op, int64_t n, int64_t m, bool f32) {
-    if (use_partition(op, f32, n, m, false) || use_partition(op, f32, n, m, true)) {
-        // either plan may run: reserve the larger of the two layouts below
-        const size_t part = part_layout(n, m, f32).total;
-        size_t other = 0;
-        for (int counts = 0; counts < 2; ++counts) {
-            const HistPlan P = hist_plan(op, n, m, counts != 0);
-            if (!P.cache) other = std::max(other, align_up((size_t)(P.grid + kMergeSlices) * m * 16, 256));
-        }
-        return align_up((size_t)m * 8, 256) + (op == PVJP_MUL ? align_up((size_t)m * 4, 256) : 0) +
-               std::max(part, other);
-    }
-    size_t part = 0;
+    size_t body = 0;
     for (int counts = 0; counts < 2; ++counts) {
-        const HistPlan P = hist_plan(op, n, m, counts != 0);
-        if (!P.cache) {
+        if (use_range(op, f32, n, m, counts != 0)) {
+            // chunks' partials and the merge slices: acc 8 + zeros 4
+            body = std::max(body, align_up((size_t)(range_plan(op, n, m).C + kMergeSlices) * m * 12, 256));
+        } else if (use_partition(op, f32, n, m, counts != 0)) {
+            body = std::max(body, part_layout(n, m, f32).total);
+        } else {
             // per-block partials and the merge slices: acc 8 + zeros 4 + counts 4
-            const size_t b = align_up((size_t)(P.grid + kMergeSlices) * m * 16, 256);
-            if (b > part) part = b;
+            const HistPlan P = hist_plan(op, n, m, counts != 0);
+            if (!P.cache) body = std::max(body, align_up((size_t)(P.grid + kMergeSlices) * m * 16, 256));
         }
     }
-    return align_up((size_t)m * 8, 256) + (op == PVJP_MUL ? align_up((size_t)m * 4, 256) : 0) + part;
+    return align_up((size_t)m * 8, 256) + (op == PVJP_MUL ? align_up((size_t)m * 4, 256) : 0) + body;
 }
 
 // The partition shared by the accumulators: the tile sort, the run
@@ -1483,6 +1596,28 @@ static void run_hist(const int32_t* inds, const T* vs, int64_t n, int32_t m, T* 
         off += align_up((size_t)m * 4, 256);
     }
     const bool counts = count != nullptr;
+    if constexpr (sizeof(T) == 4 || !part_keys<OP>()) {
+        if (use_range(OP, sizeof(T) == 4, n, m, counts)) {
+            const RangePlan P = range_plan(OP, n, m);
+            uint64_t* pacc = reinterpret_cast<uint64_t*>(w + off);
+            uint64_t* macc = pacc + (size_t)P.C * m;
+            int32_t* pz = reinterpret_cast<int32_t*>(macc + (size_t)kMergeSlices * m);
+            int32_t* mz = pz + (size_t)P.C * m;
+            const dim3 g((unsigned)(P.C * P.R)), b(kRangeBlock);
+            if (aligned(inds, 16) && aligned(vs, 16))
+                hipLaunchKernelGGL((hist_range_kernel<T, OP, true>), g, b, 0, st, inds, vs, n, m, P.chunk, P.R, P.per,
+                                   pacc, pz);
+            else
+                hipLaunchKernelGGL((hist_range_kernel<T, OP, false>), g, b, 0, st, inds, vs, n, m, P.chunk, P.R, P.per,
+                                   pacc, pz);
+            hipLaunchKernelGGL(hist_merge1_kernel<OP>, dim3((unsigned)ceil_div(m, 256), kMergeSlices), dim3(256), 0,
+                               st, pacc, pz, nullptr, P.C, m, macc, mz, nullptr);
+            hipLaunchKernelGGL((hist_merge2_kernel<T, OP, true>), dim3((unsigned)ceil_div(m, kMerge2Block)),
+                               dim3(kMerge2Block), 0, st, macc, mz, nullptr, m, vs, gacc, nullptr,
+                               HistOut<T>{hs, winner, p, z});
+            return;
+        }
+    }
     if (use_partition(OP, sizeof(T) == 4, n, m, counts)) {
         run_partitioned<T, OP>(inds, vs, n, m, count, w, off, HistOut<T>{hs, winner, p, z}, st);
         return;
@@ -1615,7 +1750,15 @@ extern "C" pvjp_status pvjp_hist_plan_info(pvjp_op op, pvjp_dtype dtype, int64_t
     PVJP_REQUIRE(n >= 0 && n <= INT32_MAX && m >= 1 && m <= kMaxBins, "pvjp_hist_plan_info: n or m out of range");
     PVJP_REQUIRE(info != nullptr, "pvjp_hist_plan_info: info is NULL");
     info[1] = info[2] = info[3] = 0;
-    if (use_partition(op, dtype == PVJP_F32, n, m, counts != 0)) {
+    if (use_range(op, dtype == PVJP_F32, n, m, counts != 0)) {
+        const RangePlan P = range_plan(op, n, m);
+        info[0] = m <= kHistLds / (int64_t)slot_bytes(op, false, false) ? PVJP_HIST_PATH_LDS : PVJP_HIST_PATH_PARTITION;
+        if (info[0] == PVJP_HIST_PATH_PARTITION) {
+            info[1] = P.per;
+            info[2] = P.chunk;
+            info[3] = P.R;
+        }
+    } else if (use_partition(op, dtype == PVJP_F32, n, m, counts != 0)) {
         info[0] = PVJP_HIST_PATH_PARTITION;
         info[1] = kPartBins;
         // runs start within seg records; a run is below kTile

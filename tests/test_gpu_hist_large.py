@@ -147,3 +147,41 @@ def test_partition_edges(ops, orc, op, n, m, dist, dtype):
         if op == "mul":
             assert np.array_equal(host(aux["z"]), ref["z"])
             assert rel_l2(host(aux["p"]), ref["p"]) <= bar
+
+
+# The form in ranges of bins: either side of its lines, one to six ranges, a
+# last range of one bin, ragged chunks, an unaligned view, empty bins.
+RANGES = [("add", (3 << 17) - 1, 8193), ("add", 3 << 17, 8193), ("add", (15 << 16) + 4097, 20481),
+          ("add", 1 << 21, 4096), ("add", (1 << 21) + 5, 102400), ("add", 1 << 20, 102401), ("max", 15 << 16, 40961),
+          ("min", (1 << 20) + 1, 122880), ("max", 1 << 21, 8192), ("min", 3 << 17, 20480), ("mul", 1 << 17, 13633),
+          ("mul", (1 << 18) + 3, 54528), ("mul", 1 << 18, 54529), ("mul", 1 << 17, 5462)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("op,n,m", RANGES)
+def test_range_edges(ops, orc, op, n, m, shift, dtype):
+    inds, vs, _ = workloads.hist(n + shift, m, "uniform", dtype, seed=n + m)
+    inds[::101] = -1
+    inds[7::103] = m
+    inds[inds % 17 == 3] = m - 1  # empty bins, and a hot last one
+    if op == "mul":
+        vs = np.exp(1e-3 * vs).astype(vs.dtype)
+        vs[::5003] = 0.0
+    elif op != "add":
+        vs = (np.round(vs * 8) / 8).astype(vs.dtype)
+        vs[::13] = -0.0
+        vs[5::999] = np.inf if op == "max" else -np.inf
+        vs[6::999] = -np.inf if op == "max" else np.inf
+    hs, aux = ops.hist(op, dev(inds)[shift:], dev(vs)[shift:], m)
+    ref = orc.hist(op, inds[shift:], vs[shift:], m)
+    bar = TOL_F32 if dtype == "f32" else 1e-12
+    if op in ("min", "max"):
+        assert np.array_equal(host(aux["winner"]), ref["winner"])
+        got = host(hs)
+        assert np.array_equal(got, ref["hs"]) and np.array_equal(np.signbit(got), np.signbit(ref["hs"]))
+    else:
+        assert rel_l2(host(hs), ref["hs"]) <= bar
+    if op == "mul":
+        assert np.array_equal(host(aux["z"]), ref["z"])
+        assert rel_l2(host(aux["p"]), ref["p"]) <= bar
