@@ -42,7 +42,16 @@ def _ptr(t):
     return t.data_ptr() or None
 
 
+# The current stream's handle without building a Stream object (0.1 us against
+# 1.7, twice in every call: a scan of 1,024 elements takes the host 8.7 us, was
+# 11.8).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(device=None):
+    if _raw_stream is not None and isinstance(device, torch.device) and device.type == "cuda" \
+            and device.index is not None:
+        return _raw_stream(device.index)
     return torch.cuda.current_stream(device).cuda_stream
 
 
@@ -56,7 +65,7 @@ class Workspaces:
         self._bufs = {}
 
     def get(self, key, nbytes: int, device) -> torch.Tensor:
-        dev = torch.device(device)
+        dev = device if isinstance(device, torch.device) else torch.device(device)
         k = (dev.index, _stream(dev), key)
         buf = self._bufs.get(k)
         if buf is None or buf.numel() < nbytes:
