@@ -677,7 +677,7 @@ __global__ __launch_bounds__(256) void hist_vjp_winner_kernel(const int32_t* __r
 constexpr int kPartShift = 12;
 constexpr int kPartBins = 1 << kPartShift;
 constexpr int kPartMaxBuckets = 1024;
-constexpr int64_t kPartSeg = (int64_t)1 << 17;     // records per work item, at most
+constexpr int64_t kPartSeg = (int64_t)1 << 16;     // records per work item, at most
 constexpr int64_t kPartSegMin = (int64_t)1 << 14;  // and at least
 constexpr int kPartScanThreads = 1024;
 constexpr int kTileThreads = 512;
@@ -1438,9 +1438,11 @@ struct PartLayout {
 
 static PartLayout part_layout(int64_t n, int64_t m, bool f32) {
     PartLayout L{};
-    // Work items of 2^17 records once there are 512 of them (two a CU), fewer
-    // records before that: a short input's buckets would otherwise be one item
-    // each (n = 10^6, m = 100,000 Zipf, primal and VJP: 116 us, now 48).
+    // 512 work items (two a CU) or more, of up to 2^16 records: a short input's
+    // buckets would otherwise be one item each (n = 10^6, m = 100,000 Zipf,
+    // primal and VJP: 116 us, now 48), and a long one's larger items leave a
+    // long last wave (n = 2^26, m = 2^20, items of 2^17 and 2^16: max Zipf 565,
+    // 548 us; + Zipf 716, 689; max uniform 540, 515; with 2^15 550, 686, 521).
     L.seg = (int)kPartSegMin;
     while (L.seg < kPartSeg && (int64_t)L.seg * 512 < n) L.seg *= 2;
     L.nb = (int)ceil_div(m, kPartBins);
