@@ -985,12 +985,7 @@ static void gs_prefixes(const GPtrs<T>& x, int64_t n, const GsPlan& p, typename 
     else
         hipLaunchKernelGGL((gred_tile_agg_kernel<Op, T, false, IPT>), dim3((unsigned)p.nt, B), dim3(kGrBlock), 0, st,
                            x, n, agg);
-    const unsigned gb = (unsigned)ceil_div(p.ng, kGroupBlock / kWave);
-    hipLaunchKernelGGL((group_fold_kernel<Op, false>), dim3(gb, B), dim3(kGroupBlock), 0, st, (const S*)agg, p.nt,
-                       p.ng, gagg);
-    hipLaunchKernelGGL((agg_scan_kernel<Op, false>), dim3(1, B), dim3(kAggBlock), 0, st, (const S*)gagg, p.ng, gpre);
-    hipLaunchKernelGGL((group_prefix_kernel<Op, false>), dim3(gb, B), dim3(kGroupBlock), 0, st, (const S*)agg, p.nt,
-                       p.ng, (const S*)gpre, pre);
+    scan_aggregates<Op, false>(agg, p.nt, p.ng, gagg, gpre, pre, B, st);
 }
 
 template <class Op, class T>
@@ -1037,13 +1032,7 @@ static void launch_scan_vjp(const GPtrs<T>& x, int64_t n, const void* ckpt, cons
         hipLaunchKernelGGL((gscan_vjp_agg_kernel<Op, T, IPT, true>), gt, b, 0, st, x, n, pre, yb, lagg);
     else
         hipLaunchKernelGGL((gscan_vjp_agg_kernel<Op, T, IPT, false>), gt, b, 0, st, x, n, pre, yb, lagg);
-    const unsigned gb = (unsigned)ceil_div(p.ng, kGroupBlock / kWave);
-    hipLaunchKernelGGL((group_fold_kernel<LG, true>), dim3(gb, (unsigned)B), dim3(kGroupBlock), 0, st,
-                       (const LS*)lagg, p.nt, p.ng, lgagg);
-    hipLaunchKernelGGL((agg_scan_kernel<LG, true>), dim3(1, (unsigned)B), dim3(kAggBlock), 0, st, (const LS*)lgagg,
-                       p.ng, lgpre);
-    hipLaunchKernelGGL((group_prefix_kernel<LG, true>), dim3(gb, (unsigned)B), dim3(kGroupBlock), 0, st,
-                       (const LS*)lagg, p.nt, p.ng, (const LS*)lgpre, lsuf);
+    scan_aggregates<LG, true>(lagg, p.nt, p.ng, lgagg, lgpre, lsuf, (unsigned)B, st);
     const LS* cs = lsuf;
     const int back = 2 * n * (int64_t)(Op::K * sizeof(T)) > kBackBytes;
     if (vec) {

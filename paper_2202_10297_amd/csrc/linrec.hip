@@ -381,11 +381,7 @@ static void scan_aggregates(const typename Op::S* agg, int64_t nt, typename Op::
     const int64_t ng = ceil_div(nt, kAggGroup);
     S* gagg = group_array<S>(ws, nt, 0);
     S* gpre = group_array<S>(ws, nt, 1);
-    const unsigned gb = (unsigned)ceil_div(ng, kGroupBlock / kWave);
-    hipLaunchKernelGGL((group_fold_kernel<Op, REV>), dim3(gb), dim3(kGroupBlock), 0, st, agg, nt, ng, gagg);
-    hipLaunchKernelGGL((agg_scan_kernel<Op, REV>), dim3(1), dim3(kAggBlock), 0, st, (const S*)gagg, ng, gpre);
-    hipLaunchKernelGGL((group_prefix_kernel<Op, REV>), dim3(gb), dim3(kGroupBlock), 0, st, agg, nt, ng,
-                       (const S*)gpre, pre);
+    pvjp::scan_aggregates<Op, REV>(agg, nt, ng, gagg, gpre, pre, 1, st);
 }
 
 template <class T>

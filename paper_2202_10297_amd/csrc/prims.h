@@ -188,7 +188,7 @@ __device__ __forceinline__ typename Op::S wave_exclusive_scan(typename Op::S v) 
 // --------------------------------------------- scans of tile aggregates
 // A reduce-then-scan over many tiles scans the tiles' aggregates in scan
 // order (increasing tile index, or decreasing with REV).  One block walking
-// tens of thousands of aggregates is slow (100-200 us at 32K), so tiles are
+// tens of thousands of aggregates is slow (100-200 us at 32K), so many tiles are
 // taken in groups of 64, one wave per group: group_fold_kernel folds each
 // group, agg_scan_kernel scans the group folds, group_prefix_kernel gives
 // every tile its group's prefix folded with the group's tiles before it.
@@ -200,7 +200,9 @@ constexpr int kGroupBlock = 256;
 
 // pre[i] = exclusive fold of agg in scan order.  Thread t folds a contiguous
 // run of the scan order, the runs are scanned across the block, then each
-// thread writes its run's prefixes.
+// thread writes its run's prefixes.  Up to kAggRun states a thread are loaded
+// together and stay in registers.
+constexpr int kAggRun = 2;
 template <class Op, bool REV>
 __global__ __launch_bounds__(kAggBlock) void agg_scan_kernel(const typename Op::S* __restrict__ agg, int64_t cnt,
                                                              typename Op::S* __restrict__ pre) {
@@ -208,13 +210,34 @@ __global__ __launch_bounds__(kAggBlock) void agg_scan_kernel(const typename Op::
     __shared__ S wtot[kAggBlock / kWave];
     agg += (int64_t)blockIdx.y * cnt;
     pre += (int64_t)blockIdx.y * cnt;
+    auto at = [&](int64_t v) { return REV ? cnt - 1 - v : v; };
+    S total;
+    if (cnt <= kAggRun * kAggBlock) {
+        const int per = (int)((cnt + kAggBlock - 1) / kAggBlock);
+        const int v0 = (int)threadIdx.x * per;
+        S own[kAggRun];
+#pragma unroll
+        for (int i = 0; i < kAggRun; ++i) {
+            const bool ok = i < per && v0 + i < cnt;
+            own[i] = Op::id();
+            if (ok) own[i] = agg[at(v0 + i)];
+        }
+        S run = own[0];
+#pragma unroll
+        for (int i = 1; i < kAggRun; ++i) run = Op::comb(run, own[i]);
+        S ex = block_exclusive_scan<Op, kAggBlock, false>(run, total, wtot);
+#pragma unroll
+        for (int i = 0; i < kAggRun; ++i) {
+            if (i < per && v0 + i < cnt) pre[at(v0 + i)] = ex;
+            ex = Op::comb(ex, own[i]);
+        }
+        return;
+    }
     const int64_t per = (cnt + kAggBlock - 1) / kAggBlock;
     const int64_t v0 = (int64_t)threadIdx.x * per;
     const int64_t v1 = (v0 + per < cnt) ? v0 + per : cnt;
-    auto at = [&](int64_t v) { return REV ? cnt - 1 - v : v; };
     S run = Op::id();
     for (int64_t v = v0; v < v1; ++v) run = Op::comb(run, agg[at(v)]);
-    S total;
     S ex = block_exclusive_scan<Op, kAggBlock, false>(run, total, wtot);
     for (int64_t v = v0; v < v1; ++v) {
         pre[at(v)] = ex;
@@ -252,6 +275,26 @@ __global__ __launch_bounds__(kGroupBlock) void group_prefix_kernel(const typenam
     const S own = t < nt ? agg[t] : Op::id();
     const S ex = wave_exclusive_scan<Op, REV>(own);
     if (t < nt) pre[t] = Op::comb(gpre[g], ex);
+}
+
+// The prefixes pre of nt aggregates, B scans of them back to back: by one block
+// where it takes them in one round, else in groups.  Scan and VJP (two such
+// scans) of 2x2 products in FP32 with groups and with one block, us: 10 tiles
+// 51, 42; 977 60, 52; 1,954 85, 83; with four states a thread 3,907 134, 137;
+// FP32 linear recurrence 977 tiles 44, 35; FP64 log-add-exp 977 63, 59.
+template <class Op, bool REV>
+static inline void scan_aggregates(const typename Op::S* agg, int64_t nt, int64_t ng, typename Op::S* gagg,
+                                   typename Op::S* gpre, typename Op::S* pre, unsigned B, hipStream_t st) {
+    using S = typename Op::S;
+    if (nt <= kAggRun * kAggBlock) {
+        hipLaunchKernelGGL((agg_scan_kernel<Op, REV>), dim3(1, B), dim3(kAggBlock), 0, st, agg, nt, pre);
+        return;
+    }
+    const unsigned gb = (unsigned)((ng + kGroupBlock / kWave - 1) / (kGroupBlock / kWave));
+    hipLaunchKernelGGL((group_fold_kernel<Op, REV>), dim3(gb, B), dim3(kGroupBlock), 0, st, agg, nt, ng, gagg);
+    hipLaunchKernelGGL((agg_scan_kernel<Op, REV>), dim3(1, B), dim3(kAggBlock), 0, st, (const S*)gagg, ng, gpre);
+    hipLaunchKernelGGL((group_prefix_kernel<Op, REV>), dim3(gb, B), dim3(kGroupBlock), 0, st, agg, nt, ng,
+                       (const S*)gpre, pre);
 }
 
 // ------------------------------------------------------- LDS transposes

@@ -192,3 +192,15 @@ def test_autograd(orc):
     ys = autograd.scan_generic("mat2", *t)
     sum((y * dev(g)).sum() for y, g in zip(ys, ybs)).backward()
     assert rel_l2([host(x.grad) for x in t], orc.scan_generic_vjp("mat2", xs, ybs)) <= TOL_F64
+
+
+# Either side of the tile counts that one block scans: one, a full round of one
+# and of two tiles a thread, and in groups.
+@pytest.mark.parametrize("tiles", [1, 1023, 1024, 1025, 2047, 2048, 2049])
+@pytest.mark.parametrize("op,dtype", [("logaddexp", "f32"), ("linrec", "f64"), ("mat2", "f32")])
+def test_tile_scan_edges(ops, orc, op, dtype, tiles):
+    n = tiles * tile(op, dtype) - 3
+    xs, ybs = inputs(op, n, dtype, seed=tiles)
+    ys, xb = run(ops, op, xs, ybs)
+    assert close_outputs(ys, orc.scan_generic(op, xs), 1e-13 if dtype == "f64" else 1e-6)
+    assert rel_l2(xb, orc.scan_generic_vjp(op, xs, ybs)) <= tol(dtype)
