@@ -12,7 +12,8 @@
 //               coarse bucket): count per chunk of 4096 updates, scan the
 //               (digit, chunk) counts, scatter (k, j, v) records in runs;
 //            2. within each coarse bucket, the same by fine digit
-//               (k >> S0) & 63, which leaves the records grouped by window;
+//               (k >> S0) & 63, which leaves the records grouped by window
+//               (few windows: pass 1 alone, with the window as its digit);
 //            3. per window: load it into LDS, save each target's old value
 //               (in record order, kept in the plan), write the new value,
 //               store the window back;
@@ -261,16 +262,20 @@ struct FineDigit {
     __device__ int operator()(int32_t k) const { return (k >> s0) & (kSpFine - 1); }
 };
 
-template <class T>
+// ONE: the digits are the windows, whose starts the first chunk's block writes.
+template <class T, bool ONE>
 __global__ __launch_bounds__(kSpBlock) void sp_scatter1_kernel(const int32_t* __restrict__ is, const T* __restrict__ vs,
                                                                int64_t m, int64_t n, int s1, int nc, int nch,
                                                                const int32_t* __restrict__ off1,
                                                                int32_t* __restrict__ rk, int32_t* __restrict__ rj,
-                                                               T* __restrict__ rv) {
+                                                               T* __restrict__ rv, const int32_t* __restrict__ total,
+                                                               int32_t* __restrict__ wstart) {
     extern __shared__ __align__(16) char smem[];
     __shared__ IntSum::S wtot[kSpBlock / kWave];
     const SpStage<T> L = sp_stage_layout<T>(smem, nc);
     const int c = sp_xcd_chunk(nch);
+    if (ONE && c == 0)
+        for (int d = threadIdx.x; d <= nc; d += kSpBlock) wstart[d] = d < nc ? off1[(int64_t)d * nch] : *total;
     if (c < 0 || m <= 0) return;  // with no updates there is nothing to place
     for (int d = threadIdx.x; d < nc; d += kSpBlock) {
         L.cnt[d] = 0;
@@ -561,7 +566,17 @@ __global__ __launch_bounds__(256) void sp_clear_kernel(T* __restrict__ x, int64_
 }
 
 // ------------------------------------------------------------------ host
+// Up to this many windows one pass takes the window as its digit: its runs are
+// short (four records at 1,024 windows) but meet in one L2, and half the
+// launches go.  Forward and return sweep with two passes and with one, us:
+//   FP32: n = 290,995, m = 112,253 51, 30; 2 10^6, 10^6 65, 44; 8 10^6, 5 10^6
+//   (977 windows) 182, 158; 1.6 10^7 (1,954), 2 10^6 142, 126, but 1.06 10^7 391,
+//   422; 3.3 10^7 (4,029), 4.1 10^6 275, 319
+//   FP64: 2 10^6, 4 10^5 62, 45; 4 10^6, 2.6 10^6 133, 110
+constexpr int64_t kSpOneWindows = 1024;
+
 struct SpLayout {
+    bool one;  // one bucketing pass
     int s0, s1, nc, nch1, nch2max;
     int64_t n1, n2, nt1, nt2, nw;
     size_t cnt1, tsum1, total, cstart, nch2, chb2, cnt2, tsum2, wstart, rk1, rj1, rv1, rk, rj, rv, saved, bytes;
@@ -571,16 +586,17 @@ static SpLayout sp_layout(pvjp_dtype dtype, int64_t n, int64_t m) {
     SpLayout L{};
     const size_t ts = dsize(dtype);
     L.s0 = dtype == PVJP_F64 ? sp_s0<double>() : sp_s0<float>();
-    L.s1 = L.s0 + kSpFineBits;
+    L.one = ceil_div(n > 0 ? n : 1, (int64_t)1 << L.s0) <= kSpOneWindows;
+    L.s1 = L.s0 + (L.one ? 0 : kSpFineBits);
     L.nc = (int)ceil_div(n > 0 ? n : 1, (int64_t)1 << L.s1);
     L.nch1 = (int)ceil_div(m > 0 ? m : 1, kSpChunk);
-    L.nch2max = L.nch1 + L.nc;
+    L.nch2max = L.one ? 0 : L.nch1 + L.nc;
     L.n1 = (int64_t)L.nc * L.nch1;
     L.n2 = (int64_t)L.nch2max * kSpFine;
     L.nt1 = ceil_div(L.n1, kSpScanTile);
     L.nt2 = ceil_div(L.n2, kSpScanTile);
-    L.nw = (int64_t)L.nc * kSpFine;
-    const size_t mm = (size_t)(m > 0 ? m : 1);
+    L.nw = (int64_t)L.nc * (L.one ? 1 : kSpFine);
+    const size_t mm = (size_t)(m > 0 ? m : 1), m1 = L.one ? 0 : mm;
     size_t o = 0;
     auto take = [&](size_t b) {
         const size_t at = o;
@@ -596,9 +612,9 @@ static SpLayout sp_layout(pvjp_dtype dtype, int64_t n, int64_t m) {
     L.cnt2 = take((size_t)L.n2 * 4);
     L.tsum2 = take((size_t)L.nt2 * 4);
     L.wstart = take((size_t)(L.nw + 1) * 4);
-    L.rk1 = take(mm * 4);
-    L.rj1 = take(mm * 4);
-    L.rv1 = take(mm * ts);
+    L.rk1 = take(m1 * 4);
+    L.rj1 = take(m1 * 4);
+    L.rv1 = take(m1 * ts);
     L.rk = take(mm * 4);
     L.rj = take(mm * 4);
     L.rv = take(mm * ts);
@@ -608,12 +624,15 @@ static SpLayout sp_layout(pvjp_dtype dtype, int64_t n, int64_t m) {
 }
 
 // The staging of a chunk can exceed the default 64 KiB of dynamic LDS (FP64
-// records, many coarse digits): raise the limit of both scatter kernels once.
+// records, many coarse digits): raise the limit of the scatter kernels once.
 template <class T>
 static void sp_allow_lds() {
     static const bool once = [] {
         constexpr int kMax = 160 * 1024 - 1024;  // the CU's LDS less the kernels' static share
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&sp_scatter1_kernel<T>),
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&sp_scatter1_kernel<T, false>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, kMax) != hipSuccess)
+            (void)hipGetLastError();
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&sp_scatter1_kernel<T, true>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, kMax) != hipSuccess)
             (void)hipGetLastError();
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(&sp_scatter2_kernel<T>),
@@ -644,31 +663,37 @@ static pvjp_status sp_forward(T* xs, int64_t n, const int32_t* is, const T* vs, 
     T* rv = (T*)(p + L.rv);
     T* saved = (T*)(p + L.saved);
     sp_allow_lds<T>();
-    // pass 1: coarse buckets
+    // exclusive scan of N counts in place; one tile needs no sums before it
+    auto scan_counts = [&](int32_t* a, int64_t N, int64_t nt, int32_t* tsum, int32_t* tot) {
+        if (nt > 1) hipLaunchKernelGGL(sp_tile_sum_kernel, dim3((unsigned)nt), dim3(1024), 0, st, a, N, tsum);
+        hipLaunchKernelGGL(sp_tile_scan_kernel, dim3((unsigned)nt), dim3(1024), 0, st, a, N, (const int32_t*)tsum, tot);
+    };
+    // pass 1: coarse buckets, or windows
     hipLaunchKernelGGL(sp_count1_kernel, dim3(sp_xcd_grid(L.nch1)), dim3(kSpBlock), (size_t)L.nc * 4, st, is, m, n, L.s1, L.nc,
                        L.nch1, cnt1);
-    hipLaunchKernelGGL(sp_tile_sum_kernel, dim3((unsigned)L.nt1), dim3(1024), 0, st, cnt1, L.n1, tsum1);
-    hipLaunchKernelGGL(sp_tile_scan_kernel, dim3((unsigned)L.nt1), dim3(1024), 0, st, cnt1, L.n1, (const int32_t*)tsum1,
-                       total);
-    hipLaunchKernelGGL(sp_seg_kernel, dim3(1), dim3(1024), 0, st, (const int32_t*)cnt1, L.nch1, L.nc,
-                       (const int32_t*)total, cstart, nch2, chb2);
+    scan_counts(cnt1, L.n1, L.nt1, tsum1, total);
     const size_t lds1 = sp_stage_bytes(L.nc, sizeof(T));
-    hipLaunchKernelGGL(sp_scatter1_kernel<T>, dim3(sp_xcd_grid(L.nch1)), dim3(kSpBlock), lds1, st, is, vs, m, n, L.s1, L.nc, L.nch1,
-                       (const int32_t*)cnt1, rk1, rj1, rv1);
-    // pass 2: fine buckets inside each coarse bucket
-    hipLaunchKernelGGL(sp_count2_kernel, dim3(sp_xcd_grid(L.nch2max)), dim3(kSpBlock), 0, st, (const int32_t*)rk1,
-                       L.s0, L.nc, L.nch2max,
-                       (const int32_t*)cstart, (const int32_t*)nch2, (const int32_t*)chb2, cnt2);
-    hipLaunchKernelGGL(sp_tile_sum_kernel, dim3((unsigned)L.nt2), dim3(1024), 0, st, cnt2, L.n2, tsum2);
-    hipLaunchKernelGGL(sp_tile_scan_kernel, dim3((unsigned)L.nt2), dim3(1024), 0, st, cnt2, L.n2, (const int32_t*)tsum2,
-                       (int32_t*)nullptr);
-    const size_t lds2 = sp_stage_bytes(kSpFine, sizeof(T));
-    hipLaunchKernelGGL(sp_scatter2_kernel<T>, dim3(sp_xcd_grid(L.nch2max)), dim3(kSpBlock), lds2, st,
-                       (const int32_t*)rk1, (const int32_t*)rj1, (const T*)rv1, L.s0, L.nc, L.nch2max,
-                       (const int32_t*)cstart, (const int32_t*)nch2,
-                       (const int32_t*)chb2, (const int32_t*)cnt2, rk, rj, rv);
-    hipLaunchKernelGGL(sp_wstart_kernel, dim3(flat_grid(L.nw + 1, 256, 1)), dim3(256), 0, st, L.nc,
-                       (const int32_t*)cstart, (const int32_t*)nch2, (const int32_t*)chb2, (const int32_t*)cnt2, wstart);
+    const dim3 g1(sp_xcd_grid(L.nch1)), b1(kSpBlock);
+    if (L.one) {
+        hipLaunchKernelGGL((sp_scatter1_kernel<T, true>), g1, b1, lds1, st, is, vs, m, n, L.s1, L.nc, L.nch1,
+                           (const int32_t*)cnt1, rk, rj, rv, (const int32_t*)total, wstart);
+    } else {
+        hipLaunchKernelGGL(sp_seg_kernel, dim3(1), dim3(1024), 0, st, (const int32_t*)cnt1, L.nch1, L.nc,
+                           (const int32_t*)total, cstart, nch2, chb2);
+        hipLaunchKernelGGL((sp_scatter1_kernel<T, false>), g1, b1, lds1, st, is, vs, m, n, L.s1, L.nc, L.nch1,
+                           (const int32_t*)cnt1, rk1, rj1, rv1, (const int32_t*)total, wstart);
+        // pass 2: fine buckets inside each coarse bucket
+        hipLaunchKernelGGL(sp_count2_kernel, dim3(sp_xcd_grid(L.nch2max)), b1, 0, st, (const int32_t*)rk1, L.s0, L.nc,
+                           L.nch2max, (const int32_t*)cstart, (const int32_t*)nch2, (const int32_t*)chb2, cnt2);
+        scan_counts(cnt2, L.n2, L.nt2, tsum2, nullptr);
+        const size_t lds2 = sp_stage_bytes(kSpFine, sizeof(T));
+        hipLaunchKernelGGL(sp_scatter2_kernel<T>, dim3(sp_xcd_grid(L.nch2max)), b1, lds2, st, (const int32_t*)rk1,
+                           (const int32_t*)rj1, (const T*)rv1, L.s0, L.nc, L.nch2max, (const int32_t*)cstart,
+                           (const int32_t*)nch2, (const int32_t*)chb2, (const int32_t*)cnt2, rk, rj, rv);
+        hipLaunchKernelGGL(sp_wstart_kernel, dim3(flat_grid(L.nw + 1, 256, 1)), dim3(256), 0, st, L.nc,
+                           (const int32_t*)cstart, (const int32_t*)nch2, (const int32_t*)chb2, (const int32_t*)cnt2,
+                           wstart);
+    }
     // the window sweep
     const int vec = aligned(xs, 16) ? 1 : 0;
     hipLaunchKernelGGL(sp_apply_fwd_kernel<T>, dim3((unsigned)L.nw), dim3(kSpFwdBlock), 0, st, xs, n, L.s0, vec,

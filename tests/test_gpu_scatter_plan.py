@@ -125,3 +125,36 @@ def test_scatter_planned_full_size(ops, orc):
     _, rvb = orc.scatter_vjp(is_[sel], yb)
     assert np.array_equal(host(v2)[sel], rvb.astype(np.float32))
     assert np.array_equal(host(x2), xs)
+
+
+# Either side of the windows that one bucketing pass serves (8,192 FP32 or 4,096
+# FP64 elements each): a cut last window, a count scan of one tile and of more,
+# dense windows, targets out of range, with and without accumulate.
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("windows,m", [(1, 4000), (3, 5000), (1024, 4097), (1024, 20001), (1025, 20001)])
+def test_scatter_planned_one_pass_edges(ops, orc, dtype, windows, m):
+    w = 8192 if dtype == "f32" else 4096
+    n = windows * w - 5
+    xs, is_, vs, yb = workloads.scatter(n, m, dtype, seed=windows)
+    if windows > 3:
+        g = workloads.rng(5)  # the last window and a half full of updates
+        is_ = g.permutation(np.concatenate([is_[is_ < n - 3 * w // 2], np.arange(n - 3 * w // 2, n)])).astype(np.int32)
+        vs = g.standard_normal(is_.size).astype(xs.dtype)
+    is_[::7] = -1
+    is_[3::11] = n + 2
+    m, x = is_.size, dev(xs)
+    ok = (is_ >= 0) & (is_ < n)
+    plan = ops.scatter_planned_(x, dev(is_), dev(vs))
+    rys, _ = orc.scatter(xs, is_[ok], vs[ok])
+    assert np.array_equal(host(x), rys)
+    rxb, rvb = orc.scatter_vjp(is_[ok], yb)
+    full = np.zeros(m, dtype=xs.dtype)
+    full[ok] = rvb
+    base = np.ones(m, dtype=xs.dtype)
+    acc = dev(base)
+    ops.scatter_planned_vjp_(dev(yb), m, plan, vs_bar=acc, accumulate=True)
+    assert np.array_equal(host(acc), base + full)
+    ybar = dev(yb)
+    vbar = ops.scatter_planned_vjp_(ybar, m, plan, ys=x)
+    assert np.array_equal(host(ybar), rxb) and np.array_equal(host(vbar), full)
+    assert np.array_equal(host(x), xs)
