@@ -338,8 +338,14 @@ __global__ __launch_bounds__(kScanBlock) void linrec_vjp_tile_agg_kernel(const T
 // group_prefix_kernel of prims.h.
 
 // ------------------------------------------------------------------ host
-// Inputs of more tiles than this take the three-pass form.
-constexpr int64_t kThreePassTiles = 4096;
+// Inputs of more tiles than this take the three-pass form; below it the four
+// more launches of either sweep cost more than the lookback.  Scan and VJP in
+// one pass and in three, us:
+//   FP64 (2,048 elements a tile): 342 tiles 33.8, 34.8; 489 41, 38; 649 57, 44;
+//   1,221 94, 62; 3,907 248, 176
+//   FP32 (4,096): 325 tiles 29.8, 32.0; 440 35.5, 37.5; 538 45.3, 44.0; 611 48,
+//   44; 1,954 109, 89; 3,907 201, 181
+constexpr int64_t kThreePassTiles = 448;
 constexpr size_t kAggSlot = 32;  // bytes per tile for an aggregate or a prefix (either operator)
 
 // [header | tile states | group states | tile aggregates | tile prefixes |

@@ -75,6 +75,21 @@ def test_linrec_three_pass_form(ops, orc, dtype, n):
     assert rel_l2([host(ab2), host(bb2)], [ra, rb]) <= tol(dtype)
 
 
+# Either side of the tiles where the three-pass form starts, and of the tiles
+# that one block scans between its passes.
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("tiles", [447, 448, 449, 2048, 2049])
+def test_linrec_three_pass_line(ops, orc, dtype, tiles):
+    n = tiles * (4096 if dtype == "f32" else 2048) - (tiles % 2)
+    a, b, ya, yb = workloads.linrec(n, dtype, seed=tiles)
+    A, B, ck = ops.linrec_scan(dev(a), dev(b))
+    assert rel_l2([host(A), host(B)], orc.linrec_scan(a, b)) <= tol(dtype)
+    ra, rb = orc.linrec_scan_vjp(a, b, ya, yb)
+    for c in (ck, None):
+        ab, bb = ops.linrec_scan_vjp(dev(a), dev(b), dev(ya), dev(yb), ckpt=c)
+        assert rel_l2([host(ab), host(bb)], [ra, rb]) <= tol(dtype)
+
+
 def test_linrec_checkpoint_values(ops, orc):
     n = 5000
     a, b, _, _ = workloads.linrec(n, "f64", seed=1)
