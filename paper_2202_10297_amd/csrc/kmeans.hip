@@ -30,6 +30,7 @@ constexpr int kKmPts = 256;          // points per distance block, one per lane
 constexpr int kKmSumBlocks = 1024;   // fixed partition of the objective's sum
 constexpr int kKmSmallK = 16;        // register accumulators in the gradient up to this K
 constexpr int kKmChunkMax = 4096;
+constexpr int64_t kKmFill = 256;     // blocks that the distances want
 constexpr int kKmNearPts = 128;      // points per block of the bounded search
 constexpr int kKmNearSlices = 16;    // at most this many ranges of centres in it
 
@@ -627,6 +628,9 @@ __global__ __launch_bounds__(256) void km_finish_kernel(int D, int K, int nchunk
         }
         if (lane != 0) return;
     } else {
+        // eight chunks' partials in flight (49 chunks: 14.9 us one after another,
+        // 6)
+#pragma unroll 8
         for (int c = 0; c < nchunk; ++c) {
             S += spart[(int64_t)c * KD + e];
             n += npart[(int64_t)c * K + k];
@@ -665,7 +669,12 @@ static bool km_near(int64_t N, int D, int K) {
 
 static KmPlan km_plan(int64_t N, int D, int K) {
     KmPlan p{};
+    // fewer centres a slice while the blocks (256 points and a slice each) do
+    // not fill the chip.  Objective and gradient, widest slices, these and twice
+    // the blocks, us: N = 3,117, D = 64, K = 19 48, 38, 38; N = 5,000, D = 256, K =
+    // 20 116, 82, 82; N = 30,000, D = 64, K = 50 60, 53, 53 (four times: 64).
     p.cps = km_cps(D, K);
+    while (p.cps > 4 && ceil_div(N, kKmPts) * ceil_div(K, p.cps) < kKmFill) p.cps = (p.cps + 1) / 2;
     p.cpsT = p.cps <= 4 ? 4 : (p.cps <= 8 ? 8 : (p.cps <= 16 ? 16 : 32));
     p.nslice = (int)ceil_div(K, p.cps);
     {

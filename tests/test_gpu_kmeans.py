@@ -155,3 +155,17 @@ def test_bounded_search_extreme_values(ops, orc):
         far[5] = 1e15
         _, ra = orc.kmeans_objective(X, far)
         assert np.array_equal(host(a), ra)
+
+
+# Few points: slices of fewer centres than the kernel's width, a last slice of
+# one, and chunk partials of eight and a remainder.
+@pytest.mark.parametrize("N,D,K", [(255, 16, 33), (3117, 64, 19), (2049, 128, 41), (16385, 24, 17), (65537, 8, 9)])
+def test_small_slices(ops, orc, N, D, K):
+    X, C = workloads.kmeans(N, D, K, "f32", seed=N)
+    C[K - 1] = C[1]  # equal centres in different slices: the lower one wins
+    f, a = ops.kmeans_objective(dev(X), dev(C))
+    rf, ra = orc.kmeans_objective(X, C)
+    assert np.array_equal(host(a), ra)
+    assert abs(host(f)[0] - rf) <= 1e-12 * max(1.0, rf)
+    cb, _ = ops.kmeans_vjp(dev(X), dev(C), a, f_bar=0.5)
+    assert rel_l2(host(cb), orc.kmeans_vjp(X, C, 0.5)) <= TOL_F32
