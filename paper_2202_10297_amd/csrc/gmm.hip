@@ -843,9 +843,12 @@ __device__ __forceinline__ bf16x8 twice(bf16x8 v) {
 // FP32 form, over at most 4,096 points against 32,768 here; accumulated in
 // place over 4,096 points q_bar's error was 1.4e-6 against 1.4e-7).  A 32-point
 // tile and component take 2,048 MFMA cycles and about as many of vector work
-// (forming and splitting v, squares, weights), which hardly overlap: a wave
-// waiting to issue an MFMA keeps the other wave's vector instructions from
-// issuing.  N = 10^6, D = 64, K = 200: 26.5 -> 13.0 ms.
+// (forming and splitting v, squares, weights).  A wave waiting to issue an MFMA
+// keeps the other wave's vector instructions from issuing, so each wave
+// interleaves the two itself: after every MFMA a short step of the vector work
+// that does not depend on it, held in place by a scheduling barrier (left to
+// itself the compiler groups them: 11.9 ms, now 11.2).  N = 10^6, D = 64, K =
+// 200: 26.5 -> 11.2 ms, 64% of it MFMA at the clock the card holds.
 template <int D, bool FROM_S>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void gmm_bwd_split_kernel(
     const float* __restrict__ X, int64_t N, int K, int64_t chunk, int nch, const bf16x8* __restrict__ Qs,
@@ -929,9 +932,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void g
         split_qx<D, TL>([&](int f, int pl) { return pl == 0 ? qa[f] : ql[w][f][pl - 1][lane]; },
                         [&](int tl, int s, int pl) { return xp[b][tl][s][pl][lane]; }, acc);
     };
-    // sqrt(w_i) of the tile at pb into the wave's row of sws.
-    auto weights = [&](int64_t pb) {
-        const double sv = FROM_S ? s_n : bk - 0.5 * split_square<D, TL>(acc, cs[w]);
+    // sqrt(w_i) of the lane's point of the tile at pb, for the wave's row of sws.
+    auto weight_of = [&](double sv, int64_t pb) {
         const double e = exp(0.5 * (sv - lse_n));
         const double swd = pb + wp < cend ? e : 0.0;
         wsum = fma(swd, swd, wsum);
@@ -950,7 +952,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void g
     fetch_lse(cbeg);
     __syncthreads();
     if (!FROM_S) form_z(0);
-    keep(weights(cbeg));
+    keep(weight_of(FROM_S ? s_n : bk - 0.5 * split_square<D, TL>(acc, cs[w]), cbeg));
     int b3 = 0;  // tile it is in buffer it % 3 of xt
     for (int it = 0; it < tiles; ++it) {
         const int64_t pb = cbeg + (int64_t)it * NP;
@@ -958,41 +960,133 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void g
         fetch_lse(pb + NP);
         __builtin_amdgcn_sched_barrier(0);
         // the next tile's z (past the last tile the buffers hold an old one,
-        // and its weights are zero), then this tile's v
-        if (!FROM_S) form_z((it + 1) & 1);
+        // and its weights are zero), and between its MFMAs this tile's v
         bf16x8 vf[NV][RT][3];
         float us[RT];
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) us[rt] = 0.f;
-#pragma unroll
-        for (int s = 0; s < NV; ++s) {
-            const int at = 16 * s + 8 * h;
+        // v in 32 short steps: a chunk (16 points' step s, row tile rt) has four
+        // pairs of two steps; the next chunk's operands are read half a chunk
+        // ahead
+        float xv[8], sq[8], xa[8], sa[8], ra, rb;
+        uint32_t o[3][4];
+        auto vread = [&](int c) {
+            const int at = 16 * (c / RT) + 8 * h, rt = c % RT;
             const float4 s0 = *reinterpret_cast<const float4*>(&sws[w][at]);
             const float4 s1 = *reinterpret_cast<const float4*>(&sws[w][at + 4]);
-            const float sq[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
+            const float4 x0 = *reinterpret_cast<const float4*>(&xt[b3][32 * rt + j][at]);
+            const float4 x1 = *reinterpret_cast<const float4*>(&xt[b3][32 * rt + j][at + 4]);
+            sa[0] = s0.x, sa[1] = s0.y, sa[2] = s0.z, sa[3] = s0.w;
+            sa[4] = s1.x, sa[5] = s1.y, sa[6] = s1.z, sa[7] = s1.w;
+            xa[0] = x0.x, xa[1] = x0.y, xa[2] = x0.z, xa[3] = x0.w;
+            xa[4] = x1.x, xa[5] = x1.y, xa[6] = x1.z, xa[7] = x1.w;
+        };
+        auto plane = [&](int q, int i) {
+            const bf16x2 v = {(__bf16)ra, (__bf16)rb};
+            const uint32_t u2 = __builtin_bit_cast(uint32_t, v);
+            o[q][i] = u2;
+            ra -= __builtin_bit_cast(float, u2 << 16);
+            rb -= __builtin_bit_cast(float, u2 & 0xffff0000u);
+        };
+        auto vstep = [&](int n) {
+            const int c = n >> 3, i = (n >> 1) & 3, rt = c % RT;
+            if ((n & 7) == 0)
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt) {
-                const float4 x0 = *reinterpret_cast<const float4*>(&xt[b3][32 * rt + j][at]);
-                const float4 x1 = *reinterpret_cast<const float4*>(&xt[b3][32 * rt + j][at + 4]);
-                const float xv[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
-                float v[8];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    v[i] = sq[i] * (xv[i] - mub[rt]);
-                    us[rt] = fmaf(sq[i], v[i], us[rt]);
-                }
-                split8(v, vf[s][rt]);
+                for (int e = 0; e < 8; ++e) xv[e] = xa[e], sq[e] = sa[e];
+            if ((n & 7) == 3 && c + 1 < NV * RT) vread(c + 1);
+            if ((n & 1) == 0) {
+                ra = sq[2 * i] * (xv[2 * i] - mub[rt]);
+                us[rt] = fmaf(sq[2 * i], ra, us[rt]);
+                rb = sq[2 * i + 1] * (xv[2 * i + 1] - mub[rt]);
+                us[rt] = fmaf(sq[2 * i + 1], rb, us[rt]);
+                plane(0, i);
+            } else {
+                plane(1, i);
+                plane(2, i);
             }
+            if ((n & 7) == 7)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    const u32x4 v = {o[q][0], o[q][1], o[q][2], o[q][3]};
+                    vf[c / RT][rt][q] = __builtin_bit_cast(bf16x8, v);
+                }
+        };
+        constexpr int VS = 8 * NV * RT;
+        static_assert(VS == 32, "four chunks of v");
+        int vn = 0;
+        vread(0);
+        if (!FROM_S) {
+            constexpr int NM = 6 * C::F * TL;
+            const int zb = (it + 1) & 1;
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int tl = 0; tl < TL; ++tl)
+#pragma unroll
+                    for (int t = 0; t < 16; ++t) acc[rt][tl][t] = 0.f;
+            bf16x8 qz[2][RT][3], xz[2][TL][3];
+            auto zread = [&](int s, int pl) {
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+                    if (s < 2 * (rt + 1))
+                        qz[s & 1][rt][pl] =
+                            pl == 0 ? qa[sidx(rt, s)] : ql[w][sidx(rt, s)][pl > 0 ? pl - 1 : 0][lane];
+#pragma unroll
+                for (int tl = 0; tl < TL; ++tl) xz[s & 1][tl][pl] = xp[zb][tl][s][pl][lane];
+            };
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl) zread(0, pl);
+            __builtin_amdgcn_sched_barrier(0);
+            int mn = 0;
+#pragma unroll
+            for (int s = 0; s < C::KS; ++s)
+#pragma unroll
+                for (int q = 0; q < 6; ++q) {
+                    if (q >= 2 && q < 5 && s + 1 < C::KS) zread(s + 1, 4 - q);
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                        for (int tl = 0; tl < TL; ++tl)
+                            if (s < 2 * (rt + 1)) {
+                                acc[rt][tl] =
+                                    mfma16(qz[s & 1][rt][kTermA[q]], xz[s & 1][tl][kTermB[q]], acc[rt][tl]);
+                                ++mn;
+#pragma unroll
+                                for (int e = 0; e < 2; ++e)
+                                    if (vn * NM < mn * VS) vstep(vn++);
+                                __builtin_amdgcn_sched_barrier(0);
+                            }
+                }
         }
+#pragma unroll
+        for (int e = 0; e < VS; ++e)
+            if (FROM_S) vstep(e);
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) u[rt] += us[rt];
         __builtin_amdgcn_sched_barrier(0);
-        // its contraction, then the next tile's weights
+        // its contraction, between its MFMAs the next tile's |z|^2; then its weights
         f32x16 tmp[NGT];
 #pragma unroll
         for (int g = 0; g < NGT; ++g)
 #pragma unroll
             for (int t = 0; t < 16; ++t) tmp[g][t] = 0.f;
+        // |z|^2 in steps of two rows (split_square's order)
+        double nrm[2] = {0.0, 0.0};
+        float4 cq = {0.f, 0.f, 0.f, 0.f};
+        auto nstep = [&](int n) {
+            const int rt = n / 8, t4 = (n / 2) & 3, i0 = 2 * (n & 1);
+            if (i0 == 0) cq = *reinterpret_cast<const float4*>(&cs[w][32 * rt + 8 * t4 + 4 * h]);
+            const double cv[2] = {i0 == 0 ? cq.x : cq.z, i0 == 0 ? cq.y : cq.w};
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int tl = 0; tl < TL; ++tl) {
+                    const double z = (double)acc[rt][tl][4 * t4 + i0 + i] - cv[i];
+                    nrm[tl] = fma(z, z, nrm[tl]);
+                }
+        };
+        constexpr int NS = 8 * RT;
+        int nn = 0;
 #pragma unroll
         for (int s = 0; s < NV; ++s)
 #pragma unroll
@@ -1002,15 +1096,34 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void g
                 for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
                     for (int ct = 0; ct <= rt; ++ct, ++g) {
+                        bool did = true;
                         if (ct < rt)
                             tmp[g] = mfma16(vf[s][rt][kTermA[q]], vf[s][ct][kTermB[q]], tmp[g]);
                         else if (kTermA[q] == kTermB[q])
                             tmp[g] = mfma16(vf[s][rt][kTermA[q]], vf[s][rt][kTermB[q]], tmp[g]);
                         else if (kTermA[q] == 0)
                             tmp[g] = mfma16(vf[s][rt][0], twice(vf[s][rt][kTermB[q]]), tmp[g]);
+                        else
+                            did = false;
+                        if (!FROM_S && did && nn < NS) {
+                            nstep(nn++);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
                     }
             }
-        const double swd = weights(pb + NP);
+#pragma unroll
+        for (int e = 0; e < NS; ++e)
+            if (!FROM_S && e >= nn) nstep(e);
+        double sq2 = 0.0;
+        if (!FROM_S) {
+            if (TL == 1) {
+                sq2 = nrm[0] + __shfl_xor(nrm[0], 32, kWave);
+            } else {
+                const bool up = threadIdx.x & 32;
+                sq2 = (up ? nrm[1] : nrm[0]) + __shfl_xor(up ? nrm[0] : nrm[1], 32, kWave);
+            }
+        }
+        const double swd = weight_of(FROM_S ? s_n : bk - 0.5 * sq2, pb + NP);
 #pragma unroll
         for (int g = 0; g < NGT; ++g)
 #pragma unroll
