@@ -1373,10 +1373,14 @@ static HistPlan hist_plan(int op, int64_t n, int64_t m, bool counts) {
 //   FP64 max (a second sweep for the winners), Zipf, m = 20,000: 1.6 10^6 61,
 //   71; 3.2 10^6 91, 71
 // A product's updates are compare-and-swap loops, so its line is lower (FP32,
-// n = 2^17, m = 30,000: 72, 40).
+// n = 2^17, m = 30,000: 72, 40).  An FP64 record takes 12 bytes: past 2^25 of
+// them the scratch would be half a gigabyte and more for calls whose scratch has
+// always been a few words per bin, so those keep the cache (2^25 into 10^6 bins:
+// 646 us here with 460 MB).
 static bool use_partition(int op, bool f32, int64_t n, int64_t m, bool counts) {
     const int full_slots = (int)(kHistLds / slot_bytes(op, counts, false));
     if (m <= full_slots || ceil_div(m, kPartBins) > kPartMaxBuckets) return false;
+    if (!f32 && n > (int64_t)1 << 25) return false;
     if (op == PVJP_MUL) return n >= ((int64_t)1 << 17);
     if (m > 65536) return n >= ((int64_t)1 << 20);
     return n >= (f32 || op == PVJP_ADD ? (int64_t)3 << 19 : (int64_t)1 << 21);
@@ -1436,7 +1440,7 @@ struct PartLayout {
     size_t toff, D, Ploc, ctot, clast, bitems, istart, itile, rval, rhi, rbin, pacc, pcnt, paux, total;
 };
 
-static PartLayout part_layout(int64_t n, int64_t m, bool f32) {
+static PartLayout part_layout(int64_t n, int64_t m, bool f32, int64_t most = kPartSeg) {
     PartLayout L{};
     // 512 work items (two a CU) or more, of up to 2^16 records: a short input's
     // buckets would otherwise be one item each (n = 10^6, m = 100,000 Zipf,
@@ -1444,7 +1448,7 @@ static PartLayout part_layout(int64_t n, int64_t m, bool f32) {
     // long last wave (n = 2^26, m = 2^20, items of 2^17 and 2^16: max Zipf 565,
     // 548 us; + Zipf 716, 689; max uniform 540, 515; with 2^15 550, 686, 521).
     L.seg = (int)kPartSegMin;
-    while (L.seg < kPartSeg && (int64_t)L.seg * 512 < n) L.seg *= 2;
+    while (L.seg < most && (int64_t)L.seg * 512 < n) L.seg *= 2;
     L.nb = (int)ceil_div(m, kPartBins);
     L.ntiles = (int)ceil_div(n > 0 ? n : 1, kTile);
     L.nchunks = (int)ceil_div(L.ntiles, kColChunk);
@@ -1557,11 +1561,15 @@ bool hist_lae_partition_ok(pvjp_dtype dtype, int64_t m) {
     return dtype == PVJP_F32 && use_partition(PVJP_ADD, true, INT64_MAX, m, false);  // whatever the length
 }
 
-size_t hist_lae_partition_bytes(int64_t n, int64_t m) { return part_layout(n, m, true).total; }
+// Items of up to 2^17 records: the merge forms an exponential per item and bin
+// (n = 2^26 Zipf, m = 2^16: 0.63 ms, with 2^16 0.72; m = 2^20 0.86, 0.89).
+constexpr int64_t kLaeSeg = (int64_t)1 << 17;
+
+size_t hist_lae_partition_bytes(int64_t n, int64_t m) { return part_layout(n, m, true, kLaeSeg).total; }
 
 void hist_lae_partitioned(const int32_t* inds, const float* x, int64_t n, int32_t m, float* hs, char* ws,
                           hipStream_t st) {
-    const PartLayout L = part_layout(n, m, true);
+    const PartLayout L = part_layout(n, m, true, kLaeSeg);
     part_sort<float, PVJP_ADD>(inds, x, n, m, L, ws, st);
     double* psum = reinterpret_cast<double*>(ws + L.pacc);
     uint32_t* pmax = reinterpret_cast<uint32_t*>(ws + L.pcnt);
