@@ -492,8 +492,8 @@ size_t pvjp_seg_ws_bytes(int64_t total, int64_t nseg, int tile_elems);
  * only if ws was zero-filled before. */
 pvjp_status pvjp_seg_prepare(const int64_t* host_offsets, int64_t nseg, int tile_elems, void* ws,
                              size_t ws_bytes, void* stream);
-/* Every segment's linear-recurrence scan (Sec. 5.2) in one decoupled-lookback
- * launch with the segmented operator; A, B (nullable together) and ckpt
+/* Every segment's linear-recurrence scan (Sec. 5.2): blocks walk chains of tiles
+ * with the segmented operator; A, B (nullable together) and ckpt
  * (nullable; 2 * pvjp_linrec_ckpt_len(total) elements: the state before each
  * global multiple of the checkpoint interval) as for pvjp_linrec_scan. */
 pvjp_status pvjp_seg_linrec_scan(pvjp_dtype dtype, const void* a, const void* b, int64_t total,
