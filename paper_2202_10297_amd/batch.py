@@ -6,9 +6,9 @@ A ``SegPlan`` fixes the segment table (uploaded once into its workspace by
 ``pvjp_seg_prepare``).  ``SegPlan.scan`` runs the segmented primal (and
 writes the checkpoint the return sweep recomputes from); ``SegPlan.vjp`` runs
 ``pvjp_seg_batch_vjp``; ``SegPlan.capture`` records that call into a graph
-whose ``replay`` re-launches it without host overhead.  The library's
-lookback state resets itself at the end of every launch, so replays need no
-memset nodes.
+whose ``replay`` re-launches it without host overhead.  The counter
+of the library's work queues returns to rest at the end of every launch, so
+replays need no memset nodes.
 """
 from __future__ import annotations
 

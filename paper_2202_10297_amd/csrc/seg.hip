@@ -147,36 +147,6 @@ __device__ __forceinline__ uint32_t run_heads(uint32_t* bits, const int32_t* __r
 // Waits for every load (and store) in flight.
 __device__ __forceinline__ void seg_wait_memory() { __builtin_amdgcn_s_waitcnt(0x0f70); }  // vmcnt(0)
 
-// Striped loads, and striped stores of blocked items, of a tile of `cnt`
-// elements.  Only the last tile is partial: the others load and store without
-// a branch per element.
-template <class T, int IPT>
-__device__ __forceinline__ void seg_load(const T* __restrict__ src, int cnt, T (&st)[IPT], T fill) {
-    if (cnt == kSegBlock * IPT) {
-#pragma unroll
-        for (int k = 0; k < IPT; ++k) st[k] = src[k * kSegBlock + (int)threadIdx.x];
-    } else {
-        load_striped<T, kSegBlock, IPT>(src, cnt, st, fill);
-    }
-}
-
-template <class T, int IPT, bool ADD>
-__device__ __forceinline__ void seg_store(T* __restrict__ dst, int cnt, const T (&items)[IPT], T* lds) {
-    if (ADD || cnt != kSegBlock * IPT) {
-        store_blocked<T, kSegBlock, IPT, ADD>(dst, cnt, items, lds);
-        return;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < IPT; ++j) lds[lds_pad<T>((int)threadIdx.x * IPT + j)] = items[j];
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < IPT; ++k) {
-        const int i = k * kSegBlock + (int)threadIdx.x;
-        dst[i] = lds[lds_pad<T>(i)];
-    }
-}
-
 // The carry a walk entry starts from, besides a tile's aggregate: the block
 // combines the folds before it (valid in every thread).
 template <class Op>
@@ -201,8 +171,8 @@ struct SegFwdIn {  // a tile's inputs, striped over the block
         constexpr int TS = kSegBlock * IPT;
         const int64_t base = tile * TS;
         const int cnt = (int)((total - base) < TS ? (total - base) : TS);
-        seg_load<T, IPT>(pa + base, cnt, a, T(1));
-        seg_load<T, IPT>(pb + base, cnt, b, T(0));
+        load_striped<T, kSegBlock, IPT>(pa + base, cnt, a, T(1));
+        load_striped<T, kSegBlock, IPT>(pb + base, cnt, b, T(0));
     }
 };
 
@@ -325,8 +295,8 @@ __global__ __launch_bounds__(kSegBlock) void seg_linrec_fwd_kernel(
                     ra[j] = run.a;
                     rb[j] = run.b;
                 }
-                seg_store<T, IPT, false>(A + base, cnt, ra, lds);
-                seg_store<T, IPT, false>(B + base, cnt, rb, lds);
+                store_blocked<T, kSegBlock, IPT, false>(A + base, cnt, ra, lds);
+                store_blocked<T, kSegBlock, IPT, false>(B + base, cnt, rb, lds);
             }
             carry = Op::comb(carry, tot);
             __syncthreads();
@@ -345,10 +315,10 @@ struct SegVjpIn {  // a tile's inputs, striped over the block, and a's first ele
         constexpr int TS = kSegBlock * IPT;
         const int64_t base = tile * TS;
         const int cnt = (int)((total - base) < TS ? (total - base) : TS);
-        seg_load<T, IPT>(pa + base, cnt, a, T(1));
-        if constexpr (B) seg_load<T, IPT>(pb + base, cnt, b, T(0));
-        seg_load<T, IPT>(pya + base, cnt, ya, T(0));
-        seg_load<T, IPT>(pyb + base, cnt, yb, T(0));
+        load_striped<T, kSegBlock, IPT>(pa + base, cnt, a, T(1));
+        if constexpr (B) load_striped<T, kSegBlock, IPT>(pb + base, cnt, b, T(0));
+        load_striped<T, kSegBlock, IPT>(pya + base, cnt, ya, T(0));
+        load_striped<T, kSegBlock, IPT>(pyb + base, cnt, yb, T(0));
         after = ((int)threadIdx.x == kSegBlock - 1 && base + TS < total) ? pa[base + TS] : T(1);
     }
     // a_i and a_{i+1} of the thread's run
@@ -436,8 +406,8 @@ __device__ __forceinline__ typename LinO<T>::S seg_scan_vjp_tile(const T* __rest
         rb[j] = run.dB;
     }
     seg_wait_memory();
-    seg_store<T, IPT, ACC>(abar + base, cnt, ra, lds);
-    seg_store<T, IPT, ACC>(bbar + base, cnt, rb, lds);
+    store_blocked<T, kSegBlock, IPT, ACC>(abar + base, cnt, ra, lds);
+    store_blocked<T, kSegBlock, IPT, ACC>(bbar + base, cnt, rb, lds);
     return L::comb(carry, tot);
 }
 
@@ -462,7 +432,7 @@ __device__ __forceinline__ void seg_sum_vjp_tile(int64_t total, const int32_t* _
         seg += (int)((heads >> j) & 1u);
         out[j] = (first + j < cnt) ? ybar[seg] : T(0);
     }
-    seg_store<T, IPT, ACC>(xbar + base, cnt, out, lds);
+    store_blocked<T, kSegBlock, IPT, ACC>(xbar + base, cnt, out, lds);
 }
 
 // The lin_o aggregate of one tile (c_i = a_{i+1}, 0 at segment ends; d_i =
