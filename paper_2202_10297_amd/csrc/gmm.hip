@@ -237,10 +237,12 @@ struct GmmHdr {
 
 // ------------------------------------------------------------------ forward
 // Online log-sum-exp step: one exponential whichever side is larger (a branch
-// per side runs both when the lanes disagree).
+// per side runs both when the lanes disagree).  A component of weight zero (sv
+// = -inf) adds nothing, also where it comes first in its range (m = -inf still,
+// and sv - m is no number).
 __device__ __forceinline__ void lse_step(double sv, double& m, double& ssum) {
     const bool up = sv > m;
-    const double e = exp(up ? m - sv : sv - m);
+    const double e = sv == -INFINITY ? 0.0 : exp(up ? m - sv : sv - m);
     ssum = up ? ssum * e + 1.0 : ssum + e;
     m = up ? sv : m;
 }
@@ -406,7 +408,8 @@ __global__ __launch_bounds__(256) void gmm_lse_merge_kernel(int64_t N, int ny, c
     const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
     double l_i = 0.0;
     if (p < N) {
-        // the maximum first: the exponentials are then independent
+        // the maximum first: the exponentials are then independent.  A range of
+        // weights zero has the sum 0 (and its maximum, -inf, gives exp(-inf) = 0).
         double m = -INFINITY, s = 0.0;
 #pragma unroll 8
         for (int y = 0; y < ny; ++y) m = fmax(m, msum[(int64_t)y * N + p].x);

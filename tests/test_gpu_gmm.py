@@ -196,3 +196,61 @@ def test_gmm_full_size_sampled(ops, orc):
     gs = [host(t) for t in ops.gmm_vjp(Xd, *P, lse=lse2, s=sck)]
     for name, a, b in zip(["alpha", "mu", "q", "l"], g, gs):
         assert rel_l2(b, a) <= TOL_F32, name
+
+
+def _q_of(q, l, D):
+    Q = torch.diag_embed(torch.exp(q))
+    r, c = np.tril_indices(D, -1)  # row-major below the diagonal: the packing of l
+    Q[:, r, c] = l
+    return Q
+
+
+def _exact(X, alpha, mu, q, l, comps, ell_bar=1.0):
+    """(loglik, LSE_i, the adjoints of the components `comps`) in FP64 torch."""
+    X, alpha, mu, q, l = [dev(a).double() for a in (X, alpha, mu, q, l)]
+    N, D = X.shape
+    Q = _q_of(q, l, D)
+
+    def z(k):
+        return (X - mu[k]) @ Q[k].T.contiguous()
+
+    s = torch.stack([alpha[k] + q[k].sum() - 0.5 * (z(k) ** 2).sum(1) for k in range(alpha.numel())])
+    lse = torch.logsumexp(s, 0)
+    lse_a = torch.logsumexp(alpha, 0)
+    ll = lse.sum() - N * lse_a - 0.5 * N * D * np.log(2 * np.pi)
+    r, c = np.tril_indices(D, -1)
+    out = [[], [], [], []]
+    for k in comps:
+        w = ell_bar * torch.exp(s[k] - lse)
+        zk, y = z(k), X - mu[k]
+        G = (w[:, None] * zk).T.contiguous() @ y
+        out[0].append(w.sum() - N * ell_bar * torch.exp(alpha[k] - lse_a))
+        out[1].append(Q[k].T @ (w[:, None] * zk).sum(0))
+        out[2].append(w.sum() - torch.exp(q[k]) * torch.diagonal(G))
+        out[3].append(-G[r, c])
+    return host(ll), host(lse), [host(torch.stack(o)) for o in out]
+
+
+@pytest.mark.parametrize("N,D,K", [(127, 32, 50), (10007, 32, 50), (3001, 64, 21), (131073, 32, 50),
+                                   (140001, 64, 41)])
+@pytest.mark.parametrize("where", ["first", "starts", "inside", "range", "all_but_one"])
+def test_gmm_components_of_weight_zero(ops, N, D, K, where):
+    # alpha = -inf at k = 0, at the starts of the ranges that the objective
+    # splits the components into (multiples of four, two in D = 64, and of the
+    # long form's 16 or more), inside one and over whole ones: such components
+    # add nothing, and the others' results are finite.
+    X, alpha, mu, q, l = workloads.gmm(N, D, K, seed=N + K)
+    off = {"first": [0], "starts": list(range(4, K, 4)), "inside": [1, 6, K - 1], "range": list(range(4, 12)) +
+           list(range(K // 2, K)), "all_but_one": [k for k in range(K) if k != K // 3]}[where]
+    alpha[off] = -np.inf
+    comps = sorted({0, 1, 4, 5, K // 3, K // 2, K - 1})
+    rll, rlse, ref = _exact(X, alpha, mu, q, l, comps, -0.75)
+    Xd, P = dev(X), [dev(a) for a in (alpha, mu, q, l)]
+    ll, lse, sck = ops.gmm_objective_ckpt(Xd, *P)
+    assert abs(host(ll)[0] - rll) <= TOL_F32 * abs(rll)
+    assert rel_l2(host(lse), rlse) <= TOL_F32
+    for s in (None, sck):
+        got = [host(g) for g in ops.gmm_vjp(Xd, *P, lse=lse, s=s, ell_bar=-0.75)]
+        assert all(np.isfinite(g).all() for g in got)
+        for g, r in zip(got, ref):
+            assert rel_l2(g[comps], r) <= TOL_F32
