@@ -142,8 +142,10 @@ __global__ __launch_bounds__(256) void km_dist_kernel(const float* __restrict__ 
 // x and c are taken relative to the first centre (a common offset of the data
 // would only widen the bound).  Then
 // |x - c|^2 - |x|^2 = |c|^2 - 2 x.c, with x.c as FP32 sums of bf16 products:
-// x = h + m + r, |r| <= 2^-18 |x|, and the terms hh, hm, mh, so each of the D
-// products is off by less than 3.2 2^-18 of it, and the 3 D additions (a step
+// x = h + m + r, each part rounded to nearest in 8 bits, so |m| <= 2^-8 |x| and
+// |r| <= 2^-17 |x|.  Of a product the terms hh, hm, mh are taken; those left out
+// reach 2^-16 + 2 2^-17 = 8 2^-18 of it (x = c = 1.0039139: 7.95), so each of the
+// D products is off by less than 8.1 2^-18 of it, and the 3 D additions (a step
 // of the matrix unit may truncate: 2^-23 each) by less than 4 (D + 16) 2^-23
 // of sum |x_d c_d| <= |x| |c|.  With beta the sum of both, the FP32 value g of
 // centre k is within
@@ -268,7 +270,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     }
     x2 += __shfl_xor(x2, 32, kWave);
     x2 *= 1.001f;
-    constexpr float kBeta = 3.2f * 0x1p-18f + 4.f * (16.f * KS + 16.f) * 0x1p-23f;
+    constexpr float kBeta = 8.1f * 0x1p-18f + 4.f * (16.f * KS + 16.f) * 0x1p-23f;
     const float ex = 2.f * kBeta * sqrtf(x2);
     put(0);
     float u = INFINITY, m1 = INFINITY, m2 = INFINITY, m3 = INFINITY;

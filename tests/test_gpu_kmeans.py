@@ -169,3 +169,22 @@ def test_small_slices(ops, orc, N, D, K):
     assert abs(host(f)[0] - rf) <= 1e-12 * max(1.0, rf)
     cb, _ = ops.kmeans_vjp(dev(X), dev(C), a, f_bar=0.5)
     assert rel_l2(host(cb), orc.kmeans_vjp(X, C, 0.5)) <= TOL_F32
+
+
+@pytest.mark.parametrize("N,D,K", [(270000, 16, 64), (140000, 32, 64), (70000, 64, 64)])
+def test_bounded_search_worst_products(ops, orc, N, D, K):
+    # relative to the first centre (zero) every coordinate is near 1 + 2^-8 times
+    # a power of two, where a bf16 product leaves out the most, all of one sign;
+    # the centres differ by a few units in the last place
+    g = workloads.rng(D)
+
+    def rows(n):
+        s = 1.0 + 2.0 ** -8 + g.integers(-64, 65, (n, D)) * 2.0 ** -23
+        return (s * 2.0 ** g.integers(-1, 2, (1, D))).astype(np.float32)
+
+    X, C = rows(N), rows(K)
+    C[0] = 0.0
+    f, a = ops.kmeans_objective(dev(X), dev(C))
+    rf, ra = orc.kmeans_objective(X, C)
+    assert np.array_equal(host(a), ra)
+    assert abs(host(f)[0] - rf) <= 1e-12 * rf
