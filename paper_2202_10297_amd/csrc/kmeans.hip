@@ -33,6 +33,7 @@ constexpr int kKmChunkMax = 4096;
 constexpr int64_t kKmFill = 256;     // blocks that the distances want
 constexpr int kKmNearPts = 128;      // points per block of the bounded search
 constexpr int kKmNearSlices = 16;    // at most this many ranges of centres in it
+constexpr int kKmWhole = 16;         // entries formed whole by a block of decisions, at most
 
 // Centres per slice: as many as kKmSliceBytes of FP64 holds (>= 4), at most 32.
 static int km_cps(int D, int K) {
@@ -76,8 +77,9 @@ template <int CPS>
 __global__ __launch_bounds__(256) void km_dist_kernel(const float* __restrict__ X, int64_t N, int D,
                                                       const double* __restrict__ Cw, int K, int cps,
                                                       const int32_t* __restrict__ bad, int nbad,
+                                                      const int32_t* __restrict__ open,
                                                       double* __restrict__ bd, int32_t* __restrict__ bk) {
-    if (bad && !km_any(bad, nbad)) return;  // the bounded search has it
+    if (bad && !open[blockIdx.x] && !km_any(bad, nbad)) return;  // the bounded search has them
     constexpr int kStride = kKmChunkD + 1;  // odd row stride: lanes hit distinct banks
     __shared__ float xs[kKmPts * kStride];
     const int s = blockIdx.y;
@@ -156,7 +158,8 @@ __global__ __launch_bounds__(256) void km_dist_kernel(const float* __restrict__ 
 // whose g - e exceeds the smallest g + e is not the nearest.  Per point and
 // range of centres the three smallest g - e are kept, two with their centre;
 // then the FP64 chains of those within reach decide, of a whole range where
-// its third is within reach too.
+// its third is within reach too; points with many such ranges go to the FP64
+// search after all.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -235,7 +238,8 @@ struct KmNear {
 template <int KS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void km_near_kernel(
     const float* __restrict__ X, int64_t N, int D, const float* __restrict__ C, bool vec,
-    const bf16x8* __restrict__ Cf, const float* __restrict__ cst, int ntiles, int per, KmNear* __restrict__ out) {
+    const bf16x8* __restrict__ Cf, const float* __restrict__ cst, int ntiles, int per, KmNear* __restrict__ out,
+    int32_t* __restrict__ open) {
     constexpr int U = KS * 2 * 64;  // 16-byte units per tile
     constexpr int PER = U / 256;
     static_assert(U % 256 == 0, "a tile is whole rounds of the block");
@@ -245,6 +249,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     const int j = lane & 31, h = lane >> 5;
     const int64_t p = (int64_t)blockIdx.x * kKmNearPts + w * 32 + j;
     const int t0 = blockIdx.y * per, t1 = min(ntiles, t0 + per);
+    static_assert(kKmPts % kKmNearPts == 0, "a flag per block of the FP64 search");
+    if (blockIdx.y == 0 && t == 0) open[blockIdx.x / (kKmPts / kKmNearPts)] = 0;  // the decisions set it
     u32x4 nx[PER];
     float nk = 0.f;
     auto fetch = [&](int tile) {
@@ -317,7 +323,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     if (p >= N) return;
     const float e0 = fmaf(x2, 0x1p-38f, 0x1p-100f);
     KmNear r;
-    r.u = x2 < 1e36f ? u + e0 : NAN;  // NaN: every centre's chain is formed
+    r.u = x2 < 1e36f ? u + e0 : NAN;  // NaN: the FP64 search has the point
     r.m1 = m1 - e0, r.m2 = m2 - e0, r.m3 = m3 - e0;
     r.k1 = k1, r.k2 = k2;
     out[((int64_t)blockIdx.y * 2 + h) * N + p] = r;
@@ -346,22 +352,28 @@ __device__ __forceinline__ double km_chain(const float* __restrict__ x, const fl
 }
 
 // Four lanes per point: the centres within reach, their chains, the nearest
-// (the lowest of equal ones).  Where an entry's third is within reach too, or
-// the point's norm was beyond FP32, the block afterwards forms the chains of
-// all its centres together.  Centres that all agree to within the
-// bound send every point there, some three times slower than the FP64 search.
+// (the lowest of equal ones).  Where an entry's third is within reach too, a
+// wave afterwards forms the chains of all its centres.  With more than kKmWhole
+// such entries in a block (centres that all agree to within the bound, or in
+// tight groups far from the first one), or a point's norm beyond FP32, the
+// block leaves its points to the FP64 search that follows (the flag open of
+// their 256), which costs less.  Objective in all, with that way out, without it
+// and by the FP64 search alone, us: N = 10,000, D = 256, K = 1,024, equal
+// centres 278, 5,140, 226, 16 groups of 64 centres 282, 4,250, 228; N = 65,536,
+// D = 16, K = 256, equal centres 58, 319, 40 (the most that it costs).
 __global__ __launch_bounds__(256) void km_decide_kernel(const float* __restrict__ X, int64_t N, int D,
                                                         const float* __restrict__ C, int K, bool vec,
                                                         const KmNear* __restrict__ near, int nent, int per,
                                                         const int32_t* __restrict__ bad, int ntiles,
-                                                        double* __restrict__ bd, int32_t* __restrict__ bk) {
+                                                        int32_t* __restrict__ open, double* __restrict__ bd,
+                                                        int32_t* __restrict__ bk) {
     constexpr int kEnt = 2 * kKmNearSlices;
     constexpr int32_t kNone = 0x7fffffff;
     __shared__ int32_t list[64][2 * kEnt];   // single centres
-    __shared__ int32_t whole[64 * kEnt];     // point of the block * (kEnt + 1) + entry (kEnt: every centre)
+    __shared__ int32_t whole[kKmWhole];      // point of the block * kEnt + entry
+    __shared__ double wd[kKmWhole];          // and what they gave
+    __shared__ int32_t wk[kKmWhole];
     __shared__ int32_t cnt[64], nwhole;
-    __shared__ double sd[64], rd[4];
-    __shared__ int32_t sk[64], rk[4];
     if (km_any(bad, ntiles)) return;
     const int q = threadIdx.x & 3, pt = threadIdx.x >> 2;
     const int64_t p = (int64_t)blockIdx.x * 64 + pt;
@@ -380,12 +392,13 @@ __global__ __launch_bounds__(256) void km_decide_kernel(const float* __restrict_
         u = fminf(u, __shfl_xor(u, 2, kWave));
         all = __shfl((int)all, threadIdx.x & 60, kWave);  // entry 0 is lane 0's, and all entries agree
         if (all) {
-            if (q == 0) whole[atomicAdd(&nwhole, 1)] = pt * (kEnt + 1) + kEnt;
+            if (q == 0) atomicAdd(&nwhole, kKmWhole + 1);
         } else {
             for (int e = q; e < nent; e += 4) {
                 const KmNear r = near[(int64_t)e * N + p];
                 if (r.m3 <= u) {
-                    whole[atomicAdd(&nwhole, 1)] = pt * (kEnt + 1) + e;
+                    const int at = atomicAdd(&nwhole, 1);
+                    if (at < kKmWhole) whole[at] = pt * kEnt + e;
                 } else {
                     if (r.m1 <= u) list[pt][atomicAdd(&cnt[pt], 1)] = r.k1;
                     if (r.m2 <= u) list[pt][atomicAdd(&cnt[pt], 1)] = r.k2;
@@ -394,6 +407,10 @@ __global__ __launch_bounds__(256) void km_decide_kernel(const float* __restrict_
         }
     }
     __syncthreads();
+    if (nwhole > kKmWhole) {
+        if (threadIdx.x == 0) open[(int64_t)blockIdx.x * 64 / kKmPts] = 1;
+        return;
+    }
     double best = INFINITY;
     int32_t bestk = kNone;
     auto take = [&](double d, int32_t k) {
@@ -404,34 +421,32 @@ __global__ __launch_bounds__(256) void km_decide_kernel(const float* __restrict_
         const int32_t k = __shfl_xor(bestk, o, kWave);
         take(d, k);
     };
-    if (p < N)
-        for (int i = q; i < cnt[pt]; i += 4)
-            take(km_chain(X + p * D, C + (int64_t)list[pt][i] * D, D, vec), list[pt][i]);
-    meet(1);
-    meet(2);
-    if (q == 0) sd[pt] = best, sk[pt] = bestk;
-    __syncthreads();
-    for (int i = 0; i < nwhole; ++i) {
-        const int wpt = whole[i] / (kEnt + 1), e = whole[i] % (kEnt + 1);
-        const float* x = X + ((int64_t)blockIdx.x * 64 + wpt) * D;
-        const int first = e == kEnt ? 0 : (e >> 1) * per, last = e == kEnt ? ntiles : min(ntiles, first + per);
+    for (int i = threadIdx.x / kWave; i < nwhole; i += 256 / kWave) {
+        const int e = whole[i] % kEnt;
+        const float* x = X + ((int64_t)blockIdx.x * 64 + whole[i] / kEnt) * D;
+        const int first = (e >> 1) * per, last = min(ntiles, first + per);
         best = INFINITY, bestk = kNone;
-        for (int c = 32 * first + (int)threadIdx.x; c < min(K, 32 * last); c += 256)
-            if (e == kEnt || ((c >> 2) & 1) == (e & 1)) take(km_chain(x, C + (int64_t)c * D, D, vec), c);
+        // the entry's centres: those with bit 2 equal to e's bit 0, 64 in 128
+        for (int c0 = 32 * first; c0 < min(K, 32 * last); c0 += 2 * kWave) {
+            const int l = threadIdx.x & (kWave - 1);
+            const int c = c0 + ((l & ~3) << 1) + ((e & 1) << 2) + (l & 3);
+            if (c < min(K, 32 * last)) take(km_chain(x, C + (int64_t)c * D, D, vec), c);
+        }
 #pragma unroll
         for (int o = 1; o < kWave; o *= 2) meet(o);
-        if ((threadIdx.x & 63) == 0) rd[threadIdx.x >> 6] = best, rk[threadIdx.x >> 6] = bestk;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            best = sd[wpt], bestk = sk[wpt];
-            for (int w = 0; w < 4; ++w) take(rd[w], rk[w]);
-            // no distance compares: none is a number, and centre 0 keeps the point
-            if (bestk == kNone && e == kEnt) best = km_chain(x, C, D, vec), bestk = 0;
-            sd[wpt] = best, sk[wpt] = bestk;
-        }
-        __syncthreads();
+        if ((threadIdx.x & (kWave - 1)) == 0) wd[i] = best, wk[i] = bestk;
     }
-    if (q == 0 && p < N) bd[p] = sd[pt], bk[p] = sk[pt];
+    __syncthreads();
+    best = INFINITY, bestk = kNone;
+    if (p < N) {
+        for (int i = q; i < cnt[pt]; i += 4)
+            take(km_chain(X + p * D, C + (int64_t)list[pt][i] * D, D, vec), list[pt][i]);
+        for (int i = q; i < nwhole; i += 4)
+            if (whole[i] / kEnt == pt) take(wd[i], wk[i]);
+    }
+    meet(1);
+    meet(2);
+    if (q == 0 && p < N) bd[p] = best, bk[p] = bestk;
 }
 
 // Nearest centre over the slices in increasing order (strict <: ties keep
@@ -440,15 +455,16 @@ __global__ __launch_bounds__(256) void km_decide_kernel(const float* __restrict_
 // thread in r order and then over the block in a fixed tree.
 __global__ __launch_bounds__(256) void km_combine_kernel(const double* __restrict__ bd, const int32_t* __restrict__ bk,
                                                          int64_t N, int nslice, const int32_t* __restrict__ bad,
-                                                         int nbad, int32_t* __restrict__ assign,
-                                                         double* __restrict__ part) {
+                                                         int nbad, const int32_t* __restrict__ open,
+                                                         int32_t* __restrict__ assign, double* __restrict__ part) {
     __shared__ double sh[256];
-    if (bad && !km_any(bad, nbad)) nslice = 1;  // the bounded search's decisions
+    const bool decided = bad && !km_any(bad, nbad);  // by the bounded search, but for the open points
     double acc = 0.0;
     for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < N; p += (int64_t)gridDim.x * blockDim.x) {
         double best = bd[p];
         int32_t k = bk[p];
-        for (int s = 1; s < nslice; ++s) {
+        const int ns = decided && !open[p / kKmPts] ? 1 : nslice;
+        for (int s = 1; s < ns; ++s) {
             const double v = bd[(int64_t)s * N + p];
             if (v < best) best = v, k = bk[(int64_t)s * N + p];
         }
@@ -653,7 +669,7 @@ struct KmPlan {
     int cpb, nslices_acc;
     int64_t chunk, nchunk;
     int near_ks, near_tiles, near_per, near_slices;  // the bounded search (0: not used)
-    size_t cd, bd, bk, part, spart, npart, cf, cst, bad, near, total;
+    size_t cd, bd, bk, part, spart, npart, cf, cst, bad, open, near, total;
 };
 
 // The bounded search wants enough pairs to pay for its three more launches and
@@ -729,6 +745,7 @@ static KmPlan km_plan(int64_t N, int D, int K) {
         p.cf = take((size_t)p.near_tiles * p.near_ks * 2 * 1024);
         p.cst = take((size_t)p.near_tiles * 96 * 4);
         p.bad = take((size_t)p.near_tiles * 4);
+        p.open = take((size_t)ceil_div(N, kKmPts) * 4);
         p.near = take((size_t)p.near_slices * 2 * N * sizeof(KmNear));
     }
     p.total = o;
@@ -739,8 +756,8 @@ template <int CPS>
 static void launch_dist(const float* X, int64_t N, int D, int K, const KmPlan& p, char* ws, hipStream_t st) {
     const dim3 grid((unsigned)ceil_div(N, kKmPts), (unsigned)p.nslice);
     hipLaunchKernelGGL((km_dist_kernel<CPS>), grid, dim3(kKmPts), 0, st, X, N, D, (const double*)(ws + p.cd), K,
-                       p.cps, p.near_ks ? (const int32_t*)(ws + p.bad) : nullptr, p.near_tiles, (double*)(ws + p.bd),
-                       (int32_t*)(ws + p.bk));
+                       p.cps, p.near_ks ? (const int32_t*)(ws + p.bad) : nullptr, p.near_tiles,
+                       (const int32_t*)(ws + p.open), (double*)(ws + p.bd), (int32_t*)(ws + p.bk));
 }
 
 template <int KS>
@@ -750,13 +767,14 @@ static void launch_near(const float* X, int64_t N, int D, const float* C, int K,
     bf16x8* cf = reinterpret_cast<bf16x8*>(ws + p.cf);
     float* cst = reinterpret_cast<float*>(ws + p.cst);
     int32_t* bad = reinterpret_cast<int32_t*>(ws + p.bad);
+    int32_t* open = reinterpret_cast<int32_t*>(ws + p.open);
     KmNear* near = reinterpret_cast<KmNear*>(ws + p.near);
     hipLaunchKernelGGL(km_near_prep_kernel<KS>, dim3((unsigned)p.near_tiles), dim3(256), 0, st, C, K, D, vec, cf, cst,
                        bad);
     hipLaunchKernelGGL(km_near_kernel<KS>, dim3((unsigned)ceil_div(N, kKmNearPts), (unsigned)p.near_slices), dim3(256),
-                       0, st, X, N, D, C, vec, cf, cst, p.near_tiles, p.near_per, near);
+                       0, st, X, N, D, C, vec, cf, cst, p.near_tiles, p.near_per, near, open);
     hipLaunchKernelGGL(km_decide_kernel, dim3((unsigned)ceil_div(N, 64)), dim3(256), 0, st, X, N, D, C, K, vec, near,
-                       2 * p.near_slices, p.near_per, bad, p.near_tiles, (double*)(ws + p.bd), (int32_t*)(ws + p.bk));
+                       2 * p.near_slices, p.near_per, bad, p.near_tiles, open, (double*)(ws + p.bd), (int32_t*)(ws + p.bk));
 }
 
 template <int KM>
@@ -806,16 +824,16 @@ extern "C" pvjp_status pvjp_kmeans_objective(const float* X, int64_t N, int D, c
         else if (p.near_ks == 4) launch_near<4>(X, N, D, C, K, p, w, st);
         else if (p.near_ks == 8) launch_near<8>(X, N, D, C, K, p, w, st);
         else if (p.near_ks == 16) launch_near<16>(X, N, D, C, K, p, w, st);
-        // after a bounded search the FP64 one runs only if a centre's norm is
-        // beyond FP32 (or not a number): the kernel asks the flags
+        // after a bounded search the FP64 one takes the points left open, or all
+        // where a centre's norm is beyond FP32 (or not a number): it asks the flags
         if (p.cpsT == 4) launch_dist<4>(X, N, D, K, p, w, st);
         else if (p.cpsT == 8) launch_dist<8>(X, N, D, K, p, w, st);
         else if (p.cpsT == 16) launch_dist<16>(X, N, D, K, p, w, st);
         else launch_dist<32>(X, N, D, K, p, w, st);
         hipLaunchKernelGGL(km_combine_kernel, dim3((unsigned)p.sum_blocks), dim3(256), 0, st,
                            (const double*)(w + p.bd), (const int32_t*)(w + p.bk), N, p.nslice,
-                           p.near_ks ? (const int32_t*)(w + p.bad) : nullptr, p.near_tiles, assign,
-                           (double*)(w + p.part));
+                           p.near_ks ? (const int32_t*)(w + p.bad) : nullptr, p.near_tiles,
+                           (const int32_t*)(w + p.open), assign, (double*)(w + p.part));
     }
     hipLaunchKernelGGL(km_sum_kernel, dim3(1), dim3(1024), 0, st, (const double*)(w + p.part),
                        N > 0 ? p.sum_blocks : 0, f);

@@ -188,3 +188,33 @@ def test_bounded_search_worst_products(ops, orc, N, D, K):
     rf, ra = orc.kmeans_objective(X, C)
     assert np.array_equal(host(a), ra)
     assert abs(host(f)[0] - rf) <= 1e-12 * rf
+
+
+@pytest.mark.parametrize("N,D,K", [(9001, 256, 257), (70003, 35, 1000), (66001, 64, 65), (270001, 16, 64)])
+@pytest.mark.parametrize("kind", ["equal", "groups", "some"])
+def test_bounded_search_left_open(ops, orc, N, D, K, kind):
+    # too many centres within reach of the bound: blocks of points go to the FP64
+    # search, all of them or (some) a few beside blocks that are decided
+    g = workloads.rng(N + K)
+    X, C = workloads.kmeans(N, D, K, "f32", seed=N)
+    if kind == "equal":
+        C[:] = C[K // 2]
+    else:
+        far = (1000.0 * g.standard_normal((8, D))).astype(np.float32)
+        at = np.arange(N) if kind == "groups" else np.r_[300:340, 5000:5400, N - 30:N]
+        X[at] = far[g.integers(0, 8, at.size)] + g.standard_normal((at.size, D)).astype(np.float32)
+        k0 = 0 if kind == "groups" else K // 2
+        C[k0:] = far[g.integers(0, 8, K - k0)] + g.standard_normal((K - k0, D)).astype(np.float32)
+    C[K - 1] = C[1]
+    sub = np.unique(np.r_[0:600, 4900:5500, N - 300:N])  # the oracle's share
+    f, a = ops.kmeans_objective(dev(X), dev(C))
+    _, ra = orc.kmeans_objective(X[sub], C)
+    assert np.array_equal(host(a)[sub], ra)
+    # a second call on the same workspace, whose flags the first one set
+    X2, C2 = workloads.kmeans(N, D, K, "f32", seed=N + 1)
+    f2, a2 = ops.kmeans_objective(dev(X2), dev(C2))
+    _, ra2 = orc.kmeans_objective(X2[sub], C2)
+    assert np.array_equal(host(a2)[sub], ra2)
+    # f is the sum of the points' distances to their centres
+    d = torch.sum((dev(X2).double() - dev(C2).double()[a2.long()]) ** 2)
+    assert abs(host(f2)[0] - host(d)) <= 1e-12 * host(d)
