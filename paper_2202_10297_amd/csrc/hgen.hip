@@ -33,6 +33,7 @@
 //      the two steps back take 235).
 // Folds are formed in FP64 for FP32 and FP64 data alike.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "gops.h"
@@ -83,6 +84,12 @@ template <class T, int K>
 struct alignas(K * sizeof(T) < 16 ? K * sizeof(T) : 16) HgAdj {
     T c[K];
 };
+// Their type on the way back: the data's, or FP64 where they are added to x_bar,
+// so that the sum is rounded once (8 10^6 linear-recurrence elements in FP32, m
+// = 2^16: 366 us with FP32 adjoints, 443 with these).  The 2x2 product's four
+// keep the data's type: in FP64 they would not fit a record's buffer.
+template <class T, int K, bool ACC>
+using HgBack = typename std::conditional<ACC && K <= 2, double, T>::type;
 
 // Up to four component arrays of one dtype.
 template <class T>
@@ -506,12 +513,12 @@ __global__ __launch_bounds__(kHgGroup) void hg_group_carry_kernel(const char* __
 // Per tile: the forward scan with the tile's carry; the primal writes each
 // bin's fold at its last element.  The VJP also runs the reversed scan and
 // maps f over (ls, x, rs) with y_bar = hs_bar of the element's bin.
-template <class Op, class T, int W, bool VJP>
+template <class Op, class T, int W, bool VJP, class A>
 __global__ __launch_bounds__(kHgBlock) void hg_apply_kernel(const HgRec<W>* __restrict__ recs,
                                                             const int32_t* __restrict__ nvalid,
                                                             const char* __restrict__ carF,
                                                             const char* __restrict__ carR, HgOut<T> hs,
-                                                            HgIn<T> hs_bar, HgAdj<T, Op::K>* __restrict__ adj) {
+                                                            HgIn<T> hs_bar, HgAdj<A, Op::K>* __restrict__ adj) {
     constexpr int kIpt = hg_ipt(sizeof(HgRec<W>));
     using F = SegOf<Op>;
     using R = SegOf<Flip<Op>>;
@@ -571,9 +578,9 @@ __global__ __launch_bounds__(kHgBlock) void hg_apply_kernel(const HgRec<W>* __re
 #pragma unroll
         for (int k = 0; k < Op::K; ++k) yb[k] = (double)hs_bar.p[k][e[j].key];
         Op::vjp(ls[j], e[j].a, rs, la[j], yb, out);
-        HgAdj<T, Op::K> q;
+        HgAdj<A, Op::K> q;
 #pragma unroll
-        for (int k = 0; k < Op::K; ++k) q.c[k] = (T)out[k];
+        for (int k = 0; k < Op::K; ++k) q.c[k] = (A)out[k];
         adj[p0 + j] = q;
         xr = R::comb(xr, typename R::S{e[j].a, e[j].last ? 1u : 0u, 0u});
     }
@@ -593,17 +600,17 @@ __global__ __launch_bounds__(256) void hg_empty_kernel(int32_t m, HgOut<T> hs) {
 // One step back through a sort pass: dst[j] = src[pos[j]], j in the order the
 // pass read its records; a thread takes eight, the block a sub-chunk.
 constexpr int kHgBackU = kHgSub / 256;
-template <class T, int K>
+template <class A, int K>
 __global__ __launch_bounds__(256) void hg_back_kernel(const int32_t* __restrict__ pos,
                                                       const int32_t* __restrict__ nvalid,
-                                                      const HgAdj<T, K>* __restrict__ src,
-                                                      HgAdj<T, K>* __restrict__ dst) {
+                                                      const HgAdj<A, K>* __restrict__ src,
+                                                      HgAdj<A, K>* __restrict__ dst) {
     const int64_t nv = *nvalid;
     const int64_t at = (int64_t)blockIdx.x * kHgSub;
     if (at >= nv) return;
     const int64_t j0 = at + threadIdx.x;
     int p[kHgBackU];
-    HgAdj<T, K> v[kHgBackU];
+    HgAdj<A, K> v[kHgBackU];
 #pragma unroll
     for (int u = 0; u < kHgBackU; ++u) p[u] = pos[min(j0 + u * 256, nv - 1)];
 #pragma unroll
@@ -615,14 +622,14 @@ __global__ __launch_bounds__(256) void hg_back_kernel(const int32_t* __restrict_
 
 // The last step, through the first pass: x_bar in index order (0, or what was
 // there, where the index is out of range).
-template <class T, int K, bool ACC>
+template <class T, int K, bool ACC, class A>
 __global__ __launch_bounds__(256) void hg_back_write_kernel(const int32_t* __restrict__ pos, int64_t n,
                                                             const int32_t* __restrict__ nvalid,
-                                                            const HgAdj<T, K>* __restrict__ src, HgOut<T> x_bar) {
+                                                            const HgAdj<A, K>* __restrict__ src, HgOut<T> x_bar) {
     const int64_t j0 = (int64_t)blockIdx.x * kHgSub + threadIdx.x;
     const bool any = *nvalid > 0;
     int p[kHgBackU];
-    HgAdj<T, K> v[kHgBackU];
+    HgAdj<A, K> v[kHgBackU];
 #pragma unroll
     for (int u = 0; u < kHgBackU; ++u) p[u] = pos[min(j0 + u * 256, n - 1)];
 #pragma unroll
@@ -635,8 +642,8 @@ __global__ __launch_bounds__(256) void hg_back_write_kernel(const int32_t* __res
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             T* d = x_bar.p[k] + j;
-            const T a = p[u] < 0 ? T(0) : v[u].c[k];
-            *d = ACC ? (T)((double)*d + (double)a) : a;
+            const A a = p[u] < 0 ? A(0) : v[u].c[k];
+            *d = ACC ? (T)((double)*d + (double)a) : (T)a;
         }
     }
 }
@@ -658,9 +665,12 @@ struct HgLayout {
 // (a shorter one costs the count about as much to read).
 static bool hg_compact_keys(size_t rec_bytes) { return rec_bytes >= 32; }
 
-// rec_bytes: the size of one sort record.
-static HgLayout hg_layout(int64_t n, int64_t m, size_t rec_bytes) {
+// K components of es bytes each.  A record is 4 + K es bytes; its buffers also
+// take the adjoints (HgBack).
+static HgLayout hg_layout(int64_t n, int64_t m, int K, size_t es) {
     HgLayout L{};
+    const size_t rec_bytes = 4 + K * es;
+    const size_t buf_bytes = std::max(rec_bytes, K <= 2 ? K * sizeof(double) : 0);
     const int64_t nn = n > 0 ? n : 1;
     // A block's chunk: whole sub-chunks, 32,768 elements or, so that short
     // inputs fill the chip, as many as leave some 2,048 blocks (eight a CU;
@@ -686,8 +696,8 @@ static HgLayout hg_layout(int64_t n, int64_t m, size_t rec_bytes) {
     L.cntb = take((size_t)L.nblk * kHgDigits * 4);
     L.ctot = take((size_t)L.nchunks * kHgDigits * 4);
     L.nvalid = take(4);
-    L.recA = take((size_t)nn * rec_bytes);
-    L.recB = take((size_t)nn * rec_bytes);
+    L.recA = take((size_t)nn * buf_bytes);
+    L.recB = take((size_t)nn * buf_bytes);
     const bool ck = hg_compact_keys(rec_bytes);
     L.keyA = take(ck ? (size_t)nn * 4 : 0);
     L.keyB = take(ck ? (size_t)nn * 4 : 0);
@@ -771,7 +781,7 @@ template <class Op, class T>
 static void hg_primal(const int32_t* inds, int64_t n, int32_t m, const void* const* x, void* const* hs, char* w,
                       hipStream_t st) {
     constexpr int W = hg_words<T, Op::K>();
-    const HgLayout L = hg_layout(n, m, sizeof(HgRec<W>));
+    const HgLayout L = hg_layout(n, m, Op::K, sizeof(T));
     HgIn<T> xi{};
     HgOut<T> ho{};
     for (int k = 0; k < Op::K; ++k) {
@@ -781,17 +791,19 @@ static void hg_primal(const int32_t* inds, int64_t n, int32_t m, const void* con
     const HgRec<W>* recs = hg_prepare<Op, T, false>(inds, n, m, xi, w, L, st);
     int32_t* nvalid = reinterpret_cast<int32_t*>(w + L.nvalid);
     hipLaunchKernelGGL((hg_empty_kernel<Op, T>), dim3((unsigned)ceil_div(m, 256)), dim3(256), 0, st, m, ho);
-    hipLaunchKernelGGL((hg_apply_kernel<Op, T, W, false>), dim3((unsigned)L.ntiles), dim3(kHgBlock), 0, st, recs,
+    hipLaunchKernelGGL((hg_apply_kernel<Op, T, W, false, T>), dim3((unsigned)L.ntiles), dim3(kHgBlock), 0, st, recs,
                        nvalid, w + L.carF, w + L.carR, ho, HgIn<T>{}, (HgAdj<T, Op::K>*)nullptr);
 }
 
-template <class Op, class T>
-static void hg_vjp(const int32_t* inds, int64_t n, int32_t m, const void* const* x, const void* const* hs_bar,
-                   void* const* x_bar, bool acc, char* w, hipStream_t st) {
+template <class Op, class T, bool ACC>
+static void hg_vjp_t(const int32_t* inds, int64_t n, int32_t m, const void* const* x, const void* const* hs_bar,
+                     void* const* x_bar, char* w, hipStream_t st) {
     constexpr int W = hg_words<T, Op::K>();
-    using Adj = HgAdj<T, Op::K>;
-    static_assert(sizeof(Adj) <= sizeof(HgRec<W>), "adjoints fit a record buffer");
-    const HgLayout L = hg_layout(n, m, sizeof(HgRec<W>));
+    using A = HgBack<T, Op::K, ACC>;
+    using Adj = HgAdj<A, Op::K>;
+    static_assert(sizeof(Adj) <= sizeof(HgRec<W>) || (Op::K <= 2 && sizeof(Adj) <= Op::K * sizeof(double)),
+                  "adjoints fit a record buffer");
+    const HgLayout L = hg_layout(n, m, Op::K, sizeof(T));
     HgIn<T> xi{}, hb{};
     HgOut<T> xb{};
     for (int k = 0; k < Op::K; ++k) {
@@ -804,18 +816,24 @@ static void hg_vjp(const int32_t* inds, int64_t n, int32_t m, const void* const*
     const int32_t* pos = reinterpret_cast<const int32_t*>(w + L.pos);
     Adj* from = reinterpret_cast<Adj*>(w + ((const char*)recs == w + L.recA ? L.recB : L.recA));
     Adj* to = reinterpret_cast<Adj*>(const_cast<HgRec<W>*>(recs));  // free once the adjoints are formed
-    hipLaunchKernelGGL((hg_apply_kernel<Op, T, W, true>), dim3((unsigned)L.ntiles), dim3(kHgBlock), 0, st, recs,
+    hipLaunchKernelGGL((hg_apply_kernel<Op, T, W, true, A>), dim3((unsigned)L.ntiles), dim3(kHgBlock), 0, st, recs,
                        nvalid, w + L.carF, w + L.carR, HgOut<T>{}, hb, from);
     const dim3 grid((unsigned)(L.npad / kHgSub));
     for (int pass = L.passes - 1; pass > 0; --pass) {
-        hipLaunchKernelGGL((hg_back_kernel<T, Op::K>), grid, dim3(256), 0, st, pos + (int64_t)pass * L.npad, nvalid,
+        hipLaunchKernelGGL((hg_back_kernel<A, Op::K>), grid, dim3(256), 0, st, pos + (int64_t)pass * L.npad, nvalid,
                            from, to);
         std::swap(from, to);
     }
+    hipLaunchKernelGGL((hg_back_write_kernel<T, Op::K, ACC, A>), grid, dim3(256), 0, st, pos, n, nvalid, from, xb);
+}
+
+template <class Op, class T>
+static void hg_vjp(const int32_t* inds, int64_t n, int32_t m, const void* const* x, const void* const* hs_bar,
+                   void* const* x_bar, bool acc, char* w, hipStream_t st) {
     if (acc)
-        hipLaunchKernelGGL((hg_back_write_kernel<T, Op::K, true>), grid, dim3(256), 0, st, pos, n, nvalid, from, xb);
+        hg_vjp_t<Op, T, true>(inds, n, m, x, hs_bar, x_bar, w, st);
     else
-        hipLaunchKernelGGL((hg_back_write_kernel<T, Op::K, false>), grid, dim3(256), 0, st, pos, n, nvalid, from, xb);
+        hg_vjp_t<Op, T, false>(inds, n, m, x, hs_bar, x_bar, w, st);
 }
 
 static pvjp_status hg_check(const char* name, pvjp_gop op, pvjp_dtype dtype, const int32_t* inds,
@@ -847,7 +865,7 @@ using namespace pvjp;
 
 extern "C" size_t pvjp_hist_generic_ws_bytes(pvjp_gop op, pvjp_dtype dtype, int64_t n, int64_t m) {
     if (hg_components(op) == 0 || !valid_dtype(dtype) || n < 0 || m < 1 || m > kHgMaxBins) return 0;
-    return hg_layout(n, m, 4 + (size_t)hg_components(op) * dsize(dtype)).total;
+    return hg_layout(n, m, hg_components(op), dsize(dtype)).total;
 }
 
 extern "C" pvjp_status pvjp_hist_generic(pvjp_gop op, pvjp_dtype dtype, const int32_t* inds, const void* const* x,

@@ -167,3 +167,23 @@ def test_every_index_out_of_range(ops, m):
         xb = [dev(np.full(n, 0.25, dtype=np.float32)) for _ in dx]
         ops.hist_generic_vjp("linrec", di, dx, [dev(h) for h in hb], x_bar=xb, accumulate=acc)
         assert all(np.all(host(g) == np.float32(base)) for g in xb)
+
+
+@pytest.mark.parametrize("op", ["logaddexp", "linrec"])
+@pytest.mark.parametrize("n,m", [(5003, 7), (100003, 700), (100003, 1 << 17)])
+def test_accumulate_rounds_once(ops, orc, op, n, m):
+    # FP32: x_bar + the FP64 adjoint, rounded once, also where the two nearly
+    # cancel.  x_bar holds minus the adjoint, off by about 2^-12 of it: rounding
+    # the adjoint to FP32 before the sum would leave 2^-12 of relative error.  The
+    # FP64 adjoint's own error (1e-12 of its norm, the FP64 bar) allows 2^-24 of
+    # the sum and 1e-10 of the largest adjoint.
+    inds, xs, hb = workloads.hist_generic(op, n, m, "uniform", "f32", seed=n + m)
+    inds[::97] = -1
+    ref = orc.hist_generic_vjp(op, inds, [x.astype(np.float64) for x in xs], [h.astype(np.float64) for h in hb])
+    g = workloads.rng(n)
+    base = [(-r * (1 + 2.0 ** -12 * g.standard_normal(n))).astype(np.float32) for r in ref]
+    got = ops.hist_generic_vjp(op, dev(inds), [dev(x) for x in xs], [dev(h) for h in hb],
+                               x_bar=[dev(b) for b in base], accumulate=True)
+    for a, b, r in zip(got, base, ref):
+        exact = b.astype(np.float64) + r
+        assert np.all(np.abs(host(a) - exact) <= 2.0 ** -24 * np.abs(exact) + 1e-10 * np.abs(r).max())
