@@ -91,6 +91,97 @@ __device__ __forceinline__ void acc_update(uint64_t* a, int32_t* zc, T v, int64_
     }
 }
 
+// What the lanes of a wave have in common, for updates that the whole wave
+// makes together: equal neighbours in the input (sorted indices, one bin far
+// ahead of the others) would otherwise queue at one LDS word, some three cycles
+// a lane for a sum and a whole round of compare and swap for a product.
+struct AccSum {
+    struct S {
+        double v;
+    };
+    __device__ static __forceinline__ S id() { return S{0.0}; }
+    __device__ static __forceinline__ S comb(S x, S y) { return S{x.v + y.v}; }
+};
+// Whether ok holds in all 64 lanes with one value of j.
+__device__ __forceinline__ bool wave_one(bool ok, int32_t j) {
+    return __ballot(ok && j == __builtin_amdgcn_readfirstlane(j)) == ~0ull;
+}
+
+// The lifted product that restarts at a run's first lane.
+struct RunMul {
+    struct S {
+        double v;
+        uint32_t f, pad;
+    };
+    __device__ static __forceinline__ S id() { return S{1.0, 0u, 0u}; }
+    __device__ static __forceinline__ S comb(S x, S y) { return y.f ? y : S{x.v * y.v, x.f, 0u}; }
+};
+
+// N products a lane into LDS words, by the whole wave (bit i of todo: the lane
+// has the i-th): compare and swap until it succeeds.  Where many lanes fail at
+// their first try and neighbours have the same bin (sorted indices, one bin far
+// ahead of the others), each run of such lanes is multiplied up first and its
+// last lane alone goes on; where they hold one bin apart from each other, so are
+// they.  A bin has COPIES words in a row.  n = 2^22 FP32 products into 40,000
+// bins with and without this, us: uniform 38, 37; Zipf 346, 654; sorted 53, 593;
+// all into one 144, 20,900.
+constexpr int kMulCrowd = 16;
+template <int N, int COPIES>
+__device__ __forceinline__ void wave_mul_lds(uint64_t* acc, const int32_t (&j)[N], const double (&v)[N],
+                                             uint32_t todo) {
+    uint32_t late = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        if (!((todo >> i) & 1u)) continue;
+        unsigned long long* p = reinterpret_cast<unsigned long long*>(&acc[j[i]]);
+        unsigned long long old = *p, assumed = old;
+        old = atomicCAS(p, assumed, (unsigned long long)__double_as_longlong(__longlong_as_double(assumed) * v[i]));
+        if (old == assumed) continue;
+        if (__popcll(__ballot(true)) >= kMulCrowd)
+            late |= 1u << i;
+        else
+            mul_f64_atomic(&acc[j[i]], v[i]);
+    }
+    if (__ballot(late != 0) == 0) return;
+    const int lane = threadIdx.x & (kWave - 1);
+#pragma unroll 1
+    for (int i = 0; i < N; ++i) {
+        int32_t at = j[0];
+        double x = v[0];
+#pragma unroll
+        for (int u = 1; u < N; ++u) {  // moves, not an indexed load from scratch memory
+            at = i == u ? j[u] : at;
+            x = i == u ? v[u] : x;
+            __asm__ volatile("" : "+v"(at), "+v"(x));
+        }
+        bool ok = (late >> i) & 1u;
+        const uint64_t left = __ballot(ok);
+        if (left == 0) continue;
+        const int32_t before = lanes_dpp<kDppWaveShr1>(at);
+        const uint64_t heads = __ballot(lane == 0 || at / COPIES != before / COPIES);
+        if (2 * __popcll(heads) < __popcll(left)) {
+            x = wave_inclusive_scan<RunMul, false>(RunMul::S{ok ? x : 1.0, (uint32_t)(heads >> lane) & 1u, 0u}).v;
+            const uint64_t upto = (2ull << lane) - 1ull;  // lanes 0 .. lane
+            const int first = 63 - __builtin_clzll(heads & upto);
+            ok = (lane == kWave - 1 || ((heads >> (lane + 1)) & 1u)) && (left & upto) >> first != 0;
+        } else {
+            uint64_t seek = left;
+            for (int r = 0; r < 3 && seek; ++r) {
+                const int first = __builtin_ctzll(seek);
+                const bool mine = ok && at / COPIES == __builtin_amdgcn_readlane(at, first) / COPIES;
+                const uint64_t same = __ballot(mine);
+                seek &= ~same;
+                if (__popcll(same) < kMulCrowd / 2) continue;
+                const double t =
+                    lanes_read(wave_inclusive_scan<RunMul, false>(RunMul::S{mine ? x : 1.0, 0u, 0u}), kWave - 1).v;
+                if (lane == first) mul_f64_atomic(&acc[at], t);
+                ok = ok && !mine;
+            }
+        }
+        if (ok) mul_f64_atomic(&acc[at], x);
+    }
+}
+
 // Merge of a whole slot into the global accumulator.
 template <int OP>
 __device__ __forceinline__ void acc_merge(uint64_t* g, int32_t* gz, uint64_t a, int32_t zc) {
@@ -244,10 +335,15 @@ __global__ __launch_bounds__(kHistBlock) void hist_acc_kernel(
 
 // The bins in R ranges, each as large as one CU's LDS holds.  R blocks, one per
 // range, read the same chunk of the input and keep the updates of their own
-// range; the chunk's partials are merged as in FULL mode.  Blocks go to the
-// XCDs round-robin, and the R blocks of a chunk are eight apart, so they share
-// one L2: the input comes from HBM once (n = 2^26, R = 4: of 17 M lines read, 4.5
-// M miss L2) and the kernel is bound by the CUs' reads from L2, 10.7 TB/s.
+// range; the chunk's partials are merged as in FULL mode.  Chunk c is the pieces
+// of 4,096 elements c, c + C, ..., so that every chunk meets every part of the
+// input: of a sorted one, a chunk in one piece falls into one range, and one of
+// its R blocks does all the work (with that and each element its own atomic, n =
+// 2^25 sorted FP32 values into 65,536 bins took 660 us, now 142; all into one bin
+// 685, now 148).  Blocks go to the XCDs round-robin, and the R blocks of a chunk
+// are eight apart, so they share one L2: the input comes from HBM once (n = 2^26,
+// R = 4: of 17 M lines read, 4.5 M miss L2) and the kernel is bound by the CUs'
+// reads from L2, 10.7 TB/s.
 // Sorting the records into buckets first (hpart_tile_kernel and its
 // successors) moves each one out to HBM and back instead.  All kernels of the
 // primal, n = 2^26 FP32 values, +: 65,536 bins 295 -> 213 us, 20,000 328 -> 120.
@@ -259,14 +355,13 @@ constexpr int range_bins(int op) { return 160 * 1024 / (op == PVJP_MUL ? 12 : 8)
 template <class T, int OP, bool VEC>
 __global__ __launch_bounds__(kRangeBlock) void hist_range_kernel(const int32_t* __restrict__ inds,
                                                                  const T* __restrict__ vs, int64_t n, int32_t m,
-                                                                 int64_t chunk, int R, int32_t per,
-                                                                 uint64_t* __restrict__ pacc,
+                                                                 int R, int32_t per, uint64_t* __restrict__ pacc,
                                                                  int32_t* __restrict__ pz) {
     constexpr int BATCH = sizeof(T) == 4 ? 4 : 2;
     __shared__ uint64_t acc[range_bins(OP)];
     __shared__ int32_t zc[OP == PVJP_MUL ? range_bins(OP) : 1];
     const int xcd = (int)blockIdx.x % kXcds, slot = (int)blockIdx.x / kXcds;
-    const int64_t c = (int64_t)(slot / R) * kXcds + xcd;
+    const int64_t c = (int64_t)(slot / R) * kXcds + xcd, C = gridDim.x / R;
     const int32_t k0 = (slot % R) * per;
     const uint32_t cnt = (uint32_t)(m - k0 < per ? m - k0 : per);
     for (uint32_t j = threadIdx.x; j < cnt; j += kRangeBlock) {
@@ -274,34 +369,59 @@ __global__ __launch_bounds__(kRangeBlock) void hist_range_kernel(const int32_t* 
         if (OP == PVJP_MUL) zc[j] = 0;
     }
     __syncthreads();
-    const int64_t lo = c * chunk;
-    const int64_t hi = (lo + chunk < n) ? lo + chunk : n;
-    constexpr int64_t kStride = 4 * kRangeBlock * BATCH;
     Quad<T> cur[BATCH], nxt[BATCH];
+    auto at = [&](int64_t piece, int u) { return 4 * ((piece + u * C) * kRangeBlock + threadIdx.x); };
 #pragma unroll
-    for (int u = 0; u < BATCH; ++u)
-        cur[u] = load_quad<T, VEC>(inds, vs, lo + 4 * ((int64_t)u * kRangeBlock + threadIdx.x), hi);
-    for (int64_t base = lo; base < hi; base += kStride) {
-        const int64_t nb = base + kStride;
+    for (int u = 0; u < BATCH; ++u) cur[u] = load_quad<T, VEC>(inds, vs, at(c, u), n);
+    for (int64_t piece = c; piece * (4 * kRangeBlock) < n; piece += BATCH * C) {
 #pragma unroll
-        for (int u = 0; u < BATCH; ++u)
-            nxt[u] = load_quad<T, VEC>(inds, vs, nb + 4 * ((int64_t)u * kRangeBlock + threadIdx.x), hi);
+        for (int u = 0; u < BATCH; ++u) nxt[u] = load_quad<T, VEC>(inds, vs, at(piece + BATCH * C, u), n);
 #pragma unroll
         for (int u = 0; u < BATCH; ++u) {
             const int32_t kk[4] = {cur[u].k.x, cur[u].k.y, cur[u].k.z, cur[u].k.w};
+            if (part_keys<OP>()) {
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                // an index below 0 or beyond m is in no range
-                const uint32_t j = (uint32_t)kk[t] - (uint32_t)k0;
-                if (j >= cnt) continue;
-                if (!part_keys<OP>()) {
-                    acc_update<T, OP>(&acc[j], &zc[OP == PVJP_MUL ? j : 0], cur[u].v[t], 0);
-                } else {
-                    const int64_t e = base + 4 * ((int64_t)u * kRangeBlock + threadIdx.x) + t;
-                    const uint64_t key = elem_key<OP>(cur[u].v[t], e);
+                for (int t = 0; t < 4; ++t) {
+                    const uint32_t j = (uint32_t)kk[t] - (uint32_t)k0;
+                    if (j >= cnt) continue;
+                    const uint64_t key = elem_key<OP>(cur[u].v[t], at(piece, u) + t);
                     if (key > __hip_atomic_load(&acc[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))
                         atomicMax(reinterpret_cast<unsigned long long*>(&acc[j]), (unsigned long long)key);
                 }
+                continue;
+            }
+            // an index below 0 or beyond m is in no range
+            int32_t j[4];
+            double x[4];
+            uint32_t todo = 0;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                j[t] = kk[t] - k0;
+                x[t] = (double)cur[u].v[t];
+                const bool in = (uint32_t)j[t] < cnt, zero = OP == PVJP_MUL && cur[u].v[t] == T(0);
+                if (OP == PVJP_MUL && in && zero) atomicAdd(&zc[j[t]], 1);
+                todo |= (uint32_t)(in && !zero) << t;
+            }
+            if (OP == PVJP_MUL) {
+                wave_mul_lds<4, 1>(acc, j, x, todo);
+            } else {
+                if (__ballot(kk[0] == kk[3])) {  // else no thread's four are equal
+                    // runs of one bin: a thread's four together, and the wave's where all agree
+                    const bool same = kk[0] == kk[1] && kk[1] == kk[2] && kk[2] == kk[3];
+                    double s = 0.0;
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) s += (todo >> t) & 1u ? x[t] : 0.0;
+                    if (wave_one(same, kk[0])) {
+                        s = lanes_read(wave_inclusive_scan<AccSum, false>(AccSum::S{s}), kWave - 1).v;
+                        todo = (threadIdx.x & (kWave - 1)) == 0 && (uint32_t)j[0] < cnt;
+                    } else if (same) {
+                        todo = todo != 0;
+                    }
+                    if (same) x[0] = s;
+                }
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    if ((todo >> t) & 1u) atomicAdd(reinterpret_cast<double*>(&acc[j[t]]), x[t]);
             }
         }
 #pragma unroll
@@ -748,6 +868,19 @@ __global__ __launch_bounds__(kTileThreads) void hpart_tile_kernel(const int32_t*
 #pragma unroll
     for (int u = 0; u < kTileQuads; ++u) {
         const int32_t kk[4] = {q[u].k.x, q[u].k.y, q[u].k.z, q[u].k.w};
+        // a wave whose elements all go to one bucket (sorted indices) counts once
+        bool in = true;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) in &= (uint32_t)kk[t] < (uint32_t)m && ((kk[t] ^ kk[0]) >> kPartShift) == 0;
+        if (wave_one(in, kk[0] >> kPartShift)) {
+            const int lane = threadIdx.x & (kWave - 1);
+            int r = 0;
+            if (lane == 0) r = atomicAdd(&bcnt[kk[0] >> kPartShift], 4 * kWave);
+            r = __builtin_amdgcn_readfirstlane(r) + 4 * lane;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) rank[4 * u + t] = r + t;
+            continue;
+        }
 #pragma unroll
         for (int t = 0; t < 4; ++t)
             rank[4 * u + t] = ((uint32_t)kk[t] < (uint32_t)m) ? atomicAdd(&bcnt[kk[t] >> kPartShift], 1) : -1;
@@ -878,8 +1011,7 @@ __global__ __launch_bounds__(kColThreads) void hpart_colscan_kernel(const int32_
 // the last non-empty run's start over seg, none for an empty bucket.
 constexpr int kBscanThreads = 256;
 __global__ __launch_bounds__(kBscanThreads) void hpart_bscan_kernel(int32_t* __restrict__ ctot,
-                                                                    const int32_t* __restrict__ clast,
-                                                                    int nchunks, int seg,
+                                                                    int32_t* clast, int nchunks, int seg,
                                                                     int32_t* __restrict__ bitems) {
     __shared__ IntSum::S wtot[kBscanThreads / kWave];
     __shared__ int lastp;
@@ -899,7 +1031,10 @@ __global__ __launch_bounds__(kBscanThreads) void hpart_bscan_kernel(int32_t* __r
         carry += tot.v;
     }
     __syncthreads();
-    if (threadIdx.x == 0) bitems[b] = lastp >= 0 ? lastp / seg + 1 : 0;
+    if (threadIdx.x == 0) {
+        bitems[b] = lastp >= 0 ? lastp / seg + 1 : 0;
+        clast[(int64_t)b * nchunks] = lastp;  // all of the row has been read
+    }
 }
 
 // One block: work-item starts per bucket.
@@ -914,32 +1049,35 @@ __global__ __launch_bounds__(kPartScanThreads) void hpart_scan_kernel(const int3
     if (b == 0) istart[nb] = itot.v;
 }
 
-// First tile of every work item: item i of bucket b takes the tiles whose run
-// of b starts in [i * seg, (i + 1) * seg), i.e. from the first tile
-// t with P[b][t] >= i * seg, where P[b][t] = Ploc + the chunk prefix is
-// the start of b's run in tile t within the bucket.  Non-empty runs start at
-// 0 and are shorter than seg, so up to the last non-empty run every
-// such interval holds a run start, and exactly one thread finds the first
-// tile of each item.
+// The tiles [itile, itend) of every work item: item i of bucket b takes the
+// runs of b that start in [i * seg, (i + 1) * seg), where P[b][t] = Ploc + the
+// chunk prefix is the start of b's run in tile t within the bucket.  Non-empty
+// runs start at 0 and are shorter than seg, so up to the last non-empty run
+// (at lastp, in the bucket's first word of clast) every such interval holds a
+// run start, and exactly one thread finds an item's first tile (for i > 0 the
+// first t with P[b][t] >= i * seg, which may be empty) and one its last.
+// Without the empty tiles on either side (sorted indices leave a bucket nothing
+// else), the waves of an item share those that hold records.
 __global__ __launch_bounds__(256) void hpart_items_kernel(const int32_t* __restrict__ Ploc,
-                                                          const int32_t* __restrict__ cpre, int ntiles, int nb,
-                                                          int nchunks, int seg, const int32_t* __restrict__ istart,
-                                                          int32_t* __restrict__ itile) {
+                                                          const int32_t* __restrict__ cpre,
+                                                          const int32_t* __restrict__ clast, int ntiles, int nb,
+                                                          int nchunks, uint32_t seg,
+                                                          const int32_t* __restrict__ istart,
+                                                          int32_t* __restrict__ itile, int32_t* __restrict__ itend) {
     const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (g >= (int64_t)nb * ntiles) return;
     const int b = (int)(g / ntiles), t = (int)(g % ntiles);
     auto P = [&](int tt) {
-        return (int64_t)Ploc[(int64_t)b * ntiles + tt] + cpre[(int64_t)b * nchunks + tt / kColChunk];
+        return (uint32_t)(Ploc[(int64_t)b * ntiles + tt] + cpre[(int64_t)b * nchunks + tt / kColChunk]);
     };
-    const int items = istart[b + 1] - istart[b];
-    int64_t i;
-    if (t == 0) {
-        i = 0;
-    } else {
-        i = P(t) / seg;
-        if (i == 0 || i * seg <= P(t - 1)) return;
-    }
-    if (i < items) itile[istart[b] + i] = t;
+    const int last = clast[(int64_t)b * nchunks];
+    if (last < 0) return;  // an empty bucket has no items
+    const uint32_t p = P(t), i = p / seg;
+    const uint32_t next = t + 1 < ntiles ? P(t + 1) : 0u;
+    // beyond the last run every start is the bucket's length, which exceeds lastp
+    const bool run = t + 1 < ntiles ? next > p : p == (uint32_t)last;
+    if (i == 0 ? (run && p == 0u) : (p <= (uint32_t)last && i * seg > P(t - 1))) itile[istart[b] + i] = t;
+    if (run && (p == (uint32_t)last || next / seg > i)) itend[istart[b] + i] = t + 1;
 }
 
 // One block per work item accumulates its bucket's 4096 bins in LDS.  The
@@ -965,6 +1103,10 @@ constexpr int kXcdMapBuckets = 128;
 constexpr int kAccGroup = 8;
 constexpr int kAccSlots = 4;  // records per lane and group in flight
 constexpr int kAccPar = 2;    // groups read side by side
+// Two blocks a CU need eight waves a SIMD, and a wave then has 80 scalar
+// registers (with 83 one block stayed: n = 2^25 + into 300,000 bins, 80 us, with
+// 80 65).
+#define PVJP_ACC_BOUNDS __launch_bounds__(kAccBlock) __attribute__((amdgpu_num_sgpr(80)))
 
 // Uniform run table of one group: run u holds records [pre[u], pre[u + 1])
 // of the group's flat sequence, at record slot off[u] + r.
@@ -1002,47 +1144,60 @@ __device__ __forceinline__ uint32_t acc_slot(const AccGroup& G, int r) {
     return o + (uint32_t)r;
 }
 
-template <class T, int OP, bool COUNTS>
-__device__ __forceinline__ void acc_record(uint64_t* acc, int32_t* cnt, int32_t* aux, uint32_t copy,
-                                           int64_t tile_base, uint32_t at, T v, uint32_t bn) {
-    const uint32_t j = bn & (kPartBins - 1);
-    uint64_t* w = &acc[j * kAccCopies + copy];
-    if (part_keys<OP>()) {
-        // the tile start plus the position in the tile: the element index
-        // (part of an FP32 key; FP64 winners are found in a second sweep)
-        const int64_t e = tile_base + (int64_t)(at & ~(uint32_t)(kTile - 1)) + (int64_t)(bn >> 16);
-        // A key only ever grows, so a record whose key does not exceed the
-        // word read now cannot win and skips the atomic.  A read of one word
-        // by many lanes is a broadcast, while atomics on one word serialise:
-        // on a hot bin almost every record stops here, and on a uniform one
-        // the expected number of winners among k records is the k-th
-        // harmonic number.
-        const uint64_t key = elem_key<OP>(v, e);
-        if (key > __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))
-            atomicMax(reinterpret_cast<unsigned long long*>(w), (unsigned long long)key);
-    } else if (OP == PVJP_MUL) {
-        if (v == T(0))
-            atomicAdd(&aux[j], 1);
-        else
-            mul_f64_atomic(w, (double)v);
-    } else {
-        atomicAdd(reinterpret_cast<double*>(w), (double)v);
+// One lane's records (NS of them in flight) into the item's accumulators, the
+// whole wave calling.
+template <class T, int OP, bool COUNTS, int NS>
+__device__ __forceinline__ void acc_records(uint64_t* acc, int32_t* cnt, int32_t* aux, uint32_t copy,
+                                            int64_t tile_base, const bool (&ok)[NS], const uint32_t (&at)[NS],
+                                            const T (&v)[NS], const uint32_t (&bn)[NS]) {
+    if (OP == PVJP_MUL) {
+        int32_t w[NS];
+        double x[NS];
+        uint32_t todo = 0;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const uint32_t j = bn[s] & (kPartBins - 1);
+            w[s] = (int32_t)(j * kAccCopies + copy);
+            x[s] = (double)v[s];
+            if (ok[s] && v[s] == T(0)) atomicAdd(&aux[j], 1);
+            if (COUNTS && ok[s]) atomicAdd(&cnt[j], 1);
+            todo |= (uint32_t)(ok[s] && v[s] != T(0)) << s;
+        }
+        wave_mul_lds<NS, kAccCopies>(acc, w, x, todo);
+        return;
     }
-    if (COUNTS) atomicAdd(&cnt[j], 1);
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        if (!ok[s]) continue;
+        const uint32_t j = bn[s] & (kPartBins - 1);
+        uint64_t* w = &acc[j * kAccCopies + copy];
+        if (part_keys<OP>()) {
+            // the tile start plus the position in the tile: the element index
+            // (part of an FP32 key; FP64 winners are found in a second sweep)
+            const int64_t e = tile_base + (int64_t)(at[s] & ~(uint32_t)(kTile - 1)) + (int64_t)(bn[s] >> 16);
+            // A key only ever grows, so a record whose key does not exceed the
+            // word read now cannot win and skips the atomic.  A read of one word
+            // by a whole wave is a broadcast while an atomic on it serialises:
+            // on a hot bin almost every record stops here, and on a uniform one
+            // the expected number of winners among k records is the k-th
+            // harmonic number.
+            const uint64_t key = elem_key<OP>(v[s], e);
+            if (key > __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))
+                atomicMax(reinterpret_cast<unsigned long long*>(w), (unsigned long long)key);
+        } else {
+            atomicAdd(reinterpret_cast<double*>(w), (double)v[s]);
+        }
+        if (COUNTS) atomicAdd(&cnt[j], 1);
+    }
 }
 
-// The work item of this block (-1: none) with its bucket and tiles.  With
-// many buckets (short runs): blocks go to the XCDs round-robin, so each XCD
-// takes an equal contiguous range of the items (the grid is a multiple of
-// kXcds and covers them) and items of adjacent buckets, whose runs share
-// cache lines in every tile, meet in one L2.  With few buckets the runs span
-// whole lines and items go in grid order.
 struct PartItem {
     int item, b, ta, tb;
 };
 
-__device__ __forceinline__ PartItem part_item(int nb, int ntiles, const int32_t* __restrict__ istart,
-                                              const int32_t* __restrict__ itile) {
+__device__ __forceinline__ PartItem part_item(int nb, const int32_t* __restrict__ istart,
+                                              const int32_t* __restrict__ itile,
+                                              const int32_t* __restrict__ itend) {
     PartItem I{-1, 0, 0, 0};
     const int nitems = istart[nb];
     int item = (int)blockIdx.x;
@@ -1060,12 +1215,14 @@ __device__ __forceinline__ PartItem part_item(int nb, int ntiles, const int32_t*
     I.item = item;
     I.b = lo;
     I.ta = itile[item];
-    I.tb = (item + 1 < istart[lo + 1]) ? itile[item + 1] : ntiles;
+    I.tb = itend[item];
     return I;
 }
 
 // Walks the item's records (see above) and hands each lane's records to
-// fn(tile_base, ok, slot, value, bin word), the whole wave calling.
+// fn(tile_base, ok, slot, value, bin word), arrays of those in flight, the
+// whole wave calling.  Few tiles hold an item of long runs (sorted indices, one
+// bin far ahead of the others): their runs are split between the waves.
 template <class T, bool KEYS, class Fn>
 __device__ __forceinline__ void part_walk(const uint32_t* __restrict__ rval, const uint32_t* __restrict__ rhi,
                                           const void* __restrict__ rbin, const uint32_t* __restrict__ D, int ntiles,
@@ -1073,13 +1230,20 @@ __device__ __forceinline__ void part_walk(const uint32_t* __restrict__ rval, con
     constexpr int NW = kAccBlock / kWave;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
-    const int span = (I.tb - I.ta + NW - 1) / NW;
-    const int w0 = I.ta + wave * span;
+    const int tiles = I.tb - I.ta;  // at least one
+    static_assert(NW == 16, "the split below");
+    const int split = tiles == 1 ? 4 : (tiles < NW ? __builtin_clz(tiles - 1) - 28 : 0);  // 2^split waves a run
+    const uint32_t part = (uint32_t)wave & ((1u << split) - 1u);
+    const uint32_t f0 = part << (16 - split), f1 = (part + 1) << (16 - split);  // the wave's share of 2^16
+    const int span = (tiles + NW - 1) / NW;
+    const int w0 = I.ta + (wave >> split) * span;
     const int w1 = (w0 + span < I.tb) ? w0 + span : I.tb;
     const uint32_t* Db = D + (int64_t)I.b * ntiles;
     for (int c0 = w0; c0 < w1; c0 += kWave) {
         // lane l: the descriptor of tile c0 + l (an empty run past the share)
-        const uint32_t dl = (c0 + lane < w1) ? Db[c0 + lane] : 0u;
+        uint32_t dl = (c0 + lane < w1) ? Db[c0 + lane] : 0u;
+        const uint32_t len = dl >> 16, a = (len * f0) >> 16, b = (len * f1) >> 16;
+        dl = ((dl & 0xffffu) + a) | ((b - a) << 16);
         const int nc = (w1 - c0 < kWave) ? w1 - c0 : kWave;
         const int64_t tbase = (int64_t)c0 * kTile;
         const char* cv = reinterpret_cast<const char*>(rval + tbase);
@@ -1087,8 +1251,7 @@ __device__ __forceinline__ void part_walk(const uint32_t* __restrict__ rval, con
         const char* cb = reinterpret_cast<const char*>(rbin) + tbase * (KEYS ? 4 : 2);
         // a pass reads kAccPar groups of kAccGroup consecutive runs side by
         // side; fewer runs than one pass takes are split evenly between them
-        const bool split = nc < kAccPar * kAccGroup;
-        const int ps = split ? (nc + kAccPar - 1) / kAccPar : kAccGroup;
+        const int ps = nc < kAccPar * kAccGroup ? (nc + kAccPar - 1) / kAccPar : kAccGroup;
         for (int g = 0; g < nc; g += kAccPar * ps) {
             AccGroup G[kAccPar];
             int R = 0;
@@ -1102,6 +1265,7 @@ __device__ __forceinline__ void part_walk(const uint32_t* __restrict__ rval, con
             for (int r0 = 0; r0 < R; r0 += kAccSlots * kWave) {
                 uint32_t at[kAccPar * kAccSlots], vv[kAccPar * kAccSlots], bb[kAccPar * kAccSlots];
                 uint32_t vh[kAccPar * kAccSlots];
+                T v[kAccPar * kAccSlots];
                 bool ok[kAccPar * kAccSlots];
 #pragma unroll
                 for (int s = 0; s < kAccPar * kAccSlots; ++s) {
@@ -1119,7 +1283,8 @@ __device__ __forceinline__ void part_walk(const uint32_t* __restrict__ rval, con
                                  : (uint32_t)*reinterpret_cast<const uint16_t*>(cb + (at[s] << 1));
                 }
 #pragma unroll
-                for (int s = 0; s < kAccPar * kAccSlots; ++s) fn(tbase, ok[s], at[s], val_of<T>(vv[s], vh[s]), bb[s]);
+                for (int s = 0; s < kAccPar * kAccSlots; ++s) v[s] = val_of<T>(vv[s], vh[s]);
+                fn(tbase, ok, at, v, bb);
             }
         }
     }
@@ -1133,12 +1298,13 @@ __host__ __device__ constexpr bool part_aux() {
 }
 
 template <class T, int OP, bool COUNTS>
-__global__ __launch_bounds__(kAccBlock) void hpart_acc_kernel(const uint32_t* __restrict__ rval,
+__global__ PVJP_ACC_BOUNDS void hpart_acc_kernel(const uint32_t* __restrict__ rval,
                                                               const uint32_t* __restrict__ rhi,
                                                               const void* __restrict__ rbin, int nb, int ntiles,
                                                               const uint32_t* __restrict__ D,
                                                               const int32_t* __restrict__ istart,
                                                               const int32_t* __restrict__ itile,
+                                                              const int32_t* __restrict__ itend,
                                                               uint64_t* __restrict__ pacc,
                                                               int32_t* __restrict__ pcnt,
                                                               int32_t* __restrict__ paux) {
@@ -1148,7 +1314,7 @@ __global__ __launch_bounds__(kAccBlock) void hpart_acc_kernel(const uint32_t* __
     __shared__ uint64_t acc[kPartBins * kAccCopies];
     __shared__ int32_t cnt[COUNTS ? kPartBins : 1];
     __shared__ int32_t aux[AUX ? kPartBins : 1];
-    const PartItem I = part_item(nb, ntiles, istart, itile);
+    const PartItem I = part_item(nb, istart, itile, itend);
     if (I.item < 0) return;
     const int item = I.item;
     for (int j = threadIdx.x; j < kPartBins * kAccCopies; j += kAccBlock) acc[j] = acc_identity<OP>();
@@ -1158,9 +1324,10 @@ __global__ __launch_bounds__(kAccBlock) void hpart_acc_kernel(const uint32_t* __
         for (int j = threadIdx.x; j < kPartBins; j += kAccBlock) aux[j] = WINNERS ? 0x7fffffff : 0;
     __syncthreads();
     const uint32_t copy = threadIdx.x & (kAccCopies - 1);
-    part_walk<T, KEYS>(rval, rhi, rbin, D, ntiles, I, [&](int64_t tbase, bool ok, uint32_t at, T v, uint32_t bn) {
-        if (ok) acc_record<T, OP, COUNTS>(acc, cnt, aux, copy, tbase, at, v, bn);
-    });
+    part_walk<T, KEYS>(rval, rhi, rbin, D, ntiles, I,
+                       [&](int64_t tbase, const auto& ok, const auto& at, const auto& v, const auto& bn) {
+                           acc_records<T, OP, COUNTS>(acc, cnt, aux, copy, tbase, ok, at, v, bn);
+                       });
     __syncthreads();
     for (int j = threadIdx.x; j < kPartBins; j += kAccBlock) {
         uint64_t v = acc[j * kAccCopies];
@@ -1177,11 +1344,16 @@ __global__ __launch_bounds__(kAccBlock) void hpart_acc_kernel(const uint32_t* __
     if (WINNERS) {
         // the records again: the lowest index among those equal to the extreme
         __syncthreads();
-        part_walk<T, KEYS>(rval, rhi, rbin, D, ntiles, I, [&](int64_t tbase, bool ok, uint32_t at, T v, uint32_t bn) {
-            const uint32_t j = bn & (kPartBins - 1);
-            if (!ok || elem_key<OP>(v, 0) != acc[j * kAccCopies]) return;
-            const int32_t e = (int32_t)(tbase + (int64_t)(at & ~(uint32_t)(kTile - 1)) + (int64_t)(bn >> 16));
-            if (e < __hip_atomic_load(&aux[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) atomicMin(&aux[j], e);
+        part_walk<T, KEYS>(rval, rhi, rbin, D, ntiles, I,
+                           [&](int64_t tbase, const auto& ok, const auto& at, const auto& v, const auto& bn) {
+#pragma unroll
+            for (int s = 0; s < kAccPar * kAccSlots; ++s) {
+                const uint32_t j = bn[s] & (kPartBins - 1);
+                if (!ok[s] || elem_key<OP>(v[s], 0) != acc[j * kAccCopies]) continue;
+                const int32_t e = (int32_t)(tbase + (int64_t)(at[s] & ~(uint32_t)(kTile - 1)) + (int64_t)(bn[s] >> 16));
+                if (e < __hip_atomic_load(&aux[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))
+                    atomicMin(&aux[j], e);
+            }
         });
         __syncthreads();
         for (int j = threadIdx.x; j < kPartBins; j += kAccBlock) paux[(int64_t)item * kPartBins + j] = aux[j];
@@ -1236,31 +1408,40 @@ __device__ __forceinline__ float unord32(uint32_t o) {
     return __uint_as_float((o & 0x80000000u) ? (o & 0x7fffffffu) : ~o);
 }
 
-__global__ __launch_bounds__(kAccBlock) void hpart_lae_acc_kernel(const uint32_t* __restrict__ rval,
+__global__ PVJP_ACC_BOUNDS void hpart_lae_acc_kernel(const uint32_t* __restrict__ rval,
                                                                   const void* __restrict__ rbin, int nb, int ntiles,
                                                                   const uint32_t* __restrict__ D,
                                                                   const int32_t* __restrict__ istart,
                                                                   const int32_t* __restrict__ itile,
+                                                                  const int32_t* __restrict__ itend,
                                                                   double* __restrict__ psum,
                                                                   uint32_t* __restrict__ pmax) {
     __shared__ uint32_t mx[kPartBins];
     __shared__ double sm[kPartBins * kAccCopies];
-    const PartItem I = part_item(nb, ntiles, istart, itile);
+    const PartItem I = part_item(nb, istart, itile, itend);
     if (I.item < 0) return;
     for (int j = threadIdx.x; j < kPartBins; j += kAccBlock) mx[j] = 0u;
     for (int j = threadIdx.x; j < kPartBins * kAccCopies; j += kAccBlock) sm[j] = 0.0;
     __syncthreads();
-    part_walk<float, false>(rval, nullptr, rbin, D, ntiles, I, [&](int64_t, bool ok, uint32_t, float x, uint32_t bn) {
-        if (ok) atomicMax(&mx[bn & (kPartBins - 1)], ord32(x));
+    constexpr int NS = kAccPar * kAccSlots;
+    part_walk<float, false>(rval, nullptr, rbin, D, ntiles, I,
+                            [&](int64_t, const auto& ok, const auto&, const auto& x, const auto& bn) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+            if (ok[s]) atomicMax(&mx[bn[s] & (kPartBins - 1)], ord32(x[s]));
     });
     __syncthreads();
     const uint32_t copy = threadIdx.x & (kAccCopies - 1);
-    part_walk<float, false>(rval, nullptr, rbin, D, ntiles, I, [&](int64_t, bool ok, uint32_t, float x, uint32_t bn) {
-        if (!ok) return;
-        const uint32_t j = bn & (kPartBins - 1);
-        const float m = unord32(mx[j]);
-        if (x != -INFINITY && m != -INFINITY)
-            atomicAdd(&sm[j * kAccCopies + copy], (double)(x == m ? 1.0f : expf(x - m)));
+    part_walk<float, false>(rval, nullptr, rbin, D, ntiles, I,
+                            [&](int64_t, const auto& ok, const auto&, const auto& x, const auto& bn) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            if (!ok[s]) continue;
+            const uint32_t j = bn[s] & (kPartBins - 1);
+            const float m = unord32(mx[j]);
+            if (x[s] != -INFINITY && m != -INFINITY)
+                atomicAdd(&sm[j * kAccCopies + copy], (double)(x[s] == m ? 1.0f : expf(x[s] - m)));
+        }
     });
     __syncthreads();
     for (int j = threadIdx.x; j < kPartBins; j += kAccBlock) {
@@ -1460,7 +1641,7 @@ static PartLayout part_layout(int64_t n, int64_t m, bool f32, int64_t most = kPa
         o += align_up(bytes, 256);
         return at;
     };
-    L.toff = take((size_t)L.ntiles * (L.nb + 1) * 4);
+    L.toff = take((size_t)L.ntiles * (L.nb + 1) * 4);  // afterwards the items' last tiles, at most ntiles + nb
     L.D = take((size_t)L.nb * L.ntiles * 4);
     L.Ploc = take((size_t)L.nb * L.ntiles * 4);
     L.ctot = take((size_t)L.nb * L.nchunks * 4);
@@ -1526,7 +1707,7 @@ static void part_sort(const int32_t* inds, const T* vs, int64_t n, int32_t m, co
     hipLaunchKernelGGL(hpart_bscan_kernel, dim3(L.nb), dim3(kBscanThreads), 0, st, ctot, clast, L.nchunks, L.seg, bitems);
     hipLaunchKernelGGL(hpart_scan_kernel, dim3(1), dim3(kPartScanThreads), 0, st, bitems, L.nb, istart);
     hipLaunchKernelGGL(hpart_items_kernel, dim3((unsigned)ceil_div((int64_t)L.nb * L.ntiles, 256)), dim3(256), 0, st,
-                       Ploc, ctot, L.ntiles, L.nb, L.nchunks, L.seg, istart, itile);
+                       Ploc, ctot, clast, L.ntiles, L.nb, L.nchunks, (uint32_t)L.seg, istart, itile, toff);
 }
 
 template <class T, int OP>
@@ -1538,6 +1719,7 @@ static void run_partitioned(const int32_t* inds, const T* vs, int64_t n, int32_t
     const uint32_t* D = reinterpret_cast<const uint32_t*>(base + L.D);
     const int32_t* istart = reinterpret_cast<const int32_t*>(base + L.istart);
     const int32_t* itile = reinterpret_cast<const int32_t*>(base + L.itile);
+    const int32_t* itend = reinterpret_cast<const int32_t*>(base + L.toff);
     const uint32_t* rval = reinterpret_cast<const uint32_t*>(base + L.rval);
     const uint32_t* rhi = reinterpret_cast<const uint32_t*>(base + L.rhi);
     const void* rbin = base + L.rbin;
@@ -1547,10 +1729,10 @@ static void run_partitioned(const int32_t* inds, const T* vs, int64_t n, int32_t
     const unsigned agrid = (unsigned)(ceil_div(L.items_max, (int64_t)kXcds) * kXcds);
     if (count)
         hipLaunchKernelGGL((hpart_acc_kernel<T, OP, true>), dim3(agrid), dim3(kAccBlock), 0, st, rval, rhi, rbin,
-                           L.nb, L.ntiles, D, istart, itile, pacc, pcnt, paux);
+                           L.nb, L.ntiles, D, istart, itile, itend, pacc, pcnt, paux);
     else
         hipLaunchKernelGGL((hpart_acc_kernel<T, OP, false>), dim3(agrid), dim3(kAccBlock), 0, st, rval, rhi, rbin,
-                           L.nb, L.ntiles, D, istart, itile, pacc, pcnt, paux);
+                           L.nb, L.ntiles, D, istart, itile, itend, pacc, pcnt, paux);
     hipLaunchKernelGGL((hpart_merge_kernel<T, OP>), dim3(flat_grid(m, 256, 1)), dim3(256), 0, st, pacc,
                        count ? pcnt : nullptr, paux, istart, m, vs, count, o);
 }
@@ -1577,7 +1759,8 @@ void hist_lae_partitioned(const int32_t* inds, const float* x, int64_t n, int32_
     hipLaunchKernelGGL(hpart_lae_acc_kernel, dim3(agrid), dim3(kAccBlock), 0, st,
                        reinterpret_cast<const uint32_t*>(ws + L.rval), (const void*)(ws + L.rbin), L.nb, L.ntiles,
                        reinterpret_cast<const uint32_t*>(ws + L.D), reinterpret_cast<const int32_t*>(ws + L.istart),
-                       reinterpret_cast<const int32_t*>(ws + L.itile), psum, pmax);
+                       reinterpret_cast<const int32_t*>(ws + L.itile), reinterpret_cast<const int32_t*>(ws + L.toff),
+                       psum, pmax);
     hipLaunchKernelGGL(hpart_lae_merge_kernel, dim3(flat_grid(m, 256, 1)), dim3(256), 0, st, psum, pmax,
                        reinterpret_cast<const int32_t*>(ws + L.istart), m, hs);
 }
@@ -1615,11 +1798,9 @@ static void run_hist(const int32_t* inds, const T* vs, int64_t n, int32_t m, T* 
             int32_t* mz = pz + (size_t)P.C * m;
             const dim3 g((unsigned)(P.C * P.R)), b(kRangeBlock);
             if (aligned(inds, 16) && aligned(vs, 16))
-                hipLaunchKernelGGL((hist_range_kernel<T, OP, true>), g, b, 0, st, inds, vs, n, m, P.chunk, P.R, P.per,
-                                   pacc, pz);
+                hipLaunchKernelGGL((hist_range_kernel<T, OP, true>), g, b, 0, st, inds, vs, n, m, P.R, P.per, pacc, pz);
             else
-                hipLaunchKernelGGL((hist_range_kernel<T, OP, false>), g, b, 0, st, inds, vs, n, m, P.chunk, P.R, P.per,
-                                   pacc, pz);
+                hipLaunchKernelGGL((hist_range_kernel<T, OP, false>), g, b, 0, st, inds, vs, n, m, P.R, P.per, pacc, pz);
             hipLaunchKernelGGL(hist_merge1_kernel<OP>, dim3((unsigned)ceil_div(m, 256), kMergeSlices), dim3(256), 0,
                                st, pacc, pz, nullptr, P.C, m, macc, mz, nullptr);
             hipLaunchKernelGGL((hist_merge2_kernel<T, OP, true>), dim3((unsigned)ceil_div(m, kMerge2Block)),

@@ -185,3 +185,81 @@ def test_range_edges(ops, orc, op, n, m, shift, dtype):
     if op == "mul":
         assert np.array_equal(host(aux["z"]), ref["z"])
         assert rel_l2(host(aux["p"]), ref["p"]) <= bar
+
+
+def clustered(kind, n, m, g):
+    """Indices whose equal ones lie together, or of which one bin has most."""
+    if kind == "sorted":
+        return np.sort(g.integers(0, m, n)).astype(np.int32)
+    if kind == "falling":
+        return np.sort(g.integers(0, m, n))[::-1].astype(np.int32)
+    if kind == "const":
+        return np.full(n, m // 3, np.int32)
+    if kind == "runs":  # runs of 5,000 elements and some of a few
+        lens = np.where(g.random(n // 1000 + 2) < 0.5, 5000, g.integers(1, 70, n // 1000 + 2))
+        return np.resize(np.repeat(g.integers(0, m, lens.size), lens), n).astype(np.int32)
+    hot = g.random(n) < 0.8  # one bin with four fifths of the elements
+    return np.where(hot, m - 5, g.integers(0, m, n)).astype(np.int32)
+
+
+# One range of bins, several, buckets with few and with many records an item.
+@pytest.mark.parametrize("kind", ["sorted", "falling", "const", "runs", "hot"])
+@pytest.mark.parametrize("n,m", [(700001, 9001), (1 << 20, 60000), (1050001, 100003), (1 << 21, 131073)])
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("op", ["add", "mul", "max", "min"])
+def test_clustered_indices(ops, orc, op, dtype, n, m, kind):
+    g = workloads.rng(n + m)
+    inds = clustered(kind, n, m, g)
+    inds[::1009] = -1
+    inds[500::1013] = m
+    vs = g.standard_normal(n).astype(np.float32 if dtype == "f32" else np.float64)
+    if op == "mul":
+        vs = np.exp(1e-3 * vs).astype(vs.dtype)
+        vs[::5003] = 0.0
+        vs[2501::5003] = -0.0
+    elif op != "add":
+        vs = (np.round(vs * 8) / 8).astype(vs.dtype)
+        vs[::13] = -0.0
+    ref = orc.hist(op, inds, vs, m)
+    bar = TOL_F32 if dtype == "f32" else 1e-12
+    pad = np.zeros(1, np.int32), np.zeros(1, vs.dtype)
+    odd = dev(np.r_[pad[0], inds])[1:], dev(np.r_[pad[1], vs])[1:]  # no 16-byte alignment
+    for di, dv, counts in ((dev(inds), dev(vs), False), (dev(inds), dev(vs), True), (*odd, False)):
+        hs, aux = ops.hist(op, di, dv, m, counts=counts)
+        if counts:
+            assert np.array_equal(host(aux["count"]), ref["count"])
+        if op in ("min", "max"):
+            assert np.array_equal(host(aux["winner"]), ref["winner"])
+            got = host(hs)
+            assert np.array_equal(got, ref["hs"]) and np.array_equal(np.signbit(got), np.signbit(ref["hs"]))
+        else:
+            assert rel_l2(host(hs), ref["hs"]) <= bar
+        if op == "mul":
+            assert np.array_equal(host(aux["z"]), ref["z"])
+            assert rel_l2(host(aux["p"]), ref["p"]) <= bar
+
+
+@pytest.mark.parametrize("op,dtype,n,m", [("add", "f32", 1 << 24, 65536), ("mul", "f32", 1 << 21, 40000),
+                                          ("mul", "f32", 1 << 21, 300000), ("max", "f64", 1 << 22, 100000),
+                                          ("add", "f64", 1 << 22, 300000)])
+def test_clustered_indices_take_no_multiple(ops, op, dtype, n, m):
+    # sorted indices, or all in one bin, within four times the uniform ones' time
+    # (they were 6 to 560 times it where equal neighbours queued at one word or
+    # one block of a chunk, or few waves of an item, had all the work)
+    g = workloads.rng(n + m)
+    vs = dev(np.exp(1e-3 * g.standard_normal(n)).astype(np.float32 if dtype == "f32" else np.float64))
+
+    def best(inds):
+        di, ts = dev(inds), []
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            ops.hist(op, di, vs, m)
+            b.record()
+            b.synchronize()
+            ts.append(a.elapsed_time(b))
+        return min(ts)
+
+    uniform = best(g.integers(0, m, n).astype(np.int32))
+    for kind in ("sorted", "const"):
+        assert best(clustered(kind, n, m, g)) <= 4 * uniform, kind
