@@ -1544,27 +1544,36 @@ static HistPlan hist_plan(int op, int64_t n, int64_t m, bool counts) {
 }
 
 // Where the form in ranges does not serve: the bucket-partitioned path takes m
-// beyond one block's LDS, up to the buckets of the scan block.  Short inputs keep the LDS bin cache with global
-// atomics: the partition's eight launches cost more than the atomics, which
-// are fewer where the cache holds a good part of the bins.  Primal and VJP with
-// the cache and with the partition, in us:
-//   FP32 +, Zipf, m = 20,000: n = 800,000 32, 43; 1.6 10^6 48, 49; 3.2 10^6 129, 60
-//   FP32 +, Zipf, m = 200,000: 800,000 41, 49; 1.6 10^6 92, 56
-//   FP32 max, uniform, m = 10^6: 800,000 53, 54; 1.6 10^6 86, 55
-//   FP64 max (a second sweep for the winners), Zipf, m = 20,000: 1.6 10^6 61,
-//   71; 3.2 10^6 91, 71
+// beyond one block's LDS, up to the buckets of the scan block.  Short inputs keep
+// the LDS bin cache with global atomics: the partition's eight launches cost more
+// than the atomics, fewer where the cache holds a good part of the bins.  That
+// depends on the indices, so both are weighed; with the cache and with the
+// partition, uniform and Zipf indices, us:
+//   FP32 +: n = 500,000, m = 300,000 35, 29 and 26, 39; 800,000 49, 32 and 35, 40;
+//   m = 10^6 44, 43 and 32, 51; 1,048,000 55, 38 and 45, 46; max within 10% of +
+//   with counts (two more atomics an element): n = 300,000, m = 60,000 46, 30 and
+//   28, 43; 500,000 58, 31 and 34, 46; 800,000, m = 9,000 59, 37 and 32, 40; m =
+//   10^6, 500,000 51, 45 and 35, 64
+//   FP64 max (a second sweep for the winners), Zipf, m = 20,000, with the
+//   adjoint: 1.6 10^6 61, 71; 3.2 10^6 91, 71
 // A product's updates are compare-and-swap loops, so its line is lower (FP32,
 // n = 2^17, m = 30,000: 72, 40).  An FP64 record takes 12 bytes: past 2^25 of
 // them the scratch would be half a gigabyte and more for calls whose scratch has
 // always been a few words per bin, so those keep the cache (2^25 into 10^6 bins:
 // 646 us here with 460 MB).
+// Sorted indices, or all in one bin, are the cache's best case (one read of the
+// input): n = 2^25 FP64 max into 65,536 bins 232 and 214 us, here 361 and 389,
+// where uniform indices take 1,700 and 330; FP64 + into 300,000 bins sorted 186,
+// here 263 (uniform 1,430, 270).
 static bool use_partition(int op, bool f32, int64_t n, int64_t m, bool counts) {
     const int full_slots = (int)(kHistLds / slot_bytes(op, counts, false));
     if (m <= full_slots || ceil_div(m, kPartBins) > kPartMaxBuckets) return false;
     if (!f32 && n > (int64_t)1 << 25) return false;
     if (op == PVJP_MUL) return n >= ((int64_t)1 << 17);
+    if (f32 && counts) return n >= (m < 20480 ? (int64_t)5 << 17 : m <= 1 << 19 ? (int64_t)3 << 16 : (int64_t)7 << 16);
+    if (f32) return n >= (m <= 65536 ? (int64_t)3 << 19 : m <= 1 << 19 ? (int64_t)5 << 17 : (int64_t)15 << 16);
     if (m > 65536) return n >= ((int64_t)1 << 20);
-    return n >= (f32 || op == PVJP_ADD ? (int64_t)3 << 19 : (int64_t)1 << 21);
+    return n >= (op == PVJP_ADD ? (int64_t)3 << 19 : (int64_t)1 << 21);
 }
 
 // The form in ranges reads the input once per range, the partition reads and
@@ -1574,9 +1583,13 @@ static bool use_partition(int op, bool f32, int64_t n, int64_t m, bool counts) {
 //   max: 122,000 439, 390; 140,000 (7) 436, 461
 //   *: 27,000 (2) 646, 524; 65,536 (5) 634, 643
 //   + FP64: 65,536 398, 310; 100,000 426, 351
-// Short inputs, + FP32 Zipf, with the bin cache (below) and with ranges:
-//   n = 400,000: m = 10,000 (one range) 25.7, 24.8; 20,000 25.8, 25.7; 40,000 28, 36
-//   n = 10^6: 10,000 31, 25; 40,000 42, 37; 65,000 47, 41; 100,000 53, 47
+// Short inputs, + FP32, with the bin cache (below) and with ranges, uniform and
+// Zipf indices:
+//   n = 300,000: m = 9,000 (one range) 19, 16 and 20, 15; 30,000 (two) 26, 21 and
+//   20, 21; 60,000 (three) 29, 26 and 22, 26; 100,000 (five) 27, 26 and 22, 27
+//   n = 500,000: 30,000 37, 23 and 26, 23; 60,000 40, 26 and 27, 26; 100,000 37, 29
+//   and 25, 29
+//   n = 800,000: 60,000 59, 26 and 44, 26; 100,000 52, 30 and 32, 31
 // Bins that fit 64 KB (FULL mode): m = 4,099, n = 2^21 27.5, 25.8; 2^22 31.6,
 // 29.0; 2^23 45, 46; FP64 2^22 39, 34; m = 8,000 2^22 36.5, 33.5, max 2^25 111,
 // 101; with fewer bins there is little to gain (m = 1,024, n = 2^23: 39, 42).
@@ -1589,7 +1602,7 @@ static bool use_range(int op, bool f32, int64_t n, int64_t m, bool counts) {
     if (R > (op == PVJP_MUL ? 4 : keys ? 6 : 5)) return false;
     if (m <= kHistLds / (int64_t)slot_bytes(op, false, false)) return m >= 4096 && n >= (int64_t)1 << 21;
     if (op == PVJP_MUL) return n >= (int64_t)1 << 17;
-    return n >= (R == 1 ? (int64_t)3 << 17 : (int64_t)15 << 16);
+    return n >= (R == 1 || (f32 && R <= 3) ? (int64_t)3 << 17 : f32 ? (int64_t)1 << 19 : (int64_t)15 << 16);
 }
 
 struct RangePlan {

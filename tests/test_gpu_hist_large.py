@@ -263,3 +263,27 @@ def test_clustered_indices_take_no_multiple(ops, op, dtype, n, m):
     uniform = best(g.integers(0, m, n).astype(np.int32))
     for kind in ("sorted", "const"):
         assert best(clustered(kind, n, m, g)) <= 4 * uniform, kind
+
+
+# On either side of the lengths where FP32 inputs leave the bin cache.
+@pytest.mark.parametrize("op", ["add", "max"])
+@pytest.mark.parametrize("n,m,counts", [(3 << 17, 40000, False), (3 << 17, 61440, False), (1 << 19, 61441, False),
+                                        (1 << 19, 102400, False), (5 << 17, 122881, False), (15 << 16, 600000, False),
+                                        (5 << 17, 9000, True), (3 << 16, 20480, True), (7 << 16, 600000, True)])
+@pytest.mark.parametrize("below", [1, 0])
+def test_short_input_lines(ops, orc, op, n, m, counts, below):
+    n -= below
+    inds, vs, _ = workloads.hist(n, m, "zipf", "f32", seed=n + m)
+    inds[::101] = -1
+    inds[7::103] = m
+    if op == "max":
+        vs = (np.round(vs * 8) / 8).astype(vs.dtype)
+        vs[::13] = -0.0
+    ref = orc.hist(op, inds, vs, m)
+    hs, aux = ops.hist(op, dev(inds), dev(vs), m, counts=counts)
+    if counts:
+        assert np.array_equal(host(aux["count"]), ref["count"])
+    if op == "max":
+        assert np.array_equal(host(aux["winner"]), ref["winner"]) and np.array_equal(host(hs), ref["hs"])
+    else:
+        assert rel_l2(host(hs), ref["hs"]) <= TOL_F32
