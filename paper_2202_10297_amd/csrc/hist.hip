@@ -1634,7 +1634,7 @@ struct PartLayout {
     size_t toff, D, Ploc, ctot, clast, bitems, istart, itile, rval, rhi, rbin, pacc, pcnt, paux, total;
 };
 
-static PartLayout part_layout(int64_t n, int64_t m, bool f32, int64_t most = kPartSeg) {
+static PartLayout part_layout(int64_t n, int64_t m, bool f32, bool lae = false) {
     PartLayout L{};
     // 512 work items (two a CU) or more, of up to 2^16 records: a short input's
     // buckets would otherwise be one item each (n = 10^6, m = 100,000 Zipf,
@@ -1642,8 +1642,15 @@ static PartLayout part_layout(int64_t n, int64_t m, bool f32, int64_t most = kPa
     // long last wave (n = 2^26, m = 2^20, items of 2^17 and 2^16: max Zipf 565,
     // 548 us; + Zipf 716, 689; max uniform 540, 515; with 2^15 550, 686, 521).
     L.seg = (int)kPartSegMin;
-    while (L.seg < most && (int64_t)L.seg * 512 < n) L.seg *= 2;
+    while (L.seg < (lae ? 2 : 1) * kPartSeg && (int64_t)L.seg * (lae ? 256 : 512) < n) L.seg *= 2;
     L.nb = (int)ceil_div(m, kPartBins);
+    // Log-add-exp merges by an exponential per item and bin: half as many items,
+    // of up to 2^17 records (n = 2^26 Zipf, m = 2^16: 0.63 ms, with 2^16 0.72; n =
+    // 2^24, m = 20,000 with 512, 256 and 128 items, uniform 239, 201, 184 us, Zipf
+    // 316, 225, 229), and, with many buckets, whole buckets of uniform indices
+    // (n = 2^24, m = 10^6, items of 2^15, 2^16 and of that length, uniform 184,
+    // 188, 141, Zipf 283, 278, 307; of 2^17 141 and 362).
+    if (lae && L.nb >= 128) L.seg = (int)std::min(2 * kPartSeg, std::max<int64_t>(L.seg, n / L.nb * 9 / 8));
     L.ntiles = (int)ceil_div(n > 0 ? n : 1, kTile);
     L.nchunks = (int)ceil_div(L.ntiles, kColChunk);
     L.items_max = ceil_div(n > 0 ? n : 1, L.seg) + L.nb;
@@ -1756,15 +1763,11 @@ bool hist_lae_partition_ok(pvjp_dtype dtype, int64_t m) {
     return dtype == PVJP_F32 && use_partition(PVJP_ADD, true, INT64_MAX, m, false);  // whatever the length
 }
 
-// Items of up to 2^17 records: the merge forms an exponential per item and bin
-// (n = 2^26 Zipf, m = 2^16: 0.63 ms, with 2^16 0.72; m = 2^20 0.86, 0.89).
-constexpr int64_t kLaeSeg = (int64_t)1 << 17;
-
-size_t hist_lae_partition_bytes(int64_t n, int64_t m) { return part_layout(n, m, true, kLaeSeg).total; }
+size_t hist_lae_partition_bytes(int64_t n, int64_t m) { return part_layout(n, m, true, true).total; }
 
 void hist_lae_partitioned(const int32_t* inds, const float* x, int64_t n, int32_t m, float* hs, char* ws,
                           hipStream_t st) {
-    const PartLayout L = part_layout(n, m, true, kLaeSeg);
+    const PartLayout L = part_layout(n, m, true, true);
     part_sort<float, PVJP_ADD>(inds, x, n, m, L, ws, st);
     double* psum = reinterpret_cast<double*>(ws + L.pacc);
     uint32_t* pmax = reinterpret_cast<uint32_t*>(ws + L.pcnt);

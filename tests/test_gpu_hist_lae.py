@@ -138,3 +138,19 @@ def test_hist_lae_bench_shape_sampled_bins(ops, orc):
         assert abs(got[b] - ref) <= 1e-6 * max(1.0, abs(ref)), b
         rxb = orc.reduce_generic_vjp("logaddexp", [x[sel]], [float(hb[b])])[0]
         assert rel_l2(xb[sel], rxb) <= TOL_F32, b
+
+
+@pytest.mark.parametrize("kind", ["uniform", "zipf", "sorted"])
+@pytest.mark.parametrize("n,m", [((1 << 22) + 5, 600001), ((1 << 22) + 5, 520192), (1 << 20, 524289), ((1 << 22) - 1, 20001)])
+def test_hist_lae_item_lengths(ops, n, m, kind):
+    # items of a bucket's length (128 buckets and more), of which a bucket of
+    # uniform indices is one, and of a power of two; FP32 sums are FP64 per item
+    inds, x, _ = workloads.hist(n, m, "uniform" if kind == "sorted" else kind, "f32", seed=n + m)
+    if kind == "sorted":
+        inds = np.sort(inds)
+    got = host(ops.hist_lae(dev(inds), dev(x), m)).astype(np.float64)
+    with np.errstate(divide="ignore"):
+        ref = np.log(np.bincount(inds, weights=np.exp(x.astype(np.float64)), minlength=m))
+    fin = np.isfinite(ref)
+    assert np.array_equal(np.isneginf(got), np.isneginf(ref))
+    assert rel_l2(got[fin], ref[fin]) <= 1e-6
