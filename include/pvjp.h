@@ -218,15 +218,23 @@ pvjp_status pvjp_reduce_vjp(pvjp_op op, pvjp_dtype dtype, const void* x, int64_t
 /* ------------------------------------------------------------------------ */
 
 /* Workspace bytes for pvjp_hist (device memory, zero-initialised once by the
- * caller, owned by the caller, reusable across calls on one stream).  Small
- * m (the bins fit one block's LDS): per-block partial histograms, O(m) with
- * a few hundred rows.  Up to about 10^5 bins, long inputs: partial histograms
- * in ranges of bins, up to 288 rows of m.  Beyond that and at most 2^22 bins, or
- * with counts, or FP64 extremes: every tile of 8192 elements is sorted by
- * bucket, with 4 (FP64: 8) bytes per element for its value and 4 for its bin
- * in the bucket (min/max: with the position in the tile), plus per-tile bucket
- * offsets and per-item partials.  The bytes cover calls with and without
- * counts. */
+ * caller, owned by the caller, reusable across calls on one stream).  Bins that
+ * fit one block's LDS (8,192 of them; 5,461 for products or with counts, 4,096
+ * with both): per-block partial histograms, O(m) with a few hundred rows.  With
+ * more bins, by length, type and operator:
+ *  - short inputs (FP32 +, min and max below 196,608 to 983,040 elements by m and
+ *    counts, products below 2^17, FP64 below 2^20 to 2^21; FP64 + of up to 102,400
+ *    bins below 393,216 to 983,040) and more than 2^22 bins keep an LDS cache of
+ *    bins in front of device-memory atomics: up to 12 bytes a bin;
+ *  - up to 102,400 bins (products 54,528, FP32 min and max 122,880; not FP64 min
+ *    and max, not with counts): partial histograms in ranges of bins, up to 288
+ *    rows of 12 bytes a bin, 106 MB at most;
+ *  - otherwise every tile of 8192 elements is sorted by bucket, with 4 (FP64: 8)
+ *    bytes per element for its value and 4 for its bin in the bucket (min/max:
+ *    with the position in the tile), plus per-tile bucket offsets and per-item
+ *    partials.
+ * The bytes cover calls with and without counts and, beyond one block's LDS, every
+ * call with fewer elements or bins: a workspace for the longest serves them all. */
 size_t pvjp_hist_ws_bytes(pvjp_op op, pvjp_dtype dtype, int64_t n, int64_t m);
 /* Which path pvjp_hist takes for (op, dtype, n, m, counts != 0), for tests
  * and tuning: info[0] = PVJP_HIST_PATH_*; for the partitioned path info[1] =

@@ -1557,10 +1557,8 @@ static HistPlan hist_plan(int op, int64_t n, int64_t m, bool counts) {
 //   FP64 max (a second sweep for the winners), Zipf, m = 20,000, with the
 //   adjoint: 1.6 10^6 61, 71; 3.2 10^6 91, 71
 // A product's updates are compare-and-swap loops, so its line is lower (FP32,
-// n = 2^17, m = 30,000: 72, 40).  An FP64 record takes 12 bytes: past 2^25 of
-// them the scratch would be half a gigabyte and more for calls whose scratch has
-// always been a few words per bin, so those keep the cache (2^25 into 10^6 bins:
-// 646 us here with 460 MB).
+// n = 2^17, m = 30,000: 72, 40).  An FP64 record takes 12 bytes of workspace, an
+// FP32 one 8.
 // Sorted indices, or all in one bin, are the cache's best case (one read of the
 // input): n = 2^25 FP64 max into 65,536 bins 232 and 214 us, here 361 and 389,
 // where uniform indices take 1,700 and 330; FP64 + into 300,000 bins sorted 186,
@@ -1568,7 +1566,6 @@ static HistPlan hist_plan(int op, int64_t n, int64_t m, bool counts) {
 static bool use_partition(int op, bool f32, int64_t n, int64_t m, bool counts) {
     const int full_slots = (int)(kHistLds / slot_bytes(op, counts, false));
     if (m <= full_slots || ceil_div(m, kPartBins) > kPartMaxBuckets) return false;
-    if (!f32 && n > (int64_t)1 << 25) return false;
     if (op == PVJP_MUL) return n >= ((int64_t)1 << 17);
     if (f32 && counts) return n >= (m < 20480 ? (int64_t)5 << 17 : m <= 1 << 19 ? (int64_t)3 << 16 : (int64_t)7 << 16);
     if (f32) return n >= (m <= 65536 ? (int64_t)3 << 19 : m <= 1 << 19 ? (int64_t)5 << 17 : (int64_t)15 << 16);
@@ -1595,11 +1592,13 @@ static bool use_partition(int op, bool f32, int64_t n, int64_t m, bool counts) {
 // 101; with fewer bins there is little to gain (m = 1,024, n = 2^23: 39, 42).
 // Counts would take half the bins again and FP64 extremes need their winners:
 // both keep the other paths.
-static bool use_range(int op, bool f32, int64_t n, int64_t m, bool counts) {
+static int range_most(int op, bool f32) {  // ranges, at most
     const bool keys = op == PVJP_MIN || op == PVJP_MAX;
-    if (counts || (keys && !f32)) return false;
+    return op == PVJP_MUL ? 4 : !keys ? 5 : f32 ? 6 : 0;
+}
+static bool use_range(int op, bool f32, int64_t n, int64_t m, bool counts) {
     const int64_t R = ceil_div(m, range_bins(op));
-    if (R > (op == PVJP_MUL ? 4 : keys ? 6 : 5)) return false;
+    if (counts || R > range_most(op, f32)) return false;
     if (m <= kHistLds / (int64_t)slot_bytes(op, false, false)) return m >= 4096 && n >= (int64_t)1 << 21;
     if (op == PVJP_MUL) return n >= (int64_t)1 << 17;
     return n >= (R == 1 || (f32 && R <= 3) ? (int64_t)3 << 17 : f32 ? (int64_t)1 << 19 : (int64_t)15 << 16);
@@ -1616,11 +1615,14 @@ struct RangePlan {
 // than the updates (n = 400,000, m = 10,000: 29.4 us with chunks of 32,768, 24.8
 // with 8,192 or 16,384; m = 65,000, n = 10^6: 45.6, 42.4 with 16,384, 41.0 with
 // 8,192).
+static int64_t range_chunks(int64_t n, int64_t R) {  // at most
+    return std::min<int64_t>(kXcds * (kCuCount / kXcds / R), std::max<int64_t>(kXcds, n / 8192 / kXcds * kXcds));
+}
 static RangePlan range_plan(int op, int64_t n, int64_t m) {
     RangePlan P{};
     P.R = (int)ceil_div(m, range_bins(op));
     P.per = (int32_t)ceil_div(m, P.R);
-    P.C = std::min<int64_t>(kXcds * (kCuCount / kXcds / P.R), std::max<int64_t>(kXcds, n / 8192 / kXcds * kXcds));
+    P.C = range_chunks(n, P.R);
     const int64_t quantum = 4 * kRangeBlock;
     P.chunk = ceil_div(ceil_div(n, P.C), quantum) * quantum;
     P.C = ceil_div(ceil_div(n, P.chunk), kXcds) * kXcds;
@@ -1630,11 +1632,11 @@ static RangePlan range_plan(int op, int64_t n, int64_t m) {
 struct PartLayout {
     int nb, ntiles, nchunks;
     int seg;  // records per work item
-    int64_t items_max;
+    int64_t items_max, items_cap;  // for this n, for any up to it
     size_t toff, D, Ploc, ctot, clast, bitems, istart, itile, rval, rhi, rbin, pacc, pcnt, paux, total;
 };
 
-static PartLayout part_layout(int64_t n, int64_t m, bool f32, bool lae = false) {
+static PartLayout part_layout(int64_t n, int64_t m, bool f32, bool aux, bool lae = false) {
     PartLayout L{};
     // 512 work items (two a CU) or more, of up to 2^16 records: a short input's
     // buckets would otherwise be one item each (n = 10^6, m = 100,000 Zipf,
@@ -1654,6 +1656,9 @@ static PartLayout part_layout(int64_t n, int64_t m, bool f32, bool lae = false) 
     L.ntiles = (int)ceil_div(n > 0 ? n : 1, kTile);
     L.nchunks = (int)ceil_div(L.ntiles, kColChunk);
     L.items_max = ceil_div(n > 0 ? n : 1, L.seg) + L.nb;
+    // shorter inputs have shorter items, so that some have more of them
+    L.items_cap = std::max(std::min<int64_t>(ceil_div(n > 0 ? n : 1, kPartSegMin), lae ? 256 : 512),
+                           ceil_div(n > 0 ? n : 1, kPartSeg)) + L.nb;
     const size_t slots = (size_t)L.ntiles * kTile;
     size_t o = 0;
     auto take = [&](size_t bytes) {
@@ -1668,31 +1673,42 @@ static PartLayout part_layout(int64_t n, int64_t m, bool f32, bool lae = false) 
     L.clast = take((size_t)L.nb * L.nchunks * 4);
     L.bitems = take((size_t)L.nb * 4);
     L.istart = take((size_t)(L.nb + 1) * 4);
-    L.itile = take((size_t)L.items_max * 4);
+    L.itile = take((size_t)L.items_cap * 4);
     L.rval = take(slots * 4);
     L.rhi = take(f32 ? 0 : slots * 4);
     L.rbin = take(slots * 4);  // 2 bytes per record for + and *, 4 for min/max
-    L.pacc = take((size_t)L.items_max * kPartBins * 8);
-    L.pcnt = take((size_t)L.items_max * kPartBins * 4);
-    L.paux = take((size_t)L.items_max * kPartBins * 4);
+    L.pacc = take((size_t)L.items_cap * kPartBins * 8);
+    L.pcnt = take((size_t)L.items_cap * kPartBins * 4);
+    L.paux = take(aux ? (size_t)L.items_cap * kPartBins * 4 : 0);
     L.total = o;
     return L;
 }
 
-// Covers both plans (with and without counts): the FULL/CACHE choice and the
-// grid depend on whether counts are requested.
+// Whether a bin keeps a word beside its accumulator (part_aux).
+static bool aux_word(int op, bool f32) { return op == PVJP_MUL || (!f32 && (op == PVJP_MIN || op == PVJP_MAX)); }
+
+// Covers calls with and without counts, and whatever form a call with fewer
+// elements, or with fewer bins beyond one block's LDS, takes: a workspace for the
+// longest input serves the shorter ones.
 static size_t hist_ws(int op, int64_t n, int64_t m, bool f32) {
     size_t body = 0;
+    bool beyond = false;
     for (int counts = 0; counts < 2; ++counts) {
-        if (use_range(op, f32, n, m, counts != 0)) {
+        const HistPlan P = hist_plan(op, n, m, counts != 0);
+        // per-block partials and the merge slices: acc 8 + zeros 4 + counts 4 (no
+        // fewer than the ranges', which take bins that fit LDS too)
+        if (!P.cache) body = std::max(body, align_up((size_t)(P.grid + kMergeSlices) * m * 16, 256));
+        beyond |= P.cache;
+    }
+    if (beyond) {
+        const int64_t most = (int64_t)kPartMaxBuckets * kPartBins;
+        if (f32 && op != PVJP_MUL ? m <= most : n >= (op == PVJP_MUL ? (int64_t)1 << 17 : (int64_t)1 << 20))
+            body = std::max(body, part_layout(n, std::min(m, most), f32, aux_word(op, f32)).total);
+        for (int64_t R = 1; R <= range_most(op, f32); ++R) {
             // chunks' partials and the merge slices: acc 8 + zeros 4
-            body = std::max(body, align_up((size_t)(range_plan(op, n, m).C + kMergeSlices) * m * 12, 256));
-        } else if (use_partition(op, f32, n, m, counts != 0)) {
-            body = std::max(body, part_layout(n, m, f32).total);
-        } else {
-            // per-block partials and the merge slices: acc 8 + zeros 4 + counts 4
-            const HistPlan P = hist_plan(op, n, m, counts != 0);
-            if (!P.cache) body = std::max(body, align_up((size_t)(P.grid + kMergeSlices) * m * 16, 256));
+            const int64_t bins = std::min<int64_t>(m, R * range_bins(op));
+            if (n >= (op == PVJP_MUL ? (int64_t)1 << 17 : (int64_t)3 << 17))
+                body = std::max(body, align_up((size_t)(range_chunks(n, R) + kMergeSlices) * bins * 12, 256));
         }
     }
     return align_up((size_t)m * 8, 256) + (op == PVJP_MUL ? align_up((size_t)m * 4, 256) : 0) + body;
@@ -1733,7 +1749,7 @@ static void part_sort(const int32_t* inds, const T* vs, int64_t n, int32_t m, co
 template <class T, int OP>
 static void run_partitioned(const int32_t* inds, const T* vs, int64_t n, int32_t m, int32_t* count, char* w,
                             size_t off, const HistOut<T>& o, hipStream_t st) {
-    const PartLayout L = part_layout(n, m, sizeof(T) == 4);
+    const PartLayout L = part_layout(n, m, sizeof(T) == 4, part_aux<T, OP>());
     char* base = w + off;
     part_sort<T, OP>(inds, vs, n, m, L, base, st);
     const uint32_t* D = reinterpret_cast<const uint32_t*>(base + L.D);
@@ -1763,11 +1779,11 @@ bool hist_lae_partition_ok(pvjp_dtype dtype, int64_t m) {
     return dtype == PVJP_F32 && use_partition(PVJP_ADD, true, INT64_MAX, m, false);  // whatever the length
 }
 
-size_t hist_lae_partition_bytes(int64_t n, int64_t m) { return part_layout(n, m, true, true).total; }
+size_t hist_lae_partition_bytes(int64_t n, int64_t m) { return part_layout(n, m, true, false, true).total; }
 
 void hist_lae_partitioned(const int32_t* inds, const float* x, int64_t n, int32_t m, float* hs, char* ws,
                           hipStream_t st) {
-    const PartLayout L = part_layout(n, m, true, true);
+    const PartLayout L = part_layout(n, m, true, false, true);
     part_sort<float, PVJP_ADD>(inds, x, n, m, L, ws, st);
     double* psum = reinterpret_cast<double*>(ws + L.pacc);
     uint32_t* pmax = reinterpret_cast<uint32_t*>(ws + L.pcnt);
@@ -1969,7 +1985,7 @@ extern "C" pvjp_status pvjp_hist_plan_info(pvjp_op op, pvjp_dtype dtype, int64_t
         info[0] = PVJP_HIST_PATH_PARTITION;
         info[1] = kPartBins;
         // runs start within seg records; a run is below kTile
-        info[2] = part_layout(n, m, dtype == PVJP_F32).seg + kTile;
+        info[2] = part_layout(n, m, dtype == PVJP_F32, false).seg + kTile;
         info[3] = ceil_div(m, kPartBins);
     } else {
         info[0] = hist_plan(op, n, m, counts != 0).cache ? PVJP_HIST_PATH_CACHE : PVJP_HIST_PATH_LDS;

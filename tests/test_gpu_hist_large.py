@@ -287,3 +287,19 @@ def test_short_input_lines(ops, orc, op, n, m, counts, below):
         assert np.array_equal(host(aux["winner"]), ref["winner"]) and np.array_equal(host(hs), ref["hs"])
     else:
         assert rel_l2(host(hs), ref["hs"]) <= TOL_F32
+
+
+@pytest.mark.parametrize("op", ["add", "max", "mul"])
+def test_long_f64(ops, orc, op):
+    # more than 2^25 FP64 records of 12 bytes
+    n, m = (1 << 25) + 4097, 131073
+    inds, vs, _ = workloads.hist(n, m, "uniform", "f64", seed=7)
+    if op == "mul":
+        vs = np.exp(1e-3 * vs)
+        vs[::50003] = 0.0
+    ref = orc.hist(op, inds, vs, m)
+    hs, aux = ops.hist(op, dev(inds), dev(vs), m)
+    if op == "max":
+        assert np.array_equal(host(aux["winner"]), ref["winner"]) and np.array_equal(host(hs), ref["hs"])
+    else:
+        assert rel_l2(host(hs), ref["hs"]) <= 1e-12
