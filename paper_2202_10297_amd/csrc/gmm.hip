@@ -30,6 +30,8 @@
 // and v_k and applies the parameter maps.
 #include <math.h>
 
+#include <algorithm>
+
 #include "common.h"
 #include "prims.h"
 
@@ -1291,10 +1293,21 @@ struct GmmLayout {
 // part only, and the FP64 log-likelihood of few points keeps the FP32 chains'
 // rounding (the two forms differ by about 5e-8 N^(-1/2) of it).  At least five
 // components keep most of a block's eight waves busy.
-static bool gmm_split(int64_t N, int K) { return N >= ((int64_t)1 << 17) && K >= 5; }
+constexpr int64_t kGmmSplitN = (int64_t)1 << 17;
+static bool gmm_split(int64_t N, int K) { return N >= kGmmSplitN && K >= 5; }
 
 static GmmLayout gmm_layout(int64_t N, int D, int K) {
     GmmLayout L{};
+    const int64_t n1 = N > 0 ? N : 1;
+    // Chunks, and (max, sum) entries of component ranges, of this input or any
+    // shorter one, some of which have more of them: of the FP32 form first.
+    int64_t nch_most = 1, sums_most = 0;
+    {
+        const int64_t target = std::max<int64_t>(4096 / K, 1), n = std::min(n1, gmm_split(N, K) ? kGmmSplitN : n1);
+        nch_most = std::max(std::min(ceil_div(n, 128), target), ceil_div(n, 16384));
+        const int64_t batches = ceil_div(K, D == 64 ? 2 : 4);
+        if (batches > 1) sums_most = std::min(n * batches, 128 * (1024 + std::min<int64_t>(ceil_div(n, 128), 1024)));
+    }
     const int RT = D / 32;
     const int NF = 16 * RT * (RT + 1) / 2, NGT = RT * (RT + 1) / 2;
     L.split = gmm_split(N, K);
@@ -1305,6 +1318,7 @@ static GmmLayout gmm_layout(int64_t N, int D, int K) {
         for (int64_t r = 1;; ++r) {
             const int64_t per = 256 * r / groups > 0 ? 256 * r / groups : 1;
             L.chunk = ceil_div(ceil_div(N, per), 64) * 64;
+            nch_most = std::max(nch_most, per);
             if (L.chunk <= 32768) break;
         }
         L.nch = ceil_div(N, L.chunk);
@@ -1316,6 +1330,8 @@ static GmmLayout gmm_layout(int64_t N, int D, int K) {
         if (rows < 1) rows = 1;
         L.kper = (int)ceil_div(K, rows);
         L.ny = (int)ceil_div(K, L.kper);
+        if (K >= 32)
+            sums_most = std::max(sums_most, std::min(N * (K / 16), 256 * (4096 + std::min<int64_t>(L.fgrid, 4096))));
     } else {
         // About 4,096 blocks of at least 128 points.  Fewer are faster for small N
         // (objective and gradient at N = 10,007, D = 32, K = 50 with 1,024, 2,048
@@ -1350,13 +1366,13 @@ static GmmLayout gmm_layout(int64_t N, int D, int K) {
     L.Qs = take(L.split ? (size_t)K * (RT * (RT + 1) * 3 * 64 + D / 4) * 16 : 0);
     L.cvec = take((size_t)K * D * 4);
     L.bias = take((size_t)K * 8);
-    L.fparts = take((size_t)L.fgrid * 8);
+    L.fparts = take((size_t)ceil_div(n1, 128) * 8);
     L.lse = take((size_t)(N > 0 ? N : 1) * 8);
-    L.gpart = take((size_t)K * L.nch * NGT * 1024 * 4);
-    L.vpart = take((size_t)K * L.nch * D * 4);
-    L.wpart = take((size_t)K * L.nch * 8);
+    L.gpart = take((size_t)K * nch_most * NGT * 1024 * 4);
+    L.vpart = take((size_t)K * nch_most * D * 4);
+    L.wpart = take((size_t)K * nch_most * 8);
     L.sred = take((size_t)K * (NGT * 1024 + D + 1) * 8);
-    L.msum = take(L.ny > 1 ? (size_t)L.ny * (N > 0 ? N : 1) * 16 : 0);
+    L.msum = take((size_t)sums_most * 16);
     L.total = o;
     return L;
 }

@@ -693,8 +693,10 @@ static HgLayout hg_layout(int64_t n, int64_t m, int K, size_t es) {
         o += align_up(bytes, 256);
         return at;
     };
-    L.cntb = take((size_t)L.nblk * kHgDigits * 4);
-    L.ctot = take((size_t)L.nchunks * kHgDigits * 4);
+    // chunks grow with the length: a shorter input may have more blocks, up to 2,048
+    const int64_t most = std::max(std::min<int64_t>(ceil_div(nn, kHgSub), 2048), L.nblk);
+    L.cntb = take((size_t)most * kHgDigits * 4);
+    L.ctot = take((size_t)ceil_div(most, kHgColChunk) * kHgDigits * 4);
     L.nvalid = take(4);
     L.recA = take((size_t)nn * buf_bytes);
     L.recB = take((size_t)nn * buf_bytes);

@@ -18,6 +18,8 @@
 // nearest.
 #include <math.h>
 
+#include <algorithm>
+
 #include "common.h"
 #include "prims.h"
 
@@ -691,45 +693,58 @@ static KmPlan km_plan(int64_t N, int D, int K) {
     // not fill the chip.  Objective and gradient, widest slices, these and twice
     // the blocks, us: N = 3,117, D = 64, K = 19 48, 38, 38; N = 5,000, D = 256, K =
     // 20 116, 82, 82; N = 30,000, D = 64, K = 50 60, 53, 53 (four times: 64).
+    const int64_t n0 = N > 0 ? N : 1;
+    auto width = [](int cps) { return cps <= 4 ? 4 : (cps <= 8 ? 8 : (cps <= 16 ? 16 : 32)); };
     p.cps = km_cps(D, K);
     while (p.cps > 4 && ceil_div(N, kKmPts) * ceil_div(K, p.cps) < kKmFill) p.cps = (p.cps + 1) / 2;
-    p.cpsT = p.cps <= 4 ? 4 : (p.cps <= 8 ? 8 : (p.cps <= 16 ? 16 : 32));
+    p.cpsT = width(p.cps);
     p.nslice = (int)ceil_div(K, p.cps);
+    // (point, slice) pairs and widened centres of any shorter input, which may
+    // have more slices: those of cps centres end where the step before fills the
+    // chip
+    int64_t pairs = 0, wide = 0;
+    for (int cps = km_cps(D, K), up = 0;; up = cps, cps = (cps + 1) / 2) {
+        const int64_t most = up ? kKmPts * ((kKmFill - 1) / ceil_div(K, up)) : n0;
+        pairs = std::max(pairs, std::min(n0, most) * ceil_div(K, cps));
+        wide = std::max(wide, ceil_div(K, cps) * width(cps));
+        if (cps <= 4) break;
+    }
     {
         const int64_t b = ceil_div(N > 0 ? N : 1, 256);
         p.sum_blocks = (int)(b < kKmSumBlocks ? b : kKmSumBlocks);
     }
     const int64_t n1 = N > 0 ? N : 1;
     p.small = K <= kKmSmallK && D <= 256;
+    int64_t want = 1024;  // about so many blocks
     if (p.small) {
         p.cpb = K;
         p.nslices_acc = 1;
-        p.chunk = ceil_div(n1, 1024);  // about 1024 blocks
+        p.chunk = ceil_div(n1, want);
         if (p.chunk < 64) p.chunk = 64;
     } else {
         p.cpb = 1024 / D;
         if (p.cpb > K) p.cpb = K;
         if (p.cpb < 1) p.cpb = 1;
         p.nslices_acc = (int)ceil_div(K, p.cpb);
-        int64_t want = ceil_div(1024, p.nslices_acc);  // enough blocks to fill the chip
-        if (want < 1) want = 1;
+        want = ceil_div(1024, p.nslices_acc);  // enough blocks to fill the chip
         p.chunk = ceil_div(n1, want);
         if (p.chunk < 64) p.chunk = 64;
         if (p.chunk > kKmChunkMax) p.chunk = kKmChunkMax;
     }
     p.nchunk = ceil_div(n1, p.chunk);
+    const int64_t chunks = std::max(std::min(ceil_div(n1, 64), want), p.nchunk);  // of any shorter input
     size_t o = 0;
     auto take = [&](size_t b) {
         const size_t at = o;
         o += align_up(b > 0 ? b : 1, 256);
         return at;
     };
-    p.cd = take((size_t)p.nslice * D * p.cpsT * 8);
-    p.bd = take((size_t)p.nslice * n1 * 8);
-    p.bk = take((size_t)p.nslice * n1 * 4);
+    p.cd = take((size_t)wide * D * 8);
+    p.bd = take((size_t)pairs * 8);
+    p.bk = take((size_t)pairs * 4);
     p.part = take((size_t)kKmSumBlocks * 8);
-    p.spart = take((size_t)p.nchunk * K * D * 8);
-    p.npart = take((size_t)p.nchunk * K * 4);
+    p.spart = take((size_t)chunks * K * D * 8);
+    p.npart = take((size_t)chunks * K * 4);
     if (km_near(N, D, K)) {
         p.near_ks = D <= 32 ? 2 : D <= 64 ? 4 : D <= 128 ? 8 : 16;
         p.near_tiles = (int)ceil_div(K, 32);
@@ -746,7 +761,10 @@ static KmPlan km_plan(int64_t N, int D, int K) {
         p.cst = take((size_t)p.near_tiles * 96 * 4);
         p.bad = take((size_t)p.near_tiles * 4);
         p.open = take((size_t)ceil_div(N, kKmPts) * 4);
-        p.near = take((size_t)p.near_slices * 2 * N * sizeof(KmNear));
+        int64_t entries = N;  // of any shorter input: s slices while 512 / s blocks or fewer
+        for (int64_t sl = 2; sl <= std::min(kKmNearSlices, p.near_tiles); ++sl)
+            entries = std::max(entries, sl * std::min(N, kKmNearPts * (ceil_div(512, sl - 1) - 1)));
+        p.near = take((size_t)entries * 2 * sizeof(KmNear));
     }
     p.total = o;
     return p;

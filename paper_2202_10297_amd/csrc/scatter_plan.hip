@@ -582,7 +582,7 @@ struct SpLayout {
     size_t cnt1, tsum1, total, cstart, nch2, chb2, cnt2, tsum2, wstart, rk1, rj1, rv1, rk, rj, rv, saved, bytes;
 };
 
-static SpLayout sp_layout(pvjp_dtype dtype, int64_t n, int64_t m) {
+static SpLayout sp_layout_of(pvjp_dtype dtype, int64_t n, int64_t m) {
     SpLayout L{};
     const size_t ts = dsize(dtype);
     L.s0 = dtype == PVJP_F64 ? sp_s0<double>() : sp_s0<float>();
@@ -620,6 +620,17 @@ static SpLayout sp_layout(pvjp_dtype dtype, int64_t n, int64_t m) {
     L.rv = take(mm * ts);
     L.saved = take(mm * ts);
     L.bytes = o;
+    return L;
+}
+
+// The plan's bytes also cover shorter arrays, some of which have more windows to
+// count than this one has coarse buckets.
+static SpLayout sp_layout(pvjp_dtype dtype, int64_t n, int64_t m) {
+    SpLayout L = sp_layout_of(dtype, n, m);
+    if (!L.one) {
+        const size_t b = sp_layout_of(dtype, kSpOneWindows << L.s0, m).bytes;
+        if (b > L.bytes) L.bytes = b;
+    }
     return L;
 }
 
