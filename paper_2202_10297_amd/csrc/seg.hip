@@ -493,8 +493,17 @@ __global__ __launch_bounds__(kSegBlock) void seg_vjp_fold_kernel(const T* __rest
 // tiles 5.2 TB/s (2,818 with each tile's loads behind the stores of the last and
 // the heads from a bitmap).  64 segments, 5 M elements, take 55 us with the folds
 // (1,150 while their chains were not cut), 2,048 1,480 (2,020).
+// Sixteen FP64 elements a thread fill the registers: with the next tile's inputs
+// among them the kernel takes 396, one wave a SIMD; without, held to two waves,
+// 2,000 segments of 64 .. 2^19 elements take 1,286 us (1,549 with them, 1,420 as
+// one launch over the tiles), 4,096 of 64 .. 2^14 141 (185, 183).
+template <class T, int IPT>
+constexpr bool seg_ahead() {
+    return sizeof(T) * IPT <= 64;
+}
+
 template <class T, int IPT, bool ACC>
-__global__ __launch_bounds__(kSegBlock) void seg_batch_vjp_kernel(
+__global__ __launch_bounds__(kSegBlock, (seg_ahead<T, IPT>() ? 1 : 2)) void seg_batch_vjp_kernel(
     const T* __restrict__ a, const T* __restrict__ b, const T* __restrict__ ya, const T* __restrict__ yb,
     int64_t total, int64_t nseg, const int64_t* __restrict__ offs, const int32_t* __restrict__ seg0,
     const T* __restrict__ ckpt, T* __restrict__ abar, T* __restrict__ bbar, const T* __restrict__ sum_ybar,
@@ -534,10 +543,12 @@ __global__ __launch_bounds__(kSegBlock) void seg_batch_vjp_kernel(
                 carry = seg_piece_carry<LinO<T>>(states, wk.x, wk.y, wtot_l);
             }
             SegVjpIn<T, IPT> in;
-            in.template load<true>(a, b, ya, yb, total, wk.first);
+            constexpr bool kAhead = seg_ahead<T, IPT>();
+            if (kAhead) in.template load<true>(a, b, ya, yb, total, wk.first);
             for (int64_t t = wk.first, end = t - wk.len; t > end; --t) {
+                if (!kAhead) in.template load<true>(a, b, ya, yb, total, t);
                 carry = seg_scan_vjp_tile<T, IPT, ACC>(a, b, ya, yb, total, ckpt, abar, bbar, t,
-                                                       t - 1 > end ? t - 1 : -1, in, carry, lds,
+                                                       kAhead && t - 1 > end ? t - 1 : -1, in, carry, lds,
                                                        run_heads<IPT>(bits, seg0, offs, nseg, t), wtot_p, wtot_l);
                 __syncthreads();
             }
