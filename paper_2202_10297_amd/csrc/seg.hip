@@ -202,11 +202,27 @@ __device__ __forceinline__ typename SegLinRec<T>::S seg_fwd_agg(const T* __restr
                                                                 const int32_t* __restrict__ seg0, int64_t tile,
                                                                 T* lds, uint32_t* bits,
                                                                 typename SegLinRec<T>::S* wtot) {
-    typename SegLinRec<T>::S e[IPT], tot;
+    using Op = SegLinRec<T>;
+    constexpr int TS = kSegBlock * IPT;
+    typename Op::S e[IPT], tot;
+    // The elements after the tile's last head: few of them need no tile (20,000
+    // segments of 64 .. 600 elements, FP32, a chain per tile: 38.6 us, now 35.8).
+    const int64_t head = offs[seg0[tile + 1]], left = (tile + 1) * TS - head;
+    if (left <= 4 * kSegBlock) {
+        if (left <= 0) return Op::id();  // the next tile starts at a head
+        const int64_t i0 = head + 4 * (int64_t)threadIdx.x, end = min((tile + 1) * TS, total);
+        typename Op::S agg = Op::id();
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (i0 + j < end) agg = Op::comb(agg, typename Op::S{a[i0 + j], b[i0 + j], 0u, 0u});
+        (void)block_exclusive_scan<Op, kSegBlock, false>(agg, tot, wtot);
+        __syncthreads();
+        return tot;
+    }
     SegFwdIn<T, IPT> in;
     in.load(a, b, total, tile);
     const auto agg = seg_fwd_run<T, IPT>(in, run_heads<IPT>(bits, seg0, offs, nseg, tile), lds, e);
-    (void)block_exclusive_scan<SegLinRec<T>, kSegBlock, false>(agg, tot, wtot);
+    (void)block_exclusive_scan<Op, kSegBlock, false>(agg, tot, wtot);
     __syncthreads();  // the tile's LDS is free
     return tot;
 }

@@ -168,3 +168,33 @@ def test_cut_chains(batch, orc, dtype, case):
         ab, bb, _ = plan.vjp(dev(a), dev(b), dev(ya), dev(yb), ck, sum_ybar=dev(sy))
         assert rel_l2([host(A), host(B)], R[:2]) <= tol(dtype)
         assert rel_l2([host(ab), host(bb)], R[2:]) <= tol(dtype)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("tile", [1024, 2048, 4096])
+def test_tails_after_the_last_head(batch, orc, dtype, tile):
+    # the last head of a tile 0, 1, 1,023, 1,024 and 1,025 elements before its end
+    # (up to 1,024 are folded without the tile) and at its start, the next tile
+    # with and without a head
+    starts, t = [0], 0
+    for left in (0, 1, 2, 1023, 1024, 1025, tile):
+        for more in (0, 3 * tile + 5):
+            t += tile
+            if 0 <= left <= tile:
+                starts.append(t - left)
+            t += more - more % tile
+            starts.append(t + 7)
+            t += tile
+    starts = np.unique(starts)
+    lengths = np.diff(np.r_[starts, t + 11]).astype(np.int64)
+    a, b, ya, yb, sy = seg_inputs(lengths, dtype, seed=tile)
+    plan = batch.SegPlan(lengths, torch.float32 if dtype == "f32" else torch.float64, tile=tile)
+    A, B, ck = plan.scan(dev(a), dev(b))
+    ab, bb, _ = plan.vjp(dev(a), dev(b), dev(ya), dev(yb), ck, sum_ybar=dev(sy))
+    refs = [[], [], [], []]
+    for s, e in zip(plan.offsets[:-1], plan.offsets[1:]):
+        for lst, v in zip(refs, orc.linrec_scan(a[s:e], b[s:e]) + orc.linrec_scan_vjp(a[s:e], b[s:e], ya[s:e], yb[s:e])):
+            lst.append(v)
+    R = [np.concatenate(x) for x in refs]
+    assert rel_l2([host(A), host(B)], R[:2]) <= tol(dtype)
+    assert rel_l2([host(ab), host(bb)], R[2:]) <= tol(dtype)
