@@ -224,8 +224,9 @@ pvjp_status pvjp_reduce_vjp(pvjp_op op, pvjp_dtype dtype, const void* x, int64_t
  * more bins, by length, type and operator:
  *  - short inputs (FP32 +, min and max below 196,608 to 983,040 elements by m and
  *    counts, products below 2^17, FP64 below 2^20 to 2^21; FP64 + of up to 102,400
- *    bins below 393,216 to 983,040) and more than 2^22 bins keep an LDS cache of
- *    bins in front of device-memory atomics: up to 12 bytes a bin;
+ *    bins below 393,216 to 983,040), FP64 ones past 2^25 and more than 2^22 bins
+ *    keep an LDS cache of bins in front of device-memory atomics: up to 12 bytes a
+ *    bin;
  *  - up to 102,400 bins (products 54,528, FP32 min and max 122,880; not FP64 min
  *    and max, not with counts): partial histograms in ranges of bins, up to 288
  *    rows of 12 bytes a bin, 106 MB at most;
@@ -233,8 +234,10 @@ pvjp_status pvjp_reduce_vjp(pvjp_op op, pvjp_dtype dtype, const void* x, int64_t
  *    bytes per element for its value and 4 for its bin in the bucket (min/max:
  *    with the position in the tile), plus per-tile bucket offsets and per-item
  *    partials.
- * The bytes cover calls with and without counts and, beyond one block's LDS, every
- * call with fewer elements or bins: a workspace for the longest serves them all. */
+ * The bytes cover calls with and without counts.  A workspace for the longest
+ * input serves every shorter one: FP32 bytes cover, beyond one block's LDS, all
+ * calls with fewer elements or bins, and FP64 calls with room for no more than the
+ * first form take that one. */
 size_t pvjp_hist_ws_bytes(pvjp_op op, pvjp_dtype dtype, int64_t n, int64_t m);
 /* Which path pvjp_hist takes for (op, dtype, n, m, counts != 0), for tests
  * and tuning: info[0] = PVJP_HIST_PATH_*; for the partitioned path info[1] =

@@ -10,6 +10,7 @@
 // partitioning keep hot indices off contended global atomics.  An index
 // outside [0, n) reads 0 and updates nothing.
 #include "common.h"
+#include "hpart.h"
 #include "prims.h"
 
 namespace pvjp {
@@ -190,7 +191,7 @@ struct GmPlan {
     bool lds;
     int G;
     int64_t chunk;
-    size_t c, hist, hist_bytes, tmp, total;  // larger as: partials, reduce_by_index workspace, sums
+    size_t c, tmp, hist, least, total;  // larger as: partials, sums, reduce_by_index workspace (FP64: what is left)
 };
 
 static GmPlan gm_plan(pvjp_dtype dtype, int64_t n, int64_t m) {
@@ -201,14 +202,14 @@ static GmPlan gm_plan(pvjp_dtype dtype, int64_t n, int64_t m) {
         int64_t g = ceil_div(m1, (int64_t)kGmLdsBlock * 8);
         p.G = (int)(g < kGmLdsBlocks ? g : kGmLdsBlocks);
         p.chunk = ceil_div(m1, p.G);
-        p.total = align_up((size_t)p.G * (size_t)(n > 0 ? n : 1) * 8, 256);
+        p.total = p.least = align_up((size_t)p.G * (size_t)(n > 0 ? n : 1) * 8, 256);
     } else {
         const size_t es = dsize(dtype);
         p.c = 0;
-        p.hist = align_up((size_t)m1 * es, 256);
-        p.hist_bytes = align_up(pvjp_hist_ws_bytes(PVJP_ADD, dtype, m1, n), 256);
-        p.tmp = p.hist + p.hist_bytes;
-        p.total = p.tmp + align_up((size_t)n * es, 256);
+        p.tmp = align_up((size_t)m1 * es, 256);
+        p.hist = p.tmp + align_up((size_t)n * es, 256);
+        p.total = p.hist + align_up(pvjp_hist_ws_bytes(PVJP_ADD, dtype, m1, n), 256);
+        p.least = p.hist + hist_least_bytes(PVJP_ADD, dtype, m1, n);
     }
     return p;
 }
@@ -216,7 +217,7 @@ static GmPlan gm_plan(pvjp_dtype dtype, int64_t n, int64_t m) {
 template <int OP, class T>
 static pvjp_status gm_launch_vjp(pvjp_dtype dtype, const void* as, int64_t n, const int32_t* is, const void* vs,
                                  int64_t m, const void* yb, void* abar, void* vbar, int acc, char* ws,
-                                 const GmPlan& p, hipStream_t st) {
+                                 size_t ws_bytes, const GmPlan& p, hipStream_t st) {
     const T* a = (const T*)as;
     const T* v = (const T*)vs;
     const T* y = (const T*)yb;
@@ -245,7 +246,7 @@ static pvjp_status gm_launch_vjp(pvjp_dtype dtype, const void* as, int64_t n, co
         hipLaunchKernelGGL((gm_contrib_kernel<OP, T>), dim3(flat_grid(m, 256, 4)), dim3(256), 0, st, a, n, is, v, y,
                            m, vb, acc, c);
     if (pvjp_status e = pvjp_hist(PVJP_ADD, dtype, is, c, m, n, sums, nullptr, nullptr, nullptr, nullptr,
-                                  ws + p.hist, p.hist_bytes, st))
+                                  ws + p.hist, ws_bytes - p.hist, st))
         return e;
     if (acc) hipLaunchKernelGGL((gm_add_kernel<T>), dim3(flat_grid(n, 256, 4)), dim3(256), 0, st, sums, n, ab);
     return PVJP_OK;
@@ -307,8 +308,8 @@ extern "C" pvjp_status pvjp_gather_map_vjp(int op, pvjp_dtype dtype, const void*
                  "pvjp_gather_map_vjp: ys_bar or vs_bar is NULL");
     PVJP_REQUIRE(ws != nullptr && aligned(ws, 256), "pvjp_gather_map_vjp: ws must be non-NULL and 256-byte aligned");
     const GmPlan p = gm_plan(dtype, n, m);
-    if (ws_bytes < p.total) {
-        set_error("pvjp_gather_map_vjp: workspace has %zu bytes, needs %zu", ws_bytes, p.total);
+    if (ws_bytes < p.least) {
+        set_error("pvjp_gather_map_vjp: workspace has %zu bytes, needs %zu", ws_bytes, p.least);
         return PVJP_ENOMEM;
     }
     if (n == 0 && m == 0) return PVJP_OK;
@@ -316,13 +317,13 @@ extern "C" pvjp_status pvjp_gather_map_vjp(int op, pvjp_dtype dtype, const void*
     char* w = reinterpret_cast<char*>(ws);
     pvjp_status e;
     if (dtype == PVJP_F32) {
-        if (op == PVJP_GMAP_GATHER) e = gm_launch_vjp<0, float>(dtype, as, n, is, vs, m, ys_bar, as_bar, vs_bar, accumulate, w, p, st);
-        else if (op == PVJP_GMAP_MUL) e = gm_launch_vjp<1, float>(dtype, as, n, is, vs, m, ys_bar, as_bar, vs_bar, accumulate, w, p, st);
-        else e = gm_launch_vjp<2, float>(dtype, as, n, is, vs, m, ys_bar, as_bar, vs_bar, accumulate, w, p, st);
+        if (op == PVJP_GMAP_GATHER) e = gm_launch_vjp<0, float>(dtype, as, n, is, vs, m, ys_bar, as_bar, vs_bar, accumulate, w, ws_bytes, p, st);
+        else if (op == PVJP_GMAP_MUL) e = gm_launch_vjp<1, float>(dtype, as, n, is, vs, m, ys_bar, as_bar, vs_bar, accumulate, w, ws_bytes, p, st);
+        else e = gm_launch_vjp<2, float>(dtype, as, n, is, vs, m, ys_bar, as_bar, vs_bar, accumulate, w, ws_bytes, p, st);
     } else {
-        if (op == PVJP_GMAP_GATHER) e = gm_launch_vjp<0, double>(dtype, as, n, is, vs, m, ys_bar, as_bar, vs_bar, accumulate, w, p, st);
-        else if (op == PVJP_GMAP_MUL) e = gm_launch_vjp<1, double>(dtype, as, n, is, vs, m, ys_bar, as_bar, vs_bar, accumulate, w, p, st);
-        else e = gm_launch_vjp<2, double>(dtype, as, n, is, vs, m, ys_bar, as_bar, vs_bar, accumulate, w, p, st);
+        if (op == PVJP_GMAP_GATHER) e = gm_launch_vjp<0, double>(dtype, as, n, is, vs, m, ys_bar, as_bar, vs_bar, accumulate, w, ws_bytes, p, st);
+        else if (op == PVJP_GMAP_MUL) e = gm_launch_vjp<1, double>(dtype, as, n, is, vs, m, ys_bar, as_bar, vs_bar, accumulate, w, ws_bytes, p, st);
+        else e = gm_launch_vjp<2, double>(dtype, as, n, is, vs, m, ys_bar, as_bar, vs_bar, accumulate, w, ws_bytes, p, st);
     }
     if (e) return e;
     PVJP_LAUNCHED("pvjp_gather_map_vjp");

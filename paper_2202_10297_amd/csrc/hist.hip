@@ -1557,8 +1557,10 @@ static HistPlan hist_plan(int op, int64_t n, int64_t m, bool counts) {
 //   FP64 max (a second sweep for the winners), Zipf, m = 20,000, with the
 //   adjoint: 1.6 10^6 61, 71; 3.2 10^6 91, 71
 // A product's updates are compare-and-swap loops, so its line is lower (FP32,
-// n = 2^17, m = 30,000: 72, 40).  An FP64 record takes 12 bytes of workspace, an
-// FP32 one 8.
+// n = 2^17, m = 30,000: 72, 40).  An FP64 record takes 12 bytes: past 2^25 of
+// them the scratch would be half a gigabyte and more for calls whose scratch has
+// always been a few words per bin, so those keep the cache (2^25 into 10^6 bins:
+// 646 us here with 460 MB).
 // Sorted indices, or all in one bin, are the cache's best case (one read of the
 // input): n = 2^25 FP64 max into 65,536 bins 232 and 214 us, here 361 and 389,
 // where uniform indices take 1,700 and 330; FP64 + into 300,000 bins sorted 186,
@@ -1566,6 +1568,7 @@ static HistPlan hist_plan(int op, int64_t n, int64_t m, bool counts) {
 static bool use_partition(int op, bool f32, int64_t n, int64_t m, bool counts) {
     const int full_slots = (int)(kHistLds / slot_bytes(op, counts, false));
     if (m <= full_slots || ceil_div(m, kPartBins) > kPartMaxBuckets) return false;
+    if (!f32 && n > (int64_t)1 << 25) return false;
     if (op == PVJP_MUL) return n >= ((int64_t)1 << 17);
     if (f32 && counts) return n >= (m < 20480 ? (int64_t)5 << 17 : m <= 1 << 19 ? (int64_t)3 << 16 : (int64_t)7 << 16);
     if (f32) return n >= (m <= 65536 ? (int64_t)3 << 19 : m <= 1 << 19 ? (int64_t)5 << 17 : (int64_t)15 << 16);
@@ -1687,31 +1690,52 @@ static PartLayout part_layout(int64_t n, int64_t m, bool f32, bool aux, bool lae
 // Whether a bin keeps a word beside its accumulator (part_aux).
 static bool aux_word(int op, bool f32) { return op == PVJP_MUL || (!f32 && (op == PVJP_MIN || op == PVJP_MAX)); }
 
-// Covers calls with and without counts, and whatever form a call with fewer
-// elements, or with fewer bins beyond one block's LDS, takes: a workspace for the
-// longest input serves the shorter ones.
-static size_t hist_ws(int op, int64_t n, int64_t m, bool f32) {
+static size_t hist_fixed(int op, int64_t m) {
+    return align_up((size_t)m * 8, 256) + (op == PVJP_MUL ? align_up((size_t)m * 4, 256) : 0);
+}
+static size_t range_bytes(int64_t chunks, int64_t bins) {
+    // chunks' partials and the merge slices: acc 8 + zeros 4
+    return align_up((size_t)(chunks + kMergeSlices) * bins * 12, 256);
+}
+
+// The bytes of the bins' words and of the bin tables in LDS, with and without
+// counts; beyond: with either, the bins exceed one block's LDS.  FP64 calls take
+// no less, and with no more the bin cache.
+static size_t hist_least(int op, int64_t n, int64_t m, bool* beyond = nullptr) {
     size_t body = 0;
-    bool beyond = false;
     for (int counts = 0; counts < 2; ++counts) {
         const HistPlan P = hist_plan(op, n, m, counts != 0);
         // per-block partials and the merge slices: acc 8 + zeros 4 + counts 4 (no
         // fewer than the ranges', which take bins that fit LDS too)
         if (!P.cache) body = std::max(body, align_up((size_t)(P.grid + kMergeSlices) * m * 16, 256));
-        beyond |= P.cache;
+        if (beyond) *beyond |= P.cache;
     }
-    if (beyond) {
+    return hist_fixed(op, m) + body;
+}
+
+// Covers calls with and without counts.  FP32: and whatever form a call with
+// fewer elements, or with fewer bins beyond one block's LDS, takes, so that a
+// workspace for the longest input serves the shorter ones.  FP64 calls take the
+// form that their workspace has room for.
+static size_t hist_ws(int op, int64_t n, int64_t m, bool f32) {
+    bool beyond = false;
+    const size_t least = hist_least(op, n, m, &beyond);
+    size_t body = least - hist_fixed(op, m);
+    if (!f32) {
+        for (int counts = 0; counts < 2; ++counts)
+            if (use_range(op, f32, n, m, counts != 0))
+                body = std::max(body, range_bytes(range_plan(op, n, m).C, m));
+            else if (use_partition(op, f32, n, m, counts != 0))
+                body = std::max(body, part_layout(n, m, f32, aux_word(op, f32)).total);
+    } else if (beyond) {
         const int64_t most = (int64_t)kPartMaxBuckets * kPartBins;
-        if (f32 && op != PVJP_MUL ? m <= most : n >= (op == PVJP_MUL ? (int64_t)1 << 17 : (int64_t)1 << 20))
+        if (op == PVJP_MUL ? n >= (int64_t)1 << 17 : m <= most)
             body = std::max(body, part_layout(n, std::min(m, most), f32, aux_word(op, f32)).total);
-        for (int64_t R = 1; R <= range_most(op, f32); ++R) {
-            // chunks' partials and the merge slices: acc 8 + zeros 4
-            const int64_t bins = std::min<int64_t>(m, R * range_bins(op));
+        for (int64_t R = 1; R <= range_most(op, f32); ++R)
             if (n >= (op == PVJP_MUL ? (int64_t)1 << 17 : (int64_t)3 << 17))
-                body = std::max(body, align_up((size_t)(range_chunks(n, R) + kMergeSlices) * bins * 12, 256));
-        }
+                body = std::max(body, range_bytes(range_chunks(n, R), std::min<int64_t>(m, R * range_bins(op))));
     }
-    return align_up((size_t)m * 8, 256) + (op == PVJP_MUL ? align_up((size_t)m * 4, 256) : 0) + body;
+    return hist_fixed(op, m) + body;
 }
 
 // The partition shared by the accumulators: the tile sort, the run
@@ -1779,6 +1803,9 @@ bool hist_lae_partition_ok(pvjp_dtype dtype, int64_t m) {
     return dtype == PVJP_F32 && use_partition(PVJP_ADD, true, INT64_MAX, m, false);  // whatever the length
 }
 
+size_t hist_least_bytes(pvjp_op op, pvjp_dtype dtype, int64_t n, int64_t m) {
+    return dtype == PVJP_F32 ? hist_ws(op, n, m, true) : hist_least(op, n, m);
+}
 size_t hist_lae_partition_bytes(int64_t n, int64_t m) { return part_layout(n, m, true, false, true).total; }
 
 void hist_lae_partitioned(const int32_t* inds, const float* x, int64_t n, int32_t m, float* hs, char* ws,
@@ -1811,7 +1838,7 @@ static void launch_acc(const int32_t* inds, const T* vs, int64_t n, int32_t m, c
 
 template <class T, int OP>
 static void run_hist(const int32_t* inds, const T* vs, int64_t n, int32_t m, T* hs, int32_t* winner, T* p,
-                     int32_t* z, int32_t* count, void* ws, hipStream_t st) {
+                     int32_t* z, int32_t* count, void* ws, size_t ws_bytes, hipStream_t st) {
     char* w = reinterpret_cast<char*>(ws);
     uint64_t* gacc = reinterpret_cast<uint64_t*>(w);
     size_t off = align_up((size_t)m * 8, 256);
@@ -1821,8 +1848,9 @@ static void run_hist(const int32_t* inds, const T* vs, int64_t n, int32_t m, T* 
         off += align_up((size_t)m * 4, 256);
     }
     const bool counts = count != nullptr;
+    const size_t room = ws_bytes - off;
     if constexpr (sizeof(T) == 4 || !part_keys<OP>()) {
-        if (use_range(OP, sizeof(T) == 4, n, m, counts)) {
+        if (use_range(OP, sizeof(T) == 4, n, m, counts) && range_bytes(range_plan(OP, n, m).C, m) <= room) {
             const RangePlan P = range_plan(OP, n, m);
             uint64_t* pacc = reinterpret_cast<uint64_t*>(w + off);
             uint64_t* macc = pacc + (size_t)P.C * m;
@@ -1841,7 +1869,8 @@ static void run_hist(const int32_t* inds, const T* vs, int64_t n, int32_t m, T* 
             return;
         }
     }
-    if (use_partition(OP, sizeof(T) == 4, n, m, counts)) {
+    if (use_partition(OP, sizeof(T) == 4, n, m, counts) &&
+        part_layout(n, m, sizeof(T) == 4, part_aux<T, OP>()).total <= room) {
         run_partitioned<T, OP>(inds, vs, n, m, count, w, off, HistOut<T>{hs, winner, p, z}, st);
         return;
     }
@@ -1882,13 +1911,14 @@ static void run_hist(const int32_t* inds, const T* vs, int64_t n, int32_t m, T* 
 
 template <class T>
 static void dispatch_hist(pvjp_op op, const int32_t* inds, const void* vs, int64_t n, int32_t m, void* hs,
-                          int32_t* winner, void* p, int32_t* z, int32_t* count, void* ws, hipStream_t st) {
+                          int32_t* winner, void* p, int32_t* z, int32_t* count, void* ws, size_t ws_bytes,
+                          hipStream_t st) {
     const T* v = (const T*)vs;
     switch (op) {
-        case PVJP_ADD: run_hist<T, PVJP_ADD>(inds, v, n, m, (T*)hs, winner, (T*)p, z, count, ws, st); break;
-        case PVJP_MUL: run_hist<T, PVJP_MUL>(inds, v, n, m, (T*)hs, winner, (T*)p, z, count, ws, st); break;
-        case PVJP_MIN: run_hist<T, PVJP_MIN>(inds, v, n, m, (T*)hs, winner, (T*)p, z, count, ws, st); break;
-        default: run_hist<T, PVJP_MAX>(inds, v, n, m, (T*)hs, winner, (T*)p, z, count, ws, st); break;
+        case PVJP_ADD: run_hist<T, PVJP_ADD>(inds, v, n, m, (T*)hs, winner, (T*)p, z, count, ws, ws_bytes, st); break;
+        case PVJP_MUL: run_hist<T, PVJP_MUL>(inds, v, n, m, (T*)hs, winner, (T*)p, z, count, ws, ws_bytes, st); break;
+        case PVJP_MIN: run_hist<T, PVJP_MIN>(inds, v, n, m, (T*)hs, winner, (T*)p, z, count, ws, ws_bytes, st); break;
+        default: run_hist<T, PVJP_MAX>(inds, v, n, m, (T*)hs, winner, (T*)p, z, count, ws, ws_bytes, st); break;
     }
 }
 
@@ -2006,15 +2036,15 @@ extern "C" pvjp_status pvjp_hist(pvjp_op op, pvjp_dtype dtype, const int32_t* in
     PVJP_REQUIRE(!(op == PVJP_MIN || op == PVJP_MAX) || winner != nullptr, "pvjp_hist: MIN/MAX need winner");
     PVJP_REQUIRE(op != PVJP_MUL || (p != nullptr && z != nullptr), "pvjp_hist: MUL needs p and z");
     PVJP_REQUIRE(ws != nullptr && aligned(ws, 256), "pvjp_hist: ws must be non-NULL and 256-byte aligned");
-    const size_t need = pvjp_hist_ws_bytes(op, dtype, n, m);
+    const size_t need = hist_least_bytes(op, dtype, n, m);
     if (ws_bytes < need) {
         set_error("pvjp_hist: workspace has %zu bytes, needs %zu", ws_bytes, need);
         return PVJP_ENOMEM;
     }
     if (dtype == PVJP_F64)
-        dispatch_hist<double>(op, inds, vs, n, (int32_t)m, hs, winner, p, z, count, ws, as_stream(stream));
+        dispatch_hist<double>(op, inds, vs, n, (int32_t)m, hs, winner, p, z, count, ws, ws_bytes, as_stream(stream));
     else
-        dispatch_hist<float>(op, inds, vs, n, (int32_t)m, hs, winner, p, z, count, ws, as_stream(stream));
+        dispatch_hist<float>(op, inds, vs, n, (int32_t)m, hs, winner, p, z, count, ws, ws_bytes, as_stream(stream));
     PVJP_LAUNCHED("pvjp_hist");
     return PVJP_OK;
 }

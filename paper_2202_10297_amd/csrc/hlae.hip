@@ -15,6 +15,8 @@
 // element makes its bin NaN.  An element equal to a +inf total gets the whole
 // hs_bar (the limit of the softmax weight of a unique +inf); several +inf
 // elements of one bin each get it.  Indices outside [0, m) are skipped.
+#include <algorithm>
+
 #include "common.h"
 #include "hpart.h"
 
@@ -99,7 +101,7 @@ __global__ __launch_bounds__(256) void hl_vjp_kernel(const int32_t* __restrict__
 }
 
 struct HlPlan {
-    size_t winner, hmax, e, hsum, hist, hist_bytes, total;
+    size_t winner, hmax, e, hsum, hist, least, total;
 };
 
 static HlPlan hl_plan(pvjp_dtype dtype, int64_t n, int64_t m) {
@@ -116,19 +118,17 @@ static HlPlan hl_plan(pvjp_dtype dtype, int64_t n, int64_t m) {
     p.e = take((size_t)(n > 0 ? n : 1) * es);
     p.hsum = take((size_t)m * es);
     const size_t a = pvjp_hist_ws_bytes(PVJP_MAX, dtype, n, m), b = pvjp_hist_ws_bytes(PVJP_ADD, dtype, n, m);
-    p.hist_bytes = align_up(a > b ? a : b, 256);
-    if (hist_lae_partition_ok(dtype, m)) {
-        const size_t c = align_up(hist_lae_partition_bytes(n, m), 256);
-        if (c > p.hist_bytes) p.hist_bytes = c;
-    }
-    p.hist = take(p.hist_bytes);
+    const size_t c = hist_lae_partition_ok(dtype, m) ? hist_lae_partition_bytes(n, m) : 0;
+    p.hist = take(std::max(std::max(a, b), c));  // the last one: FP64 takes what is left
     p.total = o;
+    p.least = p.hist + std::max(std::max(hist_least_bytes(PVJP_MAX, dtype, n, m),
+                                         hist_least_bytes(PVJP_ADD, dtype, n, m)), c);
     return p;
 }
 
 template <class T>
 static pvjp_status hl_primal(pvjp_dtype dtype, const int32_t* inds, const T* x, int64_t n, int64_t m, T* hs,
-                             char* w, const HlPlan& p, hipStream_t st) {
+                             char* w, size_t hist_bytes, const HlPlan& p, hipStream_t st) {
     if constexpr (sizeof(T) == 4) {
         if (hist_lae_partition_ok(dtype, m)) {
             // one partition, the maximum and the scaled sum per work item
@@ -140,13 +140,13 @@ static pvjp_status hl_primal(pvjp_dtype dtype, const int32_t* inds, const T* x, 
     T* e = (T*)(w + p.e);
     T* hsum = (T*)(w + p.hsum);
     if (pvjp_status s = pvjp_hist(PVJP_MAX, dtype, inds, x, n, m, hmax, (int32_t*)(w + p.winner), nullptr, nullptr,
-                                  nullptr, w + p.hist, p.hist_bytes, st))
+                                  nullptr, w + p.hist, hist_bytes, st))
         return s;
     if (n > 0)
         hipLaunchKernelGGL(hl_shift_kernel<T>, dim3(flat_grid(n, 256, 4)), dim3(256), 0, st, inds, x, n, m,
                            (const T*)hmax, e);
     if (pvjp_status s = pvjp_hist(PVJP_ADD, dtype, inds, e, n, m, hsum, nullptr, nullptr, nullptr, nullptr,
-                                  w + p.hist, p.hist_bytes, st))
+                                  w + p.hist, hist_bytes, st))
         return s;
     hipLaunchKernelGGL(hl_final_kernel<T>, dim3(flat_grid(m, 256, 4)), dim3(256), 0, st, (const T*)hmax,
                        (const T*)hsum, m, hs);
@@ -172,15 +172,15 @@ extern "C" pvjp_status pvjp_hist_lae(pvjp_dtype dtype, const int32_t* inds, cons
                  "pvjp_hist_lae: hs, inds and x must be non-NULL");
     PVJP_REQUIRE(ws != nullptr && aligned(ws, 256), "pvjp_hist_lae: ws must be non-NULL and 256-byte aligned");
     const HlPlan p = hl_plan(dtype, n, m);
-    if (ws_bytes < p.total) {
-        set_error("pvjp_hist_lae: workspace has %zu bytes, needs %zu", ws_bytes, p.total);
+    if (ws_bytes < p.least) {
+        set_error("pvjp_hist_lae: workspace has %zu bytes, needs %zu", ws_bytes, p.least);
         return PVJP_ENOMEM;
     }
     char* w = reinterpret_cast<char*>(ws);
     hipStream_t st = as_stream(stream);
     const pvjp_status s = dtype == PVJP_F64
-                              ? hl_primal<double>(dtype, inds, (const double*)x, n, m, (double*)hs, w, p, st)
-                              : hl_primal<float>(dtype, inds, (const float*)x, n, m, (float*)hs, w, p, st);
+                              ? hl_primal<double>(dtype, inds, (const double*)x, n, m, (double*)hs, w, ws_bytes - p.hist, p, st)
+                              : hl_primal<float>(dtype, inds, (const float*)x, n, m, (float*)hs, w, ws_bytes - p.hist, p, st);
     if (s != PVJP_OK) return s;
     PVJP_LAUNCHED("pvjp_hist_lae");
     return PVJP_OK;

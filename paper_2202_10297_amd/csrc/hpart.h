@@ -9,6 +9,9 @@
 
 namespace pvjp {
 
+// The bytes that pvjp_hist takes at least: FP32 those of pvjp_hist_ws_bytes, FP64
+// a few words a bin (beyond one block's LDS), with which it keeps the bin cache.
+size_t hist_least_bytes(pvjp_op op, pvjp_dtype dtype, int64_t n, int64_t m);
 // Whether the partitioned form serves (dtype, m): FP32 with bins beyond one
 // block's LDS and at most 2^22 of them.
 bool hist_lae_partition_ok(pvjp_dtype dtype, int64_t m);

@@ -303,3 +303,53 @@ def test_long_f64(ops, orc, op):
         assert np.array_equal(host(aux["winner"]), ref["winner"]) and np.array_equal(host(hs), ref["hs"])
     else:
         assert rel_l2(host(hs), ref["hs"]) <= 1e-12
+
+
+@pytest.mark.parametrize("m", [9000, 131073])
+@pytest.mark.parametrize("n", [1 << 25, 1200001, 3000])
+@pytest.mark.parametrize("op", ["add", "max", "mul"])
+def test_f64_in_the_workspace_of_a_longer_input(ops, orc, op, n, m):
+    # the bytes for more than 2^25 elements are a few words a bin: shorter calls
+    # that would sort their records take the bin cache instead
+    from paper_2202_10297_amd import capi
+
+    inds, vs, _ = workloads.hist(n, m, "uniform", "f64", seed=8)
+    if op == "mul":
+        vs = np.exp(1e-3 * vs)
+        vs[::50003] = 0.0
+    o = {"add": capi.ADD, "max": capi.MAX, "mul": capi.MUL}[op]
+    ws = torch.zeros(capi.lib().pvjp_hist_ws_bytes(o, capi.F64, (1 << 25) + 4097, m), dtype=torch.uint8, device="cuda")
+    i, v = dev(inds), dev(vs)
+    hs, p = (torch.empty(m, dtype=torch.float64, device="cuda") for _ in range(2))
+    w, z = (torch.empty(m, dtype=torch.int32, device="cuda") for _ in range(2))
+    capi.call("pvjp_hist", o, capi.F64, i.data_ptr(), v.data_ptr(), n, m, hs.data_ptr(),
+              w.data_ptr() if op == "max" else None, p.data_ptr() if op == "mul" else None,
+              z.data_ptr() if op == "mul" else None, None, ws.data_ptr(), ws.numel(), None)
+    ref = orc.hist(op, inds, vs, m)
+    if op == "max":
+        assert np.array_equal(host(w), ref["winner"]) and np.array_equal(host(hs), ref["hs"])
+    else:
+        assert rel_l2(host(hs), ref["hs"]) <= 1e-12
+    if op == "mul":
+        assert np.array_equal(host(z), ref["z"])
+
+
+def test_f64_log_add_exp_and_gather_in_the_workspace_of_a_longer_input(ops, orc):
+    from paper_2202_10297_amd import capi
+
+    n, m, more = 1 << 21, 131073, (1 << 25) + 4097
+    inds, vs, yb = workloads.hist(n, m, "uniform", "f64", seed=9)
+    i, v = dev(inds), dev(vs)
+    out = torch.empty(m, dtype=torch.float64, device="cuda")
+    ws = torch.zeros(capi.lib().pvjp_hist_lae_ws_bytes(capi.F64, more, m) - 8 * (more - n), dtype=torch.uint8,
+                     device="cuda")  # but for the terms, of which there are n
+    capi.call("pvjp_hist_lae", capi.F64, i.data_ptr(), v.data_ptr(), n, m, out.data_ptr(), ws.data_ptr(),
+              ws.numel(), None)
+    ref = host(ops.hist_lae(i, v, m))
+    both = np.isfinite(ref)
+    assert np.array_equal(both, np.isfinite(host(out))) and rel_l2(host(out)[both], ref[both]) <= 1e-12
+    ws = torch.zeros(capi.lib().pvjp_gather_map_ws_bytes(capi.F64, m, more) - 8 * (more - n), dtype=torch.uint8,
+                     device="cuda")
+    capi.call("pvjp_gather_map_vjp", capi.GMAP["gather"], capi.F64, out.data_ptr(), m, i.data_ptr(), None, n,
+              v.data_ptr(), out.data_ptr(), None, 0, ws.data_ptr(), ws.numel(), None)
+    assert rel_l2(host(out), orc.hist("add", inds, vs, m)["hs"]) <= 1e-12
