@@ -9,10 +9,12 @@
 //   s_ik = alpha_k + sum_d q_kd - |z_ik|^2 / 2,
 //   loglik = sum_i LSE_k s_ik - N LSE(alpha) - N D/2 log(2 pi).
 //
-// Forward sweep (gmm_fwd): per 32-point tile a wave forms Z^T = Q_k X^T with
-// FP32 MFMA 32x32x2 (only the lower-triangular 32x32 blocks of Q_k), squares
-// and sums z in FP64, and keeps an online FP64 log-sum-exp over k.  LSE_i is
-// the per-point checkpoint of the reverse sweep.
+// Forward sweep: per 32-point tile a wave forms Z^T = Q_k X^T on MFMA (only the
+// lower-triangular 32x32 blocks of Q_k), squares and sums z in FP64, and keeps an
+// online FP64 log-sum-exp over k.  LSE_i is the per-point checkpoint of the
+// reverse sweep.  Two forms of both sweeps: FP32 MFMA 32x32x2 (gmm_fwd_kernel,
+// gmm_bwd_kernel), and for long inputs (gmm_split) every FP32 value as three bf16
+// ones on bf16 MFMA (gmm_fwd_split_kernel, gmm_bwd_split_kernel).
 //
 // Return sweep: with w_ik = ell_bar * exp(s_ik - LSE_i) (s_ik recomputed,
 // Sec. 4.1), the parameter adjoints are
@@ -24,10 +26,12 @@
 //   mu_bar_k = Q_k^T v_k,
 //   q_bar_kd = W_k - exp(q_kd) G_k[d][d],
 //   l_bar_k[r,c] = -G_k[r][c]  (r > c).
-// Per (component, point chunk) blocks write FP32 partials of S_k and u_k
-// (accumulated in the MFMA registers over at most 4096 points per wave), which
-// are summed in FP64 in a fixed order; a per-component kernel then forms G_k
-// and v_k and applies the parameter maps.
+// Per component and point chunk FP32 partials of S_k and u_k = sum_i w_ik y_ik are
+// written, which are summed in FP64 in a fixed order; a per-component kernel then
+// forms G_k and v_k and applies the parameter maps.  The FP32 form accumulates in
+// the MFMA registers over at most 4,096 points per wave; the bf16 form sums each
+// tile of 32 or 64 points from zero and adds the tiles' sums over at most 32,768
+// points.
 #include <math.h>
 
 #include <algorithm>
@@ -66,8 +70,6 @@ template <int D>
 __device__ __forceinline__ int xs_at(int p, int c) {
     return p * D + (c ^ (D == 64 ? 2 * p : 2 * (p >> 1)));
 }
-// Weighted-Z tile [r][p] (32 points per row), swizzled the same way.
-__device__ __forceinline__ int zs_at(int r, int p) { return r * 32 + (p ^ (2 * ((r >> 1) & 15))); }
 
 constexpr double kLog2Pi = 1.8378770664093454835606594728112;
 
@@ -209,19 +211,6 @@ __device__ __forceinline__ double tile_znorm_lds(const float* qs, const float* c
         }
     }
     return nrm + __shfl_xor(nrm, 32, kWave);
-}
-
-template <int D>
-__device__ __forceinline__ void load_component(const float* __restrict__ Qf, const float* __restrict__ cvec, int k,
-                                               float (&qa)[Gm<D>::NF], float (&cl)[Gm<D>::RT][16]) {
-    using C = Gm<D>;
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int f = 0; f < C::NF; ++f) qa[f] = Qf[((int64_t)k * C::NF + f) * 64 + lane];
-#pragma unroll
-    for (int rt = 0; rt < C::RT; ++rt)
-#pragma unroll
-        for (int t = 0; t < 16; ++t) cl[rt][t] = cvec[(int64_t)k * D + 32 * rt + drow(t, lane)];
 }
 
 // LDS written by a wave and read back by other lanes of the same wave: a
@@ -599,8 +588,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
 // An FP32 value is exactly the sum of three bf16 values (8 bits of its
 // significand each, rounded to nearest, so the remainders have either sign):
 // x = h + m + l.  A product's terms hh, hm, mh, hl, lh, mm in bf16 MFMA with
-// FP32 accumulators leave out ml, lm, ll, below 2^-26 of it and of either
-// sign.  One 32x32x16 bf16 step takes 32 cycles, the eight 32x32x2 FP32 steps
+// FP32 accumulators leave out ml, lm, ll, up to 2^-24 of it (|m| <= 2^-8 |x|,
+// |l| <= 2^-17 |x|: one FP32 rounding) and of either sign.  Against 64 bits, on
+// standard normal points, D = 32 and 64, K = 25 to 200, N = 131,073 to 10^6, the
+// worst relative L2 error of the FP32 form and of this: log-likelihood 1.2e-9 and
+// 1.2e-9, alpha_bar 1.6e-7 and 1.6e-7, mu_bar 1.3e-6 and 2.8e-7, q_bar 1.2e-5 and
+// 5.2e-7, l_bar 2.4e-6 and 2.2e-7.  One 32x32x16 bf16 step takes 32 cycles, the eight 32x32x2 FP32 steps
 // it replaces 512, so six of them are 2.7 times faster.  Inputs, weights, the
 // sums over chunks, |z|^2 and the log-sum-exp keep their types.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));

@@ -254,3 +254,21 @@ def test_gmm_components_of_weight_zero(ops, N, D, K, where):
         assert all(np.isfinite(g).all() for g in got)
         for g, r in zip(got, ref):
             assert rel_l2(g[comps], r) <= TOL_F32
+
+
+@pytest.mark.parametrize("D", [32, 64])
+def test_gmm_long_chunks_exact(ops, D):
+    # K = 64 at 10^6 points: chunks of 31,296, near the 32,768 that the bf16 form
+    # sums in FP32 at most; its gradient against 64 bits, with and without s.
+    N, K = 1_000_000, 64
+    X, alpha, mu, q, l = workloads.gmm(N, D, K, seed=D)
+    comps = [0, 7, 8, 63]
+    rll, rlse, ref = _exact(X, alpha, mu, q, l, comps)
+    Xd, P = dev(X), [dev(a) for a in (alpha, mu, q, l)]
+    ll, lse, sck = ops.gmm_objective_ckpt(Xd, *P)
+    assert abs(host(ll)[0] - rll) <= TOL_F32 * abs(rll)
+    assert rel_l2(host(lse), rlse) <= TOL_F32
+    for s in (None, sck):
+        got = ops.gmm_vjp(Xd, *P, lse=lse, s=s)
+        for g, r in zip(got, ref):
+            assert rel_l2(host(g)[comps], r) <= TOL_F32
