@@ -846,7 +846,7 @@ __device__ __forceinline__ bf16x8 twice(bf16x8 v) {
 // interleaves the two itself: after every MFMA a short step of the vector work
 // that does not depend on it, held in place by a scheduling barrier (left to
 // itself the compiler groups them: 11.9 ms, now 11.2).  N = 10^6, D = 64, K =
-// 200: 26.5 -> 11.2 ms, 64% of it MFMA at the clock the card holds.
+// 200: 26.5 -> 11.2 ms, MFMA busy 54% of the cycles.
 template <int D, bool FROM_S>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void gmm_bwd_split_kernel(
     const float* __restrict__ X, int64_t N, int K, int64_t chunk, int nch, const bf16x8* __restrict__ Qs,

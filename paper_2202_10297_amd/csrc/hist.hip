@@ -9,11 +9,15 @@
 //            index among the elements equal to the bin's extreme;
 //   MUL: product of the non-zero values (FP64) and a zero count.
 // Each block privatises a sub-histogram in LDS.  When all m bins fit, a bin
-// is its own LDS slot; otherwise the LDS holds a direct-mapped cache of bins
+// is its own LDS slot (hist_acc_kernel, FULL).  Up to some 10^5 bins, long inputs
+// take the bins in ranges that fit LDS (hist_range_kernel); more bins, or counts,
+// or FP64 extremes have the records sorted into buckets of 4,096 bins first
+// (hpart_*).  For short inputs the LDS holds a direct-mapped cache of bins
 // (slot = bin mod S) that bins claim on first touch, and an element whose
 // slot belongs to another bin goes straight to a global atomic.  Hot bins
 // (Zipf) are touched early and often, so they end up LDS-resident.  At the
 // end each block merges its slots into the global FP64/u64 accumulators.
+// use_range and use_partition choose.
 //
 // Return sweep (the update formula of reduce with y_bar := hs_bar[inds[i]]):
 //   ADD: vs_bar[i] += hs_bar[inds[i]]            (a gather);
@@ -346,7 +350,7 @@ __global__ __launch_bounds__(kHistBlock) void hist_acc_kernel(
 // reads from L2, 10.7 TB/s.
 // Sorting the records into buckets first (hpart_tile_kernel and its
 // successors) moves each one out to HBM and back instead.  All kernels of the
-// primal, n = 2^26 FP32 values, +: 65,536 bins 295 -> 213 us, 20,000 328 -> 120.
+// primal, n = 2^26 FP32 values, +: 65,536 bins 289 -> 210 us, 20,000 317 -> 116.
 constexpr int kRangeBlock = 1024;
 // Bins of a range: 160 KB of accumulators (products: and zero counters), one
 // block per CU.
@@ -1564,7 +1568,8 @@ static HistPlan hist_plan(int op, int64_t n, int64_t m, bool counts) {
 // Sorted indices, or all in one bin, are the cache's best case (one read of the
 // input): n = 2^25 FP64 max into 65,536 bins 232 and 214 us, here 361 and 389,
 // where uniform indices take 1,700 and 330; FP64 + into 300,000 bins sorted 186,
-// here 263 (uniform 1,430, 270).
+// here 263 (uniform 1,430, 270); FP32 products, n = 10^6, into 300,000 bins sorted
+// 21, here 78.
 static bool use_partition(int op, bool f32, int64_t n, int64_t m, bool counts) {
     const int full_slots = (int)(kHistLds / slot_bytes(op, counts, false));
     if (m <= full_slots || ceil_div(m, kPartBins) > kPartMaxBuckets) return false;
