@@ -791,8 +791,8 @@ __global__ __launch_bounds__(256) void hist_vjp_winner_kernel(const int32_t* __r
 //      coalesced stores whatever the bucket count) and records the tile's
 //      bucket offsets;
 //   2. per bucket, an exclusive scan of its run lengths over the tiles;
-//      each bucket is split into work items of about seg records (kPartSegMin
-//      .. kPartSeg) made of whole runs;
+//      each bucket is split into work items of about seg records (kPartSegMin,
+//      products kTile, .. kPartSeg) made of whole runs;
 //   3. one block per work item walks its runs and accumulates the bucket's
 //      4096 bins in LDS, then writes them out as a partial;
 //   4. merge the partials of each bin in work-item order.
@@ -803,6 +803,7 @@ constexpr int kPartBins = 1 << kPartShift;
 constexpr int kPartMaxBuckets = 1024;
 constexpr int64_t kPartSeg = (int64_t)1 << 16;     // records per work item, at most
 constexpr int64_t kPartSegMin = (int64_t)1 << 14;  // and at least
+constexpr int64_t kPartMulItems = 256;             // of products, as long as one tile's records, at most
 constexpr int kPartScanThreads = 1024;
 constexpr int kTileThreads = 512;
 constexpr int kTileQuads = 4;                              // quads of elements per thread
@@ -810,7 +811,7 @@ constexpr int kTile = 4 * kTileThreads * kTileQuads;       // 8192 elements
 constexpr int kTileBucketsPerThread = kPartMaxBuckets / kTileThreads;
 static_assert(kTile <= 65536, "an element's position in its tile must fit 16 bits");
 static_assert(kPartMaxBuckets % kTileThreads == 0, "tile threads own whole groups of buckets in the scan");
-static_assert(kTile < kPartSegMin, "a work item must hold any single run");
+static_assert(kTile <= kPartSegMin, "a work item must hold any single run");
 
 // Stores of the first cnt staged words of a tile, 16 bytes per lane.
 __device__ __forceinline__ void tile_store_u32(uint32_t* __restrict__ dst, const uint32_t* stage, int cnt) {
@@ -1056,7 +1057,7 @@ __global__ __launch_bounds__(kPartScanThreads) void hpart_scan_kernel(const int3
 // The tiles [itile, itend) of every work item: item i of bucket b takes the
 // runs of b that start in [i * seg, (i + 1) * seg), where P[b][t] = Ploc + the
 // chunk prefix is the start of b's run in tile t within the bucket.  Non-empty
-// runs start at 0 and are shorter than seg, so up to the last non-empty run
+// runs start at 0 and are no longer than seg, so up to the last non-empty run
 // (at lastp, in the bucket's first word of clast) every such interval holds a
 // run start, and exactly one thread finds an item's first tile (for i > 0 the
 // first t with P[b][t] >= i * seg, which may be empty) and one its last.
@@ -1571,7 +1572,7 @@ static HistPlan hist_plan(int op, int64_t n, int64_t m, bool counts) {
 // input): n = 2^25 FP64 max into 65,536 bins 232 and 214 us, here 361 and 389,
 // where uniform indices take 1,700 and 330; FP64 + into 300,000 bins sorted 186,
 // here 263 (uniform 1,430, 270); FP32 products, n = 10^6, into 300,000 bins sorted
-// 21, here 78.
+// 21, here 59.
 static bool use_partition(int op, bool f32, int64_t n, int64_t m, bool counts) {
     const int full_slots = (int)(kHistLds / slot_bytes(op, counts, false));
     if (m <= full_slots || ceil_div(m, kPartBins) > kPartMaxBuckets) return false;
@@ -1646,16 +1647,28 @@ struct PartLayout {
     size_t toff, D, Ploc, ctot, clast, bitems, istart, itile, rval, rhi, rbin, pacc, pcnt, paux, total;
 };
 
-static PartLayout part_layout(int64_t n, int64_t m, bool f32, bool aux, bool lae = false) {
+// Whether a bin keeps a word beside its accumulator (part_aux).
+static bool aux_word(int op, bool f32) { return op == PVJP_MUL || (!f32 && (op == PVJP_MIN || op == PVJP_MAX)); }
+
+constexpr int kPartLae = -1;
+// kind: + * min max, or log-add-exp
+static PartLayout part_layout(int64_t n, int64_t m, bool f32, int kind) {
     PartLayout L{};
+    const bool lae = kind == kPartLae, mul = kind == PVJP_MUL, aux = aux_word(kind, f32);
     // 512 work items (two a CU) or more, of up to 2^16 records: a short input's
     // buckets would otherwise be one item each (n = 10^6, m = 100,000 Zipf,
     // primal and VJP: 116 us, now 48), and a long one's larger items leave a
     // long last wave (n = 2^26, m = 2^20, items of 2^17 and 2^16: max Zipf 565,
     // 548 us; + Zipf 716, 689; max uniform 540, 515; with 2^15 550, 686, 521).
-    L.seg = (int)kPartSegMin;
-    while (L.seg < (lae ? 2 : 1) * kPartSeg && (int64_t)L.seg * (lae ? 256 : 512) < n) L.seg *= 2;
+    // Products spend longest on an item (compare and swap, a scan per 64 records
+    // of runs of one bin): of one tile's records, where those are no more than
+    // one a CU (n = 800,000, m = 100,000, items of 16,384 and 8,192 records:
+    // sorted 74, 53 us, Zipf 133, 86, uniform 37, 36; with 270 of them, n = 2
+    // 10^6, uniform 42, 44.6).
     L.nb = (int)ceil_div(m, kPartBins);
+    const int64_t tiles = ceil_div(n > 0 ? n : 1, kTile);
+    L.seg = (int)(mul && tiles + L.nb <= kPartMulItems ? kTile : kPartSegMin);
+    while (L.seg < (lae ? 2 : 1) * kPartSeg && (int64_t)L.seg * (lae ? 256 : 512) < n) L.seg *= 2;
     // Log-add-exp merges by an exponential per item and bin: half as many items,
     // of up to 2^17 records (n = 2^26 Zipf, m = 2^16: 0.63 ms, with 2^16 0.72; n =
     // 2^24, m = 20,000 with 512, 256 and 128 items, uniform 239, 201, 184 us, Zipf
@@ -1663,12 +1676,13 @@ static PartLayout part_layout(int64_t n, int64_t m, bool f32, bool aux, bool lae
     // (n = 2^24, m = 10^6, items of 2^15, 2^16 and of that length, uniform 184,
     // 188, 141, Zipf 283, 278, 307; of 2^17 141 and 362).
     if (lae && L.nb >= 128) L.seg = (int)std::min(2 * kPartSeg, std::max<int64_t>(L.seg, n / L.nb * 9 / 8));
-    L.ntiles = (int)ceil_div(n > 0 ? n : 1, kTile);
+    L.ntiles = (int)tiles;
     L.nchunks = (int)ceil_div(L.ntiles, kColChunk);
     L.items_max = ceil_div(n > 0 ? n : 1, L.seg) + L.nb;
     // shorter inputs have shorter items, so that some have more of them
     L.items_cap = std::max(std::min<int64_t>(ceil_div(n > 0 ? n : 1, kPartSegMin), lae ? 256 : 512),
                            ceil_div(n > 0 ? n : 1, kPartSeg)) + L.nb;
+    if (mul) L.items_cap = std::max(L.items_cap, std::min(tiles + L.nb, kPartMulItems));
     const size_t slots = (size_t)L.ntiles * kTile;
     size_t o = 0;
     auto take = [&](size_t bytes) {
@@ -1693,9 +1707,6 @@ static PartLayout part_layout(int64_t n, int64_t m, bool f32, bool aux, bool lae
     L.total = o;
     return L;
 }
-
-// Whether a bin keeps a word beside its accumulator (part_aux).
-static bool aux_word(int op, bool f32) { return op == PVJP_MUL || (!f32 && (op == PVJP_MIN || op == PVJP_MAX)); }
 
 static size_t hist_fixed(int op, int64_t m) {
     return align_up((size_t)m * 8, 256) + (op == PVJP_MUL ? align_up((size_t)m * 4, 256) : 0);
@@ -1733,11 +1744,11 @@ static size_t hist_ws(int op, int64_t n, int64_t m, bool f32) {
             if (use_range(op, f32, n, m, counts != 0))
                 body = std::max(body, range_bytes(range_plan(op, n, m).C, m));
             else if (use_partition(op, f32, n, m, counts != 0))
-                body = std::max(body, part_layout(n, m, f32, aux_word(op, f32)).total);
+                body = std::max(body, part_layout(n, m, f32, op).total);
     } else if (beyond) {
         const int64_t most = (int64_t)kPartMaxBuckets * kPartBins;
         if (op == PVJP_MUL ? n >= (int64_t)1 << 17 : m <= most)
-            body = std::max(body, part_layout(n, std::min(m, most), f32, aux_word(op, f32)).total);
+            body = std::max(body, part_layout(n, std::min(m, most), f32, op).total);
         for (int64_t R = 1; R <= range_most(op, f32); ++R)
             if (n >= (op == PVJP_MUL ? (int64_t)1 << 17 : (int64_t)3 << 17))
                 body = std::max(body, range_bytes(range_chunks(n, R), std::min<int64_t>(m, R * range_bins(op))));
@@ -1780,7 +1791,7 @@ static void part_sort(const int32_t* inds, const T* vs, int64_t n, int32_t m, co
 template <class T, int OP>
 static void run_partitioned(const int32_t* inds, const T* vs, int64_t n, int32_t m, int32_t* count, char* w,
                             size_t off, const HistOut<T>& o, hipStream_t st) {
-    const PartLayout L = part_layout(n, m, sizeof(T) == 4, part_aux<T, OP>());
+    const PartLayout L = part_layout(n, m, sizeof(T) == 4, OP);
     char* base = w + off;
     part_sort<T, OP>(inds, vs, n, m, L, base, st);
     const uint32_t* D = reinterpret_cast<const uint32_t*>(base + L.D);
@@ -1813,11 +1824,11 @@ bool hist_lae_partition_ok(pvjp_dtype dtype, int64_t m) {
 size_t hist_least_bytes(pvjp_op op, pvjp_dtype dtype, int64_t n, int64_t m) {
     return dtype == PVJP_F32 ? hist_ws(op, n, m, true) : hist_least(op, n, m);
 }
-size_t hist_lae_partition_bytes(int64_t n, int64_t m) { return part_layout(n, m, true, false, true).total; }
+size_t hist_lae_partition_bytes(int64_t n, int64_t m) { return part_layout(n, m, true, kPartLae).total; }
 
 void hist_lae_partitioned(const int32_t* inds, const float* x, int64_t n, int32_t m, float* hs, char* ws,
                           hipStream_t st) {
-    const PartLayout L = part_layout(n, m, true, false, true);
+    const PartLayout L = part_layout(n, m, true, kPartLae);
     part_sort<float, PVJP_ADD>(inds, x, n, m, L, ws, st);
     double* psum = reinterpret_cast<double*>(ws + L.pacc);
     uint32_t* pmax = reinterpret_cast<uint32_t*>(ws + L.pcnt);
@@ -1877,7 +1888,7 @@ static void run_hist(const int32_t* inds, const T* vs, int64_t n, int32_t m, T* 
         }
     }
     if (use_partition(OP, sizeof(T) == 4, n, m, counts) &&
-        part_layout(n, m, sizeof(T) == 4, part_aux<T, OP>()).total <= room) {
+        part_layout(n, m, sizeof(T) == 4, OP).total <= room) {
         run_partitioned<T, OP>(inds, vs, n, m, count, w, off, HistOut<T>{hs, winner, p, z}, st);
         return;
     }
@@ -2022,7 +2033,7 @@ extern "C" pvjp_status pvjp_hist_plan_info(pvjp_op op, pvjp_dtype dtype, int64_t
         info[0] = PVJP_HIST_PATH_PARTITION;
         info[1] = kPartBins;
         // runs start within seg records; a run is below kTile
-        info[2] = part_layout(n, m, dtype == PVJP_F32, false).seg + kTile;
+        info[2] = part_layout(n, m, dtype == PVJP_F32, op).seg + kTile;
         info[3] = ceil_div(m, kPartBins);
     } else {
         info[0] = hist_plan(op, n, m, counts != 0).cache ? PVJP_HIST_PATH_CACHE : PVJP_HIST_PATH_LDS;

@@ -239,6 +239,24 @@ def test_clustered_indices(ops, orc, op, dtype, n, m, kind):
             assert rel_l2(host(aux["p"]), ref["p"]) <= bar
 
 
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("n", [1 << 17, 8192 * 236, 8192 * 236 + 1])
+@pytest.mark.parametrize("kind", ["uniform", "sorted", "const"])
+def test_product_items_of_one_tile(ops, orc, dtype, n, kind):
+    # products take items of a tile's records up to 256 of them: 236 tiles and 20
+    # buckets, one tile more, and the shortest input that is sorted by bucket
+    m = 81920
+    g = workloads.rng(n)
+    inds = g.integers(0, m, n).astype(np.int32) if kind == "uniform" else clustered(kind, n, m, g)
+    vs = np.exp(1e-3 * g.standard_normal(n)).astype(np.float32 if dtype == "f32" else np.float64)
+    vs[::5003] = 0.0
+    ref = orc.hist("mul", inds, vs, m)
+    hs, aux = ops.hist("mul", dev(inds), dev(vs), m)
+    bar = TOL_F32 if dtype == "f32" else 1e-12
+    assert np.array_equal(host(aux["z"]), ref["z"])
+    assert rel_l2(host(hs), ref["hs"]) <= bar and rel_l2(host(aux["p"]), ref["p"]) <= bar
+
+
 @pytest.mark.parametrize("op,dtype,n,m", [("add", "f32", 1 << 24, 65536), ("mul", "f32", 1 << 21, 40000),
                                           ("mul", "f32", 1 << 21, 300000), ("max", "f64", 1 << 22, 100000),
                                           ("add", "f64", 1 << 22, 300000)])
