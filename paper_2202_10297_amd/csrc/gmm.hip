@@ -593,9 +593,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void g
 // standard normal points, D = 32 and 64, K = 25 to 200, N = 131,073 to 10^6, the
 // worst relative L2 error of the FP32 form and of this: log-likelihood 1.2e-9 and
 // 1.2e-9, alpha_bar 1.6e-7 and 1.6e-7, mu_bar 1.3e-6 and 2.8e-7, q_bar 1.2e-5 and
-// 5.2e-7, l_bar 2.4e-6 and 2.2e-7.  One 32x32x16 bf16 step takes 32 cycles, the eight 32x32x2 FP32 steps
-// it replaces 512, so six of them are 2.7 times faster.  Inputs, weights, the
-// sums over chunks, |z|^2 and the log-sum-exp keep their types.
+// 5.2e-7, l_bar 2.4e-6 and 2.2e-7.  One 32x32x16 bf16 step takes 32 cycles, the
+// eight 32x32x2 FP32 steps it replaces 512, so six of them are 2.7 times faster.
+// Inputs, weights, the sums over chunks, |z|^2 and the log-sum-exp keep their
+// types.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));

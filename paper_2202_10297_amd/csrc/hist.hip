@@ -400,7 +400,7 @@ __global__ __launch_bounds__(kRangeBlock) void hist_range_kernel(const int32_t* 
             uint32_t todo = 0;
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
-                j[t] = kk[t] - k0;
+                j[t] = (int32_t)((uint32_t)kk[t] - (uint32_t)k0);
                 x[t] = (double)cur[u].v[t];
                 const bool in = (uint32_t)j[t] < cnt, zero = OP == PVJP_MUL && cur[u].v[t] == T(0);
                 if (OP == PVJP_MUL && in && zero) atomicAdd(&zc[j[t]], 1);
@@ -1198,6 +1198,12 @@ __device__ __forceinline__ void acc_records(uint64_t* acc, int32_t* cnt, int32_t
     }
 }
 
+// The work item of this block (-1: none) with its bucket and tiles.  With
+// many buckets (short runs): blocks go to the XCDs round-robin, so each XCD
+// takes an equal contiguous range of the items (the grid is a multiple of
+// kXcds and covers them) and items of adjacent buckets, whose runs share
+// cache lines in every tile, meet in one L2.  With few buckets the runs span
+// whole lines and items go in grid order.
 struct PartItem {
     int item, b, ta, tb;
 };

@@ -239,6 +239,23 @@ def test_clustered_indices(ops, orc, op, dtype, n, m, kind):
             assert rel_l2(host(aux["p"]), ref["p"]) <= bar
 
 
+@pytest.mark.parametrize("op", ["add", "mul", "max"])
+@pytest.mark.parametrize("n,m", [(5000, 100), (100001, 30000), (1 << 20, 50000), (1 << 20, 300000)])
+def test_indices_far_outside_are_skipped(ops, orc, op, n, m):
+    # every form's test of the range: no difference to a range's first bin wraps
+    g = workloads.rng(n + m)
+    inds = g.integers(0, m, n).astype(np.int32)
+    inds[::7] = np.iinfo(np.int32).min + np.arange(inds[::7].size, dtype=np.int32) % 70000
+    inds[3::7] = np.iinfo(np.int32).max
+    vs = np.exp(1e-3 * g.standard_normal(n)).astype(np.float32)
+    ref = orc.hist(op, inds, vs, m)
+    hs, aux = ops.hist(op, dev(inds), dev(vs), m)
+    if op == "max":
+        assert np.array_equal(host(aux["winner"]), ref["winner"]) and np.array_equal(host(hs), ref["hs"])
+    else:
+        assert rel_l2(host(hs), ref["hs"]) <= TOL_F32
+
+
 @pytest.mark.parametrize("dtype", ["f32", "f64"])
 @pytest.mark.parametrize("n", [1 << 17, 8192 * 236, 8192 * 236 + 1])
 @pytest.mark.parametrize("kind", ["uniform", "sorted", "const"])
